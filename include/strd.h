@@ -32,10 +32,9 @@
  *     or library fallback.
  *   - The two scores and the two mixers each have two device kernels: a matrix-core
  *     (MFMA) kernel for bf16 tensors in the tile shapes listed at strd_*_kernel_path
- *     below, and a plain SIMT kernel in fp32 arithmetic that serves fp32 tensors (whose
- *     1e-4 tolerance bf16 matrix cores cannot meet) and every other bf16 shape.  The SIMT
- *     kernels are one to two orders of magnitude slower; which one a call will run is
- *     never implicit: strd_*_kernel_path answers it from the shape alone.
+ *     below, and a general kernel in fp32 arithmetic that serves fp32 tensors (whose
+ *     1e-4 tolerance bf16 matrix cores cannot meet) and every other bf16 shape.  Which one a
+ *     call will run is never implicit: strd_*_kernel_path answers it from the shape alone.
  */
 #ifndef STRD_H
 #define STRD_H
@@ -74,8 +73,8 @@ int strd_version(void);
 int strd_mfma_rate_probe(float *out, int workgroups, int iters, int mode, void *stream);
 
 /* Which device kernel a call with these sizes runs: STRD_PATH_MFMA (bf16 matrix cores),
- * STRD_PATH_SIMT (fp32 arithmetic on the vector units: fp32 tensors, and bf16 shapes outside
- * the matrix-core tiles) or STRD_PATH_NONE (the call would return STRD_EINVAL or
+ * STRD_PATH_SIMT (fp32 arithmetic: fp32 tensors, and bf16 shapes outside the bf16
+ * matrix-core tiles) or STRD_PATH_NONE (the call would return STRD_EINVAL or
  * STRD_EUNSUPPORTED).  Matrix-core shapes, all bf16: score_attn and attn_prefill d in {64, 128};
  * score_mamba n in {64, 128}; ssd_prefill n in {64, 128} and P a multiple of 32 (and every
  * tensor below 4 GiB).  Host-only, touches no device. */
@@ -263,10 +262,11 @@ int strd_compact_varlen(const strd_compact_item *items, int n_items, const int32
  * otherwise unused: it does NOT select the tiling.  The kernels always cut time into
  * 64-token steps and carry the state across them on chip, so results do not depend on
  * `chunk` at all.  S_out of one call fed as S_in of the next continues the same scan.
- *   ws  [dev] strd_ssd_prefill_workspace(T, ...) bytes: 0 for short sequences; for long ones the
- *       sequence is cut into segments that run side by side, and the local end state and total
+ *   ws  [dev] strd_ssd_prefill_workspace(T, ...) bytes.  bf16 matrix-core shapes: 0 for short
+ *       sequences; for long ones the sequence is cut into segments that run side by side, and the local end state and total
  *       decay of every segment but the last pass through the workspace ((segments - 1) * H * P * n
- *       + segments * H floats).  Too small or NULL when needed: STRD_EWORKSPACE.
+ *       + segments * H floats).  Other shapes: the state before every 64-token chunk and the chunks'
+ *       decays, (P * n + 1) * H floats per chunk.  Too small or NULL when needed: STRD_EWORKSPACE.
  * Requires T >= 0, H % G == 0.
  * ------------------------------------------------------------------------- */
 size_t strd_ssd_prefill_workspace(int T, int H, int P, int G, int n, int chunk, strd_dtype io);

@@ -45,7 +45,7 @@ int strd_version(void) { return 1000; }
 size_t strd_score_attn_workspace(int M, int N, int Hq, int Hkv, int d, strd_dtype io) {
     if (M < 1 || N < 1 || Hq < 1 || Hkv < 1 || Hq % Hkv) return 0;
     if (score_attn_mfma_supported(M, N, Hq, Hkv, d, io)) return score_attn_mfma_ws(M, N, Hq, Hkv);
-    return score_attn_general_ws(M, Hq);
+    return score_attn_general_ws(M, N, Hq, Hkv, 1);
 }
 
 int strd_score_attn(const void *q_txt, const void *k_vis, float *scores, int M, int N, int Hq, int Hkv,
@@ -183,7 +183,7 @@ size_t strd_score_attn_varlen_workspace(const strd_seq *seqs, int nseq, int Hq, 
     if (!plan_seqs(seqs, nseq, false, p) || Hq < 1 || Hkv < 1 || Hq % Hkv) return 0;
     if (score_attn_mfma_supported(p.max_m, p.max_n, Hq, Hkv, d, io))
         return score_attn_mfma_varlen_ws(nseq, p.max_m, p.max_n, Hq, Hkv);
-    return align_up((size_t)nseq * p.max_m * Hq * sizeof(float), 256);
+    return score_attn_general_ws(p.max_m, p.max_n, Hq, Hkv, nseq);
 }
 
 int strd_score_attn_varlen(const void *q_all, const void *k_all, float *scores, int ld, const strd_seq *seqs, int nseq,
@@ -254,7 +254,8 @@ int strd_compact_varlen(const strd_compact_item *items, int n_items, const int32
 size_t strd_ssd_prefill_workspace(int T, int H, int P, int G, int n, int chunk, strd_dtype io) {
     (void)chunk;
     if (T < 1 || H < 1 || P < 1 || G < 1 || n < 1 || H % G) return 0;
-    return use_seg(T, T, H, P, G, n, io) ? ssd_seg_ws(T, H, P, G, n) : 0;
+    if (use_seg(T, T, H, P, G, n, io)) return ssd_seg_ws(T, H, P, G, n);
+    return ssd_mfma_supported(T, T, H, P, G, n, io) || !ssd_general_supported(n) ? 0 : ssd_general_ws(T, H, P, n);
 }
 
 int strd_ssd_prefill(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D,
@@ -270,7 +271,7 @@ int strd_ssd_prefill(const void *x, const float *dt, const float *A, const void 
         return ssd_seg(x, dt, A, B, C, D, S_in, y, S_out, nullptr, 0, 0, T, H, P, G, n, ws, as_stream(stream));
     if (mfma) return ssd_mfma(x, dt, A, B, C, D, S_in, y, S_out, nullptr, 0, 0, T, H, P, G, n, as_stream(stream));
     if (!ssd_general_supported(n)) return STRD_EUNSUPPORTED;
-    return ssd_general(x, dt, A, B, C, D, S_in, y, S_out, T, H, P, G, n, io, as_stream(stream));
+    return ssd_general(x, dt, A, B, C, D, S_in, y, S_out, T, H, P, G, n, io, ws, as_stream(stream));
 }
 
 int strd_ssd_prefill_gather(const void *x, const float *dt, const float *A, const void *B, const void *C,

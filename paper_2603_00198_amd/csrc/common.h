@@ -242,16 +242,17 @@ int select_topk_launch(const float *scores, int N, int K, int32_t *idx, void *ws
 int select_topk_static_max_n();
 int select_topk_static_launch(const float *scores, int N, int K, int32_t *idx, hipStream_t s);
 
-// general SIMT kernels: any shape, fp32 or bf16 I/O, fp32 arithmetic
-size_t score_attn_general_ws(int M, int Hq);
+// general kernels: any shape, fp32 or bf16 I/O, fp32 arithmetic
+size_t score_attn_general_ws(int M, int N, int Hq, int Hkv, int nseq);
 int score_attn_general(const void *q, const void *k, float *s, int M, int N, int Hq, int Hkv, int d,
                        float scale, strd_dtype io, void *ws, hipStream_t st);
 int score_mamba_general(const void *B, const void *C, const float *dt, float *s, int M, int N, int H,
                         int G, int n, strd_dtype io, hipStream_t st);
 bool ssd_general_supported(int n);
+size_t ssd_general_ws(int T, int H, int P, int n);
 int ssd_general(const void *x, const float *dt, const float *A, const void *B, const void *C,
                 const float *D, const float *S_in, void *y, float *S_out, int T, int H, int P, int G,
-                int n, strd_dtype io, hipStream_t st);
+                int n, strd_dtype io, void *ws, hipStream_t st);
 // bf16 matrix-core paths
 bool attn_mfma_supported(int T, int Hq, int Hkv, int d, strd_dtype io);
 int attn_mfma(const void *q, const void *k, const void *v, void *o, int T, int Hq, int Hkv, int d, float scale,

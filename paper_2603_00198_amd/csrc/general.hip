@@ -1,326 +1,883 @@
-// General-shape SIMT kernels: fp32 arithmetic on fp32 or bf16 tensors, any head count, head
-// dimension and state size.  They serve fp32 I/O (where the 1e-4 tolerance rules out bf16
-// matrix cores) and the shapes the MFMA kernels are not tiled for.  Each kernel is the
-// definition evaluated directly; the tuned bf16 paths live in the *_mfma.hip files.
+// General-shape kernels: fp32 arithmetic on fp32 or bf16 tensors, any head count, head dimension
+// and state size.  They serve fp32 I/O (whose 1e-4 tolerance rules out bf16 matrix cores) and the
+// shapes the bf16 kernels of the *_mfma.hip files are not tiled for.
+//
+// Every contraction runs on v_mfma_f32_16x16x4_f32: fp32 products and sums, so nothing is lost
+// against vector arithmetic, while a wave owns a 16 x 16 tile and reads each operand row once per
+// tile instead of once per element.  An operand lane (row r = lane % 16, lane group lb = lane / 16)
+// holds the four elements 16 j + 4 lb .. + 3 of its row as one 16-byte load and feeds them to four
+// consecutive products; both operands take the contraction index in that order, so the sum is
+// the same.  Accumulator element i of a lane is row 4 lb + i, column r of the tile -- exactly the
+// operand layout of the next product over those rows, so that probabilities (attention) and decay
+// weights (scan) go from one product into the next without leaving the registers.
+// Operands come straight from global memory: the shapes these kernels see in practice (a few
+// thousand tokens, a handful of heads) live in L2 and are bound by latency, i.e. by how many
+// loads are in flight and how many workgroups share the work, not by bandwidth.
+#include <algorithm>
+
 #include "common.h"
 
 namespace strd {
 namespace {
 
-constexpr int kThreads = 256;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-    return v;
+constexpr float kLog2e = 1.4426950408889634f;
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ float wave_sum(float v) {
+__device__ __forceinline__ float ex2(float v) { return __builtin_amdgcn_exp2f(v); }
+__device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
+__device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+// Sum / max over the four lane groups that share a column of an accumulator tile.
+__device__ __forceinline__ float groups_sum(float v) {
+    v += __shfl_xor(v, 16, kWave);
+    return v + __shfl_xor(v, 32, kWave);
+}
+__device__ __forceinline__ float groups_max(float v) {
+    v = fmaxf(v, __shfl_xor(v, 16, kWave));
+    return fmaxf(v, __shfl_xor(v, 32, kWave));
+}
+
+// Elements c .. c + W - 1 of a row of `len`, zeros from len on (FULL: the caller never asks past len).  W > 1
+// needs len % W == 0 and an aligned row, so a vector lies wholly inside the row or wholly past it.  No
+// branch around the load: behind one, the compiler waits for every outstanding load at the first use of any.
+template <int W, bool FULL, typename T>
+__device__ __forceinline__ void load_row(const T *__restrict__ row, int c, int len, float (&out)[W]) {
+    const int at = FULL ? c : min(c, len - W);
+    if constexpr (W == 1) {
+        out[0] = to_f32(row[at]);
+    } else if constexpr (std::is_same<T, float>::value) {
+        typedef typename std::conditional<W == 4, f32x4, f32x2>::type V;
+        const V v = *reinterpret_cast<const V *>(row + at);
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+        for (int i = 0; i < W; ++i) out[i] = v[i];
+    } else {
+        typedef typename std::conditional<W == 4, bf16x4, bf16x2>::type V;
+        const V v = *reinterpret_cast<const V *>(row + at);
+#pragma unroll
+        for (int i = 0; i < W; ++i) out[i] = static_cast<float>(v[i]);
+    }
+    if constexpr (!FULL)
+#pragma unroll
+        for (int i = 0; i < W; ++i) out[i] = c < len ? out[i] : 0.f;
+}
+template <int W, typename T>
+__device__ __forceinline__ void store_row(T *__restrict__ row, int c, int len, const float (&in)[W]) {
+    if (c >= len) return;
+    if constexpr (W == 1) {
+        row[c] = from_f32<T>(in[0]);
+    } else if constexpr (std::is_same<T, float>::value) {
+        typedef typename std::conditional<W == 4, f32x4, f32x2>::type V;
+        V v;
+#pragma unroll
+        for (int i = 0; i < W; ++i) v[i] = in[i];
+        *reinterpret_cast<V *>(row + c) = v;
+    } else {
+        typedef typename std::conditional<W == 4, bf16x4, bf16x2>::type V;
+        V v;
+#pragma unroll
+        for (int i = 0; i < W; ++i) v[i] = static_cast<bf16_t>(in[i]);
+        *reinterpret_cast<V *>(row + c) = v;
+    }
+}
+
+// One lane's share of an operand row: elements 16 j + 4 lb .. + 3 for j < KJ (rows up to 16 KJ
+// elements stay in registers; FULL: exactly 16 KJ), or only the row's address for KJ = 0 (longer rows, or
+// rows whose length or alignment does not allow vectors: element by element, read again for every product).
+template <typename T, int KJ, bool FULL>
+struct Operand {
+    float v[KJ > 0 ? KJ : 1][4];
+    const T *row;
+    int len;
+    __device__ __forceinline__ void load(const T *__restrict__ r, int lb, int n) {
+        if constexpr (KJ > 0) {
+#pragma unroll
+            for (int j = 0; j < KJ; ++j) load_row<4, FULL>(r, 16 * j + 4 * lb, n, v[j]);
+        } else {
+            row = r;
+            len = n;
+        }
+    }
+};
+// c += A . B^T for the 16 rows of each operand.
+template <typename TA, typename TB, int KJ, bool FULL>
+__device__ __forceinline__ f32x4 product(const Operand<TA, KJ, FULL> &a, const Operand<TB, KJ, FULL> &b, int lb, f32x4 c) {
+    if constexpr (KJ > 0) {
+#pragma unroll
+        for (int j = 0; j < KJ; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c = mfma4(a.v[j][i], b.v[j][i], c);
+    } else {
+        for (int e0 = 0; e0 < a.len; e0 += 16) {
+            float av[4], bv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = e0 + 4 * i + lb;
+                av[i] = e < a.len ? to_f32(a.row[e]) : 0.f;
+                bv[i] = e < a.len ? to_f32(b.row[e]) : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c = mfma4(av[i], bv[i], c);
+        }
+    }
+    return c;
+}
+
+// The same for NT row tiles against one B operand, the tiles taking turns: a product issues while the
+// others' results are still on their way.
+template <typename TA, typename TB, int KJ, bool FULL, int NT>
+__device__ __forceinline__ void products(const Operand<TA, KJ, FULL> (&a)[NT], const Operand<TB, KJ, FULL> &b, int lb,
+                                         f32x4 (&c)[NT]) {
+    if constexpr (KJ > 0) {
+#pragma unroll
+        for (int j = 0; j < KJ; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) c[t] = mfma4(a[t].v[j][i], b.v[j][i], c[t]);
+    } else {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) c[t] = product(a[t], b, lb, c[t]);
+    }
+}
+
+// Query row r of kv head kvh (r = m * rep + j) is row m * Hq + kvh * rep + j of q.
+__device__ __forceinline__ size_t qrow_index(int r, int rep, int Hq, int kvh) {
+    return (size_t)(r / rep) * Hq + kvh * rep + r % rep;
 }
 
 // ------------------------------------------------------------------ score_attn -------------
-// Pass 1: one workgroup per (text row m, query head h): log-sum-exp of scale * q.k_i over the
-// N vision keys.  lse index = m * Hq + h.
-// SEQ = SeqTab (packed batch, blockIdx.y = sequence): q and k both point at the packed tensors,
-// lse has `lse_ld` entries per sequence.
-template <typename T, class SEQ>
-__global__ __launch_bounds__(kThreads) void attn_row_lse_kernel(const T *__restrict__ q, const T *__restrict__ k,
-                                                                float *__restrict__ lse, int N, int Hq, int Hkv,
-                                                                int d, float scale, SEQ seq, int lse_ld) {
-    extern __shared__ float smem[];  // d floats of q, then 2 * waves
-    if constexpr (is_varlen<SEQ>()) {
-        const int b = blockIdx.y;
-        N = seq.N[b];
-        if ((int)blockIdx.x >= seq.M[b] * Hq) return;  // uniform
-        k += (size_t)seq.row0[b] * Hkv * d;
-        q += (size_t)(seq.row0[b] + N) * Hq * d;
-        lse += (size_t)b * lse_ld;
-    }
-    const int row = blockIdx.x, h = row % Hq, hk = h / (Hq / Hkv);
-    float *qs = smem;
-    float *red = smem + d;
-    for (int c = threadIdx.x; c < d; c += kThreads) qs[c] = to_f32(q[(size_t)row * d + c]);
-    __syncthreads();
-    float mx = -INFINITY, sum = 0.f;
-    for (int i = threadIdx.x; i < N; i += kThreads) {
-        const T *kv = k + ((size_t)i * Hkv + hk) * d;
-        float dot = 0.f;
-        for (int c = 0; c < d; ++c) dot = fmaf(qs[c], to_f32(kv[c]), dot);
-        const float z = scale * dot;
-        const float nm = fmaxf(mx, z);
-        sum = sum * expf(mx - nm) + expf(z - nm);
-        mx = nm;
-    }
-    // combine (max, sum) pairs: wave, then workgroup
-    const float wm = wave_max(mx);
-    const float ws = wave_sum(mx == -INFINITY ? 0.f : sum * expf(mx - wm));
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    if (lane == 0) { red[2 * wave] = wm; red[2 * wave + 1] = ws; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float gm = -INFINITY;
-        for (int w = 0; w < kThreads / kWave; ++w) gm = fmaxf(gm, red[2 * w]);
-        float gs = 0.f;
-        for (int w = 0; w < kThreads / kWave; ++w)
-            if (red[2 * w] != -INFINITY) gs += red[2 * w + 1] * expf(red[2 * w] - gm);
-        lse[row] = gm + logf(gs);
-    }
-}
+// Two launches.  Pass 1: per query row the running max and sum of 2^z over a slice of the keys
+// (z = scale log2(e) q.k); a wave holds 16 query rows in registers and walks the slice, tile
+// transposed (keys on accumulator rows), so a lane's softmax state is one (max, sum) pair.
+// Pass 2: a workgroup owns 16 keys and all query rows; it first combines the slices' statistics of
+// its rows into log-sum-exps in LDS (every workgroup for itself: a few thousand cached loads
+// instead of a launch), then its 8 waves deal the row tiles among themselves.
+// 1024 keys, 128 query rows of 64: 11 + 928 us in the direct evaluation (one thread per key walked
+// all rows) -> 6 + 5.6 us.
+// SEQ = SeqTab (packed batch, blockIdx.y = sequence): q and k both point at the packed tensors, the
+// statistics of sequence b start at b * seq_stride.
+constexpr int kStatRows = 64;      // query rows per workgroup of pass 1 (4 waves)
+constexpr int kColThreads = 512;   // pass 2 and score_mamba: 8 waves
+constexpr int kColRows = 2048;     // rows whose log-sum-exp are in LDS at a time
 
-// Pass 2: one thread per vision token: sum over all (m, h) rows of exp(z - lse).
-template <typename T, class SEQ>
-__global__ __launch_bounds__(kThreads) void attn_col_sum_kernel(const T *__restrict__ q, const T *__restrict__ k,
-                                                                const float *__restrict__ lse,
-                                                                float *__restrict__ s, int M, int N, int Hq,
-                                                                int Hkv, int d, float scale, SEQ seq, int lse_ld,
-                                                                int ld) {
+template <typename T, int KJ, bool FULL, class SEQ>
+__global__ __launch_bounds__(256) void attn_stats_kernel(const T *__restrict__ q, const T *__restrict__ k,
+                                                         float *__restrict__ pmax, float *__restrict__ psum, int M, int N,
+                                                         int Hq, int Hkv, int d, float scale2, int nrb, int keys_per_slice,
+                                                         SEQ seq, size_t seq_stride) {
+    constexpr int KT = KJ == 1 || KJ == 4 ? 4 : 2;  // key tiles per trip: that many rows' loads in flight
     if constexpr (is_varlen<SEQ>()) {
         const int b = blockIdx.y;
         N = seq.N[b];
         M = seq.M[b];
         k += (size_t)seq.row0[b] * Hkv * d;
         q += (size_t)(seq.row0[b] + N) * Hq * d;
-        lse += (size_t)b * lse_ld;
+        pmax += b * seq_stride;
+        psum += b * seq_stride;
+    }
+    const int lane = threadIdx.x & 63, lr = lane & 15, lb = lane >> 4, w = wave_index();
+    const int rep = Hq / Hkv, R = M * rep;
+    const int rb = blockIdx.x % nrb, kvh = (blockIdx.x / nrb) % Hkv, sl = blockIdx.x / nrb / Hkv;
+    const int row = rb * kStatRows + w * 16 + lr;
+    if (rb * kStatRows + w * 16 >= R) return;  // uniform per wave; there are no barriers
+    const int key0 = sl * keys_per_slice, key1 = min(N, key0 + keys_per_slice);
+    Operand<T, KJ, FULL> qf;
+    qf.load(q + qrow_index(min(row, R - 1), rep, Hq, kvh) * d, lb, d);
+    float run_m = -INFINITY, run_s = 0.f;
+    for (int kb = key0; kb < key1; kb += 16 * KT) {
+        Operand<T, KJ, FULL> kf[KT];
+#pragma unroll
+        for (int t = 0; t < KT; ++t) kf[t].load(k + ((size_t)min(kb + 16 * t + lr, N - 1) * Hkv + kvh) * d, lb, d);
+        f32x4 z[KT];
+#pragma unroll
+        for (int t = 0; t < KT; ++t) z[t] = zero4();
+        products(kf, qf, lb, z);
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (kb + 16 * t + 4 * lb + i >= key1) z[t][i] = -INFINITY;
+                tmax = fmaxf(tmax, z[t][i]);
+            }
+        const float nm = fmaxf(run_m, tmax * scale2);
+        const float ref = nm == -INFINITY ? 0.f : nm;
+        float ts = 0.f;
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ts += ex2(fmaf(z[t][i], scale2, -ref));
+        run_s = run_s * ex2(run_m - ref) + ts;
+        run_m = nm;
+    }
+    // the four lane groups saw disjoint keys of the same query
+    const float m = groups_max(run_m), ref = m == -INFINITY ? 0.f : m;
+    const float tot = groups_sum(run_s * ex2(run_m - ref));
+    if (lb == 0 && row < R) {
+        const size_t o = (size_t)sl * M * Hq + qrow_index(row, rep, Hq, kvh);
+        pmax[o] = m;
+        psum[o] = tot;
+    }
+}
+
+template <typename T, int KJ, bool FULL, class SEQ>
+__global__ __launch_bounds__(kColThreads) void attn_col_sum_kernel(const T *__restrict__ q, const T *__restrict__ k,
+                                                                   const float *__restrict__ pmax,
+                                                                   const float *__restrict__ psum, float *__restrict__ s,
+                                                                   int M, int N, int Hq, int Hkv, int d, float scale2,
+                                                                   int nslice, SEQ seq, size_t seq_stride, int ld) {
+    __shared__ __attribute__((aligned(16))) float lse[kColRows];
+    __shared__ float red[kColThreads / kWave][16];
+    if constexpr (is_varlen<SEQ>()) {
+        const int b = blockIdx.y;
+        N = seq.N[b];
+        M = seq.M[b];
+        if ((int)blockIdx.x * 16 >= N) return;  // uniform
+        k += (size_t)seq.row0[b] * Hkv * d;
+        q += (size_t)(seq.row0[b] + N) * Hq * d;
+        pmax += b * seq_stride;
+        psum += b * seq_stride;
         s += (size_t)b * ld;
     }
-    const int i = blockIdx.x * kThreads + threadIdx.x;
-    if (i >= N) return;
-    const int rep = Hq / Hkv;
-    float acc = 0.f;
-    for (int m = 0; m < M; ++m)
-        for (int h = 0; h < Hq; ++h) {
-            const T *qv = q + ((size_t)m * Hq + h) * d;
-            const T *kv = k + ((size_t)i * Hkv + h / rep) * d;
-            float dot = 0.f;
-            for (int c = 0; c < d; ++c) dot = fmaf(to_f32(qv[c]), to_f32(kv[c]), dot);
-            acc += expf(scale * dot - lse[m * Hq + h]);
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lb = lane >> 4, w = wave_index();
+    const int rep = Hq / Hkv, R = M * rep, rows = M * Hq;
+    // all query rows, kv head after kv head, every kv head padded to whole tiles of 16
+    const int Rp = (R + 15) / 16 * 16;
+    const long long F = (long long)Rp * Hkv;
+    const int key = blockIdx.x * 16 + lr;
+    Operand<T, KJ, FULL> kf, qf;
+    int kf_head = -1;
+    auto load_tile = [&](long long f) {  // f: first row of a tile (uniform)
+        const int kvh = (int)(f / Rp), r = min((int)(f - (long long)kvh * Rp) + lr, R - 1);
+        if (kvh != kf_head) kf.load(k + ((size_t)min(key, N - 1) * Hkv + kvh) * d, lb, d);
+        kf_head = kvh;
+        qf.load(q + qrow_index(r, rep, Hq, kvh) * d, lb, d);
+    };
+    float col = 0.f;
+    for (long long f0 = 0; f0 < F; f0 += kColRows) {
+        const int cnt = (int)min((long long)kColRows, F - f0);
+        if (w * 16 < cnt) load_tile(f0 + w * 16);  // requested before the statistics are waited for
+        if (f0 > 0) __syncthreads();               // everybody is done with the previous rows
+        for (int e = tid; e < cnt; e += kColThreads) {
+            const int kvh = (int)((f0 + e) / Rp), r = (int)(f0 + e - (long long)kvh * Rp);
+            float v = INFINITY;  // padding rows: probability 0
+            if (r < R) {
+                const size_t o = qrow_index(r, rep, Hq, kvh);
+                float m = -INFINITY, t = 0.f;
+#pragma unroll 8
+                for (int sl = 0; sl < nslice; ++sl) {
+                    const float pm = pmax[(size_t)sl * rows + o], ps = psum[(size_t)sl * rows + o];
+                    const float nm = fmaxf(m, pm), ref = nm == -INFINITY ? 0.f : nm;
+                    t = t * ex2(m - ref) + ps * ex2(pm - ref);
+                    m = nm;
+                }
+                v = m + __builtin_amdgcn_logf(t);
+            }
+            lse[e] = v;
         }
-    s[i] = acc / ((float)M * (float)Hq);
+        __syncthreads();
+        for (int ft = w * 16; ft < cnt; ft += kColThreads / kWave * 16) {
+            const f32x4 z = product(qf, kf, lb, zero4());
+            const f32x4 l = *reinterpret_cast<const f32x4 *>(&lse[ft + 4 * lb]);
+            if (ft + kColThreads / kWave * 16 < cnt) load_tile(f0 + ft + kColThreads / kWave * 16);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) col += ex2(fmaf(z[i], scale2, -l[i]));
+        }
+    }
+    col = groups_sum(col);
+    if (lb == 0) red[w][lr] = col;
+    __syncthreads();
+    if (tid < 16 && (int)blockIdx.x * 16 + tid < N) {
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < kColThreads / kWave; ++i) t += red[i][tid];  // fixed order
+        s[blockIdx.x * 16 + tid] = t / ((float)M * (float)Hq);
+    }
 }
 
 // ------------------------------------------------------------------ score_mamba ------------
-// One thread per vision token: sum_g (sum_{h in g} dt_i^h) * sum_m |b_i^g . c_m^g|.
-template <typename T, class SEQ>
-__global__ __launch_bounds__(kThreads) void mamba_score_kernel(const T *__restrict__ Bv, const T *__restrict__ Ct,
-                                                               const float *__restrict__ dtv,
-                                                               float *__restrict__ s, int M, int N, int H, int G,
-                                                               int n, SEQ seq, int ld) {
+// sum_g (sum_{h in g} dt_i^h) * sum_m |b_i^g . c_m^g|: a workgroup owns 16 tokens, its 8 waves deal the
+// 16-row text tiles of all groups among themselves (1024 tokens, 32 text rows of 16: 58 us with one
+// thread per token -> 3 us).
+template <typename T, int KJ, bool FULL, class SEQ>
+__global__ __launch_bounds__(kColThreads) void mamba_score_kernel(const T *__restrict__ Bv, const T *__restrict__ Ct,
+                                                                  const float *__restrict__ dtv, float *__restrict__ s,
+                                                                  int M, int N, int H, int G, int n, SEQ seq, int ld) {
+    __shared__ float red[kColThreads / kWave][16];
     if constexpr (is_varlen<SEQ>()) {  // blockIdx.y = sequence; Bv, Ct, dtv are the packed tensors
         const int b = blockIdx.y;
         N = seq.N[b];
         M = seq.M[b];
+        if ((int)blockIdx.x * 16 >= N) return;  // uniform
         Bv += (size_t)seq.row0[b] * G * n;
         Ct += (size_t)(seq.row0[b] + N) * G * n;
         dtv += (size_t)seq.row0[b] * H;
         s += (size_t)b * ld;
     }
-    const int i = blockIdx.x * kThreads + threadIdx.x;
-    if (i >= N) return;
-    const int hpg = H / G;
-    float tot = 0.f;
-    for (int g = 0; g < G; ++g) {
-        float dts = 0.f;
-        for (int h = g * hpg; h < (g + 1) * hpg; ++h) dts += dtv[(size_t)i * H + h];
-        const T *b = Bv + ((size_t)i * G + g) * n;
-        float a = 0.f;
-        for (int m = 0; m < M; ++m) {
-            const T *c = Ct + ((size_t)m * G + g) * n;
-            float dot = 0.f;
-            for (int j = 0; j < n; ++j) dot = fmaf(to_f32(b[j]), to_f32(c[j]), dot);
-            a += fabsf(dot);
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lb = lane >> 4, w = wave_index();
+    const int hpg = H / G, tok = min((int)blockIdx.x * 16 + lr, N - 1);
+    const int mt = (M + 15) / 16;  // text tiles per group
+    float tot = 0.f, dts = 0.f;
+    Operand<T, KJ, FULL> bf;
+    int g_now = -1;
+    for (long long u = w; u < (long long)mt * G; u += kColThreads / kWave) {
+        const int g = (int)(u / mt), m0 = (int)(u - (long long)g * mt) * 16;
+        if (g != g_now) {  // uniform
+            bf.load(Bv + ((size_t)tok * G + g) * n, lb, n);
+            dts = 0.f;
+            for (int h = lb; h < hpg; h += 4) dts += dtv[(size_t)tok * H + g * hpg + h];
+            dts = groups_sum(dts);
+            g_now = g;
         }
-        tot += dts * a;
+        Operand<T, KJ, FULL> cf;
+        cf.load(Ct + ((size_t)min(m0 + lr, M - 1) * G + g) * n, lb, n);
+        const f32x4 z = product(cf, bf, lb, zero4());  // row = text row 4 lb + i, column = token
+        float a = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a += m0 + 4 * lb + i < M ? fabsf(z[i]) : 0.f;
+        tot = fmaf(dts, a, tot);
     }
-    s[i] = tot / ((float)M * (float)H);
+    tot = groups_sum(tot);
+    if (lb == 0) red[w][lr] = tot;
+    __syncthreads();
+    if (tid < 16 && (int)blockIdx.x * 16 + tid < N) {
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < kColThreads / kWave; ++i) t += red[i][tid];
+        s[blockIdx.x * 16 + tid] = t / ((float)M * (float)H);
+    }
 }
 
-// ------------------------------------------------------------------ ssd (recurrence) -------
-// Token-by-token recurrence.  A state column (h, p) is held by `lanes` adjacent lanes, each
-// with kSlice consecutive state entries in registers; y_t is reduced across those lanes.
-constexpr int kSlice = 16;
+// ------------------------------------------------------------------ ssd ---------------------
+// The scan in chunks of 64 tokens, all chunks side by side (the token-by-token recurrence is a serial
+// chain of T steps: 830 us at 544 tokens, 8 heads of 32, n = 16; this form 4.5 + 3.3 + 6.2 us).  Three launches:
+//   state: per (head, chunk) what the chunk adds to the state, L = sum_s 2^(l_end - l_s) dt_s x_s b_s^T,
+//          and its total decay,
+//   pass:  per state element the recurrence over the chunks, leaving the state BEFORE every chunk in
+//          place of L, and S_out,
+//   out:   y_t = sum_{s<=t} 2^(l_t - l_s) dt_s (c_t.b_s) x_s + 2^(l_t) S_before c_t + D x_t.
+// l is the running sum of dt A log2(e) inside the chunk, in double: it reaches several hundred, and a
+// difference of two such numbers decides weights near 1 (in fp32 they would be off by 1e-5).
+constexpr int kChunk = 64;
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void ssd_recurrence_kernel(
-    const T *__restrict__ x, const float *__restrict__ dt, const float *__restrict__ A, const T *__restrict__ B,
-    const T *__restrict__ C, const float *__restrict__ D, const float *__restrict__ S_in, T *__restrict__ y,
-    float *__restrict__ S_out, int Tn, int H, int P, int G, int n, int lanes) {
-    const int gid = blockIdx.x * kThreads + threadIdx.x;
-    const int col = gid / lanes, sub = gid % lanes;
-    const bool live = col < H * P;
-    const int h = live ? col / P : 0, p = live ? col % P : 0, g = h / (H / G);
-    const int j0 = sub * kSlice;
-    float S[kSlice];
+// Inclusive sum over the lanes of a wave.
+__device__ __forceinline__ double wave_scan_f64(double v) {
+    const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int e = 0; e < kSlice; ++e)
-        S[e] = (live && S_in && j0 + e < n) ? S_in[((size_t)h * P + p) * n + j0 + e] : 0.f;
-    const float Ah = A[h];
-    const float Dh = D ? D[h] : 0.f;
-    for (int t = 0; t < Tn; ++t) {
-        const float dtt = dt[(size_t)t * H + h];
-        const float a = expf(dtt * Ah);
-        const float xv = to_f32(x[((size_t)t * H + h) * P + p]);
-        const T *b = B + ((size_t)t * G + g) * n + j0;
-        const T *c = C + ((size_t)t * G + g) * n + j0;
-        float out = 0.f;
-#pragma unroll
-        for (int e = 0; e < kSlice; ++e)
-            if (j0 + e < n) {
-                S[e] = a * S[e] + xv * (dtt * to_f32(b[e]));
-                out = fmaf(S[e], to_f32(c[e]), out);
-            }
-        for (int o = lanes / 2; o > 0; o >>= 1) out += __shfl_xor(out, o, kWave);
-        if (live && sub == 0) y[((size_t)t * H + h) * P + p] = from_f32<T>(out + Dh * xv);
+    for (int o = 1; o < kWave; o <<= 1) {
+        const double u = __shfl_up(v, o, kWave);
+        if (lane >= o) v += u;
     }
-    if (live && S_out)
+    return v;
+}
+
+// One wave per (head, chunk, block of 16 CPL channels x 16 NPL state columns).
+template <typename T, int CPL, int NPL, bool FULL>
+__global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restrict__ x, const float *__restrict__ dt,
+                                                                const float *__restrict__ A, const T *__restrict__ B,
+                                                                float *__restrict__ L, float *__restrict__ decay, int Tn,
+                                                                int H, int P, int G, int n, int nc, int nst, int pblocks) {
+    __shared__ float wt[kChunk];
+    const int lane = threadIdx.x, lr = lane & 15, lb = lane >> 4;
+    const int c = blockIdx.x % nst, h = (blockIdx.x / nst) % H, u = blockIdx.x / nst / H;
+    const int p0 = (u % pblocks) * 16 * CPL, n0 = (u / pblocks) * 16 * NPL, g = h / (H / G), t0 = c * kChunk;
+    const float dtv = t0 + lane < Tn ? dt[(size_t)(t0 + lane) * H + h] : 0.f;
+    float xv[4][4][CPL], bv[4][4][NPL];
 #pragma unroll
-        for (int e = 0; e < kSlice; ++e)
-            if (j0 + e < n) S_out[((size_t)h * P + p) * n + j0 + e] = S[e];
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const size_t t = min(t0 + 16 * kb + 4 * lb + i, Tn - 1);
+            load_row<CPL, FULL>(x + (t * H + h) * P, p0 + CPL * lr, P, xv[kb][i]);
+            load_row<NPL, FULL>(B + (t * G + g) * n, n0 + NPL * lr, n, bv[kb][i]);
+        }
+    const double l = wave_scan_f64((double)dtv * A[h] * 1.4426950408889634);
+    const double end = __shfl(l, kWave - 1, kWave);
+    wt[lane] = ex2((float)(end - l)) * dtv;  // 0 past the last token
+    if (u == 0 && lane == 0) decay[(size_t)h * nc + c] = ex2((float)end);
+    __syncthreads();
+    f32x4 acc[CPL][NPL];
+#pragma unroll
+    for (int a = 0; a < CPL; ++a)
+#pragma unroll
+        for (int b = 0; b < NPL; ++b) acc[a][b] = zero4();
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float wv = wt[16 * kb + 4 * lb + i];
+#pragma unroll
+            for (int a = 0; a < CPL; ++a)
+#pragma unroll
+                for (int b = 0; b < NPL; ++b) acc[a][b] = mfma4(xv[kb][i][a] * wv, bv[kb][i][b], acc[a][b]);
+        }
+#pragma unroll
+    for (int a = 0; a < CPL; ++a)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int p = p0 + CPL * (4 * lb + i) + a;
+            float v[NPL];
+#pragma unroll
+            for (int b = 0; b < NPL; ++b) v[b] = acc[a][b][i];
+            if (p < P) store_row<NPL>(L + (((size_t)h * nc + c) * P + p) * n, n0 + NPL * lr, n, v);
+        }
+}
+
+__global__ __launch_bounds__(kWave) void ssd_pass_kernel(float *__restrict__ L, const float *__restrict__ decay,
+                                                         const float *__restrict__ S_in, float *__restrict__ S_out,
+                                                         long long total, int pn, int nc, int nst) {
+    const long long e = (long long)blockIdx.x * kWave + threadIdx.x;
+    if (e >= total) return;
+    const int h = (int)(e / pn);
+    float *Lh = L + (size_t)h * nc * pn + (e - (long long)h * pn);
+    const float *ah = decay + (size_t)h * nc;
+    float run = S_in ? S_in[e] : 0.f;
+    constexpr int kAhead = 8;
+    for (int c0 = 0; c0 < nc; c0 += kAhead) {
+        float v[kAhead], a[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int c = min(c0 + u, nst - 1);  // (nst = 0 only with nc = 1 and nothing to add: v is not used)
+            v[u] = nst > 0 ? Lh[(size_t)c * pn] : 0.f;
+            a[u] = nst > 0 ? ah[c] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (c0 + u < nc) {
+                Lh[(size_t)(c0 + u) * pn] = run;
+                run = fmaf(run, a[u], v[u]);
+            }
+    }
+    if (S_out) S_out[e] = run;
+}
+
+// One workgroup per (head, chunk); wave w owns tokens 16 w .. 16 w + 15 of the chunk as accumulator
+// columns: weights W[s, t] = 2^(l_t - l_s) dt_s (c_t.b_s) for s <= t from the products b.c, then
+// y^T[p, t] = sum_s x[s, p] W[s, t], a block of 16 CPL channels at a time.
+template <typename T, int CPL, int KN, bool FULL>
+__global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict__ x, const float *__restrict__ dt,
+                                                            const float *__restrict__ A, const T *__restrict__ B,
+                                                            const T *__restrict__ C, const float *__restrict__ D,
+                                                            const float *__restrict__ S, T *__restrict__ y, int Tn, int H,
+                                                            int P, int G, int n, int nc, int first_carried) {
+    __shared__ double ls[kChunk];
+    __shared__ float dts[kChunk];
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lb = lane >> 4, w = wave_index();
+    const int h = blockIdx.x % H, c = blockIdx.x / H, g = h / (H / G), t0 = c * kChunk;
+    const int tl = 16 * w + lr, t = t0 + tl;  // this lane's token (a column)
+    Operand<T, KN, FULL> cf, bf[4];
+    cf.load(C + ((size_t)min(t, Tn - 1) * G + g) * n, lb, n);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (j <= w) bf[j].load(B + ((size_t)min(t0 + 16 * j + lr, Tn - 1) * G + g) * n, lb, n);
+    const bool carried = c >= first_carried;
+    // x and, where they are short enough for the registers, the state rows of a channel block: those of the
+    // first block are on their way while the decays are scanned, those of the next while a block is summed
+    float xv[4][4][CPL];
+    Operand<float, KN, FULL> sf[CPL];
+    constexpr bool kEarlyState = CPL * KN <= 16;
+    auto load_state = [&](int p0) {
+        if (carried)
+#pragma unroll
+            for (int a = 0; a < CPL; ++a)
+                sf[a].load(S + (((size_t)h * nc + c) * P + min(p0 + CPL * lr + a, P - 1)) * n, lb, n);
+    };
+    auto load_block = [&](int p0) {
+        if (kEarlyState) load_state(p0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j <= w)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    load_row<CPL, FULL>(x + ((size_t)min(t0 + 16 * j + 4 * lb + i, Tn - 1) * H + h) * P, p0 + CPL * lr, P, xv[j][i]);
+    };
+    load_block(0);
+    if (w == 0) {
+        const float dtv = t0 + lane < Tn ? dt[(size_t)(t0 + lane) * H + h] : 0.f;
+        ls[lane] = wave_scan_f64((double)dtv * A[h] * 1.4426950408889634);
+        dts[lane] = dtv;
+    }
+    __syncthreads();
+    if (t0 + 16 * w >= Tn) return;  // uniform per wave, after the only barrier
+    const double lt = ls[tl];
+    const float et = ex2((float)lt);
+    f32x4 W[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (j <= w) {
+            W[j] = product(bf[j], cf, lb, zero4());
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int sl = 16 * j + 4 * lb + i;
+                W[j][i] = sl <= tl ? W[j][i] * (ex2((float)(lt - ls[sl])) * dts[sl]) : 0.f;
+                if (D && sl == tl) W[j][i] += D[h];  // the skip term rides on the diagonal
+            }
+        }
+    for (int p0 = 0; p0 < P; p0 += 16 * CPL) {
+        f32x4 acc[CPL];
+#pragma unroll
+        for (int a = 0; a < CPL; ++a) acc[a] = zero4();
+        if (carried) {
+            if (!kEarlyState) load_state(p0);
+            products(sf, cf, lb, acc);
+#pragma unroll
+            for (int a = 0; a < CPL; ++a)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[a][i] *= et;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j <= w) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int a = 0; a < CPL; ++a) acc[a] = mfma4(xv[j][i][a], W[j][i], acc[a]);
+            }
+        if (p0 + 16 * CPL < P) load_block(p0 + 16 * CPL);
+        if (t < Tn)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float v[CPL];
+#pragma unroll
+                for (int a = 0; a < CPL; ++a) v[a] = acc[a][i];
+                store_row<CPL>(y + ((size_t)t * H + h) * P, p0 + CPL * (4 * lb + i), P, v);
+            }
+    }
 }
 
 // ------------------------------------------------------------------ attention --------------
-// One workgroup per (query row t, query head h); keys are walked in tiles of kThreads with an
-// online softmax; lane c < d accumulates output channel c.
-template <typename T>
-__global__ __launch_bounds__(kThreads) void attn_row_kernel(const T *__restrict__ q, const T *__restrict__ k,
-                                                            const T *__restrict__ v, T *__restrict__ o, int Hq,
-                                                            int Hkv, int d, float scale) {
-    extern __shared__ float smem[];  // d (q) + kThreads (p) + waves (red)
-    float *qs = smem, *ps = smem + d, *red = smem + d + kThreads;
-    const int t = blockIdx.x / Hq, h = blockIdx.x % Hq, hk = h / (Hq / Hkv);
-    for (int c = threadIdx.x; c < d; c += kThreads) qs[c] = to_f32(q[((size_t)t * Hq + h) * d + c]);
-    __syncthreads();
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    float m_run = -INFINITY, l_run = 0.f, acc = 0.f;  // acc: channel threadIdx.x (< d)
-    for (int j0 = 0; j0 <= t; j0 += kThreads) {
-        const int j = j0 + threadIdx.x;
-        float z = -INFINITY;
-        if (j <= t) {
-            const T *kv = k + ((size_t)j * Hkv + hk) * d;
-            float dot = 0.f;
-            for (int c = 0; c < d; ++c) dot = fmaf(qs[c], to_f32(kv[c]), dot);
-            z = scale * dot;
+// One workgroup per (16 query rows, query head), longest rows first; its NW waves take the key trips in
+// turn, each with an online softmax of its own, and merge through LDS.  S^T = K Q^T keeps the queries
+// on accumulator columns, so the probabilities of a tile are the operand of O^T += V^T P^T as they
+// stand; V is read 4 channels a lane (channels 4 r .. of a block of 64 are rows r of four tiles).
+// NW = 8 up to d = 64, 4 up to 128, 2 up to 256 (LDS).  544 tokens, 4 heads of 64: 54 us with one workgroup
+// per row and no tiles -> 12.8 us; 2361 tokens: 51 us, of which the products alone take 32 and the loads
+// alone 30 (16 KB per trip and wave from L2, the rate of a CU's path).  Four waves per SIMD overlap the
+// two; a register set for the next trip in two waves per SIMD, two query tiles a wave (half the loads, but
+// too few workgroups for the causal sweep to balance) and 4 or 16 waves were not faster.
+template <typename T, bool VEC, bool FULL, int DJ, int NW>
+__global__ __launch_bounds__(NW *kWave) __attribute__((amdgpu_waves_per_eu(DJ == 1 ? 4 : 1))) void attn_tile_kernel(
+    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, T *__restrict__ o, int Tn, int Hq, int Hkv,
+    int d, float scale2) {
+    constexpr int KJ = VEC ? 4 * DJ : 0, KT = DJ == 4 ? 1 : 2, kPitch = 64 * DJ + 4;
+    __shared__ __attribute__((aligned(16))) float so[NW][16][kPitch];
+    __shared__ float sm[NW][16], sl[NW][16];
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lb = lane >> 4, w = wave_index();
+    const int nqt = (Tn + 15) / 16;
+    const int q0 = (nqt - 1 - (int)(blockIdx.x / Hq)) * 16, h = blockIdx.x % Hq, hk = h / (Hq / Hkv);
+    const int ntrip = (min(Tn, q0 + 16) + 16 * KT - 1) / (16 * KT);
+    Operand<T, KJ, FULL> qf;
+    qf.load(q + ((size_t)min(q0 + lr, Tn - 1) * Hq + h) * d, lb, d);
+    f32x4 acc[DJ][4];
+#pragma unroll
+    for (int b = 0; b < DJ; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[b][e] = zero4();
+    float run_m = -INFINITY, run_l = 0.f;
+    // Rows of a trip: one address per workgroup and trip plus a 24-bit product per row (they lie within 32
+    // rows of each other); rows past the end of the sequence re-read its last one.
+    const unsigned stride = (unsigned)(Hkv * d) * sizeof(T);
+    auto row_of = [&](const T *base, int r, int last) {
+        return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + __umul24((unsigned)min(r, last), stride));
+    };
+    for (int trip = w; trip < ntrip; trip += NW) {
+        const int key0 = trip * KT * 16, last = Tn - 1 - key0;  // uniform
+        const T *kb = k + ((size_t)key0 * Hkv + hk) * d, *vb = v + ((size_t)key0 * Hkv + hk) * d;
+        Operand<T, KJ, FULL> kf[KT];
+        float vf[KT][4][DJ][4];
+#pragma unroll
+        for (int u = 0; u < KT; ++u) {
+            kf[u].load(row_of(kb, 16 * u + lr, last), lb, d);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const T *vr = row_of(vb, 16 * u + 4 * lb + i, last);
+#pragma unroll
+                for (int b = 0; b < DJ; ++b) {
+                    if constexpr (VEC) {
+                        load_row<4, FULL>(vr, 64 * b + 4 * lr, d, vf[u][i][b]);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int ch = 64 * b + 4 * lr + e;
+                            vf[u][i][b][e] = ch < d ? to_f32(vr[ch]) : 0.f;
+                        }
+                    }
+                }
+            }
         }
-        const float wm = wave_max(z);
-        if (lane == 0) red[wave] = wm;
-        __syncthreads();
-        float tm = -INFINITY;
-        for (int w = 0; w < kThreads / kWave; ++w) tm = fmaxf(tm, red[w]);
-        const float m_new = fmaxf(m_run, tm);
-        const float pj = (j <= t) ? expf(z - m_new) : 0.f;
-        ps[threadIdx.x] = pj;
-        const float wsum = wave_sum(pj);
-        __syncthreads();  // ps complete, red (max) consumed
-        if (lane == 0) red[wave] = wsum;
-        __syncthreads();
-        float tsum = 0.f;
-        for (int w = 0; w < kThreads / kWave; ++w) tsum += red[w];
-        const float corr = expf(m_run - m_new);  // 0 on the first tile (m_run = -inf)
-        l_run = l_run * corr + tsum;
-        m_run = m_new;
-        if (threadIdx.x < d) {
-            acc *= corr;
-            const int cnt = min(kThreads, t + 1 - j0);
-            for (int jj = 0; jj < cnt; ++jj)
-                acc = fmaf(ps[jj], to_f32(v[((size_t)(j0 + jj) * Hkv + hk) * d + threadIdx.x]), acc);
-        }
-        __syncthreads();  // before ps / red are overwritten
+        f32x4 z[KT];
+#pragma unroll
+        for (int u = 0; u < KT; ++u) z[u] = zero4();
+        products(kf, qf, lb, z);
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < KT; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (key0 + 16 * u + 4 * lb + i > q0 + lr) z[u][i] = -INFINITY;
+                tmax = fmaxf(tmax, z[u][i]);
+            }
+        // (a trip starts at or before the block's first query: every query sees a key of every trip)
+        const float nm = fmaxf(run_m, groups_max(tmax) * scale2);
+        const float ref = nm == -INFINITY ? 0.f : nm, corr = ex2(run_m - ref);
+        float ts = 0.f;
+#pragma unroll
+        for (int u = 0; u < KT; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                z[u][i] = ex2(fmaf(z[u][i], scale2, -ref));
+                ts += z[u][i];
+            }
+        run_l = run_l * corr + ts;
+        run_m = nm;
+#pragma unroll
+        for (int b = 0; b < DJ; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[b][e][i] *= corr;
+#pragma unroll
+        for (int u = 0; u < KT; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int b = 0; b < DJ; ++b)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[b][e] = mfma4(vf[u][i][b][e], z[u][i], acc[b][e]);
     }
-    if (threadIdx.x < d) o[((size_t)t * Hq + h) * d + threadIdx.x] = from_f32<T>(acc / l_run);
+    run_l = groups_sum(run_l);
+#pragma unroll
+    for (int b = 0; b < DJ; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<f32x4 *>(&so[w][lr][64 * b + 16 * lb + 4 * i]) =
+                f32x4{acc[b][0][i], acc[b][1][i], acc[b][2][i], acc[b][3][i]};
+    if (lb == 0) {
+        sm[w][lr] = run_m;
+        sl[w][lr] = run_l;
+    }
+    __syncthreads();
+    for (int e = tid; e < 16 * d; e += NW * kWave) {
+        const int r = e / d, ch = e - r * d;
+        if (q0 + r >= Tn) break;
+        float mx = sm[0][r];  // wave 0 always has a trip
+#pragma unroll
+        for (int u = 1; u < NW; ++u) mx = fmaxf(mx, sm[u][r]);
+        const float ref = mx == -INFINITY ? 0.f : mx;
+        float num = 0.f, den = 0.f;
+#pragma unroll
+        for (int u = 0; u < NW; ++u) {
+            const float cw = ex2(sm[u][r] - ref);  // 0 for a wave without trips
+            num = fmaf(cw, so[u][r][ch], num);
+            den = fmaf(cw, sl[u][r], den);
+        }
+        o[((size_t)(q0 + r) * Hq + h) * d + ch] = from_f32<T>(num / den);
+    }
+}
+
+// Rows of `len` elements from bases `p...` can be read 4 elements at a time.
+template <typename T, typename... Ptr>
+inline bool vec4(int len, const Ptr *...p) {
+    return len % 4 == 0 && ((... | (uintptr_t)p) % (4 * sizeof(T))) == 0;
+}
+// LAUNCH(operand registers, exact): rows of `len` elements fill 1, 4 or 8 operand vectors a lane, exactly or
+// with zeros behind them; 0: longer rows or no vectors, operands are read per product.
+#define STRD_BY_ROW(LAUNCH, vec, len)                \
+    if (!(vec) || (len) > 128) { LAUNCH(0, false); } \
+    else if ((len) == 16) { LAUNCH(1, true); }       \
+    else if ((len) < 16) { LAUNCH(1, false); }       \
+    else if ((len) == 64) { LAUNCH(4, true); }       \
+    else if ((len) < 64) { LAUNCH(4, false); }       \
+    else if ((len) == 128) { LAUNCH(8, true); }      \
+    else { LAUNCH(8, false); }
+
+struct StatPlan {
+    int nrb, nslice, keys_per_slice;
+};
+// About 1024 workgroups of pass 1 over all sequences, and at most 32 slices: pass 2 reads every slice's
+// statistics once per workgroup.
+StatPlan stat_plan(int M, int N, int Hq, int Hkv, int nseq) {
+    StatPlan p;
+    p.nrb = ceil_div(M * (Hq / Hkv), kStatRows);
+    const long long units = (long long)p.nrb * Hkv * nseq;
+    const int want = (int)std::max(1LL, std::min({32LL, 1024 / std::min(1024LL, units), (long long)ceil_div(N, 64)}));
+    p.keys_per_slice = ceil_div(ceil_div(N, want), 64) * 64;
+    p.nslice = ceil_div(N, p.keys_per_slice);
+    return p;
 }
 
 }  // namespace
 
 // ------------------------------------------------------------------ host launchers ---------
-size_t score_attn_general_ws(int M, int Hq) { return align_up((size_t)M * Hq * sizeof(float), 256); }
+size_t score_attn_general_ws(int M, int N, int Hq, int Hkv, int nseq) {
+    return align_up((size_t)2 * stat_plan(M, N, Hq, Hkv, nseq).nslice * M * Hq * nseq * sizeof(float), 256);
+}
 
 template <typename T, class SEQ>
-static void score_attn_launch(const void *q, const void *k, float *s, int M, int N, int Hq, int Hkv, int d, float scale,
-                              float *lse, size_t sm, const SEQ &seq, int nseq, int ld, hipStream_t st) {
-    attn_row_lse_kernel<T, SEQ><<<dim3(M * Hq, nseq), kThreads, sm, st>>>((const T *)q, (const T *)k, lse, N, Hq, Hkv, d,
-                                                                         scale, seq, M * Hq);
-    attn_col_sum_kernel<T, SEQ><<<dim3(ceil_div(N, kThreads), nseq), kThreads, 0, st>>>((const T *)q, (const T *)k, lse, s,
-                                                                                      M, N, Hq, Hkv, d, scale, seq,
-                                                                                      M * Hq, ld);
+static int score_attn_launch(const void *q, const void *k, float *s, int M, int N, int Hq, int Hkv, int d, float scale,
+                             void *ws, const SEQ &seq, int nseq, int ld, hipStream_t st) {
+    const StatPlan p = stat_plan(M, N, Hq, Hkv, nseq);
+    const long long grid1 = (long long)p.nrb * Hkv * p.nslice;
+    if (grid1 > 0x7FFFFFFFLL) return STRD_EUNSUPPORTED;
+    const size_t stride = (size_t)p.nslice * M * Hq;
+    float *pmax = (float *)ws, *psum = pmax + stride * nseq;
+#define STRD_SCORE_ATTN(KJ, FULL)                                                                                         \
+    attn_stats_kernel<T, KJ, FULL, SEQ><<<dim3((unsigned)grid1, nseq), 256, 0, st>>>(                                      \
+        (const T *)q, (const T *)k, pmax, psum, M, N, Hq, Hkv, d, scale * kLog2e, p.nrb, p.keys_per_slice, seq, stride);  \
+    attn_col_sum_kernel<T, KJ, FULL, SEQ><<<dim3(ceil_div(N, 16), nseq), kColThreads, 0, st>>>(                            \
+        (const T *)q, (const T *)k, pmax, psum, s, M, N, Hq, Hkv, d, scale * kLog2e, p.nslice, seq, stride, ld)
+    STRD_BY_ROW(STRD_SCORE_ATTN, vec4<T>(d, (const T *)q, (const T *)k), d)
+#undef STRD_SCORE_ATTN
+    return launch_status();
 }
 
 int score_attn_general(const void *q, const void *k, float *s, int M, int N, int Hq, int Hkv, int d,
                        float scale, strd_dtype io, void *ws, hipStream_t st) {
-    const size_t sm = (size_t)(d + 2 * (kThreads / kWave)) * sizeof(float);
-    if (sm > 60000) return STRD_EUNSUPPORTED;
-    if (io == STRD_F32)
-        score_attn_launch<float>(q, k, s, M, N, Hq, Hkv, d, scale, (float *)ws, sm, OneSeq(), 1, 0, st);
-    else
-        score_attn_launch<bf16_t>(q, k, s, M, N, Hq, Hkv, d, scale, (float *)ws, sm, OneSeq(), 1, 0, st);
-    return launch_status();
+    if (io == STRD_F32) return score_attn_launch<float>(q, k, s, M, N, Hq, Hkv, d, scale, ws, OneSeq(), 1, 0, st);
+    return score_attn_launch<bf16_t>(q, k, s, M, N, Hq, Hkv, d, scale, ws, OneSeq(), 1, 0, st);
 }
 
-// Packed batch: grids sized for the longest sequence, lse of sequence b at ws + b * max_m * Hq floats.
+// Packed batch: grids sized for the longest sequence, statistics of every sequence in a region of its own.
 int score_attn_general_varlen(const void *q, const void *k, float *s, int ld, const SeqTab &tab, int nseq, int max_m,
                               int max_n, int Hq, int Hkv, int d, float scale, strd_dtype io, void *ws, hipStream_t st) {
-    const size_t sm = (size_t)(d + 2 * (kThreads / kWave)) * sizeof(float);
-    if (sm > 60000) return STRD_EUNSUPPORTED;
     if (io == STRD_F32)
-        score_attn_launch<float>(q, k, s, max_m, max_n, Hq, Hkv, d, scale, (float *)ws, sm, tab, nseq, ld, st);
-    else
-        score_attn_launch<bf16_t>(q, k, s, max_m, max_n, Hq, Hkv, d, scale, (float *)ws, sm, tab, nseq, ld, st);
+        return score_attn_launch<float>(q, k, s, max_m, max_n, Hq, Hkv, d, scale, ws, tab, nseq, ld, st);
+    return score_attn_launch<bf16_t>(q, k, s, max_m, max_n, Hq, Hkv, d, scale, ws, tab, nseq, ld, st);
+}
+
+template <typename T, class SEQ>
+static int score_mamba_launch(const void *B, const void *C, const float *dt, float *s, int M, int N, int H, int G, int n,
+                              const SEQ &seq, int nseq, int ld, hipStream_t st) {
+    const dim3 grid(ceil_div(N, 16), nseq);
+#define STRD_SCORE_MAMBA(KJ, FULL)                                                                                 \
+    mamba_score_kernel<T, KJ, FULL, SEQ><<<grid, kColThreads, 0, st>>>((const T *)B, (const T *)C, dt, s, M, N, H, G, n, \
+                                                                       seq, ld)
+    STRD_BY_ROW(STRD_SCORE_MAMBA, vec4<T>(n, (const T *)B, (const T *)C), n)
+#undef STRD_SCORE_MAMBA
     return launch_status();
 }
 
 int score_mamba_general(const void *B, const void *C, const float *dt, float *s, int M, int N, int H,
                         int G, int n, strd_dtype io, hipStream_t st) {
-    const int grid = ceil_div(N, kThreads);
-    if (io == STRD_F32)
-        mamba_score_kernel<float, OneSeq><<<grid, kThreads, 0, st>>>((const float *)B, (const float *)C, dt, s, M, N, H, G, n,
-                                                                     OneSeq(), 0);
-    else
-        mamba_score_kernel<bf16_t, OneSeq><<<grid, kThreads, 0, st>>>((const bf16_t *)B, (const bf16_t *)C, dt, s, M, N, H, G,
-                                                                      n, OneSeq(), 0);
-    return launch_status();
+    if (io == STRD_F32) return score_mamba_launch<float>(B, C, dt, s, M, N, H, G, n, OneSeq(), 1, 0, st);
+    return score_mamba_launch<bf16_t>(B, C, dt, s, M, N, H, G, n, OneSeq(), 1, 0, st);
 }
 
 int score_mamba_general_varlen(const void *B, const void *C, const float *dt, float *s, int ld, const SeqTab &tab, int nseq, int max_n,
                                int H, int G, int n, strd_dtype io, hipStream_t st) {
-    const dim3 grid(ceil_div(max_n, kThreads), nseq);
-    if (io == STRD_F32)
-        mamba_score_kernel<float, SeqTab><<<grid, kThreads, 0, st>>>((const float *)B, (const float *)C, dt, s, 0, 0, H, G, n,
-                                                                     tab, ld);
-    else
-        mamba_score_kernel<bf16_t, SeqTab><<<grid, kThreads, 0, st>>>((const bf16_t *)B, (const bf16_t *)C, dt, s, 0, 0, H, G,
-                                                                      n, tab, ld);
-    return launch_status();
+    if (io == STRD_F32) return score_mamba_launch<float>(B, C, dt, s, 0, max_n, H, G, n, tab, nseq, ld, st);
+    return score_mamba_launch<bf16_t>(B, C, dt, s, 0, max_n, H, G, n, tab, nseq, ld, st);
 }
 
-bool ssd_general_supported(int n) { return n >= 1 && n <= kSlice * kWave; }
+bool ssd_general_supported(int n) { return n >= 1 && n <= 1024; }
+
+// Workspace: the state before every chunk [H][chunks][P][n] and the chunks' total decays [H][chunks].
+size_t ssd_general_ws(int T, int H, int P, int n) {
+    const size_t nc = ceil_div(T, kChunk);
+    return align_up((size_t)H * nc * P * n * sizeof(float), 256) + align_up((size_t)H * nc * sizeof(float), 256);
+}
+
+template <typename T>
+static int ssd_launch(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D,
+                      const float *S_in, void *y, float *S_out, int Tn, int H, int P, int G, int n, void *ws,
+                      hipStream_t st) {
+    const int nc = ceil_div(Tn, kChunk), nst = S_out ? nc : nc - 1;  // chunks whose contribution to the state is needed
+    float *L = (float *)ws;
+    float *decay = (float *)((char *)ws + align_up((size_t)H * nc * P * n * sizeof(float), 256));
+    const bool vec = vec4<T>(P, (const T *)x, (const T *)y) && vec4<T>(n, (const T *)B, (const T *)C);
+    const int cpl = !vec ? 1 : P > 32 ? 4 : 2, npl = vec && n >= 64 ? 4 : 1;
+    const int pblocks = ceil_div(P, 16 * cpl), nblocks = ceil_div(n, 16 * npl);
+    const long long grid1 = (long long)nst * H * pblocks * nblocks, total = (long long)H * P * n, grid3 = (long long)nc * H;
+    if (grid1 > 0x7FFFFFFFLL || grid3 > 0x7FFFFFFFLL || (long long)P * n > 0x7FFFFFFFLL)
+        return STRD_EUNSUPPORTED;
+    const long long grid2 = (total + kWave - 1) / kWave;
+    if (grid2 > 0x7FFFFFFFLL) return STRD_EUNSUPPORTED;
+#define STRD_SSD_STATE(CC, NN, FF)                                                                                   \
+    ssd_chunk_state_kernel<T, CC, NN, FF><<<(unsigned)grid1, kWave, 0, st>>>((const T *)x, dt, A, (const T *)B, L, decay, \
+                                                                             Tn, H, P, G, n, nc, nst, pblocks)
+#define STRD_SSD_STATE_N(CC, FF)                   \
+    if (npl == 4) { STRD_SSD_STATE(CC, 4, FF); }   \
+    else { STRD_SSD_STATE(CC, 1, FF); }
+    if (nst > 0) {
+        const bool full = P % (16 * cpl) == 0 && n % (16 * npl) == 0;
+        if (cpl == 4 && full) { STRD_SSD_STATE_N(4, true) }
+        else if (cpl == 4) { STRD_SSD_STATE_N(4, false) }
+        else if (cpl == 2 && full) { STRD_SSD_STATE_N(2, true) }
+        else if (cpl == 2) { STRD_SSD_STATE_N(2, false) }
+        else STRD_SSD_STATE(1, 1, false);
+    }
+#undef STRD_SSD_STATE_N
+#undef STRD_SSD_STATE
+    // nothing to pass on where one chunk starts from zero and nobody asks for its state
+    if (nst > 0 || S_in)
+        ssd_pass_kernel<<<(unsigned)grid2, kWave, 0, st>>>(L, decay, S_in, S_out, total, P * n, nc, nst);
+    const int first_carried = S_in ? 0 : 1;
+#define STRD_SSD_OUT(CC, KK, FF)                                                                                     \
+    ssd_chunk_out_kernel<T, CC, KK, FF><<<(unsigned)grid3, 256, 0, st>>>((const T *)x, dt, A, (const T *)B, (const T *)C, D, \
+                                                                         L, (T *)y, Tn, H, P, G, n, nc, first_carried)
+#define STRD_SSD_OUT4(KK, FF) STRD_SSD_OUT(4, KK, FF)
+#define STRD_SSD_OUT2(KK, FF) STRD_SSD_OUT(2, KK, FF)
+    const bool pfull = P % (16 * cpl) == 0;
+    const int nn = pfull ? n : n - (n == 16 || n == 64 || n == 128);  // "exact" needs whole channel blocks as well
+    if (cpl == 4) { STRD_BY_ROW(STRD_SSD_OUT4, true, nn) }
+    else if (cpl == 2) { STRD_BY_ROW(STRD_SSD_OUT2, true, nn) }
+    else STRD_SSD_OUT(1, 0, false);
+#undef STRD_SSD_OUT2
+#undef STRD_SSD_OUT4
+#undef STRD_SSD_OUT
+    return launch_status();
+}
 
 int ssd_general(const void *x, const float *dt, const float *A, const void *B, const void *C,
                 const float *D, const float *S_in, void *y, float *S_out, int T, int H, int P, int G,
-                int n, strd_dtype io, hipStream_t st) {
-    int lanes = 1;
-    while (lanes * kSlice < n) lanes <<= 1;  // power of two <= 64, so a column never straddles a wave
-    const long long threads = (long long)H * P * lanes;
-    if (threads > (1LL << 30)) return STRD_EUNSUPPORTED;
-    const int grid = (int)((threads + kThreads - 1) / kThreads);
-    if (io == STRD_F32)
-        ssd_recurrence_kernel<float><<<grid, kThreads, 0, st>>>((const float *)x, dt, A, (const float *)B, (const float *)C, D, S_in, (float *)y, S_out, T, H, P, G, n, lanes);
-    else
-        ssd_recurrence_kernel<bf16_t><<<grid, kThreads, 0, st>>>((const bf16_t *)x, dt, A, (const bf16_t *)B, (const bf16_t *)C, D, S_in, (bf16_t *)y, S_out, T, H, P, G, n, lanes);
-    return launch_status();
+                int n, strd_dtype io, void *ws, hipStream_t st) {
+    if (T == 0) {  // no tokens: the state goes through
+        const long long total = (long long)H * P * n;
+        if (!S_out) return STRD_OK;
+        if ((total + kWave - 1) / kWave > 0x7FFFFFFFLL || (long long)P * n > 0x7FFFFFFFLL) return STRD_EUNSUPPORTED;
+        ssd_pass_kernel<<<(unsigned)((total + kWave - 1) / kWave), kWave, 0, st>>>(nullptr, nullptr, S_in, S_out, total, P * n,
+                                                                                  0, 0);
+        return launch_status();
+    }
+    if (io == STRD_F32) return ssd_launch<float>(x, dt, A, B, C, D, S_in, y, S_out, T, H, P, G, n, ws, st);
+    return ssd_launch<bf16_t>(x, dt, A, B, C, D, S_in, y, S_out, T, H, P, G, n, ws, st);
 }
 
-bool attn_general_supported(int d) { return d >= 1 && d <= kThreads; }
+bool attn_general_supported(int d) { return d >= 1 && d <= 256; }
+
+template <typename T>
+static int attn_launch(const void *q, const void *k, const void *v, void *o, int Tn, int Hq, int Hkv, int d, float scale,
+                       hipStream_t st) {
+    const long long grid = (long long)ceil_div(Tn, 16) * Hq;
+    if (grid > 0x7FFFFFFFLL || (long long)Hkv * d * (long long)sizeof(T) >= 1 << 24) return STRD_EUNSUPPORTED;
+#define STRD_ATTN(VV, FF, DD, NN)                                                                                      \
+    attn_tile_kernel<T, VV, FF, DD, NN><<<(unsigned)grid, NN * kWave, 0, st>>>((const T *)q, (const T *)k, (const T *)v, \
+                                                                               (T *)o, Tn, Hq, Hkv, d, scale * kLog2e)
+    if (!vec4<T>(d, (const T *)q, (const T *)k, (const T *)v)) {
+        if (d <= 64) STRD_ATTN(false, false, 1, 8);
+        else if (d <= 128) STRD_ATTN(false, false, 2, 4);
+        else STRD_ATTN(false, false, 4, 2);
+    } else if (d == 64) STRD_ATTN(true, true, 1, 8);
+    else if (d < 64) STRD_ATTN(true, false, 1, 8);
+    else if (d == 128) STRD_ATTN(true, true, 2, 4);
+    else if (d < 128) STRD_ATTN(true, false, 2, 4);
+    else if (d == 256) STRD_ATTN(true, true, 4, 2);
+    else STRD_ATTN(true, false, 4, 2);
+#undef STRD_ATTN
+    return launch_status();
+}
 
 int attn_general(const void *q, const void *k, const void *v, void *o, int T, int Hq, int Hkv, int d,
                  float scale, strd_dtype io, hipStream_t st) {
     if (T == 0) return STRD_OK;
-    if ((long long)T * Hq > 0x7FFFFFFFLL) return STRD_EUNSUPPORTED;
-    const size_t sm = (size_t)(d + kThreads + kThreads / kWave) * sizeof(float);
-    if (io == STRD_F32)
-        attn_row_kernel<float><<<T * Hq, kThreads, sm, st>>>((const float *)q, (const float *)k, (const float *)v, (float *)o, Hq, Hkv, d, scale);
-    else
-        attn_row_kernel<bf16_t><<<T * Hq, kThreads, sm, st>>>((const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v, (bf16_t *)o, Hq, Hkv, d, scale);
-    return launch_status();
+    if (io == STRD_F32) return attn_launch<float>(q, k, v, o, T, Hq, Hkv, d, scale, st);
+    return attn_launch<bf16_t>(q, k, v, o, T, Hq, Hkv, d, scale, st);
 }
 
 }  // namespace strd

@@ -1,0 +1,89 @@
+"""The general kernels (fp32 arithmetic, any shape) at the edges of their tiles: one token, a tile, a
+chunk and one more; rows of exactly 16, 64, 128 elements, rows with a padded end, rows read element by
+element; several key slices and row tiles; with and without a carried state.  Against the fp64 oracle at
+a tenth of the fp32 tolerance: sums of at most a few hundred products of 24-bit numbers stay within
+1e-5 of the largest result.  Needs a GPU."""
+import pytest
+import torch
+
+import oracle
+import paper_2603_00198_amd as strd
+from paper_2603_00198_amd import synth
+from util import TOL, assert_close
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+f = synth.np64
+F32, BF16 = torch.float32, torch.bfloat16
+BOUND = {F32: 1e-5, BF16: TOL[BF16]}
+
+
+def _say(msg):
+    print("[case] " + msg, flush=True)
+
+
+def _draw(seed, dtype):
+    g = torch.Generator().manual_seed(seed)
+    return lambda *shape: torch.randn(*shape, generator=g).to(dtype)
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("T,d", [(1, 64), (16, 64), (17, 20), (33, 7), (257, 64), (130, 128), (95, 80), (70, 130), (49, 256)])
+def test_attention(T, d, dtype):
+    if dtype == BF16 and d in (64, 128):
+        d += 4   # the bf16 matrix-core kernel owns 64 and 128
+    _say("general attn T=%d d=%d %s" % (T, d, dtype))
+    rn = _draw(T + d, dtype)
+    q, k, v = rn(T, 6, d), rn(T, 3, d), rn(T, 3, d)
+    assert_close(f(strd.attn_prefill(q.to(DEV), k.to(DEV), v.to(DEV))), oracle.attn(f(q), f(k), f(v)), BOUND[dtype], "o",
+                 units=(0, 1))
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("N,M,Hq,Hkv,d", [(1, 1, 1, 1, 16), (17, 5, 6, 2, 64), (300, 23, 4, 4, 12), (2100, 40, 8, 2, 128),
+                                          (129, 9, 3, 1, 130), (65, 700, 8, 2, 33)])
+def test_score_attn(N, M, Hq, Hkv, d, dtype):
+    if dtype == BF16 and d in (64, 128):
+        d += 4
+    _say("general score_attn N=%d M=%d Hq=%d Hkv=%d d=%d %s" % (N, M, Hq, Hkv, d, dtype))
+    rn = _draw(N + M, dtype)
+    q, k = rn(M, Hq, d), rn(N, Hkv, d)
+    assert_close(f(strd.score_attn(q.to(DEV), k.to(DEV))), oracle.score_attn(f(q), f(k)), BOUND[dtype], "s", units=(0,))
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("N,M,G,H,n", [(1, 1, 1, 1, 1), (33, 16, 1, 8, 16), (100, 37, 3, 6, 20), (47, 200, 2, 10, 128),
+                                       (260, 5, 8, 8, 130)])
+def test_score_mamba(N, M, G, H, n, dtype):
+    if dtype == BF16 and n in (64, 128):
+        n -= 4
+    _say("general score_mamba N=%d M=%d G=%d H=%d n=%d %s" % (N, M, G, H, n, dtype))
+    rn = _draw(N + M, dtype)
+    B, C, dt = rn(N, G, n), rn(M, G, n), torch.nn.functional.softplus(_draw(N, F32)(N, H))
+    assert_close(f(strd.score_mamba(B.to(DEV), C.to(DEV), dt.to(DEV))), oracle.score_mamba(f(B), f(C), f(dt)), BOUND[dtype],
+                 "s", units=(0,))
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("carry", [True, False])
+@pytest.mark.parametrize("T,H,P,G,n", [(0, 2, 32, 1, 16), (1, 2, 32, 1, 16), (64, 4, 64, 2, 64), (65, 3, 20, 1, 40),
+                                       (200, 2, 80, 1, 128), (130, 2, 33, 2, 7), (577, 8, 32, 1, 16), (129, 1, 64, 1, 200)])
+def test_scan(T, H, P, G, n, carry, dtype):
+    if dtype == BF16 and n in (64, 128):
+        n -= 4
+    _say("general scan T=%d H=%d P=%d G=%d n=%d carry=%s %s" % (T, H, P, G, n, carry, dtype))
+    rn, r32 = _draw(T + P, dtype), _draw(T + n, F32)
+    x, B, C = rn(T, H, P), rn(T, G, n), rn(T, G, n)
+    dt = torch.nn.functional.softplus(r32(T, H))
+    A = -torch.exp(2 * torch.rand(H, generator=torch.Generator().manual_seed(T)))
+    D, S_in = (r32(H), r32(H, P, n)) if carry else (None, None)
+    dev = lambda t: None if t is None else t.to(DEV)
+    y, S = strd.ssd_prefill(dev(x), dev(dt), dev(A), dev(B), dev(C), dev(D), dev(S_in))
+    if T == 0:
+        assert torch.equal(S.cpu(), S_in if carry else torch.zeros(H, P, n))
+        return
+    y_ref, S_ref = oracle.ssd_seq(f(x), f(dt), f(A), f(B), f(C), None if D is None else f(D), None if S_in is None else f(S_in))
+    assert_close(f(y), y_ref, BOUND[dtype], "y", units=(1,))
+    assert_close(f(S), S_ref, 1e-5 if dtype == F32 else BOUND[dtype], "S", units=(0,))
+    y2, none = strd.ssd_prefill(dev(x), dev(dt), dev(A), dev(B), dev(C), dev(D), dev(S_in), want_state=False)
+    assert none is None and torch.equal(y2, y)
