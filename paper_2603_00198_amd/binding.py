@@ -1,12 +1,14 @@
-"""ctypes binding of libstrd.so: same names as the C entry points, torch tensors in and out.
+"""Binding of libstrd.so: same names as the C entry points, torch tensors in and out.
 
-Only marshalling happens here: shape checks, output/workspace allocation through torch
-(device memory plumbing) and the current HIP stream.  Every step of the path runs in the
-library's kernels; if the library is missing the import of any function fails loudly.
+Only marshalling happens: shape checks, output/workspace allocation through torch (device memory
+plumbing) and the current HIP stream -- in the extension module strd_host (csrc/host.cpp) for the
+calls of a layer, where the host's time per call counts, and through ctypes here for the rest.  Every
+step of the path runs in the library's kernels; if a library is missing the first call fails loudly.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional, Sequence, Tuple
 
@@ -91,6 +93,25 @@ def lib():
     return _lib
 
 
+_host = None
+
+
+def host():
+    """The extension module that marshals the calls of a layer (raises if it has not been built)."""
+    global _host
+    if _host is None:
+        lib()
+        path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "strd_host.so")
+        if not os.path.exists(path):
+            raise StrdError("%s is missing: run `python -m paper_2603_00198_amd.build`" % path)
+        spec = importlib.util.spec_from_file_location("strd_host", path)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        mod.set_error(StrdError)
+        _host = mod
+    return _host
+
+
 def exported_symbols() -> Sequence[str]:
     return tuple(_SIGNATURES)
 
@@ -145,43 +166,13 @@ def _ws(nbytes: int, like: torch.Tensor) -> Tuple[Optional[torch.Tensor], int]:
 def score_attn(q_txt: torch.Tensor, k_vis: torch.Tensor, scale: Optional[float] = None,
                out: Optional[torch.Tensor] = None, ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """s[N] fp32 from text queries [M,Hq,d] and vision keys [N,Hkv,d]."""
-    _dev(q_txt, k_vis, out, ws)
-    M, Hq, d = q_txt.shape
-    N, Hkv, d2 = k_vis.shape
-    if d != d2 or q_txt.dtype != k_vis.dtype:
-        raise StrdError("q/k mismatch")
-    io = _io(q_txt)
-    if scale is None:
-        scale = d ** -0.5
-    if out is None:
-        out = torch.empty(N, dtype=torch.float32, device=q_txt.device)
-    need = lib().strd_score_attn_workspace(M, N, Hq, Hkv, d, io)
-    if ws is None:
-        ws, _ = _ws(need, q_txt)
-    _check(lib().strd_score_attn(_ptr(q_txt), _ptr(k_vis), _ptr(out), M, N, Hq, Hkv, d, scale, io,
-                                 _ptr(ws), 0 if ws is None else ws.numel(), _stream()), "score_attn")
-    return out
+    return (_host or host()).score_attn(q_txt, k_vis, scale, out, ws)
 
 
 def score_mamba(B_vis: torch.Tensor, C_txt: torch.Tensor, dt_vis: torch.Tensor,
                 out: Optional[torch.Tensor] = None, ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """s[N] fp32 from vision b [N,G,n], text c [M,G,n] and vision dt [N,H] (fp32)."""
-    _dev(B_vis, C_txt, dt_vis, out, ws)
-    N, G, n = B_vis.shape
-    M = C_txt.shape[0]
-    H = dt_vis.shape[1]
-    if C_txt.shape[1:] != (G, n) or dt_vis.shape[0] != N or dt_vis.dtype != torch.float32 \
-            or B_vis.dtype != C_txt.dtype:
-        raise StrdError("B/C/dt mismatch")
-    io = _io(B_vis)
-    if out is None:
-        out = torch.empty(N, dtype=torch.float32, device=B_vis.device)
-    need = lib().strd_score_mamba_workspace(M, N, H, G, n, io)
-    if ws is None:
-        ws, _ = _ws(need, B_vis)
-    _check(lib().strd_score_mamba(_ptr(B_vis), _ptr(C_txt), _ptr(dt_vis), _ptr(out), M, N, H, G, n, io,
-                                  _ptr(ws), 0 if ws is None else ws.numel(), _stream()), "score_mamba")
-    return out
+    return (_host or host()).score_mamba(B_vis, C_txt, dt_vis, out, ws)
 
 
 def score_mamba_full(B_vis: torch.Tensor, C_txt: torch.Tensor, dt_all: torch.Tensor, A: torch.Tensor,
@@ -209,18 +200,7 @@ def score_mamba_full(B_vis: torch.Tensor, C_txt: torch.Tensor, dt_all: torch.Ten
 def select_topk(scores: torch.Tensor, K: int, out: Optional[torch.Tensor] = None,
                 ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """idx[K] int32 ascending: the K highest scores, ties to the lowest index."""
-    _dev(scores, out, ws)
-    if scores.dtype != torch.float32 or scores.dim() != 1:
-        raise StrdError("scores must be a 1-D fp32 tensor")
-    N = scores.shape[0]
-    if out is None:
-        out = torch.empty(K, dtype=torch.int32, device=scores.device)
-    need = lib().strd_select_topk_workspace(N, K)
-    if ws is None:
-        ws, _ = _ws(need, scores)
-    _check(lib().strd_select_topk(_ptr(scores), N, K, _ptr(out), _ptr(ws), 0 if ws is None else ws.numel(),
-                                  _stream()), "select_topk")
-    return out
+    return (_host or host()).select_topk(scores, K, out, ws)
 
 
 def select_topk_noalloc(scores: torch.Tensor, K: int, out: torch.Tensor) -> torch.Tensor:
@@ -267,23 +247,7 @@ def compact_batch(srcs: Sequence[torch.Tensor], idx: torch.Tensor, N: int, M: in
                   pos_in: Optional[torch.Tensor] = None, want_pos: bool = False,
                   outs: Optional[Sequence[torch.Tensor]] = None):
     """One-launch gather of several [N+M, ...] tensors by the same idx; returns (dsts, pos_out or None)."""
-    _dev(idx, pos_in, *srcs)
-    if idx.dtype != torch.int32:
-        raise StrdError("idx must be int32")
-    K = idx.shape[0]
-    if outs is None:
-        outs = [torch.empty((K + M,) + tuple(t.shape[1:]), dtype=t.dtype, device=t.device) for t in srcs]
-    _dev(*outs)
-    items = (_CompactItem * max(len(srcs), 1))()
-    for i, (t, o) in enumerate(zip(srcs, outs)):
-        if t.shape[0] != N + M or o.shape[0] != K + M or o.dtype != t.dtype or o.shape[1:] != t.shape[1:]:
-            raise StrdError("compact_batch: tensor %d has the wrong shape" % i)
-        items[i].src, items[i].dst = t.data_ptr(), o.data_ptr()
-        items[i].row_bytes = int(torch.Size(t.shape[1:]).numel()) * t.element_size()
-    pos_out = torch.empty(K + M, dtype=torch.int32, device=idx.device) if (want_pos or pos_in is not None) else None
-    _check(lib().strd_compact_batch(ctypes.cast(items, _vp), len(srcs), _ptr(idx), N, M, K, _ptr(pos_in),
-                                    _ptr(pos_out), _stream()), "compact_batch")
-    return list(outs), pos_out
+    return (_host or host()).compact_batch(srcs, idx, N, M, pos_in, want_pos, outs)
 
 
 def mfma_rate_probe(workgroups: int, iters: int, random_operands: bool, out: Optional[torch.Tensor] = None,
@@ -303,88 +267,27 @@ class _Seq(ctypes.Structure):
     _fields_ = [("N", ctypes.c_int32), ("M", ctypes.c_int32), ("K", ctypes.c_int32)]
 
 
-def _seq_array(seqs):
-    arr = (_Seq * len(seqs))()
-    for i, (n, m, k) in enumerate(seqs):
-        arr[i].N, arr[i].M, arr[i].K = int(n), int(m), int(k)
-    return arr
-
-
-def _varlen_ld(seqs, ld):
-    return (max(int(n) for n, _, _ in seqs) + 3) // 4 * 4 if ld is None else int(ld)
-
-
 def score_attn_varlen(q_all: torch.Tensor, k_all: torch.Tensor, seqs, scale: Optional[float] = None,
                       ld: Optional[int] = None, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """scores [nseq, ld] fp32 of a packed batch: q_all [rows,Hq,d], k_all [rows,Hkv,d]."""
-    _dev(q_all, k_all, out)
-    rows, Hq, d = q_all.shape
-    Hkv = k_all.shape[1]
-    if k_all.shape[0] != rows or k_all.shape[2] != d or q_all.dtype != k_all.dtype \
-            or rows != sum(int(n) + int(m) for n, m, _ in seqs):
-        raise StrdError("score_attn_varlen: q/k/seqs mismatch")
-    io, ld, arr = _io(q_all), _varlen_ld(seqs, ld), _seq_array(seqs)
-    if scale is None:
-        scale = d ** -0.5
-    if out is None:
-        out = torch.zeros(len(seqs), ld, dtype=torch.float32, device=q_all.device)
-    ws, nb = _ws(lib().strd_score_attn_varlen_workspace(ctypes.cast(arr, _vp), len(seqs), Hq, Hkv, d, io), q_all)
-    _check(lib().strd_score_attn_varlen(_ptr(q_all), _ptr(k_all), _ptr(out), ld, ctypes.cast(arr, _vp), len(seqs), Hq, Hkv,
-                                        d, scale, io, _ptr(ws), nb, _stream()), "score_attn_varlen")
-    return out
+    return (_host or host()).score_attn_varlen(q_all, k_all, seqs, scale, ld, out)
 
 
 def score_mamba_varlen(B_all: torch.Tensor, C_all: torch.Tensor, dt_all: torch.Tensor, seqs,
                        ld: Optional[int] = None, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """scores [nseq, ld] fp32 of a packed batch: B_all, C_all [rows,G,n], dt_all [rows,H] fp32."""
-    _dev(B_all, C_all, dt_all, out)
-    rows, G, n = B_all.shape
-    H = dt_all.shape[1]
-    if C_all.shape != B_all.shape or dt_all.shape[0] != rows or dt_all.dtype != torch.float32 \
-            or B_all.dtype != C_all.dtype or rows != sum(int(a) + int(m) for a, m, _ in seqs):
-        raise StrdError("score_mamba_varlen: B/C/dt/seqs mismatch")
-    io, ld, arr = _io(B_all), _varlen_ld(seqs, ld), _seq_array(seqs)
-    if out is None:
-        out = torch.zeros(len(seqs), ld, dtype=torch.float32, device=B_all.device)
-    ws, nb = _ws(lib().strd_score_mamba_varlen_workspace(ctypes.cast(arr, _vp), len(seqs), H, G, n, io), B_all)
-    _check(lib().strd_score_mamba_varlen(_ptr(B_all), _ptr(C_all), _ptr(dt_all), _ptr(out), ld, ctypes.cast(arr, _vp),
-                                         len(seqs), H, G, n, io, _ptr(ws), nb, _stream()), "score_mamba_varlen")
-    return out
+    return (_host or host()).score_mamba_varlen(B_all, C_all, dt_all, seqs, ld, out)
 
 
 def select_topk_varlen(scores: torch.Tensor, seqs, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """idx [sum K] int32: per sequence, the K_b best of scores[b, :N_b], ascending, local to the sequence."""
-    _dev(scores, out)
-    if scores.dtype != torch.float32 or scores.dim() != 2 or scores.shape[0] != len(seqs):
-        raise StrdError("select_topk_varlen: scores must be fp32 [nseq, ld]")
-    arr = _seq_array(seqs)
-    if out is None:
-        out = torch.empty(sum(int(k) for _, _, k in seqs), dtype=torch.int32, device=scores.device)
-    _check(lib().strd_select_topk_varlen(_ptr(scores), scores.shape[1], ctypes.cast(arr, _vp), len(seqs), _ptr(out),
-                                         _stream()), "select_topk_varlen")
-    return out
+    return (_host or host()).select_topk_varlen(scores, seqs, out)
 
 
 def compact_varlen(srcs: Sequence[torch.Tensor], idx: torch.Tensor, seqs, pos_in: Optional[torch.Tensor] = None,
                    want_pos: bool = False):
     """One-launch gather of several packed [rows, ...] tensors; returns (dsts [sum(K+M), ...], pos_out or None)."""
-    _dev(idx, pos_in, *srcs)
-    rows = sum(int(n) + int(m) for n, m, _ in seqs)
-    rows_out = sum(int(k) + int(m) for _, m, k in seqs)
-    if idx.dtype != torch.int32 or idx.shape[0] != sum(int(k) for _, _, k in seqs):
-        raise StrdError("compact_varlen: idx must be int32 [sum K]")
-    outs = [torch.empty((rows_out,) + tuple(t.shape[1:]), dtype=t.dtype, device=t.device) for t in srcs]
-    items = (_CompactItem * max(len(srcs), 1))()
-    for i, (t, o) in enumerate(zip(srcs, outs)):
-        if t.shape[0] != rows:
-            raise StrdError("compact_varlen: tensor %d has the wrong number of rows" % i)
-        items[i].src, items[i].dst = t.data_ptr(), o.data_ptr()
-        items[i].row_bytes = int(torch.Size(t.shape[1:]).numel()) * t.element_size()
-    pos_out = torch.empty(rows_out, dtype=torch.int32, device=idx.device) if (want_pos or pos_in is not None) else None
-    arr = _seq_array(seqs)
-    _check(lib().strd_compact_varlen(ctypes.cast(items, _vp), len(srcs), _ptr(idx), ctypes.cast(arr, _vp), len(seqs),
-                                     _ptr(pos_in), _ptr(pos_out), _stream()), "compact_varlen")
-    return outs, pos_out
+    return (_host or host()).compact_varlen(srcs, idx, seqs, pos_in, want_pos)
 
 
 def ssd_prefill(x: torch.Tensor, dt: torch.Tensor, A: torch.Tensor, B: torch.Tensor, C: torch.Tensor,
@@ -392,25 +295,7 @@ def ssd_prefill(x: torch.Tensor, dt: torch.Tensor, A: torch.Tensor, B: torch.Ten
                 want_state: bool = True, out: Optional[torch.Tensor] = None,
                 ws: Optional[torch.Tensor] = None):
     """Mamba-2 scan: returns (y [T,H,P], S_out [H,P,n] fp32 or None)."""
-    _dev(x, dt, A, B, C, D, S_in, out, ws)
-    T, H, P = x.shape
-    G, n = B.shape[1:]
-    if dt.shape != (T, H) or A.shape != (H,) or B.shape != (T, G, n) or C.shape != (T, G, n) \
-            or dt.dtype != torch.float32 or A.dtype != torch.float32 or B.dtype != x.dtype or C.dtype != x.dtype:
-        raise StrdError("ssd_prefill: inconsistent shapes or dtypes")
-    for t, shp in ((D, (H,)), (S_in, (H, P, n))):
-        if t is not None and (tuple(t.shape) != shp or t.dtype != torch.float32):
-            raise StrdError("ssd_prefill: D / S_in must be fp32 of shape %s" % (shp,))
-    io = _io(x)
-    y = out if out is not None else torch.empty_like(x)
-    S_out = torch.empty(H, P, n, dtype=torch.float32, device=x.device) if want_state else None
-    need = lib().strd_ssd_prefill_workspace(T, H, P, G, n, chunk, io)
-    if ws is None:
-        ws, _ = _ws(need, x)
-    _check(lib().strd_ssd_prefill(_ptr(x), _ptr(dt), _ptr(A), _ptr(B), _ptr(C), _ptr(D), _ptr(S_in), _ptr(y),
-                                  _ptr(S_out), T, H, P, G, n, chunk, io, _ptr(ws),
-                                  0 if ws is None else ws.numel(), _stream()), "ssd_prefill")
-    return y, S_out
+    return (_host or host()).ssd_prefill(x, dt, A, B, C, D, S_in, chunk, want_state, out, ws)
 
 
 def ssd_prefill_gather(x: torch.Tensor, dt: torch.Tensor, A: torch.Tensor, B: torch.Tensor, C: torch.Tensor,
@@ -418,44 +303,13 @@ def ssd_prefill_gather(x: torch.Tensor, dt: torch.Tensor, A: torch.Tensor, B: to
                        S_in: Optional[torch.Tensor] = None, chunk: int = 256, want_state: bool = True,
                        out: Optional[torch.Tensor] = None, ws: Optional[torch.Tensor] = None):
     """Mamba-2 scan over rows idx (vision) + the M text rows of the uncompacted inputs [N+M, ...]."""
-    _dev(x, dt, A, B, C, D, S_in, idx, out, ws)
-    Ttot, H, P = x.shape
-    G, n = B.shape[1:]
-    K = idx.shape[0]
-    if Ttot != N + M or dt.shape != (Ttot, H) or A.shape != (H,) or B.shape != (Ttot, G, n) or C.shape != (Ttot, G, n) \
-            or dt.dtype != torch.float32 or A.dtype != torch.float32 or B.dtype != x.dtype or C.dtype != x.dtype \
-            or idx.dtype != torch.int32:
-        raise StrdError("ssd_prefill_gather: inconsistent shapes or dtypes")
-    io = _io(x)
-    y = out if out is not None else torch.empty((K + M, H, P), dtype=x.dtype, device=x.device)
-    S_out = torch.empty(H, P, n, dtype=torch.float32, device=x.device) if want_state else None
-    if ws is None:
-        ws, _ = _ws(lib().strd_ssd_prefill_workspace(K + M, H, P, G, n, chunk, io), x)
-    _check(lib().strd_ssd_prefill_gather(_ptr(x), _ptr(dt), _ptr(A), _ptr(B), _ptr(C), _ptr(D), _ptr(S_in), _ptr(idx),
-                                         _ptr(y), _ptr(S_out), N, M, K, H, P, G, n, chunk, io, _ptr(ws),
-                                         0 if ws is None else ws.numel(), _stream()),
-           "ssd_prefill_gather")
-    return y, S_out
+    return (_host or host()).ssd_prefill_gather(x, dt, A, B, C, idx, N, M, D, S_in, chunk, want_state, out, ws)
 
 
 def attn_prefill(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, scale: Optional[float] = None,
                  out: Optional[torch.Tensor] = None, ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Causal GQA attention: o [T,Hq,d]."""
-    _dev(q, k, v, out, ws)
-    T, Hq, d = q.shape
-    Hkv = k.shape[1]
-    if k.shape != (T, Hkv, d) or v.shape != (T, Hkv, d) or k.dtype != q.dtype or v.dtype != q.dtype:
-        raise StrdError("attn_prefill: inconsistent shapes or dtypes")
-    io = _io(q)
-    if scale is None:
-        scale = d ** -0.5
-    o = out if out is not None else torch.empty_like(q)
-    need = lib().strd_attn_prefill_workspace(T, Hq, Hkv, d, io)
-    if ws is None:
-        ws, _ = _ws(need, q)
-    _check(lib().strd_attn_prefill(_ptr(q), _ptr(k), _ptr(v), _ptr(o), T, Hq, Hkv, d, scale, io, _ptr(ws),
-                                   0 if ws is None else ws.numel(), _stream()), "attn_prefill")
-    return o
+    return (_host or host()).attn_prefill(q, k, v, scale, out, ws)
 
 
 def avgpool(src: torch.Tensor, N: int, M: int, K: int, pos_in: Optional[torch.Tensor] = None,
@@ -476,38 +330,14 @@ def ssd_decode_step(x: torch.Tensor, dt: torch.Tensor, A: torch.Tensor, B: torch
                     D: Optional[torch.Tensor], S: torch.Tensor) -> torch.Tensor:
     """One token of the recurrence: x [H,P], dt [H] fp32, B, C [G,n], S [H,P,n] fp32 updated in
     place; returns y [H,P]."""
-    _dev(x, dt, A, B, C, D, S)
-    H, P = x.shape
-    G, n = B.shape
-    if dt.shape != (H,) or A.shape != (H,) or C.shape != (G, n) or S.shape != (H, P, n) or S.dtype != torch.float32 \
-            or dt.dtype != torch.float32 or A.dtype != torch.float32 or B.dtype != x.dtype or C.dtype != x.dtype \
-            or (D is not None and (D.shape != (H,) or D.dtype != torch.float32)):
-        raise StrdError("ssd_decode_step: inconsistent shapes or dtypes")
-    y = torch.empty_like(x)
-    _check(lib().strd_ssd_decode_step(_ptr(x), _ptr(dt), _ptr(A), _ptr(B), _ptr(C), _ptr(D), _ptr(S), _ptr(y), H, P,
-                                      G, n, _io(x), _stream()), "ssd_decode_step")
-    return y
+    return (_host or host()).ssd_decode_step(x, dt, A, B, C, D, S)
 
 
 def attn_decode_step(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Tensor, scale: Optional[float] = None,
                      ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """The newest token's attention over the T cached rows (its own included): q [Hq,d],
     k_cache, v_cache [T,Hkv,d]; returns o [Hq,d]."""
-    _dev(q, k_cache, v_cache, ws)
-    Hq, d = q.shape
-    T, Hkv = k_cache.shape[:2]
-    if k_cache.shape != (T, Hkv, d) or v_cache.shape != (T, Hkv, d) or k_cache.dtype != q.dtype \
-            or v_cache.dtype != q.dtype:
-        raise StrdError("attn_decode_step: inconsistent shapes or dtypes")
-    io = _io(q)
-    if scale is None:
-        scale = d ** -0.5
-    o = torch.empty_like(q)
-    if ws is None:
-        ws, _ = _ws(lib().strd_attn_decode_step_workspace(T, Hq, Hkv, d, io), q)
-    _check(lib().strd_attn_decode_step(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(o), T, Hq, Hkv, d, scale, io,
-                                       _ptr(ws), 0 if ws is None else ws.numel(), _stream()), "attn_decode_step")
-    return o
+    return (_host or host()).attn_decode_step(q, k_cache, v_cache, scale, ws)
 
 
 def schedule_budgets(alpha: Sequence[float], N0: int, K_min: int = 0):
@@ -528,27 +358,10 @@ def schedule_sigmoid(L: int, a_start: float = 1.0, a_end: float = 0.125, k: floa
 
 
 # ------------------------------------------------------------------ block glue -------------
-def _rows(t: torch.Tensor, what: str) -> int:
-    """Row pitch in elements of a 2-D GPU tensor whose rows are contiguous (a column slice is fine)."""
-    if not t.is_cuda:
-        raise StrdError("tensors must live on the GPU")
-    if t.dim() != 2 or t.stride(1) != 1:
-        raise StrdError("%s: rows must be contiguous" % what)
-    return t.stride(0)
-
-
 def linear(x: torch.Tensor, w: torch.Tensor, residual: Optional[torch.Tensor] = None,
            out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """x [T,Kd] . w [Kd,Nd] (+ residual [T,Nd]): the library's own kernel for large bf16 products, rocBLAS otherwise."""
-    _dev(x, w, residual, out)
-    T, Kd = x.shape
-    Nd = w.shape[1]
-    if w.shape[0] != Kd or w.dtype != x.dtype or (residual is not None and (residual.shape != (T, Nd) or
-                                                                             residual.dtype != x.dtype)):
-        raise StrdError("linear: x [T,Kd], w [Kd,Nd], residual [T,Nd], one dtype")
-    out = out if out is not None else torch.empty((T, Nd), dtype=x.dtype, device=x.device)
-    _check(lib().strd_linear(_ptr(x), _ptr(w), _ptr(residual), _ptr(out), T, Kd, Nd, _io(x), _stream()), "linear")
-    return out
+    return (_host or host()).linear(x, w, residual, out)
 
 
 def _linear_by(entry: str, x, w, residual, out):
@@ -592,42 +405,18 @@ def rmsnorm(x: torch.Tensor, w: torch.Tensor, eps: float = 1e-5, out: Optional[t
 def gated_rmsnorm(y: torch.Tensor, z: torch.Tensor, w: torch.Tensor, groups: int = 1, eps: float = 1e-5,
                   out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """rmsnorm(y * silu(z)) * w per group of channels; z may be a column slice of a wider matrix."""
-    _dev(y, w, out)
-    T, D = y.shape
-    if not y.is_contiguous() or z.shape != (T, D) or w.shape != (D,) or z.dtype != y.dtype or w.dtype != y.dtype:
-        raise StrdError("gated_rmsnorm: y, z [T,D], w [D], one dtype")
-    out = out if out is not None else torch.empty_like(y)
-    _check(lib().strd_gated_rmsnorm(_ptr(y), _ptr(z), _rows(z, "z"), _ptr(w), _ptr(out), T, D, groups, eps, _io(y),
-                                    _stream()), "gated_rmsnorm")
-    return out
+    return (_host or host()).gated_rmsnorm(y, z, w, groups, eps, out)
 
 
 def conv1d_silu(xbc: torch.Tensor, w: torch.Tensor, b: Optional[torch.Tensor], Cx: int, Cb: int):
     """Causal depthwise conv (w [Cx+2Cb, W]) + SiLU over the first Cx+2Cb columns of xbc (may be a
     column slice); returns contiguous x [T,Cx], B [T,Cb], C [T,Cb]."""
-    _dev(w, b)
-    T = xbc.shape[0]
-    Ct = Cx + 2 * Cb
-    if xbc.shape[1] < Ct or w.dim() != 2 or w.shape[0] != Ct or w.dtype != xbc.dtype or not w.is_contiguous() \
-            or (b is not None and (b.shape != (Ct,) or b.dtype != xbc.dtype)):
-        raise StrdError("conv1d_silu: xbc [T, >=Cx+2Cb], w [Cx+2Cb, W], b [Cx+2Cb], one dtype")
-    e = lambda c: torch.empty((T, c), dtype=xbc.dtype, device=xbc.device)
-    xo, Bo, Co = e(Cx), e(Cb), e(Cb)
-    _check(lib().strd_conv1d_silu(_ptr(xbc), _rows(xbc, "xbc"), _ptr(w), _ptr(b), _ptr(xo), _ptr(Bo), _ptr(Co), T, Cx, Cb,
-                                  w.shape[1], _io(xbc), _stream()), "conv1d_silu")
-    return xo, Bo, Co
+    return (_host or host()).conv1d_silu(xbc, w, b, Cx, Cb)
 
 
 def softplus_dt(raw: torch.Tensor, bias: Optional[torch.Tensor] = None) -> torch.Tensor:
     """dt [T,H] fp32 = softplus(raw + bias); raw [T,H] may be a column slice, bias [H] fp32."""
-    _dev(bias)
-    T, H = raw.shape
-    if bias is not None and (bias.shape != (H,) or bias.dtype != torch.float32):
-        raise StrdError("softplus_dt: bias [H] fp32")
-    dt = torch.empty((T, H), dtype=torch.float32, device=raw.device)
-    _check(lib().strd_softplus_dt(_ptr(raw), _rows(raw, "raw"), 0, _ptr(bias), _ptr(dt), T, H, _io(raw), _stream()),
-           "softplus_dt")
-    return dt
+    return (_host or host()).softplus_dt(raw, bias)
 
 
 HYBRID_LAYERS = 62

@@ -517,9 +517,9 @@ int select_topk_varlen_max_n() { return 8 * kTile; }
 int select_topk_varlen_launch(const float *scores, int ld, const SeqTab &tab, int nseq, int max_n, int32_t *idx,
                               hipStream_t s) {
     const size_t smem = (size_t)kBins * kCopies * sizeof(uint32_t);
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&select_topk_kernel<2, SeqTab>), smem) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(&select_topk_kernel<8, SeqTab>), smem))
-        return STRD_EHIP;
+    const void *kernel = max_n <= 2 * kTile ? reinterpret_cast<const void *>(&select_topk_kernel<2, SeqTab>)
+                                            : reinterpret_cast<const void *>(&select_topk_kernel<8, SeqTab>);
+    if (!allow_dynamic_lds(kernel, smem)) return STRD_EHIP;
     if (max_n <= 2 * kTile)
         select_topk_kernel<2, SeqTab><<<nseq, kThreads, smem, s>>>(scores, 0, 0, idx, tab, ld);
     else
@@ -540,10 +540,10 @@ int select_topk_launch(const float *scores, int N, int K, int32_t *idx, void *ws
         return launch_status();
     }
     const size_t smem = (size_t)kBins * kCopies * sizeof(uint32_t);
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&select_topk_kernel<2>), smem) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(&select_topk_kernel<8>), smem) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(&select_topk_kernel<0>), smem))
-        return STRD_EHIP;
+    const void *kernel = N <= 2 * kTile   ? reinterpret_cast<const void *>(&select_topk_kernel<2>)
+                         : N <= 8 * kTile ? reinterpret_cast<const void *>(&select_topk_kernel<8>)
+                                          : reinterpret_cast<const void *>(&select_topk_kernel<0>);
+    if (!allow_dynamic_lds(kernel, smem)) return STRD_EHIP;
     if (N <= 2 * kTile)
         select_topk_kernel<2><<<1, kThreads, smem, s>>>(scores, N, K, idx, OneSeq(), 0);
     else if (N <= 8 * kTile)
