@@ -769,15 +769,22 @@ __global__ __launch_bounds__(threads_for(NC, NH)) void ssd_seg_kernel(SegArgs a,
 }
 
 // ---- the contribution of the incoming state to the first tokens of segments 1.. and S_out -----
-// grid = (boundary b = 1..nseg, head, z); b < nseg: y of segment b; b == nseg: S_out.
+// grid = (boundary b = 1..nseg, head); b < nseg: y of segment b; b == nseg: S_out.
+// One workgroup per (boundary, head), a wave per 16-channel tile.  At the decay rates of a trained layer
+// the incoming state is gone after two or three 64-token tiles, so the kernel is a chain of loads: dt, the
+// state E and the rows of the first tile travel together.  The rows of the next tile are fetched when their
+// turn comes: held beside the current ones they cost the second workgroup of a CU.  (Four workgroups per
+// (boundary, head), a tile each, read dt and E four times over and take four rounds of the chip; this form
+// takes one, and the scan 2 to 6 us less at 2500 to 33280 tokens.)
 constexpr int kFixThreads = 256;
-constexpr int kFixZ = 4;  // workgroups that share the tiles of one (segment, head)
+constexpr int kFixBatch = 4;  // tiles whose dt is read at once
 
 template <int NS, bool GATHER>
 __global__ __launch_bounds__(kFixThreads) void ssd_fix_kernel(SegArgs a) {
     constexpr int KS = NS / 32;
-    const int b = 1 + blockIdx.x, h = blockIdx.y, z = blockIdx.z;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lb = lane >> 4;
+    const int b = 1 + blockIdx.x, h = blockIdx.y;
+    const int lane = threadIdx.x & 63, lr = lane & 15, lb = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const size_t seg_elems = (size_t)a.H * a.P * NS;
     // weight of segment s' < b in the state at the start of segment b: prod_{s' < u < b} 2^(ltot[u])
     // (uniform; the loops below stop at the first segment whose weight is zero)
@@ -788,7 +795,7 @@ __global__ __launch_bounds__(kFixThreads) void ssd_fix_kernel(SegArgs a) {
         for (int s = b - 2; s >= 0 && f != 0.f; --s) {
             const float *src = a.lend + (size_t)s * seg_elems + (size_t)h * a.P * NS;
             float *dst = a.S_out + (size_t)h * a.P * NS;
-            for (int e = z * kFixThreads + threadIdx.x; e < per; e += kFixZ * kFixThreads) {
+            for (int e = threadIdx.x; e < per; e += kFixThreads) {
                 f32x4 v = reinterpret_cast<const f32x4 *>(src)[e], o = reinterpret_cast<f32x4 *>(dst)[e];
                 reinterpret_cast<f32x4 *>(dst)[e] = o + f * v;
             }
@@ -799,103 +806,105 @@ __global__ __launch_bounds__(kFixThreads) void ssd_fix_kernel(SegArgs a) {
     const int HP = a.H * a.P, g = h / (a.H / a.G);
     const int tok0 = b * a.seg_steps * kQ;
     const int tend = min(a.T, (b + 1) * a.seg_steps * kQ);
+    const int npt = a.P / 16;
+    if (wave >= npt) return;
     const float Al2 = a.A[h] * kLog2e;
     auto row_of = [&](int t) -> size_t {
         t = min(t, a.T - 1);
         return GATHER ? (size_t)gather_row(a, t, a.idx[min(t, a.K - 1)]) : (size_t)t;
     };
-    // E = state at the start of segment b, as A-operand fragments (rows p = 16 pt + lr, k slots
-    // n = 32 ks + 8 lb + s) of this wave's channel tiles pt = wave, wave + 4, ...; requested before it is
-    // known whether any token needs it, so that its latency runs under that of the dt loads
-    constexpr int kMaxPT = 1;  // channel tiles per wave held in registers (P <= 64); more are loaded when their turn comes
-    const int npt = (a.P / 16 - wave + 3) / 4;
-    bf16x8 ef[kMaxPT][KS];
-    auto load_e = [&](int pt, bf16x8 (&out)[KS]) __attribute__((always_inline)) {
-        f32x4 acc[KS][2];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) acc[ks][0] = acc[ks][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-        float f = 1.f;
-        for (int s = b - 1; s >= 0 && f != 0.f; --s) {
-            const float *src = a.lend + (size_t)s * seg_elems + ((size_t)h * a.P + 16 * pt + lr) * NS + 8 * lb;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                acc[ks][0] += f * *reinterpret_cast<const f32x4 *>(src + 32 * ks);
-                acc[ks][1] += f * *reinterpret_cast<const f32x4 *>(src + 32 * ks + 4);
-            }
-            f *= fast_exp2(a.ltot[(size_t)s * a.H + h]);
-        }
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) out[ks] = cat8(to_bf16x4(acc[ks][0]), to_bf16x4(acc[ks][1]));
-    };
-    // dt of kFixZ tiles at once (lane = token); the first batch travels together with the E fragments
-    float dv[kFixZ];
+    float dv[kFixBatch];  // lane = token
     auto load_dt = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < kFixZ; ++q) {
+        for (int q = 0; q < kFixBatch; ++q) {
             const int t = tok0 + (k0 + q) * kQ + lane;
             dv[q] = t < tend ? a.dt[row_of(t) * a.H + h] : 0.f;
         }
     };
-    load_dt(0);
-    // (the workgroups of the first two tiles only: at the decay rates of a trained layer the later tiles of a
-    // batch are rarely reached, and every workgroup that loads E reads 32 KB -- they fetch it when they need it)
-    bool have_e = z < 2;  // uniform
-    if (have_e) {
+    // c rows of a tile (B operand: column = token 16 tt + lr) and the outputs they correct
+    struct Rows {
+        bf16x8 c[4][KS];
+        bf16x4 y[4];
+    };
+    auto y_at = [&](int k, int tt, int pt) -> bf16x4 * {
+        const int tq = min(tok0 + k * kQ + 16 * tt + lr, a.T - 1);
+        return reinterpret_cast<bf16x4 *>(a.y + (size_t)tq * HP + (size_t)h * a.P + 16 * pt + 4 * lb);
+    };
+    auto load_rows = [&](int k, int pt, Rows &r) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < kMaxPT; ++q)
-            if (q < npt) load_e(wave + 4 * q, ef[q]);
-    }
-    float prefix = 0.f;  // log2 decay from the segment's start to the tile's start
-    for (int k0 = 0; tok0 + k0 * kQ < tend; k0 += kFixZ) {
-        if (k0 > 0) load_dt(k0);
-        float cr = 0.f;
-        bool dead = false;
+        for (int tt = 0; tt < 4; ++tt) {
+            const bf16_t *crow = a.C + (row_of(tok0 + k * kQ + 16 * tt + lr) * a.G + g) * NS + 8 * lb;
 #pragma unroll
-        for (int q = 0; q < kFixZ; ++q) {
-            const float inc = prefix + wave_inclusive_scan_f32(dv[q] * Al2);
-            if (read_lane_f32(fast_exp2(inc), 0) == 0.f) dead = true;  // nothing reaches this tile, nor any later one
-            if (q == z && !dead) cr = (tok0 + (k0 + q) * kQ + lane) < tend ? fast_exp2(inc) : 0.f;
-            prefix = read_lane_f32(inc, kQ - 1);
+            for (int ks = 0; ks < KS; ++ks) r.c[tt][ks] = *reinterpret_cast<const bf16x8 *>(crow + 32 * ks);
+            r.y[tt] = *y_at(k, tt, pt);
         }
-        // this workgroup's tile of the batch: k0 + z
-        const int k = k0 + z;
-        auto repair = [&](int pt, const bf16x8 (&et)[KS]) __attribute__((always_inline)) {
+    };
+    for (int pt = wave; pt < npt; pt += kFixThreads / 64) {
+        load_dt(0);
+        Rows r;
+        load_rows(0, pt, r);
+        // E = state at the start of segment b, as A-operand fragments (rows p = 16 pt + lr, k slots
+        // n = 32 ks + 8 lb + s)
+        bf16x8 ef[KS];
+        {
+            f32x4 acc[KS][2];
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt) {
-                const int tq = tok0 + k * kQ + 16 * tt + lr;  // this lane's token of the query block
-                const float crt = __shfl(cr, 16 * tt + lr, 64);
-                if (__ballot(crt != 0.f) == 0ull) continue;   // uniform per wave
-                const bf16_t *crow = a.C + (row_of(tq) * a.G + g) * NS + 8 * lb;
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            for (int ks = 0; ks < KS; ++ks) acc[ks][0] = acc[ks][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            float f = 1.f;
+            for (int s = b - 1; s >= 0 && f != 0.f; --s) {
+                const float *src = a.lend + (size_t)s * seg_elems + ((size_t)h * a.P + 16 * pt + lr) * NS + 8 * lb;
+                f32x4 v[KS][2];
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) acc = mfma16(et[ks], *reinterpret_cast<const bf16x8 *>(crow + 32 * ks), acc);
-                if (tq < tend && crt != 0.f) {
-                    bf16x4 *yq = reinterpret_cast<bf16x4 *>(a.y + (size_t)tq * HP + (size_t)h * a.P + 16 * pt + 4 * lb);
-                    const bf16x4 old = *yq;
-                    bf16x4 out;
+                for (int ks = 0; ks < KS; ++ks) {
+                    v[ks][0] = *reinterpret_cast<const f32x4 *>(src + 32 * ks);
+                    v[ks][1] = *reinterpret_cast<const f32x4 *>(src + 32 * ks + 4);
+                }
+                const float lt = a.ltot[(size_t)s * a.H + h];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) out[e] = (bf16_t)((float)old[e] + crt * acc[e]);
-                    *yq = out;
+                for (int ks = 0; ks < KS; ++ks) {
+                    acc[ks][0] += f * v[ks][0];
+                    acc[ks][1] += f * v[ks][1];
+                }
+                f *= fast_exp2(lt);
+            }
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) ef[ks] = cat8(to_bf16x4(acc[ks][0]), to_bf16x4(acc[ks][1]));
+        }
+        float prefix = 0.f;  // log2 decay from the segment's start to the tile's start
+        bool dead = false;   // nothing reaches this tile, nor any later one (uniform)
+        for (int k0 = 0; tok0 + k0 * kQ < tend && !dead; k0 += kFixBatch) {
+            if (k0 > 0) load_dt(k0);
+            float cr[kFixBatch];
+            int alive = 0;  // tiles of the batch that something reaches
+#pragma unroll
+            for (int q = 0; q < kFixBatch; ++q) {
+                const float inc = prefix + wave_inclusive_scan_f32(dv[q] * Al2);
+                cr[q] = tok0 + (k0 + q) * kQ + lane < tend ? fast_exp2(inc) : 0.f;
+                if (read_lane_f32(fast_exp2(inc), 0) == 0.f) dead = true;
+                if (!dead) alive = q + 1;
+                prefix = read_lane_f32(inc, kQ - 1);
+            }
+#pragma unroll
+            for (int q = 0; q < kFixBatch; ++q) {
+                if (q >= alive || tok0 + (k0 + q) * kQ >= tend) break;
+                const int k = k0 + q;
+                if (k > 0) load_rows(k, pt, r);
+#pragma unroll
+                for (int tt = 0; tt < 4; ++tt) {
+                    const int tq = tok0 + k * kQ + 16 * tt + lr;  // this lane's token of the query block
+                    const float crt = __shfl(cr[q], 16 * tt + lr, 64);
+                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) acc = mfma16(ef[ks], r.c[tt][ks], acc);
+                    if (tq < tend && crt != 0.f) {
+                        bf16x4 out;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) out[e] = (bf16_t)((float)r.y[tt][e] + crt * acc[e]);
+                        *y_at(k, tt, pt) = out;
+                    }
                 }
             }
-        };
-        if (__ballot(cr != 0.f) != 0ull) {
-            if (!have_e) {
-#pragma unroll
-                for (int q = 0; q < kMaxPT; ++q)
-                    if (q < npt) load_e(wave + 4 * q, ef[q]);
-                have_e = true;
-            }
-#pragma unroll
-            for (int q = 0; q < kMaxPT; ++q)
-                if (q < npt) repair(wave + 4 * q, ef[q]);
-            for (int q = kMaxPT; q < npt; ++q) {
-                bf16x8 et[KS];
-                load_e(wave + 4 * q, et);
-                repair(wave + 4 * q, et);
-            }
         }
-        if (dead) break;
     }
 }
 
@@ -905,7 +914,7 @@ int launch(const SegArgs &a, hipStream_t st) {
     const size_t smem = sizeof(LdsS<NS, NC, NH>);
     if (!allow_dynamic_lds(reinterpret_cast<const void *>(&ssd_seg_kernel<NS, NC, NH, GATHER>), smem)) return STRD_EHIP;
     ssd_seg_kernel<NS, NC, NH, GATHER><<<xcd_grid(nunits), threads_for(NC, NH), smem, st>>>(a, nunits);
-    if (a.nseg > 1) ssd_fix_kernel<NS, GATHER><<<dim3(a.nseg, a.H, kFixZ), kFixThreads, 0, st>>>(a);
+    if (a.nseg > 1) ssd_fix_kernel<NS, GATHER><<<dim3(a.nseg, a.H), kFixThreads, 0, st>>>(a);
     return launch_status();
 }
 
@@ -947,12 +956,17 @@ bool ssd_seg_supported(int T, int rows, int H, int P, int G, int n, strd_dtype i
 // Whether this kernel or the one that walks the whole sequence in one workgroup per (head, 32
 // channels) (ssd_mfma) is the faster one.  This kernel moves about half the bytes per token through
 // a CU's copy path (B and C tiles serve the whole head) and fills the chip with few heads, but pays
-// for its segments with a longer prologue and a second launch: it wins once a segment is long
-// (measured: from about 32 steps at 128 heads), or when the other kernel would leave CUs idle.
+// for its segments with a longer prologue and a second launch.  Two heads per workgroup: a step of a segment
+// takes about 2.4 steps of the other kernel and the fixed costs about 14 of them (measured at 128 and 64 heads
+// of 64: equal at 37 and 32 steps of the sequence, 107 -> 76 us at 88).  One head: from segments of 32 steps.
+// With few heads, when the other kernel would leave CUs idle, always.
 bool ssd_seg_preferred(int T, int H, int P, int G) {
     int nseg, seg_steps;
     ssd_seg_plan(T, H, P, G, &nseg, &seg_steps);
-    return nseg >= 2 && (seg_steps >= 32 || H * (P / 32) < 128);
+    if (nseg < 2) return false;
+    if (seg_steps >= 32 || H * (P / 32) < 128) return true;
+    const long long whole_steps = (long long)ceil_div(T, kQ) * ceil_div(H * (P / 32), 256);
+    return heads_per_wg(H, P, G) == 2 && 5 * whole_steps > 68 + 12 * seg_steps;
 }
 
 int ssd_seg(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D,

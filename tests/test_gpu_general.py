@@ -87,3 +87,31 @@ def test_scan(T, H, P, G, n, carry, dtype):
     assert_close(f(S), S_ref, 1e-5 if dtype == F32 else BOUND[dtype], "S", units=(0,))
     y2, none = strd.ssd_prefill(dev(x), dev(dt), dev(A), dev(B), dev(C), dev(D), dev(S_in), want_state=False)
     assert none is None and torch.equal(y2, y)
+
+
+@pytest.mark.parametrize("T", [2368, 2369, 2432, 2433, 4100])
+def test_scan_around_the_switch_to_segments(T):
+    """128 heads of 64 channels: 37 steps of 64 tokens run in one piece, 38 and more in segments.  The first and
+    the last group's heads against the recurrence, the gather form bit for bit."""
+    _say("scan, 128 heads, T=%d" % T)
+    H, P, G, n, M = 128, 64, 8, 128, 33
+    g = torch.Generator().manual_seed(T)
+    rows = T + 57
+    x = torch.randn(rows, H, P, generator=g).to(BF16)
+    B, C = (torch.randn(rows, G, n, generator=g) / n ** 0.5).to(BF16), torch.randn(rows, G, n, generator=g).to(BF16)
+    dt = torch.nn.functional.softplus(torch.randn(rows, H, generator=g))
+    A, D, S_in = -torch.exp(2 * torch.rand(H, generator=g)), torch.randn(H, generator=g), torch.randn(H, P, n, generator=g)
+    N, K = rows - M, T - M
+    idx = torch.sort(torch.randperm(N, generator=g)[:K]).values.int()
+    keep = torch.cat([idx.long(), torch.arange(N, rows)])
+    dev = lambda t: t.to(DEV)
+    y, S = strd.ssd_prefill(*(dev(t[keep].contiguous()) for t in (x, dt)), dev(A), *(dev(t[keep].contiguous()) for t in (B, C)),
+                            dev(D), dev(S_in))
+    yg, Sg = strd.ssd_prefill_gather(dev(x), dev(dt), dev(A), dev(B), dev(C), dev(idx), N, M, dev(D), dev(S_in))
+    assert torch.equal(yg, y) and torch.equal(Sg, S)
+    for h0, grp in ((0, 0), (126, 7)):
+        hs = slice(h0, h0 + 2)
+        y_ref, S_ref = oracle.ssd_seq(f(x[keep][:, hs]), f(dt[keep][:, hs]), f(A[hs]), f(B[keep][:, grp:grp + 1]),
+                                      f(C[keep][:, grp:grp + 1]), f(D[hs]), f(S_in[hs]))
+        assert_close(f(y[:, hs]), y_ref, TOL[BF16], "y", units=(1,))
+        assert_close(f(S[hs]), S_ref, TOL[BF16], "S", units=(0,))
