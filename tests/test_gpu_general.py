@@ -115,3 +115,24 @@ def test_scan_around_the_switch_to_segments(T):
                                       f(C[keep][:, grp:grp + 1]), f(D[hs]), f(S_in[hs]))
         assert_close(f(y[:, hs]), y_ref, TOL[BF16], "y", units=(1,))
         assert_close(f(S[hs]), S_ref, TOL[BF16], "S", units=(0,))
+
+
+# token rows x columns whose last round of 256 tiles is cut: into quarters (a whole tile; an edge row of tiles
+# with one token; an edge column; the corner), into halves, with an edge row inside a half cut; and one left whole
+@pytest.mark.parametrize("T,Nd", [(256, 256), (4097, 4096), (4096 + 256, 4096), (4096 + 100, 4096 + 64), (4096, 4096 + 136),
+                                  (5 * 256, 31 * 256), (9 * 256 + 5, 56 * 256), (12 * 256, 44 * 256 + 8)])
+def test_projection_with_a_cut_last_round(T, Nd):
+    """Every element against the fp32 product of the same bf16 operands: one bf16 step of the result plus the
+    rounding of 64 sums of products of standard normals (under 1e-5)."""
+    _say("projection T=%d Nd=%d" % (T, Nd))
+    Kd = 64
+    g = torch.Generator(device=DEV).manual_seed(T + Nd)
+    x = torch.randn(T, Kd, generator=g, device=DEV).to(BF16)
+    w = torch.randn(Kd, Nd, generator=g, device=DEV).to(BF16)
+    res = torch.randn(T, Nd, generator=g, device=DEV).to(BF16)
+    out = torch.full((T + 1, Nd), 7.0, device=DEV, dtype=BF16)
+    strd.linear_mfma(x, w, residual=res, out=out[:T])
+    ref = x.float() @ w.float() + res.float()
+    err = (out[:T].float() - ref).abs()
+    assert bool((err <= ref.abs() * 2.0 ** -8 + 1e-4).all()), float(err.max())
+    assert bool((out[T] == 7.0).all()), "wrote past the last row"
