@@ -17,10 +17,16 @@
 // kernel took 18 % longer at 33 K tokens.
 // K and V stream through LDS in chunks of KC keys, double-buffered, shared by the waves; the next
 // chunk is copied global -> LDS asynchronously (no register staging) during the current one.
-// Two shapes: 4 waves that request their own copies and 64-key chunks (two workgroups per CU) for
-// short sequences; 8 computing waves, 4 copy waves and 128-key chunks (one workgroup per CU) for
-// long ones.  Workgroups are issued longest-first (last query block first), the query heads of one
-// kv group back to back on one XCD.
+// Long sequences: 8 computing waves, 4 copy waves, 128-key chunks.  Short ones: two groups of 4 computing
+// waves that own the same queries and take 64-key chunks in turn, each with a softmax of its own, and 4 copy
+// waves that serve both; the groups meet at the end through LDS.  One workgroup per CU either way.  (One group
+// of 4 waves that request their own copies, two workgroups per CU, has the longest query blocks take twice the
+// steps, leaves a SIMD with one wave where there are fewer workgroups than CUs, and has the computing waves
+// stand still for the copies: 32 query heads of 128, 843 tokens 23.7 us -> 17.6, 2048 tokens 54.3 -> 41.3; two
+// groups that request their own copies 20.0 and 46.6.  Chunks of 32 keys requested three steps ahead are no
+// faster: the step is bound by the waves' own products and softmax.  The old form is kept for the shortest sequences, a few chunks.)
+// Workgroups are issued longest-first (last query block first), the query heads of one kv group back to
+// back on one XCD.
 #include "common.h"
 
 namespace strd {
@@ -55,18 +61,22 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// NW computing waves and NC copy waves; NC = 0: the computing waves request the copies themselves.
-template <int D, int NW, int NC, int KC>
-__global__ __launch_bounds__((NW + NC) * kWave) __attribute__((amdgpu_waves_per_eu(2, NC ? 3 : 2))) void attn_mfma_kernel(
+// G groups of NW computing waves, and NC copy waves (G = 1); NC = 0: the computing waves request the copies of
+// their group themselves.  Group g takes chunks g, g + G, ...
+template <int D, int NW, int NC, int KC, int G>
+__global__ __launch_bounds__((G * NW + NC) * kWave) __attribute__((amdgpu_waves_per_eu(2, NC ? 3 : 2))) void attn_mfma_kernel(
     const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v, bf16_t *__restrict__ o, int T,
     int Hq, int Hkv, float scale2, int nqb, int xcd_map) {
     constexpr int KS = D / 32, DT = D / 16, kBM = 32 * NW;
     using TileT = Tile<D, NC ? NC : NW, KC>;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    TileT &lds = *reinterpret_cast<TileT *>(smem_raw);
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lb = lane >> 4;
     const float lazy_raw = kLazy / scale2;  // the slack of the softmax reference, in raw score units
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, in a scalar register
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, in a scalar register
+    const int grp = G == 1 ? 0 : wv / NW, w = G == 1 ? wv : wv % NW;
+    const bool copies = NC > 0 && wv >= G * NW;              // a copy wave: it serves all groups
+    TileT *const all = reinterpret_cast<TileT *>(smem_raw);
+    TileT &lds = all[copies ? 0 : grp];
     // Workgroup b runs on XCD b % 8, each with an L2 of its own.  When the kv heads divide evenly over
     // the XCDs, all query heads and query blocks of one kv head go to one XCD, so its K and V stream
     // through one L2 (and the query heads of the group, issued back to back, share each chunk there)
@@ -92,7 +102,7 @@ __global__ __launch_bounds__((NW + NC) * kWave) __attribute__((amdgpu_waves_per_
     const int wq0 = __builtin_amdgcn_readfirstlane(t0 + 32 * w);
     const int wmax = min(T - 1, wq0 + 31);       // last key any query of the wave may see
     const int nkeys = min(T, t0 + kBM);
-    const int nchunk = (nkeys + KC - 1) / KC;
+    const int nchunk = (nkeys + KC - 1) / KC, nstep = (nchunk + G - 1) / G;
 
     // K / V chunks go global -> LDS directly, one chunk ahead of the products.  Requesting a copy
     // blocks a wave for as long as the CU's copy path is busy with earlier ones (about half of the
@@ -101,35 +111,39 @@ __global__ __launch_bounds__((NW + NC) * kWave) __attribute__((amdgpu_waves_per_
     // requests its share.  The slots of a lane are recomputed for every chunk (a few integer
     // operations) rather than held in registers.
     using AT = typename TileT::A;
-    const int cw = NC ? w - NW : w;
+    const int cw = NC ? wv - G * NW : w;
     const uint32_t kv_row = (uint32_t)Hkv * D * 2;
     const uint32_t kv_col = (uint32_t)kvh * D * 2;
-    int next_chunk = 0;
-    auto stage = [&](int b) __attribute__((always_inline)) {  // requests the next chunk in sequence; rows past T re-read row T - 1
+    // requests a chunk into buffer b of a group's tiles; rows past T re-read row T - 1
+    auto stage = [&](TileT &dst, int chunk, int b) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < AT::kIssues; ++i) {
             int row, cv;
             AT::slot(cw, lane, i, row, cv);
-            const uint32_t off = (uint32_t)min(next_chunk * KC + row, T - 1) * kv_row + kv_col + (uint32_t)cv * 16;
-            AT::issue(reinterpret_cast<const char *>(k) + off, &lds.k[b], cw, i);
+            const uint32_t off = (uint32_t)min(chunk * KC + row, T - 1) * kv_row + kv_col + (uint32_t)cv * 16;
+            AT::issue(reinterpret_cast<const char *>(k) + off, &dst.k[b], cw, i);
         }
 #pragma unroll
         for (int i = 0; i < AT::kIssues; ++i) {
             int row, cv;
             AT::slot(cw, lane, i, row, cv);
-            const uint32_t off = (uint32_t)min(next_chunk * KC + row, T - 1) * kv_row + kv_col + (uint32_t)cv * 16;
-            AT::issue(reinterpret_cast<const char *>(v) + off, &lds.v[b], cw, i);
+            const uint32_t off = (uint32_t)min(chunk * KC + row, T - 1) * kv_row + kv_col + (uint32_t)cv * 16;
+            AT::issue(reinterpret_cast<const char *>(v) + off, &dst.v[b], cw, i);
         }
-        ++next_chunk;
     };
-    if (NC > 0 && w >= NW) {  // copy wave
-        stage(0);
-        async_tile_wait();
-        lds_barrier();
-        for (int chunk = 0; chunk < nchunk; ++chunk) {
-            stage((chunk & 1) ^ 1);  // chunk + 1 (past the last chunk: clamped rows, never read)
+    if (copies) {
+        // (the chunk after a group's last one: clamped rows, never read)
+        auto stage_step = [&](int step) __attribute__((always_inline)) {
+#pragma unroll
+            for (int gr = 0; gr < G; ++gr) stage(all[gr], step * G + gr, step & 1);
             async_tile_wait();
             lds_barrier();
+        };
+        stage_step(0);
+        for (int step = 0; step < nstep; ++step) stage_step(step + 1);
+        if (G > 1) {
+            __syncthreads();  // the two barriers of the groups' meeting
+            __syncthreads();
         }
         return;
     }
@@ -155,13 +169,13 @@ __global__ __launch_bounds__((NW + NC) * kWave) __attribute__((amdgpu_waves_per_
 
     constexpr int kRowB = TileT::kPitch * 2;  // row pitch of the tiles in bytes
     if (NC == 0) {
-        stage(0);
+        stage(lds, grp, 0);
         async_tile_wait();
     }
-    lds_barrier();  // chunk 0 has landed
-    for (int chunk = 0; chunk < nchunk; ++chunk) {
-        const int cur = chunk & 1;
-        if (NC == 0) stage(cur ^ 1);  // chunk + 1 (past the last chunk: clamped rows, never read)
+    lds_barrier();  // the groups' first chunks have landed
+    for (int step = 0; step < nstep; ++step) {
+        const int cur = step & 1, chunk = step * G + grp;
+        if (NC == 0) stage(lds, chunk + G, cur ^ 1);  // the group's next chunk (past the last chunk: clamped rows, never read)
 #pragma unroll
         for (int kt = 0; kt < KC / 32; ++kt) {
             const int kb = chunk * KC + 32 * kt;
@@ -228,13 +242,16 @@ __global__ __launch_bounds__((NW + NC) * kWave) __attribute__((amdgpu_waves_per_
                         float t = tm[qt];
                         t = fmaxf(t, __shfl_xor(t, 16, kWave));
                         t = fmaxf(t, __shfl_xor(t, 32, kWave));
-                        const float nm = fmaxf(m_run[qt], t);  // finite: key 0 is visible to every query
-                        const float corr = ex2((m_run[qt] - nm) * scale2);
+                        // finite in the first group: key 0 is visible to every query; a query may not see any
+                        // key of the others, whose chunks start later
+                        const float nm = fmaxf(m_run[qt], t);
+                        const bool unseen = G > 1 && nm == -INFINITY;
+                        const float corr = unseen ? 1.f : ex2((m_run[qt] - nm) * scale2);
                         l_run[qt] *= corr;
 #pragma unroll
                         for (int dt = 0; dt < DT; ++dt) oacc[dt][qt] *= corr;
                         m_run[qt] = nm;
-                        m_neg[qt] = -nm * scale2;
+                        m_neg[qt] = unseen ? 0.f : -nm * scale2;
                     }
                 }
                 // The row sum is taken of the probabilities as they enter the second product, i.e. rounded to
@@ -275,17 +292,49 @@ __global__ __launch_bounds__((NW + NC) * kWave) __attribute__((amdgpu_waves_per_
             }
         }
         if (NC == 0) async_tile_wait();
-        lds_barrier();  // chunk + 1 has landed, every wave is done with this one
+        lds_barrier();  // the next chunk has landed, every wave is done with this one
     }
 
+    // this wave's row sums: the four lane groups of a query hold different keys
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
-        float l_tot = l_run[qt];
-        l_tot += __shfl_xor(l_tot, 16, kWave);
-        l_tot += __shfl_xor(l_tot, 32, kWave);
+        l_run[qt] += __shfl_xor(l_run[qt], 16, kWave);
+        l_run[qt] += __shfl_xor(l_run[qt], 32, kWave);
+    }
+    if constexpr (G > 1) {
+        // the later groups leave their accumulators, maxima and sums in LDS (the chunks are done with), lane by
+        // lane in the layout the first group's waves hold theirs
+        static_assert(G == 2, "one partner per wave");
+        constexpr int kPart = DT * 2 + 1;  // f32x4s per lane: accumulators, then (max, sum) of both query tiles
+        f32x4 *part = reinterpret_cast<f32x4 *>(smem_raw) + (size_t)w * kPart * kWave + lane;
+        static_assert((size_t)NW * kPart * kWave * sizeof(f32x4) <= G * sizeof(TileT), "partials fit the tiles' LDS");
+        async_tile_wait();  // (copies past the last chunk)
+        __syncthreads();
+        if (grp == 1) {
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                part[(2 * dt) * kWave] = oacc[dt][0];
+                part[(2 * dt + 1) * kWave] = oacc[dt][1];
+            }
+            part[2 * DT * kWave] = f32x4{m_run[0], l_run[0], m_run[1], l_run[1]};
+        }
+        __syncthreads();
+        if (grp == 1) return;
+        const f32x4 ml = part[2 * DT * kWave];
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+            const float mo = ml[2 * qt], nm = fmaxf(m_run[qt], mo);
+            const float ca = ex2((m_run[qt] - nm) * scale2), cb = ex2((mo - nm) * scale2);  // 0 where it saw no key
+            l_run[qt] = l_run[qt] * ca + ml[2 * qt + 1] * cb;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) oacc[dt][qt] = oacc[dt][qt] * ca + part[(2 * dt + qt) * kWave] * cb;
+        }
+    }
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
         const int tq = qt ? tq1 : tq0;
         if (tq < T) {
-            const float inv = 1.f / l_tot;
+            const float inv = 1.f / l_run[qt];
             bf16_t *op = o + ((size_t)tq * Hq + h) * D + 4 * lb;
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
@@ -298,17 +347,17 @@ __global__ __launch_bounds__((NW + NC) * kWave) __attribute__((amdgpu_waves_per_
     }
 }
 
-template <int D, int NW, int NC, int KC>
+template <int D, int NW, int NC, int KC, int G>
 int launch(const void *q, const void *k, const void *v, void *o, int T, int Hq, int Hkv, float scale, hipStream_t st) {
-    const size_t smem = sizeof(Tile<D, NC ? NC : NW, KC>);
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&attn_mfma_kernel<D, NW, NC, KC>), smem))
+    const size_t smem = G * sizeof(Tile<D, NC ? NC : NW, KC>);
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&attn_mfma_kernel<D, NW, NC, KC, G>), smem))
         return STRD_EHIP;
     const int nqb = ceil_div(T, 32 * NW);
     // XCD-aware order when the kv heads per XCD and the query heads per kv head are powers of two
     const int per = Hkv / kXcd, gq = Hq / Hkv;
     const bool pow2 = Hkv % kXcd == 0 && (per & (per - 1)) == 0 && (gq & (gq - 1)) == 0 && per <= 128;
     const int xcd_map = pow2 ? 1 + __builtin_ctz(per) + 8 * __builtin_ctz(gq) : 0;
-    attn_mfma_kernel<D, NW, NC, KC><<<nqb * Hq, (NW + NC) * kWave, smem, st>>>((const bf16_t *)q, (const bf16_t *)k,
+    attn_mfma_kernel<D, NW, NC, KC, G><<<nqb * Hq, (G * NW + NC) * kWave, smem, st>>>((const bf16_t *)q, (const bf16_t *)k,
                                                                         (const bf16_t *)v, (bf16_t *)o, T, Hq, Hkv,
                                                                         scale * kLog2e, nqb, xcd_map);
     return launch_status();
@@ -324,15 +373,19 @@ bool attn_mfma_supported(int T, int Hq, int Hkv, int d, strd_dtype io) {
 
 int attn_mfma(const void *q, const void *k, const void *v, void *o, int T, int Hq, int Hkv, int d, float scale,
               hipStream_t st) {
-    // Long sequences: 8 computing waves (256 queries) per workgroup share 128-key chunks that 4 copy
-    // waves bring in, one workgroup per CU -- half the K/V copies per query, a barrier every four
-    // tiles instead of every two, and no computing wave ever blocks on the copy path (12 % faster
-    // at 33 K tokens than the other form).  Short ones keep 4 waves that copy for themselves and
-    // 64-key chunks, which makes twice as many workgroups; the crossover lies near 1.5 workgroups of
-    // the long form per CU.
-    const bool big = (long long)ceil_div(T, 256) * Hq >= 384;
-    if (d == 128) return big ? launch<128, 8, 4, 128>(q, k, v, o, T, Hq, Hkv, scale, st) : launch<128, 4, 0, 64>(q, k, v, o, T, Hq, Hkv, scale, st);
-    if (d == 64) return big ? launch<64, 8, 4, 128>(q, k, v, o, T, Hq, Hkv, scale, st) : launch<64, 4, 0, 64>(q, k, v, o, T, Hq, Hkv, scale, st);
+    // Long sequences: 8 computing waves (256 queries) per workgroup share 128-key chunks -- half the K/V copies
+    // per query, and a barrier every four tiles instead of every two.  They need about 1.5 workgroups per CU to
+    // balance the causal sweep (equal at 320, 7 % faster at 384 and d = 128).  Below, two key groups; the merge at the end costs
+    // what they save up to about 256 tokens (four chunks).
+    const bool big = (long long)ceil_div(T, 256) * Hq >= 384, tiny = T <= 256;
+    if (d == 128)
+        return big    ? launch<128, 8, 4, 128, 1>(q, k, v, o, T, Hq, Hkv, scale, st)
+               : tiny ? launch<128, 4, 0, 64, 1>(q, k, v, o, T, Hq, Hkv, scale, st)
+                      : launch<128, 4, 4, 64, 2>(q, k, v, o, T, Hq, Hkv, scale, st);
+    if (d == 64)
+        return big    ? launch<64, 8, 4, 128, 1>(q, k, v, o, T, Hq, Hkv, scale, st)
+               : tiny ? launch<64, 4, 0, 64, 1>(q, k, v, o, T, Hq, Hkv, scale, st)
+                      : launch<64, 4, 4, 64, 2>(q, k, v, o, T, Hq, Hkv, scale, st);
     return STRD_EUNSUPPORTED;
 }
 

@@ -136,3 +136,15 @@ def test_projection_with_a_cut_last_round(T, Nd):
     err = (out[:T].float() - ref).abs()
     assert bool((err <= ref.abs() * 2.0 ** -8 + 1e-4).all()), float(err.max())
     assert bool((out[T] == 7.0).all()), "wrote past the last row"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T", [256, 257, 288, 320, 321, 385, 448, 515, 1021])
+def test_attention_with_two_key_groups(T, d):
+    """Sequences of a few 64-key chunks: one group of waves up to 256 tokens, two from there on (an even and an odd
+    number of chunks, a last chunk of one key, query tiles that see no key of the second group)."""
+    _say("attn, key groups, T=%d d=%d" % (T, d))
+    rn = _draw(T + d, BF16)
+    q, k, v = rn(T, 4, d), rn(T, 2, d), rn(T, 2, d)
+    assert_close(f(strd.attn_prefill(q.to(DEV), k.to(DEV), v.to(DEV))), oracle.attn(f(q), f(k), f(v)), TOL[BF16], "o",
+                 units=(0, 1))
