@@ -3,7 +3,7 @@
 //     s_i = 1/(M*Hq) * sum_{m,h} softmax_i( scale * q_m^h . k_i^{kv(h)} ),  softmax over the N keys.
 // The [M*Hq x N] probability table is never stored; it is produced twice, tile by tile:
 //   pass 1 (stats)   per query row: running max and sum of 2^z over a slice of the keys,
-//   combine          per query row: log2-sum-exp over the slices,
+//   combine          per query row: log2-sum-exp over the slices (for few rows and slices inside pass 2),
 //   pass 2 (colsum)  per key: sum over the query rows of 2^(z - lse),
 //   reduce           sum over kv heads, times 1/(M*Hq).
 // with z = q.k * scale * log2(e).  Both passes compute the tile transposed, Z^T[key, query]
@@ -25,6 +25,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kThreads = 256;
 constexpr int kRows = 128;  // rows (keys in pass 1, queries in pass 2) per LDS tile
 constexpr int kTW = 2;      // 32-wide register tiles per wave (queries in pass 1, keys in pass 2)
+constexpr int kNarrowBlocks = 128;  // see make_plan
+constexpr long long kFusedStats = 4096;
+constexpr int kFuseSlices = 8;  // slices whose statistics a thread has in flight
 constexpr float kLog2e = 1.4426950408889634f;
 
 template <int D>
@@ -58,13 +61,12 @@ __device__ __forceinline__ size_t qrow_index(int r, int rep, int Hq, int kvh) {
 // ---------------------------------------------------------------------------------------------
 // pass 1: grid = row blocks (fastest) x kv heads x key slices
 // SEQ = SeqTab (packed batch, blockIdx.y = sequence): q and k point at the packed tensors and every
-// sequence has `seq_stride` floats of pmax / psum of its own; the grid and the key slices are those of
+// sequence has `seq_stride` pairs of `stat` of its own; the grid and the key slices are those of
 // the longest sequence, so a shorter one leaves slices empty (max = -inf, sum = 0).
 template <int D, class SEQ>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_stats_kernel(const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
-                                                              float *__restrict__ pmax, float *__restrict__ psum, int M,
-                                                              int N, int Hq, int Hkv, float scale2, int nrb,
-                                                              int keys_per_slice, int nunits, SEQ seq, size_t seq_stride) {
+                                                              float2 *__restrict__ stat, int M, int N,
+                                                              int Hq, int Hkv, float scale2, int nrb, int keys_per_slice, int nunits, SEQ seq, size_t seq_stride) {
     constexpr int KS = D / 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     Tile<D> &lds = *reinterpret_cast<Tile<D> *>(smem_raw);
@@ -74,8 +76,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         M = seq.M[b];
         k += (size_t)seq.row0[b] * Hkv * D;
         q += (size_t)(seq.row0[b] + N) * Hq * D;
-        pmax += b * seq_stride;
-        psum += b * seq_stride;
+        stat += b * seq_stride;
     }
     const int tid = threadIdx.x, lane = tid & 63, lc = lane & 31, half = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, in a scalar register
@@ -200,37 +201,33 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         const float ref = (nm == -INFINITY) ? 0.f : nm;
         const float tot = run_s[qt] * ex2(run_m[qt] - ref) + os * ex2(om - ref);
         if (half == 0 && row[qt] < R) {
-            const size_t o = (size_t)sl * M * Hq + qrow_index(row[qt], rep, Hq, kvh);
-            pmax[o] = nm;
-            psum[o] = tot;
+            stat[((size_t)sl * Hkv + kvh) * R + row[qt]] = make_float2(nm, tot);
         }
     }
 }
 
-// combine: lse2[row] = log2 sum over slices.  A workgroup takes 16 rows; thread (j, r) = (tid / 16,
+// combine: with the rows counted kv head by kv head, lse2[row] = log2 sum over slices.  A workgroup takes 16 rows; thread (j, r) = (tid / 16,
 // tid % 16) folds slices j, j + 16, ... of row r (16 adjacent rows per load: coalesced), then the 16
 // partial (max, sum) pairs of a row meet in LDS in a fixed order.
 template <class SEQ>
-__global__ __launch_bounds__(kThreads) void attn_lse_kernel(const float *__restrict__ pmax, const float *__restrict__ psum,
-                                                            float *__restrict__ lse2, int rows, int nslice, SEQ seq,
+__global__ __launch_bounds__(kThreads) void attn_lse_kernel(const float2 *__restrict__ stat, float *__restrict__ lse2, int rows, int nslice, SEQ seq,
                                                             int Hq, size_t seq_stride, int lse_ld) {
     __shared__ float sm[16][17], ss[16][17];
     if constexpr (is_varlen<SEQ>()) {
         const int b = blockIdx.y;
         rows = seq.M[b] * Hq;
         if ((int)blockIdx.x * 16 >= rows) return;  // uniform
-        pmax += b * seq_stride;
-        psum += b * seq_stride;
+        stat += b * seq_stride;
         lse2 += (size_t)b * lse_ld;
     }
     const int j = threadIdx.x >> 4, rr = threadIdx.x & 15;
     const int r = min(blockIdx.x * 16 + rr, rows - 1);
     float m = -INFINITY, tot = 0.f;
     for (int s = j; s < nslice; s += 16) {  // online (max, sum) over this thread's slices
-        const float pm = pmax[(size_t)s * rows + r], ps = psum[(size_t)s * rows + r];
-        if (pm != -INFINITY) {
-            const float nm = fmaxf(m, pm);
-            tot = tot * ex2(m - nm) + ps * ex2(pm - nm);
+        const float2 v = stat[(size_t)s * rows + r];
+        if (v.x != -INFINITY) {
+            const float nm = fmaxf(m, v.x);
+            tot = tot * ex2(m - nm) + v.y * ex2(v.x - nm);
             m = nm;
         }
     }
@@ -247,13 +244,32 @@ __global__ __launch_bounds__(kThreads) void attn_lse_kernel(const float *__restr
     }
 }
 
+// The same for one row, in one thread; the pairs of its slices are `step` apart.
+__device__ __forceinline__ float slice_lse(const float2 *stat, size_t step, int nslice) {
+    float m = -INFINITY, tot = 0.f;
+    for (int s0 = 0; s0 < nslice; s0 += kFuseSlices) {
+        float2 v[kFuseSlices];
+#pragma unroll
+        for (int j = 0; j < kFuseSlices; ++j) v[j] = stat[min(s0 + j, nslice - 1) * step];
+        float gm = m;
+#pragma unroll
+        for (int j = 0; j < kFuseSlices; ++j) gm = fmaxf(gm, v[j].x);
+        tot *= ex2(m - gm);
+#pragma unroll
+        for (int j = 0; j < kFuseSlices; ++j) tot += s0 + j < nslice ? v[j].y * ex2(v[j].x - gm) : 0.f;
+        m = gm;
+    }
+    return m + __log2f(tot);
+}
+
 // ---------------------------------------------------------------------------------------------
-// pass 2: grid = kv heads (fastest) x key blocks
-template <int D, class SEQ>
+// pass 2: grid = kv heads (fastest) x key blocks of 4 waves of 32 TW keys
+template <int D, class SEQ, int TW, bool FUSE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_colsum_kernel(const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
-                                                               const float *__restrict__ lse2, float *__restrict__ part,
-                                                               int M, int N, int Hq, int Hkv, float scale2, SEQ seq,
-                                                               int lse_ld, size_t part_stride) {
+                                                               const float *__restrict__ lse2, const float2 *__restrict__ stat,
+                                                               float *__restrict__ part, int M, int N, int Hq, int Hkv,
+                                                               float scale2, int nslice, SEQ seq, int lse_ld,
+                                                               size_t seq_stride, size_t part_stride) {
     constexpr int KS = D / 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     Tile<D> &lds = *reinterpret_cast<Tile<D> *>(smem_raw);
@@ -261,10 +277,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         const int b = blockIdx.y;
         N = seq.N[b];
         M = seq.M[b];
-        if ((int)(blockIdx.x / Hkv) * (4 * 32 * kTW) >= N) return;  // uniform: key block past this sequence's keys
+        if ((int)(blockIdx.x / Hkv) * (4 * 32 * TW) >= N) return;  // uniform: key block past this sequence's keys
         k += (size_t)seq.row0[b] * Hkv * D;
         q += (size_t)(seq.row0[b] + N) * Hq * D;
-        lse2 += (size_t)b * lse_ld;
+        if (FUSE) stat += b * seq_stride;
+        else lse2 += (size_t)b * lse_ld;
         part += b * part_stride;
     }
     const int tid = threadIdx.x, lane = tid & 63, lc = lane & 31, half = lane >> 5;
@@ -274,10 +291,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int nchunk = (R + kRows - 1) / kRows;
 
     // this wave's key fragments (A operand: lane = key row)
-    bf16x8 ak[kTW][KS];
-    const int kbase = kb * (4 * 32 * kTW) + w * (32 * kTW);
+    bf16x8 ak[TW][KS];
+    const int kbase = kb * (4 * 32 * TW) + w * (32 * TW);
 #pragma unroll
-    for (int kt = 0; kt < kTW; ++kt) {
+    for (int kt = 0; kt < TW; ++kt) {
         const bf16_t *kp = k + ((size_t)min(kbase + 32 * kt + lc, N - 1) * Hkv + kvh) * D;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) ak[kt][ks] = *reinterpret_cast<const bf16x8 *>(kp + 16 * ks + 8 * half);
@@ -290,7 +307,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     float stage_lse = 0.f;
     // rows per kv head are usually a power of two: shift and mask instead of a division per copy
     const int rep_shift = (rep & (rep - 1)) == 0 ? __builtin_ctz(rep) : -1;  // uniform
-    auto stage = [&](int chunk, int b) {
+    auto stage = [&](int chunk, int b, bool with_lse) {
         int lane_now = lane;
         asm volatile("" : "+v"(lane_now));  // keeps the slot arithmetic here instead of in registers across the loop
 #pragma unroll
@@ -302,27 +319,33 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                                              : qrow_index(rr, rep, Hq, kvh);
             AT::issue(q + qi * D + st_col * 8, &lds.t[b], w, i);
         }
-        if (tid < kRows) {
+        if (with_lse && tid < kRows) {
             const int rr = chunk * kRows + tid;
             // rows past the end get lse = +inf, so their probabilities are exactly 0
-            stage_lse = (rr < R) ? lse2[qrow_index(rr, rep, Hq, kvh)] : INFINITY;
+            const int rc = min(rr, R - 1);
+            if constexpr (FUSE) {
+                stage_lse = slice_lse(stat + (size_t)kvh * R + rc, (size_t)Hkv * R, nslice);
+            } else {
+                stage_lse = lse2[(size_t)kvh * R + rc];
+            }
+            if (rr >= R) stage_lse = INFINITY;
         }
     };
     auto stage_lse_store = [&](int b) {
         if (tid < kRows) lds.lse[b][tid] = stage_lse;
     };
 
-    float col[kTW * 16];
+    float col[TW * 16];
 #pragma unroll
-    for (int j = 0; j < kTW * 16; ++j) col[j] = 0.f;
+    for (int j = 0; j < TW * 16; ++j) col[j] = 0.f;
 
-    stage(0, 0);
+    stage(0, 0, true);
     stage_lse_store(0);
     async_tile_wait();
     __syncthreads();
     for (int chunk = 0; chunk < nchunk; ++chunk) {
         const int cur = chunk & 1;
-        stage(min(chunk + 1, nchunk - 1), cur ^ 1);
+        stage(min(chunk + 1, nchunk - 1), cur ^ 1, chunk + 1 < nchunk);
         // Units of work: (query tile qt, key tile kt), 8 products each, then 16 exponentials folded
         // into the column sums.  The products of the next unit are issued before the exponentials
         // of the current one (two accumulators), so the matrix pipe works while the wave does its
@@ -352,9 +375,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                 __builtin_amdgcn_sched_group_barrier(0x002, 16 / KS, 0);  // adds of the previous ones
             }
         };
-        static_assert(kTW == 2, "two key tiles per wave");
         bf16x8 qf[KS];
-        if (chunk * kRows + kRows <= R) {  // uniform: every query tile of the chunk is real -- one straight block
+        if constexpr (TW == 1) {
+            for (int qt = 0; qt < kRows / 32 && chunk * kRows + 32 * qt < R; ++qt) {
+                load_q(qt, qf);
+                fold(0, products(0, qf), lds.lse[cur][32 * qt + lc]);
+            }
+        } else if (chunk * kRows + kRows <= R) {  // uniform: every query tile of the chunk is real -- one straight block
             load_q(0, qf);
             float lse = lds.lse[cur][lc];
             f32x16 acc0 = products(0, qf), acc1;
@@ -389,9 +416,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
     // butterfly over the 32 query lanes of each half: afterwards lane lc holds the total of
     // register lc (= key tile lc / 16, accumulator row lc % 16)
-    static_assert(kTW == 2, "the butterfly below reduces 32 registers over 32 lanes");
+    if constexpr (TW == 1) {  // 16 registers: lanes 16 apart add up first, the rest is the butterfly over 16
 #pragma unroll
-    for (int step = 0; step < 5; ++step) {
+        for (int j = 0; j < 16; ++j) col[j] += __shfl_xor(col[j], 16, kWave);
+    }
+#pragma unroll
+    for (int step = TW == 1; step < 5; ++step) {
         const int mask = 16 >> step, cnt = 16 >> step;
         const bool up = (lc & mask) != 0;
 #pragma unroll
@@ -402,6 +432,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         }
     }
     const int kt = lc >> 4, i = lc & 15;
+    if (kt >= TW) return;
     const int key = kbase + 32 * kt + 8 * (i / 4) + 4 * half + (i % 4);
     if (key < N) part[(size_t)kvh * N + key] = col[0];
 }
@@ -425,20 +456,31 @@ __global__ __launch_bounds__(kThreads) void attn_score_reduce_kernel(const float
 }
 
 struct Plan {
-    int nrb, nslice, keys_per_slice;
+    int nrb, nslice, keys_per_slice, tw;
+    bool fuse;
 };
 
-Plan make_plan(int M, int N, int Hq, int Hkv) {
+Plan make_plan(int M, int N, int Hq, int Hkv, int nseq) {
     Plan p;
     const int R = M * (Hq / Hkv);
     p.nrb = ceil_div(R, 4 * 32 * kTW);
-    // enough key slices to give the chip a few waves of workgroups, at least one LDS tile each
-    int want = ceil_div(1024, p.nrb * Hkv);
+    // enough key slices to give the chip a few waves of workgroups over the whole batch, at least one LDS
+    // tile each (20 sequences of 1500 keys, 128 text rows: 161 us with slices as for one sequence, 139 with these)
+    const long long per_slice = (long long)p.nrb * Hkv * nseq;
+    int want = (int)((1024 + per_slice - 1) / per_slice);
     const int max_slices = ceil_div(N, kRows);
     if (want > max_slices) want = max_slices;
     if (want < 1) want = 1;
     p.keys_per_slice = ceil_div(ceil_div(N, want), kRows) * kRows;
     p.nslice = ceil_div(N, p.keys_per_slice);
+    // Pass 2 with half the keys per wave while that still leaves compute units without a workgroup: the
+    // rows are staged twice as often, but by twice as many units (1024 keys, 500 text rows: 64 us -> 55; even
+    // from 8192 keys of 8 kv heads on, 4 % slower at 16384).
+    p.tw = (long long)ceil_div(N, 4 * 32 * kTW) * Hkv * nseq <= kNarrowBlocks ? 1 : 2;
+    // Every workgroup of pass 2 combines the slices of its head's rows by itself while that is less than
+    // the launch it saves (1024 keys, 16 text rows, 512 pairs per head: 16.0 us -> 13.7; 4000 keys, 20 rows,
+    // 2560 pairs: 18.0 -> 16.6; 2304 keys, 100 rows, 7200 pairs: 27.3 -> 30.1).
+    p.fuse = (long long)R * p.nslice <= kFusedStats;
     return p;
 }
 
@@ -447,34 +489,35 @@ Plan make_plan(int M, int N, int Hq, int Hkv) {
 template <int D, class SEQ>
 int run(const void *q, const void *k, float *s, int M, int N, int Hq, int Hkv, float scale, void *ws, const SEQ &seq,
         int nseq, int ld, hipStream_t st) {
-    const Plan p = make_plan(M, N, Hq, Hkv);
+    const Plan p = make_plan(M, N, Hq, Hkv, nseq);
     const size_t smem = sizeof(Tile<D>);
+    const auto colsum = p.tw == 1 ? (p.fuse ? &attn_colsum_kernel<D, SEQ, 1, true> : &attn_colsum_kernel<D, SEQ, 1, false>)
+                                  : (p.fuse ? &attn_colsum_kernel<D, SEQ, 2, true> : &attn_colsum_kernel<D, SEQ, 2, false>);
     if (!allow_dynamic_lds(reinterpret_cast<const void *>(&attn_stats_kernel<D, SEQ>), smem) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(&attn_colsum_kernel<D, SEQ>), smem))
+        !allow_dynamic_lds(reinterpret_cast<const void *>(colsum), smem))
         return STRD_EHIP;
-    // per sequence: pmax | psum | lse | part, sequence after sequence inside each of the four regions
+    // per sequence: stat | lse | part, sequence after sequence inside each of the three regions
     const size_t rows = (size_t)M * Hq;
     const size_t stat_stride = rows * p.nslice, part_stride = (size_t)Hkv * N;
-    float *pmax = (float *)ws, *psum = pmax + stat_stride * nseq;
-    float *lse2 = psum + stat_stride * nseq, *part = lse2 + align_up(rows * nseq, 64);
+    float2 *stat = (float2 *)ws;
+    float *lse2 = (float *)(stat + stat_stride * nseq), *part = lse2 + align_up(rows * nseq, 64);
     const float scale2 = scale * kLog2e;
     const int nunits = p.nrb * Hkv * p.nslice;
     attn_stats_kernel<D, SEQ><<<dim3(xcd_grid(nunits), nseq), kThreads, smem, st>>>(
-        (const bf16_t *)q, (const bf16_t *)k, pmax, psum, M, N, Hq, Hkv, scale2, p.nrb, p.keys_per_slice, nunits, seq,
-        stat_stride);
-    attn_lse_kernel<SEQ><<<dim3(ceil_div((int)rows, 16), nseq), kThreads, 0, st>>>(pmax, psum, lse2, (int)rows, p.nslice, seq, Hq,
-                                                                                  stat_stride, (int)rows);
-    const int nkb = ceil_div(N, 4 * 32 * kTW);
-    attn_colsum_kernel<D, SEQ><<<dim3(nkb * Hkv, nseq), kThreads, smem, st>>>((const bf16_t *)q, (const bf16_t *)k, lse2, part,
-                                                                              M, N, Hq, Hkv, scale2, seq, (int)rows,
-                                                                              part_stride);
+        (const bf16_t *)q, (const bf16_t *)k, stat, M, N, Hq, Hkv, scale2, p.nrb, p.keys_per_slice, nunits, seq, stat_stride);
+    if (!p.fuse)
+        attn_lse_kernel<SEQ><<<dim3(ceil_div((int)rows, 16), nseq), kThreads, 0, st>>>(stat, lse2, (int)rows, p.nslice, seq, Hq,
+                                                                                      stat_stride, (int)rows);
+    colsum<<<dim3(ceil_div(N, 4 * 32 * p.tw) * Hkv, nseq), kThreads, smem, st>>>(
+        (const bf16_t *)q, (const bf16_t *)k, lse2, stat, part, M, N, Hq, Hkv, scale2, p.nslice, seq, (int)rows, stat_stride,
+        part_stride);
     attn_score_reduce_kernel<SEQ><<<dim3(ceil_div(N, kThreads), nseq), kThreads, 0, st>>>(
         part, s, N, Hkv, 1.f / ((float)M * (float)Hq), seq, Hq, part_stride, ld);
     return launch_status();
 }
 
 size_t ws_bytes(int M, int N, int Hq, int Hkv, int nseq) {
-    const Plan p = make_plan(M, N, Hq, Hkv);
+    const Plan p = make_plan(M, N, Hq, Hkv, nseq);
     const size_t rows = (size_t)M * Hq;
     return align_up((2 * rows * p.nslice * nseq + align_up(rows * nseq, 64) + (size_t)Hkv * N * nseq) * sizeof(float), 256);
 }

@@ -148,3 +148,15 @@ def test_attention_with_two_key_groups(T, d):
     q, k, v = rn(T, 4, d), rn(T, 2, d), rn(T, 2, d)
     assert_close(f(strd.attn_prefill(q.to(DEV), k.to(DEV), v.to(DEV))), oracle.attn(f(q), f(k), f(v)), TOL[BF16], "o",
                  units=(0, 1))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N,M,Hq,Hkv", [(1, 1, 2, 2), (127, 3, 4, 2), (1024, 65, 4, 2), (1025, 17, 6, 2), (2048, 128, 8, 4),
+                                        (2048, 129, 8, 4), (16384, 5, 4, 2), (16385, 5, 4, 2), (16385, 40, 4, 2)])
+def test_score_attn_narrow_and_fused(N, M, Hq, Hkv, d):
+    """Column sums with 128 and with 256 keys per workgroup (the line is at 128 workgroups of 256), and with the
+    slices of a row combined there (up to 4096 pairs per kv head, eight in flight) or in a launch of their own."""
+    _say("score_attn N=%d M=%d Hq=%d Hkv=%d d=%d" % (N, M, Hq, Hkv, d))
+    rn = _draw(N + M + d, BF16)
+    q, k = rn(M, Hq, d), rn(N, Hkv, d)
+    assert_close(f(strd.score_attn(q.to(DEV), k.to(DEV))), oracle.score_attn(f(q), f(k)), TOL[BF16], "s", units=(0,))
