@@ -165,17 +165,16 @@ int ssd_decode_typed(const void *x, const float *dt, const float *A, const void 
 
 // ------------------------------------------------------------------ attn_decode_step ------
 // o^h = sum_j softmax_j(scale q^h . k_j) v_j over all T cached rows, for one new query per head.
-// Pass 1: workgroup (split s, kv head) = 4 waves, each walking a quarter of the split's tokens;
-// LPT = d / 8 lanes share a token (8 channels each); a wave takes 16 tokens per trip and loads the
-// next trip while it folds the current one; the split length is chosen so that the whole grid is
-// about one resident round of the chip.  Every lane group keeps
-// its own running (max, sum, accumulator) for the REP query heads of the kv head; the groups of a
-// wave are merged by shuffles, the 4 waves through LDS, and the workgroup writes one partial
-// (max, sum, accumulator) per query head.  Pass 2 merges the partials of all splits, 32 channels
-// of one head per workgroup.  Scores are kept in log2 units.
+// Pass 1: workgroup (split s, kv head) = 4 waves that take the split's tokens in turn, 16 per trip, and
+// load the next trip while they fold the current one.  LPT = d / 8 lanes share a token (8 channels
+// each).  Every lane group keeps its own running (max, sum, accumulator) for the REP query heads of
+// the kv head; groups and waves are merged at the end and the workgroup writes one partial (max, sum,
+// accumulator) per query head.  Pass 2 merges the partials of all splits, 32 channels of one head per
+// workgroup.  Scores are kept in log2 units.
+// fp32 caches take attn_decode_partial_kernel, all on the vector units; bf16 ones attn_decode_mfma_kernel.
 constexpr float kNegBig = -1.0e30f;  // stands for "no key seen yet": finite, so differences stay finite
 constexpr int kDecWaves = 4;
-constexpr int kTokSplit = 64;    // slice granularity: one 16-token trip per wave
+constexpr int kTokRound = 16 * kDecWaves;  // tokens of one trip of the four waves
 constexpr int kMaxSplits = 1024;
 
 template <int LPT>
@@ -212,8 +211,7 @@ __global__ __launch_bounds__(kDecWaves * kWave) void attn_decode_partial_kernel(
             acc[r][i] = 0.f;
         }
     }
-    const int per_wave = tok_per_split / kDecWaves;
-    const int t_begin = split * tok_per_split + wave * per_wave, t_end = min(Tn, t_begin + per_wave);
+    const int t_begin = split * tok_per_split + wave * 16, t_end = min(Tn, (split + 1) * tok_per_split);
     const size_t row_stride = (size_t)Hkv * d;
     const T *kbase = kc + (size_t)hk * d + sub * 8, *vbase = vc + (size_t)hk * d + sub * 8;
     constexpr int kUnroll = 16 / TPI;  // 16 tokens per trip
@@ -269,11 +267,11 @@ __global__ __launch_bounds__(kDecWaves * kWave) void attn_decode_partial_kernel(
     };
     V ka[kUnroll], va[kUnroll], kb[kUnroll], vb[kUnroll];
     load_trip(t_begin < Tn ? t_begin : 0, ka, va);
-    for (int t0 = t_begin; t0 < t_end; t0 += 32) {
-        load_trip(t0 + 16, kb, vb);
+    for (int t0 = t_begin; t0 < t_end; t0 += 2 * kTokRound) {
+        load_trip(t0 + kTokRound, kb, vb);
         fold_trip(t0, ka, va);
-        load_trip(t0 + 32, ka, va);
-        if (t0 + 16 < t_end) fold_trip(t0 + 16, kb, vb);
+        load_trip(t0 + 2 * kTokRound, ka, va);
+        if (t0 + kTokRound < t_end) fold_trip(t0 + kTokRound, kb, vb);
     }
     // merge the lane groups of the wave
 #pragma unroll
@@ -323,6 +321,186 @@ __global__ __launch_bounds__(kDecWaves * kWave) void attn_decode_partial_kernel(
     }
 }
 
+// Pass 1 for bf16 caches: the products with the keys on the matrix cores.  The keys of a wave's 16 tokens are
+// the A operand of v_mfma_f32_16x16x32_bf16 (lane = token lane % 16, channels 8 (lane / 16) .. of every 32),
+// the query heads of the kv head the B operand, column lane % 4 (+ 4 hg): a lane ends up with the scores of the
+// four tokens 4 (lane / 16) .. of ONE head, so the softmax of a trip is four exponentials per lane instead of
+// sixteen.  The values are read whole rows at a time by the lanes that hold their tokens' weights -- those of
+// the other heads are a quad permutation away -- and summed in fp32 as they come.  Memory should bound this, and
+// about 530 vector instructions per trip were in its way, now 230: 24875 rows of 8 heads of 128 (102 MB, 4 query
+// heads each), both launches, 33.6 us before, 23.7 now; 8500 rows 19.6 -> 13.6; 500 rows 9.3 -> 7.2.
+// Half lines of the keys are read by two instructions, so only the values bypass the caches (29.7 us at
+// 24875 rows with both non-temporal, 27.7 with neither).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+template <int R>
+__device__ __forceinline__ float quad_pick(float v) {  // of the lane R of this lane's quad
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), R * 0x55, 0xF, 0xF, true));
+}
+template <int R>
+struct QuadPick { static constexpr int value = R; };
+
+template <int LPT, int REP>
+__global__ __launch_bounds__(kDecWaves * kWave) void attn_decode_mfma_kernel(
+    const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf16_t *__restrict__ vc, float *__restrict__ part,
+    float *__restrict__ ml, int Tn, int Hq, int Hkv, int tok_per_split, float scale_log2) {
+    constexpr int d = LPT * 8, KS = d / 32, HG = (REP + 3) / 4, RG = REP < 4 ? REP : 4;  // heads in HG groups of RG
+    constexpr int GPW = kWave / LPT;       // lane groups of a wave, a value row each
+    constexpr int NU = 16 / GPW;           // value rows per lane group and trip
+    constexpr int kSlots = kDecWaves * GPW;
+    __shared__ __attribute__((aligned(16))) float sm_acc[kSlots][RG][d];
+    __shared__ float sm_m[kDecWaves * 4][4], sm_l[kDecWaves * 4][4];
+    const int split = blockIdx.y, hk = blockIdx.x;  // the kv heads of a token range run side by side: whole rows are in flight together
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int sub = lane % LPT, grp = lane / LPT, tok = lane & 15, quarter = lane >> 4, head = (lane & 3) % RG;
+
+    const int t_begin = split * tok_per_split + wave * 16, t_end = min(Tn, (split + 1) * tok_per_split);
+    const size_t row_stride = (size_t)Hkv * d;
+    const bf16_t *kbase = kc + (size_t)hk * d + 8 * quarter, *vbase = vc + (size_t)hk * d + sub * 8;
+    // token of this lane group's u-th value row: its scores are with the lanes of the same quarter
+    const int vtok = 4 * quarter + (LPT == 16 ? 0 : grp & 1);
+    constexpr int VSTEP = LPT == 16 ? 1 : 2;
+    // Rows past the end of the cache are clamped to its last row and masked, so every load is
+    // unconditional and the next trip's loads are in flight while this trip is computed.
+    auto load_trip = [&](int t0, bf16x8 (&kv)[KS], bf16x8 (&vv)[NU]) {
+        const bf16_t *kr = kbase + (size_t)min(t0 + tok, Tn - 1) * row_stride;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) kv[ks] = *reinterpret_cast<const bf16x8 *>(kr + 32 * ks);
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+            vv[u] = __builtin_nontemporal_load(
+                reinterpret_cast<const bf16x8 *>(vbase + (size_t)min(t0 + vtok + VSTEP * u, Tn - 1) * row_stride));
+    };
+    bf16x8 ka[KS], va[NU], kb[KS], vb[NU];
+    load_trip(min(t_begin, Tn - 1), ka, va);
+    bf16x8 qf[HG][KS];
+#pragma unroll
+    for (int hg = 0; hg < HG; ++hg)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            qf[hg][ks] = *reinterpret_cast<const bf16x8 *>(q + (size_t)(hk * REP + 4 * hg + head) * d + 32 * ks + 8 * quarter);
+
+    float m[HG], l[HG], acc[REP][8];
+#pragma unroll
+    for (int hg = 0; hg < HG; ++hg) {
+        m[hg] = kNegBig;
+        l[hg] = 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < REP; ++r)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[r][i] = 0.f;
+
+    auto fold_trip = [&](int t0, const bf16x8 (&kv)[KS], const bf16x8 (&vv)[NU]) {
+        const int room = t_end - t0 - 4 * quarter;  // tokens of this lane's four that count
+        float w[HG][NU], corr[HG];
+#pragma unroll
+        for (int hg = 0; hg < HG; ++hg) {
+            f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv[ks], qf[hg][ks], z, 0, 0, 0);
+            float p[4], mn = m[hg];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                p[i] = i < room ? z[i] * scale_log2 : -INFINITY;
+                mn = fmaxf(mn, p[i]);
+            }
+            corr[hg] = __builtin_amdgcn_exp2f(m[hg] - mn);
+            m[hg] = mn;
+            float sum = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                p[i] = __builtin_amdgcn_exp2f(p[i] - mn);
+                sum += p[i];
+            }
+            l[hg] = fmaf(l[hg], corr[hg], sum);
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                const float even = p[VSTEP * u], odd = p[VSTEP * u + VSTEP - 1];
+                w[hg][u] = grp & 1 && VSTEP == 2 ? odd : even;
+            }
+        }
+        auto head_step = [&](auto pick, int r) {
+            constexpr int R = decltype(pick)::value;
+            if (r >= REP) return;
+            const float c = quad_pick<R>(corr[r / 4]);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[r][i] *= c;
+        };
+        auto value_step = [&](auto pick, int r, int u, const float (&vf)[8]) {
+            constexpr int R = decltype(pick)::value;
+            if (r >= REP) return;
+            const float pw = quad_pick<R>(w[r / 4][u]);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[r][i] = fmaf(pw, vf[i], acc[r][i]);
+        };
+#pragma unroll
+        for (int hg = 0; hg < HG; ++hg) {
+            head_step(QuadPick<0>(), 4 * hg);
+            head_step(QuadPick<1>(), 4 * hg + 1);
+            head_step(QuadPick<2>(), 4 * hg + 2);
+            head_step(QuadPick<3>(), 4 * hg + 3);
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            float vf[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) vf[i] = (float)vv[u][i];
+#pragma unroll
+            for (int hg = 0; hg < HG; ++hg) {
+                value_step(QuadPick<0>(), 4 * hg, u, vf);
+                value_step(QuadPick<1>(), 4 * hg + 1, u, vf);
+                value_step(QuadPick<2>(), 4 * hg + 2, u, vf);
+                value_step(QuadPick<3>(), 4 * hg + 3, u, vf);
+            }
+        }
+    };
+    for (int t0 = t_begin; t0 < t_end; t0 += 2 * kTokRound) {
+        load_trip(t0 + kTokRound, kb, vb);
+        fold_trip(t0, ka, va);
+        load_trip(t0 + 2 * kTokRound, ka, va);
+        if (t0 + kTokRound < t_end) fold_trip(t0 + kTokRound, kb, vb);
+    }
+
+    // merge the lane groups of the four waves, one thread per (query head, channel), in a fixed order
+#pragma unroll
+    for (int hg = 0; hg < HG; ++hg) {
+        if (hg) __syncthreads();
+#pragma unroll
+        for (int r = 0; r < RG; ++r)
+#pragma unroll
+            for (int i = 0; i < 8; i += 4)
+                *reinterpret_cast<f32x4 *>(&sm_acc[wave * GPW + grp][r][sub * 8 + i]) =
+                    f32x4{acc[4 * hg + r][i], acc[4 * hg + r][i + 1], acc[4 * hg + r][i + 2], acc[4 * hg + r][i + 3]};
+        if (tok < 4) {
+            sm_m[wave * 4 + quarter][tok] = m[hg];
+            sm_l[wave * 4 + quarter][tok] = l[hg];
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < RG * d; e += kDecWaves * kWave) {
+            const int r = e / d, c = e % d;
+            float mx = sm_m[0][r];
+#pragma unroll
+            for (int g = 1; g < kDecWaves * 4; ++g) mx = fmaxf(mx, sm_m[g][r]);
+            float num = 0.f, den = 0.f;
+#pragma unroll
+            for (int g = 0; g < kDecWaves * 4; ++g) {
+                const float cw = __builtin_amdgcn_exp2f(sm_m[g][r] - mx);
+                den = fmaf(cw, sm_l[g][r], den);
+                if (LPT == 16) num = fmaf(cw, sm_acc[g][r][c], num);
+                else num = fmaf(cw, sm_acc[2 * g][r][c] + sm_acc[2 * g + 1][r][c], num);
+            }
+            const size_t ph = (size_t)split * Hq + hk * REP + 4 * hg + r;
+            part[ph * d + c] = num;
+            if (c == 0) {
+                ml[ph * 2] = mx;
+                ml[ph * 2 + 1] = den;
+            }
+        }
+    }
+}
+
 // grid (Hq, d / 32), 256 threads: lane c4 = tid % 8 owns 4 channels, the 32 lane groups share the splits.
 template <typename T>
 __global__ __launch_bounds__(256) void attn_decode_combine_kernel(const float *__restrict__ part,
@@ -333,35 +511,44 @@ __global__ __launch_bounds__(256) void attn_decode_combine_kernel(const float *_
     __shared__ float4 sums[32][8];
     const int h = blockIdx.x, c0 = blockIdx.y * 32, tid = threadIdx.x;
     const int lane = tid % kWave, wave = tid / kWave;
+    const int c4 = tid % 8, sg = tid / 8;
+    const float *pc = part + (size_t)h * d + c0 + c4 * 4;
+    // everything is requested at once: the launch is a few dependent trips to memory and little else
+    auto load_part = [&](int s0, float4 (&v)[4]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4 *>(pc + (size_t)min(s0 + 32 * u, nsplit - 1) * Hq * d);
+    };
+    float4 v[4];
+    load_part(sg, v);
+    float2 pair[kMaxSplits / 256];
+#pragma unroll
+    for (int i = 0; i < kMaxSplits / 256; ++i)
+        pair[i] = *reinterpret_cast<const float2 *>(ml + ((size_t)min(tid + 256 * i, nsplit - 1) * Hq + h) * 2);
     float mloc = kNegBig;
-    for (int s = tid; s < nsplit; s += 256) mloc = fmaxf(mloc, ml[((size_t)s * Hq + h) * 2]);
+#pragma unroll
+    for (int i = 0; i < kMaxSplits / 256; ++i) mloc = fmaxf(mloc, pair[i].x);
 #pragma unroll
     for (int x = 32; x > 0; x >>= 1) mloc = fmaxf(mloc, __shfl_xor(mloc, x, kWave));
     if (lane == 0) red[wave] = mloc;
     __syncthreads();
     const float mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
     float dloc = 0.f;
-    for (int s = tid; s < nsplit; s += 256) {
-        const size_t ph = (size_t)s * Hq + h;
-        const float w = exp2f(ml[ph * 2] - mx);
-        wts[s] = w;
-        dloc = fmaf(w, ml[ph * 2 + 1], dloc);
+#pragma unroll
+    for (int i = 0; i < kMaxSplits / 256; ++i) {
+        const int sp = tid + 256 * i;
+        if (sp < nsplit) {
+            wts[sp] = exp2f(pair[i].x - mx);
+            dloc = fmaf(wts[sp], pair[i].y, dloc);
+        }
     }
 #pragma unroll
     for (int x = 32; x > 0; x >>= 1) dloc += __shfl_xor(dloc, x, kWave);
     if (lane == 0) red[4 + wave] = dloc;
     __syncthreads();
     const float den = (red[4] + red[5]) + (red[6] + red[7]);
-    const int c4 = tid % 8, sg = tid / 8;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    const float *pc = part + (size_t)h * d + c0 + c4 * 4;
     for (int s0 = sg; s0 < nsplit; s0 += 32 * 4) {
-        float4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int s = min(s0 + 32 * u, nsplit - 1);
-            v[u] = *reinterpret_cast<const float4 *>(pc + (size_t)s * Hq * d);
-        }
+        if (s0 != sg) load_part(s0, v);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const float w = s0 + 32 * u < nsplit ? wts[s0 + 32 * u] : 0.f;
@@ -382,11 +569,13 @@ __global__ __launch_bounds__(256) void attn_decode_combine_kernel(const float *_
     }
 }
 
-// About kDecGroups workgroups in all: one resident round of the chip, several trips per wave.
-constexpr int kDecGroups = 700;
+// At most kDecGroups workgroups, two per CU: as many on every CU counts for more than one more of them (24875
+// rows of 8 heads: 25.8 us with 700, 23.7 with 512 or 256, 25.3 with 380), and from 90000 rows on two keep more
+// of the cache under way than one.  Slices are whole trips of a wave, and a trip of all four at least.
+constexpr int kDecGroups = 512;
 inline int decode_tok_per_split(int T, int Hkv) {
     const int want = min(kMaxSplits, max(1, kDecGroups / Hkv));
-    return kTokSplit * max(1, ceil_div(T, kTokSplit * want));
+    return max(kTokRound, 16 * ceil_div(T, 16 * want));
 }
 
 template <typename T, int LPT>
@@ -398,9 +587,12 @@ int attn_decode_typed(const void *q, const void *kc, const void *vc, void *o, in
     const float sl2 = scale * 1.4426950408889634f;
     const dim3 grid(Hkv, nsplit);
 #define STRD_ADEC(R)                                                                                       \
-    attn_decode_partial_kernel<T, LPT, R><<<grid, kDecWaves * kWave, 0, st>>>((const T *)q, (const T *)kc,    \
-                                                                              (const T *)vc, part, ml, Tn, Hq, \
-                                                                              Hkv, tps, sl2)
+    if constexpr (std::is_same<T, bf16_t>::value)                                                          \
+        attn_decode_mfma_kernel<LPT, R><<<grid, kDecWaves * kWave, 0, st>>>(                               \
+            (const T *)q, (const T *)kc, (const T *)vc, part, ml, Tn, Hq, Hkv, tps, sl2);                  \
+    else                                                                                                   \
+        attn_decode_partial_kernel<T, LPT, R><<<grid, kDecWaves * kWave, 0, st>>>(                         \
+            (const T *)q, (const T *)kc, (const T *)vc, part, ml, Tn, Hq, Hkv, tps, sl2)
     switch (rep) {
     case 1: STRD_ADEC(1); break;
     case 2: STRD_ADEC(2); break;

@@ -160,3 +160,17 @@ def test_score_attn_narrow_and_fused(N, M, Hq, Hkv, d):
     rn = _draw(N + M + d, BF16)
     q, k = rn(M, Hq, d), rn(N, Hkv, d)
     assert_close(f(strd.score_attn(q.to(DEV), k.to(DEV))), oracle.score_attn(f(q), f(k)), TOL[BF16], "s", units=(0,))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rep", [1, 2, 4, 8])
+def test_decode_attention_trips(rep, d):
+    """bf16 cache, trips of 16 tokens by four waves: one token, a trip and one more, a round of the waves and one
+    more, slices longer than a round whose last wave has a trip less, an even and an odd number of trips."""
+    for T, Hkv in ((1, 2), (16, 2), (17, 1), (64, 2), (65, 2), (16 * 256 * 5 + 3, 1), (16 * 64 * 9, 8), (16 * 64 * 9 + 1, 8)):
+        _say("attn_decode_step T=%d Hkv=%d rep=%d d=%d" % (T, Hkv, rep, d))
+        rn = _draw(T + rep + d, BF16)
+        q, k, v = rn(Hkv * rep, d), rn(T, Hkv, d), rn(T, Hkv, d)
+        k[T // 2] = (3 * q.float().view(Hkv, rep, d)[:, 0]).to(BF16)   # the first head of each group: a peaked row
+        assert_close(f(strd.attn_decode_step(q.to(DEV), k.to(DEV), v.to(DEV))), oracle.attn_decode_step(f(q), f(k), f(v)),
+                     TOL[BF16], "o", units=(0,))
