@@ -4,7 +4,7 @@
 //
 // N is at most a few hundred thousand (<= 512 KB of scores), so the problem is latency-bound.
 // Up to 32768 scores (and beyond 2^20, streaming) one 1024-lane workgroup does everything in one
-// launch; between the two a chain of six short launches with one workgroup per 4096 scores is
+// launch; between the two a chain of short launches with one workgroup per 4096 scores is
 // three to four times faster than streaming (see "Wide form" below).
 // The one-launch form: an MSB radix select on the order-preserving integer image of
 // the floats, which yields the exact K-th value and how many of its duplicates to keep, then one
@@ -15,8 +15,8 @@
 // of every 4096-score tile; up to 32768 scores the keys are read from memory once and stay in
 // registers for all passes, beyond that they are re-read in batches of 8 tiles with all loads of
 // a batch in flight together.  Same-address LDS atomics serialise, so in the first pass every bin
-// has 16 copies, one per lane modulo 16, in adjacent LDS words (different banks), summed when a
-// bin is picked; later passes only count the keys of one bin of the pass before and use 2 copies
+// has 16 copies (fewer for up to 16384 scores), one per lane modulo 16, in adjacent LDS words (different
+// banks), summed when a bin is picked; later passes only count the keys of one bin of the pass before and use 2 copies
 // when those are few; once a bin holds no more than one wave's worth of keys the remaining digits
 // are skipped and one wave ranks those keys directly.  The ordered pass scans 8 tiles per barrier.  No global atomics, no
 // scratch memory, bit-exact and deterministic.
@@ -30,7 +30,11 @@ constexpr int kWaves = kThreads / kWave;
 constexpr int kBins = 2048;
 constexpr int kTile = kThreads * 4;  // scores per tile
 constexpr int kBatch = 8;            // tiles loaded together when streaming / scanned per barrier
-constexpr int kCopies = 16;          // copies of every histogram bin
+// Copies of every histogram bin.  Clearing and summing 16 copies is 128 KB of LDS traffic each; up to two tiles
+// of scores there are too few keys to queue on a counter for long.  With the tiles counted exactly and the scans at one
+// barrier (every wave adds the wave totals up for itself) 1024 scores take 4.1 us for 6.4, 8192 6.1 for 7.6, 16384 9.7 for 13.6.
+template <int TILES>
+constexpr int kCopies = TILES == 1 || TILES == 2 ? 4 : TILES == 4 ? 8 : 16;
 constexpr int kFewCopies = 2;        // copies in passes 1 and 2 when at most kFewKeys keys are still in play
 constexpr int kFewKeys = 4096;
 constexpr int kRankKeys = 64;        // at most this many keys still in play: one wave ranks them directly
@@ -79,19 +83,47 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
     return v;
 }
 
-// Cross-wave step of up to kBatch workgroup scans that share one pair of barriers.  Before the
-// call every wave has stored the inclusive total of scan b in sums[b][wave].  The first 16*kBatch
-// threads turn each row of 16 wave totals into exclusive offsets with a DPP row scan (a row of
-// 16 lanes is exactly one scan) and append the grand total as element [b][kWaves].
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+#define STRD_DPP_MAX(ctrl, row_mask) \
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, ctrl, row_mask, 0xF, false))
+    STRD_DPP_MAX(0x111, 0xF);
+    STRD_DPP_MAX(0x112, 0xF);
+    STRD_DPP_MAX(0x114, 0xF);
+    STRD_DPP_MAX(0x118, 0xF);
+    STRD_DPP_MAX(0x142, 0xA);
+    STRD_DPP_MAX(0x143, 0xC);
+#undef STRD_DPP_MAX
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
+// Smallest and largest key of the workgroup; a barrier.  buf is not written again without another one.
+__device__ __forceinline__ void block_range(uint32_t (&buf)[2][kWaves], uint32_t &kmin, uint32_t &kmax) {
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const uint32_t inv = wave_max(~kmin), top = wave_max(kmax);
+    if (lane == 0) {
+        buf[0][wave] = inv;
+        buf[1][wave] = top;
+    }
+    __syncthreads();
+    kmin = ~wave_max(buf[0][lane & (kWaves - 1)]);
+    kmax = wave_max(buf[1][lane & (kWaves - 1)]);
+}
+
+// Cross-wave step of up to kBatch workgroup scans that share one barrier.  Before the call every wave
+// has stored the inclusive total of scan b in sums[b][wave].  Every wave turns the rows of 16 wave totals into
+// offsets for itself, four rows at a time (a DPP row of 16 lanes is exactly one scan): exclusive
+// offset of this wave and grand total of every scan.  The sums may be written again after one more barrier.
 struct ScanScratch {
     uint32_t sums[kBatch][kWaves];
-    uint32_t base[kBatch][kWaves + 1];
 };
-__device__ __forceinline__ void finish_scans(ScanScratch &sc) {
+template <int B>
+__device__ __forceinline__ void finish_scans(const ScanScratch &sc, uint32_t (&base)[B], uint32_t (&total)[B]) {
+    static_assert(kWaves == 16 && B <= kBatch, "a scan is one row of 16 lanes");
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     __syncthreads();
-    if (threadIdx.x < kBatch * kWaves) {
-        const int b = threadIdx.x / kWaves, w = threadIdx.x % kWaves;
-        const uint32_t v = sc.sums[b][w];
+#pragma unroll
+    for (int b0 = 0; b0 < B; b0 += 4) {
+        const uint32_t v = sc.sums[b0 + lane / kWaves][lane % kWaves];
         uint32_t inc = v;
 #define STRD_DPP_ADD(ctrl) inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, ctrl, 0xF, 0xF, true)
         STRD_DPP_ADD(0x111);
@@ -99,10 +131,12 @@ __device__ __forceinline__ void finish_scans(ScanScratch &sc) {
         STRD_DPP_ADD(0x114);
         STRD_DPP_ADD(0x118);
 #undef STRD_DPP_ADD
-        sc.base[b][w] = inc - v;
-        if (w == kWaves - 1) sc.base[b][kWaves] = inc;
+#pragma unroll
+        for (int b = b0; b < (b0 + 4 < B ? b0 + 4 : B); ++b) {
+            base[b] = (uint32_t)__builtin_amdgcn_readlane((int)(inc - v), (b - b0) * kWaves + wave);
+            total[b] = (uint32_t)__builtin_amdgcn_readlane((int)inc, (b - b0) * kWaves + kWaves - 1);
+        }
     }
-    __syncthreads();
 }
 
 // After a histogram pass: find the bin (scanning from the top) that holds the k-th largest key
@@ -134,10 +168,11 @@ __device__ __forceinline__ void pick_bin(const uint32_t *hist, ScanScratch &sc, 
         sc.sums[0][wave] = i_hi;
         sc.sums[1][wave] = i_lo;
     }
-    finish_scans(sc);
+    uint32_t base[2], total[2];
+    finish_scans(sc, base, total);
     // keys in higher bins than this thread's: all upper-half bins come before any lower-half bin
-    const uint32_t above_hi = sc.base[0][wave] + i_hi - c_hi;
-    const uint32_t above_lo = sc.base[0][kWaves] + sc.base[1][wave] + i_lo - c_lo;
+    const uint32_t above_hi = base[0] + i_hi - c_hi;
+    const uint32_t above_lo = total[0] + base[1] + i_lo - c_lo;
     if (above_hi < k && k <= above_hi + c_hi) {
         found[0] = (uint32_t)d_hi;
         found[1] = k - above_hi;
@@ -150,6 +185,27 @@ __device__ __forceinline__ void pick_bin(const uint32_t *hist, ScanScratch &sc, 
     __syncthreads();
     bin = found[0];
     k = found[1];
+}
+
+// The k-th largest of the c <= kRankKeys values in cand (LDS, published by a barrier before the call) and how many
+// values equal to it are kept: every lane of wave 0 counts the values above and equal to its own.  A barrier.
+__device__ __forceinline__ void rank_few(const uint32_t *cand, uint32_t c, uint32_t k, uint32_t (&ranked)[2]) {
+    const int tid = threadIdx.x;
+    if (tid < kWave) {
+        c = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
+        const uint32_t mine = (uint32_t)tid < c ? cand[tid] : 0u;
+        uint32_t above = 0, equal = 0;
+        for (uint32_t j = 0; j < c; ++j) {
+            const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)j);
+            above += other > mine ? 1u : 0u;
+            equal += other == mine ? 1u : 0u;
+        }
+        if ((uint32_t)tid < c && above < k && k <= above + equal) {  // lanes with equal keys agree
+            ranked[0] = mine;
+            ranked[1] = k - above;
+        }
+    }
+    __syncthreads();
 }
 
 // TILES > 0: N <= TILES * kTile and every key stays in registers.  TILES == 0: streaming.
@@ -165,8 +221,10 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(const float *__re
         scores += (size_t)b * ld;
         idx += seq.koff[b];
     }
-    extern __shared__ __attribute__((aligned(16))) uint32_t hist[];  // [kBins][kCopies]
-    __shared__ ScanScratch scan;
+    constexpr int kCop = kCopies<TILES>;
+    extern __shared__ __attribute__((aligned(16))) uint32_t hist[];  // [kBins][kCop]
+    __shared__ ScanScratch scan[2];          // taken in turn by the batches of the write-out
+    __shared__ uint32_t range[2][kWaves];
     __shared__ uint32_t found[3][3];         // (bin, rank inside the bin, keys in the bin) of each pass
     __shared__ uint32_t cand[kRankKeys];     // direct ranking: the keys (less kmin) still in play
     __shared__ uint32_t ncand, ranked_key[2];
@@ -177,7 +235,7 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(const float *__re
         for (int b = tid * 4; b < kBins * copies; b += kThreads * 4)
             *reinterpret_cast<uint4 *>(&hist[b]) = make_uint4(0, 0, 0, 0);
     };
-    zero_hist(kCopies);
+    zero_hist(kCop);
 
     constexpr int kHeld = TILES > 0 ? TILES : 1;
     uint32_t held[kHeld][4];
@@ -225,21 +283,7 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(const float *__re
         kmin = 0u;
         kmax = 0xFFFFFFFFu;
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, kWave));
-        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, kWave));
-    }
-    if ((tid & (kWave - 1)) == 0) {
-        scan.sums[0][tid / kWave] = kmin;
-        scan.sums[1][tid / kWave] = kmax;
-    }
-    __syncthreads();  // also publishes the cleared histogram
-#pragma unroll
-    for (int wv = 0; wv < kWaves; ++wv) {
-        kmin = min(kmin, scan.sums[0][wv]);
-        kmax = max(kmax, scan.sums[1][wv]);
-    }
+    block_range(range, kmin, kmax);  // its barrier also publishes the cleared histogram
     const int nbits = 32 - __clz(kmax - kmin);     // 0 when all scores are equal
     const int npass = (nbits + 10) / 11;           // uniform
     // Pass 0 sees every key: 16 copies per bin, whatever the distribution.  A later pass only counts
@@ -259,21 +303,7 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(const float *__re
                 if (key != 0 && (rel >> shift_prev) == pfx) cand[atomicAdd(&ncand, 1u)] = rel;
             });
             __syncthreads();
-            if (tid < kWave) {
-                const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)ncand);
-                const uint32_t mine = (uint32_t)tid < c ? cand[tid] : 0u;
-                uint32_t above = 0, equal = 0;
-                for (uint32_t j = 0; j < c; ++j) {
-                    const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)j);
-                    above += other > mine ? 1u : 0u;
-                    equal += other == mine ? 1u : 0u;
-                }
-                if ((uint32_t)tid < c && above < k && k <= above + equal) {  // lanes with equal keys agree
-                    ranked_key[0] = mine;
-                    ranked_key[1] = k - above;
-                }
-            }
-            __syncthreads();
+            rank_few(cand, ncand, k, ranked_key);
             ranked = true;
             break;
         }
@@ -281,7 +311,7 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(const float *__re
         const uint32_t dmask = (1u << min(11, nbits - 11 * pass)) - 1u;
         uint32_t bin;
         if (pass > 0) {  // every lane has read its bins before the barrier inside pick_bin
-            zero_hist(few ? kFewCopies : kCopies);
+            zero_hist(few ? kFewCopies : kCop);
             __syncthreads();
         }
         const uint32_t pfx = shift_prev < 32 ? prefix >> shift_prev : 0u;
@@ -291,14 +321,14 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(const float *__re
                 hist_add<kFewCopies>(hist, (rel >> shift) & dmask, key != 0 && (shift_prev >= 32 || (rel >> shift_prev) == pfx));
             });
             __syncthreads();
-            pick_bin<kFewCopies>(hist, scan, found[pass], k, bin);
+            pick_bin<kFewCopies>(hist, scan[0], found[pass], k, bin);
         } else {
             for_each_key([&](uint32_t key) {
                 const uint32_t rel = key - kmin;
-                hist_add<kCopies>(hist, (rel >> shift) & dmask, key != 0 && (shift_prev >= 32 || (rel >> shift_prev) == pfx));
+                hist_add<kCop>(hist, (rel >> shift) & dmask, key != 0 && (shift_prev >= 32 || (rel >> shift_prev) == pfx));
             });
             __syncthreads();
-            pick_bin<kCopies>(hist, scan, found[pass], k, bin);
+            pick_bin<kCop>(hist, scan[0], found[pass], k, bin);
         }
         prefix |= bin << shift;
         few = found[pass][2] <= kFewKeys;  // uniform
@@ -308,26 +338,28 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(const float *__re
     const uint32_t thresh = kmin + (ranked ? ranked_key[0] : prefix);
     const uint32_t keep_eq = ranked ? ranked_key[1] : k;
 
-    // ---- ordered write-out: kBatch tiles per barrier ----------------------------------------
+    // ---- ordered write-out: kHold tiles per barrier -----------------------------------------
+    constexpr int kHold = TILES > 0 ? TILES : kBatch;
+    static_assert(kHold <= kBatch, "one batch when the keys stay in registers");
     uint32_t out_base = 0, eq_base = 0;  // survivors / duplicates of thresh seen in earlier tiles
-    auto emit_batch = [&](int t0, const uint32_t (&key)[kBatch][4], int ntile) {
+    auto emit_batch = [&](int t0, const uint32_t (&key)[kHold][4], ScanScratch &sc) {
         const int lane = tid & (kWave - 1), wave = tid / kWave;
-        uint32_t cnt[kBatch], inc[kBatch];  // low 16 bits: keys > thresh, high 16 bits: keys == thresh
+        uint32_t cnt[kHold], inc[kHold], base[kHold], total_of[kHold];  // low 16 bits: keys > thresh, high 16 bits: keys == thresh
 #pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
+        for (int b = 0; b < kHold; ++b) {
             cnt[b] = 0;
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 cnt[b] += (key[b][u] > thresh ? 1u : 0u) + (key[b][u] == thresh ? 0x10000u : 0u);
             inc[b] = wave_inclusive_scan(cnt[b]);
-            if (lane == kWave - 1) scan.sums[b][wave] = inc[b];
+            if (lane == kWave - 1) sc.sums[b][wave] = inc[b];
         }
-        finish_scans(scan);
+        finish_scans(sc, base, total_of);
 #pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-            if (b < ntile) {  // uniform
-                const uint32_t total = scan.base[b][kWaves];
-                const uint32_t ex = scan.base[b][wave] + inc[b] - cnt[b];
+        for (int b = 0; b < kHold; ++b) {
+            if (t0 + b < ntiles) {  // uniform
+                const uint32_t total = total_of[b];
+                const uint32_t ex = base[b] + inc[b] - cnt[b];
                 const int i0 = (t0 + b) * kTile + tid * 4;
                 uint32_t gt_before = ex & 0xFFFFu, eq_before = eq_base + (ex >> 16);
 #pragma unroll
@@ -346,152 +378,284 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(const float *__re
             }
         }
     };
-    if (TILES > 0) {
-        uint32_t key[kBatch][4];
-#pragma unroll
-        for (int t0 = 0; t0 < kHeld; t0 += kBatch) {
-#pragma unroll
-            for (int b = 0; b < kBatch; ++b)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) key[b][u] = (t0 + b < kHeld) ? held[t0 + b < kHeld ? t0 + b : 0][u] : 0u;
-            emit_batch(t0, key, min(kBatch, ntiles - t0));
-        }
+    if constexpr (TILES > 0) {
+        emit_batch(0, held, scan[0]);
     } else {
-        for (int t0 = 0; t0 < ntiles; t0 += kBatch) {
-            uint32_t key[kBatch][4];
+        for (int t0 = 0; t0 < ntiles; t0 += kHold) {
+            uint32_t key[kHold][4];
 #pragma unroll
-            for (int b = 0; b < kBatch; ++b) load_tile(scores, N, t0 + b, key[b]);
-            emit_batch(t0, key, min(kBatch, ntiles - t0));
+            for (int b = 0; b < kHold; ++b) load_tile(scores, N, t0 + b, key[b]);
+            emit_batch(t0, key, scan[(t0 / kHold) & 1]);
         }
     }
 }
-
 
 // ---------------------------------------------------------------------------------------------
-// Wide form, 32768 < N <= kWideMax * 4096: one workgroup per 4096-score tile and a chain of short
-// launches instead of one workgroup that streams the scores four times.  The same MSB radix
-// select on the raw keys (three digits of 11, 11 and 10 bits), with one histogram per digit in
-// global memory that the workgroups add their local counts to; the launch that counts digit p
-// first picks the bin of digit p - 1 (every workgroup for itself, from the finished histogram;
-// workgroup 0 leaves the result in memory for the launches after it).  The last two launches count
-// the survivors of every tile and write them out in order.  Integer atomics only: the result is
-// bit-exact and deterministic.
-constexpr int kWideMax = 256;   // tiles (workgroups) at most
-constexpr int kWideCopies = 4;  // copies of a bin in the local histogram of one tile
+// Wide form, 32768 < N <= kWideMax * 4096: one workgroup per 4096-score tile and a chain of four (above 65536 scores
+// five) short launches instead of one workgroup that streams the scores four times.  At these sizes the time is the
+// launches, so there are as few as the dependences allow without one workgroup waiting for another:
+//   range    smallest and largest key of every tile (and the histograms cleared)
+//   hist     histogram of the first 11-bit digit of key - min(key), one for all tiles
+//   collect  every workgroup picks the bin that holds the K-th key for itself; the keys of that bin ("candidates":
+//            their remaining bits and tile) go into one list, every tile leaves its counts of keys above the bin and
+//            in it.  More candidates than the list holds (zeros beside close scores) are counted by a second digit
+//            instead and the launch is made again for that one; otherwise the second has nothing to do (2 us).
+//            It is left out up to 65536 scores, where half of them would have to share one of 2048 bins.
+//   emit     every workgroup ranks the candidates for itself, counts what the tiles before it keep -- the keys
+//            above the bin from their counts, the others from the list -- and writes its tile in order.
+// Candidates that are all one value need no list.  Should there still be too many, emit streams the scores in the list's
+// place.  (Appends and writes are bounded: calls that overlap on the array of the form without a
+// workspace race, with wrong results but inside their buffers.)  The list is in no particular order, only the values in it
+// count: the result is bit-exact and deterministic.  Six launches, with a global histogram per digit of the raw
+// keys and the survivors counted in a launch of their own, took 16.7 us at 36864 scores, 19.2 at 131072 and 50 at 2^20
+// (launched back to back from a graph); these take 14.4, 16.4 and 25.
+constexpr int kWideMax = 256;     // tiles (workgroups) at most
+constexpr int kWideCopies = 4;    // copies of a bin in the local histogram of one tile
+constexpr int kWideCand = 32768;  // candidates the list holds
+constexpr int kLowBits = 21;      // a candidate is its bits below the first digit (at most 21) and, above them, its tile
+static_assert(kWideMax <= 1 << (32 - kLowBits), "the tile fits above the low bits");
 
 struct WideWs {
-    uint32_t ghist[3][kBins];       // global histograms of the three digits
-    uint32_t state[3][4];           // after picking digit p: (prefix so far, rank inside the bin)
-    uint32_t counts[kWideMax][2];   // per tile: keys above the threshold, keys equal to it
+    uint32_t ghist[2][kBins];      // histograms of the first digit and, where it is needed, the second
+    uint32_t ncand;                // candidates in the list
+    uint32_t low_inv, low_max;     // complement of their smallest low bits, their largest; these three follow ghist
+    uint32_t kmin;                 // smallest key of all
+    struct {
+        uint32_t shift, bin;       // bits below the digits picked so far, the picked bin: (key - kmin) >> shift
+        uint32_t k, count;         // rank of the K-th key inside the bin, keys in the bin
+    } pick[2];                     // after one digit, after two
+    uint32_t range[kWideMax][2];   // per tile: smallest and largest key
+    uint32_t counts[kWideMax][2];  // per tile: keys above the bin, keys in it
+    uint32_t cand[kWideCand];
 };
 
-__device__ __forceinline__ int wide_shift(int pass) { return pass == 0 ? 21 : pass == 1 ? 10 : 0; }
-__device__ __forceinline__ uint32_t wide_mask(int pass) { return pass == 2 ? 0x3FFu : 0x7FFu; }
-
-__global__ __launch_bounds__(kThreads) void topk_wide_zero_kernel(WideWs *ws) {
-    uint32_t *h = &ws->ghist[0][0];
-    for (int i = threadIdx.x; i < 3 * kBins; i += kThreads) h[i] = 0u;
-}
-
-// Picks the bin of digit PASS - 1 from its finished global histogram; returns the prefix and rank
-// after it (the same in every thread of every workgroup).
-template <int PASS>
-__device__ __forceinline__ void wide_pick(WideWs *ws, int K, uint32_t *pickbuf, ScanScratch &scan, uint32_t *found,
-                                          uint32_t &prefix, uint32_t &k) {
-    prefix = 0;
-    k = (uint32_t)K;
-    if (PASS > 1) {
-        prefix = ws->state[PASS - 2][0];
-        k = ws->state[PASS - 2][1];
-    }
-    for (int b = threadIdx.x; b < kBins; b += kThreads) pickbuf[b] = ws->ghist[PASS - 1][b];
-    __syncthreads();
-    uint32_t bin;
-    pick_bin<1>(pickbuf, scan, found, k, bin);
-    prefix |= bin << wide_shift(PASS - 1);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        ws->state[PASS - 1][0] = prefix;
-        ws->state[PASS - 1][1] = k;
-    }
-}
-
-// Launch PASS = 0, 1, 2: local histogram of digit PASS over the tile's keys that carry the digits
-// picked so far, added to the global histogram.
-template <int PASS>
-__global__ __launch_bounds__(kThreads) void topk_wide_hist_kernel(const float *__restrict__ scores, int N, int K,
-                                                                    WideWs *ws) {
-    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins * kWideCopies];
-    __shared__ uint32_t pickbuf[kBins];
-    __shared__ ScanScratch scan;
-    __shared__ uint32_t found[3];
-    const int tid = threadIdx.x;
-    for (int b = tid * 4; b < kBins * kWideCopies; b += kThreads * 4)
-        *reinterpret_cast<uint4 *>(&hist[b]) = make_uint4(0, 0, 0, 0);
+__global__ __launch_bounds__(kThreads) void topk_wide_range_kernel(const float *__restrict__ scores, int N, WideWs *ws) {
+    __shared__ uint32_t buf[2][kWaves];
     uint32_t key[4];
     load_tile(scores, N, blockIdx.x, key);
-    uint32_t prefix = 0, k = (uint32_t)K;
-    if constexpr (PASS > 0) wide_pick<PASS>(ws, K, pickbuf, scan, found, prefix, k);
-    __syncthreads();  // the cleared histogram
-    const int shift = wide_shift(PASS), shift_prev = PASS > 0 ? wide_shift(PASS - 1) : 32;
+    for (int i = blockIdx.x * kThreads + threadIdx.x; i < 2 * kBins; i += gridDim.x * kThreads) ws->ghist[i / kBins][i % kBins] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) ws->ncand = ws->low_inv = ws->low_max = 0u;
+    uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-        hist_add<kWideCopies>(hist, (key[u] >> shift) & wide_mask(PASS),
-                              key[u] != 0 && (PASS == 0 || (key[u] >> shift_prev) == (prefix >> shift_prev)));
+        if (key[u]) {
+            kmin = min(kmin, key[u]);
+            kmax = max(kmax, key[u]);
+        }
+    block_range(buf, kmin, kmax);
+    if (threadIdx.x == 0) {
+        ws->range[blockIdx.x][0] = kmin;
+        ws->range[blockIdx.x][1] = kmax;
+    }
+}
+
+// Smallest key of all tiles and the number of bits below the first digit; a barrier.
+__device__ __forceinline__ void wide_range(const WideWs *ws, uint32_t (&buf)[2][kWaves], uint32_t &kmin, int &shift) {
+    uint32_t kmax = 0u;
+    kmin = 0xFFFFFFFFu;
+    if (threadIdx.x < gridDim.x) {
+        kmin = ws->range[threadIdx.x][0];
+        kmax = ws->range[threadIdx.x][1];
+    }
+    block_range(buf, kmin, kmax);
+    shift = max(32 - __clz(kmax - kmin) - 11, 0);
+}
+
+__global__ __launch_bounds__(kThreads) void topk_wide_hist_kernel(const float *__restrict__ scores, int N, WideWs *ws) {
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins * kWideCopies];
+    __shared__ uint32_t buf[2][kWaves];
+    const int tid = threadIdx.x;
+    uint32_t key[4], kmin;
+    load_tile(scores, N, blockIdx.x, key);
+    for (int b = tid * 4; b < kBins * kWideCopies; b += kThreads * 4)
+        *reinterpret_cast<uint4 *>(&hist[b]) = make_uint4(0, 0, 0, 0);
+    int shift;
+    wide_range(ws, buf, kmin, shift);  // its barrier publishes the cleared histogram
+#pragma unroll
+    for (int u = 0; u < 4; ++u) hist_add<kWideCopies>(hist, (key[u] - kmin) >> shift, key[u] != 0);
     __syncthreads();
     for (int b = tid; b < kBins; b += kThreads) {
         const uint4 c = *reinterpret_cast<const uint4 *>(&hist[b * kWideCopies]);
         const uint32_t n = c.x + c.y + c.z + c.w;
-        if (n) atomicAdd(&ws->ghist[PASS][b], n);
+        if (n) atomicAdd(&ws->ghist[0][b], n);
     }
 }
 
-// Picks the last digit: the threshold key and how many keys equal to it survive; counts the tile's
-// keys above and equal to the threshold.
-__global__ __launch_bounds__(kThreads) void topk_wide_count_kernel(const float *__restrict__ scores, int N, int K,
-                                                                     WideWs *ws) {
-    __shared__ uint32_t pickbuf[kBins];
+template <int PASS>
+__global__ __launch_bounds__(kThreads) void topk_wide_collect_kernel(const float *__restrict__ scores, int N, int K,
+                                                                       WideWs *ws) {
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins * kWideCopies];  // the picked digit's, then the next one's
+    __shared__ uint32_t buf[2][kWaves];
     __shared__ ScanScratch scan;
-    __shared__ uint32_t found[3];
+    __shared__ uint32_t found[3], list_base;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    uint32_t key[4], kmin, bin, k = (uint32_t)K;
+    if constexpr (PASS == 1) {
+        const uint32_t c = ws->pick[0].count;
+        if (c <= (uint32_t)kWideCand || ~ws->low_inv == ws->low_max) return;  // uniform, the same in every workgroup
+    }
+    load_tile(scores, N, blockIdx.x, key);
+    for (int b = tid; b < kBins; b += kThreads) hist[b] = ws->ghist[PASS][b];
+    int shift;
+    wide_range(ws, buf, kmin, shift);  // its barrier publishes the bins
+    uint32_t prefix = 0;
+    if constexpr (PASS == 1) {
+        prefix = ws->pick[0].bin << (shift - max(shift - 11, 0));
+        k = ws->pick[0].k;
+        shift = max(shift - 11, 0);
+    }
+    pick_bin<1>(hist, scan, found, k, bin);
+    const uint32_t count = found[2];
+    bin |= prefix;
+    uint32_t cnt = 0, low_min = 0xFFFFFFFFu, low_max = 0u;  // cnt: low 16 bits: keys above the bin, high 16 bits: keys in it
+    const uint32_t low = (1u << shift) - 1u;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const uint32_t rel = key[u] - kmin, d = rel >> shift;
+        if (key[u]) cnt += (d > bin ? 1u : 0u) + (d == bin ? 0x10000u : 0u);
+        if (key[u] && d == bin) {
+            low_min = min(low_min, rel & low);
+            low_max = max(low_max, rel & low);
+        }
+    }
+    const uint32_t inc = wave_inclusive_scan(cnt);
+    if (lane == kWave - 1) scan.sums[0][wave] = inc;
+    uint32_t base[1], total[1];
+    finish_scans(scan, base, total);
+    const bool listed = count <= (uint32_t)kWideCand;  // the same in every workgroup
+    if (tid == 0) {
+        ws->counts[blockIdx.x][0] = total[0] & 0xFFFFu;
+        ws->counts[blockIdx.x][1] = total[0] >> 16;
+        list_base = listed ? atomicAdd(&ws->ncand, total[0] >> 16) : 0u;
+        if (blockIdx.x == 0) {
+            ws->kmin = kmin;
+            ws->pick[PASS].shift = (uint32_t)shift;
+            ws->pick[PASS].bin = bin;
+            ws->pick[PASS].k = k;
+            ws->pick[PASS].count = count;
+        }
+    }
+    if (total[0] >> 16 == 0) return;  // uniform
+    if (listed) {
+        __syncthreads();
+        uint32_t at = list_base + ((base[0] + inc - cnt) >> 16);  // all tiles together append `count` <= kWideCand keys
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t rel = key[u] - kmin;
+            if (key[u] && rel >> shift == bin && at < (uint32_t)kWideCand) ws->cand[at++] = (rel & low) | blockIdx.x << kLowBits;
+        }
+    } else if constexpr (PASS == 0) {
+        const int next = max(shift - 11, 0);
+        for (int b = tid * 4; b < kBins * kWideCopies; b += kThreads * 4)  // (all have read their bins: barriers in pick_bin)
+            *reinterpret_cast<uint4 *>(&hist[b]) = make_uint4(0, 0, 0, 0);
+        block_range(buf, low_min, low_max);  // its barrier publishes the cleared histogram
+        if (tid == 0) {
+            atomicMax(&ws->low_inv, ~low_min);
+            atomicMax(&ws->low_max, low_max);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t rel = key[u] - kmin;
+            hist_add<kWideCopies>(hist, (rel & low) >> next, key[u] != 0 && rel >> shift == bin);
+        }
+        __syncthreads();
+        for (int b = tid; b < kBins; b += kThreads) {
+            const uint4 c = *reinterpret_cast<const uint4 *>(&hist[b * kWideCopies]);
+            const uint32_t n = c.x + c.y + c.z + c.w;
+            if (n) atomicAdd(&ws->ghist[1][b], n);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void topk_wide_emit_kernel(const float *__restrict__ scores, int N, int K, int passes,
+                                                                    const WideWs *__restrict__ ws,
+                                                                    int32_t *__restrict__ idx) {
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins * kFewCopies];
+    __shared__ ScanScratch scan[2];
+    __shared__ uint32_t found[2][3], cand[kRankKeys], ncand, ranked[2];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     uint32_t key[4];
     load_tile(scores, N, blockIdx.x, key);
-    uint32_t thresh, keep_eq;
-    wide_pick<3>(ws, K, pickbuf, scan, found, thresh, keep_eq);
+    uint32_t before_gt = 0, before_eq = 0;  // this thread's share of the keys above / in the bin in earlier tiles
+    if (tid < (int)blockIdx.x) {
+        before_gt = ws->counts[tid][0];
+        before_eq = ws->counts[tid][1];
+    }
+    // one digit was enough, or the candidates are one value, or there was no second pass
+    const bool over = ws->pick[0].count > (uint32_t)kWideCand, one_value = over && ~ws->low_inv == ws->low_max;
+    const int last = passes == 2 && over && !one_value ? 1 : 0;
+    const uint32_t kmin = ws->kmin, bin = ws->pick[last].bin, count = ws->pick[last].count;
+    const int shift = (int)ws->pick[last].shift;
+    const uint32_t low = (1u << shift) - 1u;
+    const bool listed = count <= (uint32_t)kWideCand;
+    uint32_t k = ws->pick[last].k;                 // -> how many keys equal to the threshold survive
+    uint32_t t_low = one_value ? ws->low_max : 0;  // -> the threshold's low bits
+    if (tid == 0) ncand = 0u;
+    // f(low bits, tile) of every key in the bin that is in one of the first `tiles` tiles
+    auto for_each_candidate = [&](int tiles, auto &&f) __attribute__((always_inline)) {
+        if (listed) {
+            for (uint32_t i = tid; i < count; i += kThreads) {
+                const uint32_t c = ws->cand[i];
+                if (c >> kLowBits < (uint32_t)tiles) f(c & ((1u << kLowBits) - 1u));
+            }
+        } else {
+            for (int t = 0; t < tiles; ++t) {
+                uint32_t ck[4];
+                load_tile(scores, N, t, ck);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (ck[u] && (ck[u] - kmin) >> shift == bin) f((ck[u] - kmin) & low);
+            }
+        }
+    };
+    if (shift > 0 && !one_value) {  // uniform, as everything below: the low bits decide, by digits until few keys are left
+        uint32_t left = count;
+        int known = shift;  // the bits of t_low from here on are fixed
+        for (int pass = 0; pass < 2 && known > 0 && left > (uint32_t)kRankKeys; ++pass) {
+            const int sh = max(known - 11, 0);
+            for (int b = tid * 4; b < kBins * kFewCopies; b += kThreads * 4)
+                *reinterpret_cast<uint4 *>(&hist[b]) = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+            for_each_candidate((int)gridDim.x, [&](uint32_t c) {
+                hist_add<kFewCopies>(hist, (c >> sh) & (kBins - 1), c >> known == t_low >> known);
+            });
+            __syncthreads();
+            uint32_t digit;
+            pick_bin<kFewCopies>(hist, scan[0], found[pass], k, digit);
+            t_low |= digit << sh;
+            left = found[pass][2];
+            known = sh;
+        }
+        if (known > 0) {
+            __syncthreads();  // ncand
+            for_each_candidate((int)gridDim.x, [&](uint32_t c) {
+                if (c >> known == t_low >> known) cand[atomicAdd(&ncand, 1u) & (kRankKeys - 1)] = c;
+            });
+            __syncthreads();
+            rank_few(cand, left, k, ranked);
+            t_low = ranked[0];
+            k = ranked[1];
+        }
+        before_eq = 0;
+        for_each_candidate((int)blockIdx.x, [&](uint32_t c) {
+            before_gt += c > t_low ? 1u : 0u;
+            before_eq += c == t_low ? 1u : 0u;
+        });
+    }
+    const uint32_t thresh = kmin + (bin << shift | t_low), keep_eq = k;
     uint32_t cnt = 0;  // low 16 bits: keys > thresh, high 16 bits: keys == thresh
 #pragma unroll
     for (int u = 0; u < 4; ++u) cnt += (key[u] > thresh ? 1u : 0u) + (key[u] == thresh ? 0x10000u : 0u);
-    const uint32_t inc = wave_inclusive_scan(cnt);
-    if (lane == kWave - 1) scan.sums[0][wave] = inc;
-    finish_scans(scan);
-    if (tid == 0) {
-        const uint32_t total = scan.base[0][kWaves];
-        ws->counts[blockIdx.x][0] = total & 0xFFFFu;
-        ws->counts[blockIdx.x][1] = total >> 16;
+    const uint32_t inc = wave_inclusive_scan(cnt), inc_gt = wave_inclusive_scan(before_gt), inc_eq = wave_inclusive_scan(before_eq);
+    if (lane == kWave - 1) {
+        scan[1].sums[0][wave] = inc;
+        scan[1].sums[1][wave] = inc_gt;
+        scan[1].sums[2][wave] = inc_eq;
     }
-}
-
-// Ordered write-out of one tile; the tiles before it are accounted for by their counts.
-__global__ __launch_bounds__(kThreads) void topk_wide_emit_kernel(const float *__restrict__ scores, int N,
-                                                                    const WideWs *__restrict__ ws,
-                                                                    int32_t *__restrict__ idx) {
-    __shared__ ScanScratch scan;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    uint32_t key[4];
-    load_tile(scores, N, blockIdx.x, key);
-    const uint32_t thresh = ws->state[2][0], keep_eq = ws->state[2][1];
-    uint32_t out_base = 0, eq_base = 0;  // survivors / duplicates of thresh in the tiles before this one
-    for (int g = 0; g < (int)blockIdx.x; ++g) {  // uniform, at most kWideMax - 1 trips of two cached loads
-        const uint32_t gt = ws->counts[g][0], eq = ws->counts[g][1];
-        out_base += gt + (min(eq_base + eq, keep_eq) - min(eq_base, keep_eq));
-        eq_base += eq;
-    }
-    uint32_t cnt = 0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) cnt += (key[u] > thresh ? 1u : 0u) + (key[u] == thresh ? 0x10000u : 0u);
-    const uint32_t inc = wave_inclusive_scan(cnt);
-    if (lane == kWave - 1) scan.sums[0][wave] = inc;
-    finish_scans(scan);
-    const uint32_t ex = scan.base[0][wave] + inc - cnt;
+    uint32_t base[3], total[3];
+    finish_scans(scan[1], base, total);
+    const uint32_t eq_base = total[2], out_base = total[1] + min(eq_base, keep_eq);
+    const uint32_t ex = base[0] + inc - cnt;
     const int i0 = blockIdx.x * kTile + tid * 4;
     uint32_t gt_before = ex & 0xFFFFu, eq_before = eq_base + (ex >> 16);
 #pragma unroll
@@ -499,11 +663,20 @@ __global__ __launch_bounds__(kThreads) void topk_wide_emit_kernel(const float *_
         const bool gt = key[u] > thresh, eq = key[u] == thresh;
         if (gt || (eq && eq_before < keep_eq)) {
             const uint32_t eq_kept = min(eq_before, keep_eq) - min(eq_base, keep_eq);
-            idx[out_base + gt_before + eq_kept] = i0 + u;
+            const uint32_t o = out_base + gt_before + eq_kept;
+            if (o < (uint32_t)K) idx[o] = i0 + u;
         }
         gt_before += gt ? 1u : 0u;
         eq_before += eq ? 1u : 0u;
     }
+}
+
+template <int TILES, class SEQ>
+int launch_select(const float *scores, int N, int K, int32_t *idx, const SEQ &seq, int ld, int nseq, hipStream_t s) {
+    const size_t smem = (size_t)kBins * kCopies<TILES> * sizeof(uint32_t);
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&select_topk_kernel<TILES, SEQ>), smem)) return STRD_EHIP;
+    select_topk_kernel<TILES, SEQ><<<nseq, kThreads, smem, s>>>(scores, N, K, idx, seq, ld);
+    return launch_status();
 }
 
 }  // namespace
@@ -516,41 +689,29 @@ int select_topk_varlen_max_n() { return 8 * kTile; }
 
 int select_topk_varlen_launch(const float *scores, int ld, const SeqTab &tab, int nseq, int max_n, int32_t *idx,
                               hipStream_t s) {
-    const size_t smem = (size_t)kBins * kCopies * sizeof(uint32_t);
-    const void *kernel = max_n <= 2 * kTile ? reinterpret_cast<const void *>(&select_topk_kernel<2, SeqTab>)
-                                            : reinterpret_cast<const void *>(&select_topk_kernel<8, SeqTab>);
-    if (!allow_dynamic_lds(kernel, smem)) return STRD_EHIP;
-    if (max_n <= 2 * kTile)
-        select_topk_kernel<2, SeqTab><<<nseq, kThreads, smem, s>>>(scores, 0, 0, idx, tab, ld);
-    else
-        select_topk_kernel<8, SeqTab><<<nseq, kThreads, smem, s>>>(scores, 0, 0, idx, tab, ld);
-    return launch_status();
+    return max_n <= kTile       ? launch_select<1>(scores, 0, 0, idx, tab, ld, nseq, s)
+           : max_n <= 2 * kTile ? launch_select<2>(scores, 0, 0, idx, tab, ld, nseq, s)
+           : max_n <= 4 * kTile ? launch_select<4>(scores, 0, 0, idx, tab, ld, nseq, s)
+                                : launch_select<8>(scores, 0, 0, idx, tab, ld, nseq, s);
 }
 
 int select_topk_launch(const float *scores, int N, int K, int32_t *idx, void *ws, hipStream_t s) {
     if (select_topk_ws(N)) {
         WideWs *w = reinterpret_cast<WideWs *>(ws);
         const int G = ceil_div(N, kTile);
-        topk_wide_zero_kernel<<<1, kThreads, 0, s>>>(w);
-        topk_wide_hist_kernel<0><<<G, kThreads, 0, s>>>(scores, N, K, w);
-        topk_wide_hist_kernel<1><<<G, kThreads, 0, s>>>(scores, N, K, w);
-        topk_wide_hist_kernel<2><<<G, kThreads, 0, s>>>(scores, N, K, w);
-        topk_wide_count_kernel<<<G, kThreads, 0, s>>>(scores, N, K, w);
-        topk_wide_emit_kernel<<<G, kThreads, 0, s>>>(scores, N, w, idx);
+        topk_wide_range_kernel<<<G, kThreads, 0, s>>>(scores, N, w);
+        topk_wide_hist_kernel<<<G, kThreads, 0, s>>>(scores, N, w);
+        topk_wide_collect_kernel<0><<<G, kThreads, 0, s>>>(scores, N, K, w);
+        const int passes = N > 2 * kWideCand ? 2 : 1;
+        if (passes == 2) topk_wide_collect_kernel<1><<<G, kThreads, 0, s>>>(scores, N, K, w);
+        topk_wide_emit_kernel<<<G, kThreads, 0, s>>>(scores, N, K, passes, w, idx);
         return launch_status();
     }
-    const size_t smem = (size_t)kBins * kCopies * sizeof(uint32_t);
-    const void *kernel = N <= 2 * kTile   ? reinterpret_cast<const void *>(&select_topk_kernel<2>)
-                         : N <= 8 * kTile ? reinterpret_cast<const void *>(&select_topk_kernel<8>)
-                                          : reinterpret_cast<const void *>(&select_topk_kernel<0>);
-    if (!allow_dynamic_lds(kernel, smem)) return STRD_EHIP;
-    if (N <= 2 * kTile)
-        select_topk_kernel<2><<<1, kThreads, smem, s>>>(scores, N, K, idx, OneSeq(), 0);
-    else if (N <= 8 * kTile)
-        select_topk_kernel<8><<<1, kThreads, smem, s>>>(scores, N, K, idx, OneSeq(), 0);
-    else
-        select_topk_kernel<0><<<1, kThreads, smem, s>>>(scores, N, K, idx, OneSeq(), 0);
-    return launch_status();
+    return N <= kTile       ? launch_select<1>(scores, N, K, idx, OneSeq(), 0, 1, s)
+           : N <= 2 * kTile ? launch_select<2>(scores, N, K, idx, OneSeq(), 0, 1, s)
+           : N <= 4 * kTile ? launch_select<4>(scores, N, K, idx, OneSeq(), 0, 1, s)
+           : N <= 8 * kTile ? launch_select<8>(scores, N, K, idx, OneSeq(), 0, 1, s)
+                            : launch_select<0>(scores, N, K, idx, OneSeq(), 0, 1, s);
 }
 
 // ---- the same selection for callers that cannot allocate --------------------------------------

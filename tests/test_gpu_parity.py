@@ -146,6 +146,43 @@ def test_select_topk_many_workgroup_form(N):
     _topk_case(np.full(N, 0.25, dtype=np.float32), N // 3)            # all equal: the first N // 3 indices
 
 
+@pytest.mark.parametrize("in_bin", [1, 64, 65, 3000, 32767, 32768, 32769, 40000])
+@pytest.mark.parametrize("low_bits", [1, 11, 12, 21])
+@pytest.mark.parametrize("N", [65536, 65537])
+def test_select_topk_many_workgroup_candidates(N, in_bin, low_bits):
+    """Scores built from their bit patterns so that the first 11-bit digit of key - min(key) leaves exactly
+    `in_bin` candidates with `low_bits` bits below it, over all tiles: ranked directly up to 64, by one
+    digit or two beyond, from the list up to 32768; above, by a second count (65537 scores) or from the scores."""
+    _say("topk candidates N=%d in_bin=%d low_bits=%d" % (N, in_bin, low_bits))
+    r = np.random.default_rng(in_bin + low_bits)
+    top = r.integers(0, 2048, N)
+    top[top == 700] = 701
+    where = r.choice(np.arange(2, N), in_bin, replace=False)
+    top[where] = 700
+    off = (top.astype(np.int64) << low_bits) + r.integers(0, 1 << low_bits, N)
+    off[0], off[1] = 0, (1 << (11 + low_bits)) - 1    # the offsets span exactly 11 + low_bits bits
+    off[where[: in_bin // 3]] = off[where[-1]]        # duplicates of one candidate, spread over the tiles
+    # keys are offsets from the most negative finite one: float bits by the inverse of the order map
+    key = (np.uint64(0x00800001) + off.astype(np.uint64)).astype(np.uint32)
+    s = np.where(key & np.uint32(0x80000000), key ^ np.uint32(0x80000000), ~key).astype(np.uint32).view(np.float32)
+    s = np.where(np.isnan(s), np.float32(np.inf), s)  # the top of a 32-bit range: infinities in place of NaNs
+    above = int((off >= (701 << low_bits)).sum())
+    for rank in sorted({1, in_bin // 3, in_bin // 2 + 1, in_bin} - {0}):
+        _topk_case(s, above + rank)
+
+
+@pytest.mark.parametrize("N", [1000, 4096, 4097, 8192, 8193, 16384, 16385, 32768, 32769, 131072])
+def test_select_topk_one_value_and_zeros(N):
+    """All scores equal (no digit is taken at all) and two thirds exactly zero, on both sides of every kernel's range."""
+    _say("topk one value / zeros N=%d" % N)
+    r = np.random.default_rng(N)
+    _topk_case(np.full(N, 0.25, dtype=np.float32), N // 3)
+    s = (1.0 + 0.1 * r.random(N)).astype(np.float32)
+    s[r.random(N) < 0.66] = 0.0
+    for K in (N // 5, N // 2, N - 1):
+        _topk_case(s, K)
+
+
 # ------------------------------------------------------------------ scores -----------------
 def _mamba_case(w, seed=0):
     h = synth.hidden_states(w, DEV, seed)
