@@ -24,7 +24,8 @@
 // steps, leaves a SIMD with one wave where there are fewer workgroups than CUs, and has the computing waves
 // stand still for the copies: 32 query heads of 128, 843 tokens 23.7 us -> 17.6, 2048 tokens 54.3 -> 41.3; two
 // groups that request their own copies 20.0 and 46.6.  Chunks of 32 keys requested three steps ahead are no
-// faster: the step is bound by the waves' own products and softmax.  The old form is kept for the shortest sequences, a few chunks.)
+// faster: the step is bound by the waves' own products and softmax.  The old form is kept where it is the faster
+// one: a few chunks, or more blocks than two rounds of the chip; see attn_mfma.)
 // Workgroups are issued longest-first (last query block first), the query heads of one kv group back to
 // back on one XCD.
 #include "common.h"
@@ -375,16 +376,22 @@ int attn_mfma(const void *q, const void *k, const void *v, void *o, int T, int H
               hipStream_t st) {
     // Long sequences: 8 computing waves (256 queries) per workgroup share 128-key chunks -- half the K/V copies
     // per query, and a barrier every four tiles instead of every two.  They need about 1.5 workgroups per CU to
-    // balance the causal sweep (equal at 320, 7 % faster at 384 and d = 128).  Below, two key groups; the merge at the end costs
-    // what they save up to about 256 tokens (four chunks).
-    const bool big = (long long)ceil_div(T, 256) * Hq >= 384, tiny = T <= 256;
+    // balance the causal sweep (equal at 320, 7 % faster at 384 and d = 128).  Below, two key groups, one workgroup
+    // per CU, while two rounds of the chip hold them (512 blocks of 128 queries): past that a third round starts and
+    // only a long chain of chunks still pays for it, the longer the more (32 heads of 128, 2048 tokens 54.3 -> 41.3 us;
+    // 2500 67.7 -> 66.0, but 2700 72.7 -> 75.6; 16 heads, 5600 142.6 -> 134.9; 64 heads, 1240 37.9 -> 43.7; heads of 64,
+    // 32 of them, 2200 37.1 -> 36.6 and 2700 45.3 -> 49.9).  The rest, and up to four chunks, where the merge
+    // at the end costs what the groups save: one group that requests its own copies, two workgroups per CU.
+    const int blocks = ceil_div(T, 128);
+    const bool big = (long long)ceil_div(T, 256) * Hq >= 384;
+    const bool one = T <= 256 || (long long)blocks * Hq > 512 + (d == 128 ? 7 : 4) * (long long)blocks;
     if (d == 128)
         return big    ? launch<128, 8, 4, 128, 1>(q, k, v, o, T, Hq, Hkv, scale, st)
-               : tiny ? launch<128, 4, 0, 64, 1>(q, k, v, o, T, Hq, Hkv, scale, st)
+               : one  ? launch<128, 4, 0, 64, 1>(q, k, v, o, T, Hq, Hkv, scale, st)
                       : launch<128, 4, 4, 64, 2>(q, k, v, o, T, Hq, Hkv, scale, st);
     if (d == 64)
         return big    ? launch<64, 8, 4, 128, 1>(q, k, v, o, T, Hq, Hkv, scale, st)
-               : tiny ? launch<64, 4, 0, 64, 1>(q, k, v, o, T, Hq, Hkv, scale, st)
+               : one  ? launch<64, 4, 0, 64, 1>(q, k, v, o, T, Hq, Hkv, scale, st)
                       : launch<64, 4, 4, 64, 2>(q, k, v, o, T, Hq, Hkv, scale, st);
     return STRD_EUNSUPPORTED;
 }
