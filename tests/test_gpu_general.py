@@ -151,6 +151,17 @@ def test_attention_with_two_key_groups(T, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T,Hq", [(300, 170), (300, 184), (641, 84), (641, 96)])
+def test_attention_past_two_rounds_of_workgroups(T, Hq, d):
+    """More than 512 blocks of 128 queries, one group of waves per workgroup again; fewer, two."""
+    _say("attn, rounds, T=%d Hq=%d d=%d" % (T, Hq, d))
+    rn = _draw(T + d, BF16)
+    q, k, v = rn(T, Hq, d), rn(T, 2, d), rn(T, 2, d)
+    assert_close(f(strd.attn_prefill(q.to(DEV), k.to(DEV), v.to(DEV))), oracle.attn(f(q), f(k), f(v)), TOL[BF16], "o",
+                 units=(0, 1))
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("N,M,Hq,Hkv", [(1, 1, 2, 2), (127, 3, 4, 2), (1024, 65, 4, 2), (1025, 17, 6, 2), (2048, 128, 8, 4),
                                         (2048, 129, 8, 4), (16384, 5, 4, 2), (16385, 5, 4, 2), (16385, 40, 4, 2)])
 def test_score_attn_narrow_and_fused(N, M, Hq, Hkv, d):
