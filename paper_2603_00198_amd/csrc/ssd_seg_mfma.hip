@@ -954,22 +954,18 @@ bool ssd_seg_supported(int T, int rows, int H, int P, int G, int n, strd_dtype i
 }
 
 // Whether this kernel or the one that walks the whole sequence in one workgroup per (head, 32
-// channels) (ssd_mfma) is the faster one.  This kernel moves about half the bytes per token through
+// channels) (ssd_mfma) is taken.  This kernel moves about half the bytes per token through
 // a CU's copy path (B and C tiles serve the whole head) and fills the chip with few heads, but pays
-// for its segments with a longer prologue and a second launch.  Two heads per workgroup, in fifths of a step of the
-// other kernel: a step of a segment takes 12, a round of workgroups 16 and the second launch 64 more.  (128 heads of 64:
-// 36 to 41 steps 3 to 9 % slower, 42 steps 48.6 -> 46.6 us, 88 steps 107 -> 76.  Workgroups beyond one per CU take a
-// second round: 192 heads, 24 steps 50.8 -> 59.8, 55 steps 104.8 -> 103.5; 96 heads, 47 steps in one round 47.9 ->
-// 43.9, 55 steps in two 55.1 -> 68.4.)  One head: from segments of 32 steps.
-// With few heads, when the other kernel would leave CUs idle, always.
+// for its segments with a longer prologue and a second launch -- and with a rounding: the carried part of an
+// output passes through LDS in bf16 where ssd_mfma adds it in fp32, and a seam corrects outputs that are
+// already rounded.  So it is kept to where ssd_mfma is no choice: segments of 32 steps and more, or few heads, when
+// that kernel would leave CUs idle.  (In between it is the faster one from about 43 steps at 128 heads of 64 -- 88
+// steps 76 us against 107 -- but at every length measured there, 43 to 124 steps, further from 64 bits: 2.348e-3
+// against 2.346e-3 at 88 steps.)
 bool ssd_seg_preferred(int T, int H, int P, int G) {
     int nseg, seg_steps;
     ssd_seg_plan(T, H, P, G, &nseg, &seg_steps);
-    if (nseg < 2) return false;
-    if (seg_steps >= 32 || H * (P / 32) < 128) return true;
-    const long long whole_steps = (long long)ceil_div(T, kQ) * ceil_div(H * (P / 32), 256);
-    const long long rounds = ceil_div(H * (P / 32) / 4 * nseg, 256);
-    return heads_per_wg(H, P, G) == 2 && 5 * whole_steps > 64 + rounds * (16 + 12 * seg_steps);
+    return nseg >= 2 && (seg_steps >= 32 || H * (P / 32) < 128);
 }
 
 int ssd_seg(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D,

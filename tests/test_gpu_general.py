@@ -89,12 +89,14 @@ def test_scan(T, H, P, G, n, carry, dtype):
     assert none is None and torch.equal(y2, y)
 
 
-@pytest.mark.parametrize("T", [2368, 2369, 2432, 2433, 4100])
+@pytest.mark.parametrize("T", [2368, 2369, 2432, 2433, 4100, 7936, 7937, 8200])
 def test_scan_around_the_switch_to_segments(T):
-    """128 heads of 64 channels: 37 steps of 64 tokens run in one piece, 38 and more in segments.  The first and
-    the last group's heads against the recurrence, the gather form bit for bit."""
+    """128 heads of 64 channels: up to 124 steps of 64 tokens run in one piece (no workspace), 125 and more in four
+    segments of 32 and more (the last one shorter).  The first and the last group's heads against the recurrence, the
+    gather form bit for bit."""
     _say("scan, 128 heads, T=%d" % T)
     H, P, G, n, M = 128, 64, 8, 128, 33
+    assert (strd.lib().strd_ssd_prefill_workspace(T, H, P, G, n, 256, 1) > 0) == (T > 124 * 64)
     g = torch.Generator().manual_seed(T)
     rows = T + 57
     x = torch.randn(rows, H, P, generator=g).to(BF16)

@@ -303,3 +303,15 @@ def test_matrix_core_shapes_refuse_misaligned_tensors_and_report_their_kernel_pa
     assert kp("attn_prefill", 8448, 32, 8, 128) == strd.PATH_MFMA
     assert kp("attn_prefill", 100, 6, 3, 40) == strd.PATH_SIMT
     assert kp("attn_prefill", 100, 6, 4, 64) == strd.PATH_NONE
+
+
+@pytest.mark.parametrize("H,G,steps", [(128, 8, 124), (64, 4, 248), (96, 8, 186), (192, 8, 93), (256, 8, 62), (60, 2, 15)])
+def test_scan_rule_for_segments(H, G, steps):
+    """Heads of 64 channels, two per workgroup: segments only where each has 32 steps of 64 tokens or more -- below, the
+    kernel that adds the carried part of an output in fp32 -- and, with few heads, as soon as there are two of 8 steps.
+    Segments need a workspace, the whole-sequence kernel none."""
+    ws = lambda T: strd.lib().strd_ssd_prefill_workspace(T, H, 64, G, 128, 256, 1)
+    for T in (1, 64 * 36, 64 * 42 + 1, 64 * 88, 64 * steps - 63, 64 * steps):
+        if T <= 64 * steps:
+            assert ws(T) == 0, T
+    assert ws(64 * steps + 1) > 0 and ws(64 * steps * 4) > 0
