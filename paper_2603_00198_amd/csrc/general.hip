@@ -31,6 +31,7 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 __device__ __forceinline__ float ex2(float v) { return __builtin_amdgcn_exp2f(v); }
+__device__ __forceinline__ bool finite(float v) { return fabsf(v) < INFINITY; }
 __device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
 __device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
 // Sum / max over the four lane groups that share a column of an accumulator tile.
@@ -557,7 +558,7 @@ __global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict_
 // on accumulator columns, so the probabilities of a tile are the operand of O^T += V^T P^T as they
 // stand; V is read 4 channels a lane (channels 4 r .. of a block of 64 are rows r of four tiles).
 // NW = 8 up to d = 64, 4 up to 128, 2 up to 256 (LDS).  544 tokens, 4 heads of 64: 54 us with one workgroup
-// per row and no tiles -> 12.8 us; 2361 tokens: 51 us, of which the products alone take 32 and the loads
+// per row and no tiles -> 10.9 us; 2361 tokens: 46 us (51 when this was taken apart), of which the products alone take 32 and the loads
 // alone 30 (16 KB per trip and wave from L2, the rate of a CU's path).  Four waves per SIMD overlap the
 // two; a register set for the next trip in two waves per SIMD, two query tiles a wave (half the loads, but
 // too few workgroups for the causal sweep to balance) and 4 or 16 waves were not faster.
@@ -586,7 +587,7 @@ __global__ __launch_bounds__(NW *kWave) __attribute__((amdgpu_waves_per_eu(DJ ==
     auto row_of = [&](const T *base, int r, int last) {
         return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + __umul24((unsigned)min(r, last), stride));
     };
-    for (int trip = w; trip < ntrip; trip += NW) {
+    auto body = [&](auto edge, int trip) __attribute__((always_inline)) {
         const int key0 = trip * KT * 16, last = Tn - 1 - key0;  // uniform
         const T *kb = k + ((size_t)key0 * Hkv + hk) * d, *vb = v + ((size_t)key0 * Hkv + hk) * d;
         Operand<T, KJ, FULL> kf[KT];
@@ -642,6 +643,32 @@ __global__ __launch_bounds__(NW *kWave) __attribute__((amdgpu_waves_per_eu(DJ ==
             for (int e = 0; e < 4; ++e)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) acc[b][e][i] *= corr;
+        // A probability of 0 takes a key's values out of the sum only if they are finite (0 x inf is NaN).  Tiles past
+        // the block's queries are cleared; in the tile on the diagonal, which some of the queries see and some do not,
+        // values that are not finite are taken out of the operand and added query by query, where there are any.
+        bool odd = false;  // uniform
+        if (edge) {
+#pragma unroll
+            for (int u = 0; u < KT; ++u) {
+                const int ahead = key0 + 16 * u - q0;
+                if (ahead < 0) continue;
+                float t = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int b = 0; b < DJ; ++b)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) t = fmaf(vf[u][i][b][e], 0.f, t);
+                if (!__any(t != 0.f)) continue;
+                odd |= ahead == 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int b = 0; b < DJ; ++b)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) vf[u][i][b][e] = finite(vf[u][i][b][e]) ? vf[u][i][b][e] : 0.f;
+            }
+        }
 #pragma unroll
         for (int u = 0; u < KT; ++u)
 #pragma unroll
@@ -650,6 +677,40 @@ __global__ __launch_bounds__(NW *kWave) __attribute__((amdgpu_waves_per_eu(DJ ==
                 for (int b = 0; b < DJ; ++b)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) acc[b][e] = mfma4(vf[u][i][b][e], z[u][i], acc[b][e]);
+        if (odd) {
+            const int first = q0 - key0;  // the diagonal tile's first key, in the trip
+            const f32x4 zd = KT > 1 && first ? z[KT - 1] : z[0];
+#pragma unroll 1
+            for (int s = 0; s < 16; ++s) {
+                const float mine = s & 2 ? (s & 1 ? zd[3] : zd[2]) : (s & 1 ? zd[1] : zd[0]);
+                const float pr = __shfl(mine, 16 * (s >> 2) + lr, kWave);
+                const T *vr = row_of(vb, first + s, last);
+                if (s > lr) continue;
+#pragma unroll
+                for (int b = 0; b < DJ; ++b)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int ch = 64 * b + 16 * lb + 4 * i + e;
+                            const float val = ch < d ? to_f32(vr[ch]) : 0.f;
+                            acc[b][e][i] = finite(val) ? acc[b][e][i] : fmaf(pr, val, acc[b][e][i]);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);  // a few loads at a time: this must not cost the kernel registers
+                    }
+            }
+        }
+    };
+    // The last trip holds the diagonal (and nothing past it but the rest of its keys).  Up to d = 64 it takes a branch
+    // in the loop, which makes the compiler keep the values of a trip in registers from its start (544 tokens, 4 heads
+    // 13.0 -> 10.9 us, 4096 of 8 heads 195 -> 179); longer rows have no room for that (4096 tokens, 8 heads of 128
+    // 336 -> 410): there the last trip has code of its own and the others are as they were (336 -> 341).
+    if constexpr (DJ > 1) {
+        int trip = w;
+        for (; trip < ntrip - 1; trip += NW) body(std::false_type(), trip);
+        if (trip == ntrip - 1) body(std::true_type(), trip);
+    } else {
+        for (int trip = w; trip < ntrip; trip += NW) body(trip == ntrip - 1, trip);
     }
     run_l = groups_sum(run_l);
 #pragma unroll

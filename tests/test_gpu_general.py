@@ -187,3 +187,31 @@ def test_decode_attention_trips(rep, d):
         k[T // 2] = (3 * q.float().view(Hkv, rep, d)[:, 0]).to(BF16)   # the first head of each group: a peaked row
         assert_close(f(strd.attn_decode_step(q.to(DEV), k.to(DEV), v.to(DEV))), oracle.attn_decode_step(f(q), f(k), f(v)),
                      TOL[BF16], "o", units=(0,))
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("T,d", [(20, 20), (33, 64), (64, 7), (77, 128), (300, 48), (70, 130), (35, 256)])
+def test_attention_keeps_non_finite_rows_to_themselves(T, d, dtype):
+    """One inf or NaN in v at token s is no business of the tokens before s, of the other channels or of the other kv
+    head: they have the same bits as with 0 in its place (its probability does not change).  From s on its channel
+    is not finite.  The same for the whole row of k at s, which makes rows from s on NaN."""
+    if dtype == BF16 and d in (64, 128):
+        d += 4
+    rn = _draw(T + d, dtype)
+    q, k, v = rn(T, 4, d).to(DEV), rn(T, 2, d).to(DEV), rn(T, 2, d).to(DEV)
+    c = d // 2 - 1
+    for s in sorted({1, 15, 16, 17, T // 2, T - 2, T - 1}):
+        for bad in (float("inf"), float("nan")):
+            _say("attn T=%d d=%d %s, %f at %d" % (T, d, dtype, bad, s))
+            clean, dirty = v.clone(), v.clone()
+            clean[s, 1, c], dirty[s, 1, c] = 0.0, bad
+            want, got = strd.attn_prefill(q, k, clean), strd.attn_prefill(q, k, dirty)
+            assert not bool(torch.isfinite(got[s:, 2:, c]).any())
+            got[s:, 2:, c] = want[s:, 2:, c]
+            assert torch.equal(got, want)
+        kd = k.clone()
+        kd[s, 1] = float("nan")
+        want, got = strd.attn_prefill(q, k, v), strd.attn_prefill(q, kd, v)
+        assert bool(torch.isnan(got[s:, 2:]).all())
+        got[s:, 2:] = want[s:, 2:]
+        assert torch.equal(got, want)
