@@ -403,6 +403,18 @@ __global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restr
     wt[lane] = ex2((float)(end - l)) * dtv;  // 0 past the last token
     if (u == 0 && lane == 0) decay[(size_t)h * nc + c] = ex2((float)end);
     __syncthreads();
+    if (t0 + kChunk > Tn) {  // uniform: the rows past the end are the last one again, which 0 does not take out if it is not finite
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (t0 + 16 * kb + 4 * lb + i >= Tn) {
+#pragma unroll
+                    for (int a = 0; a < CPL; ++a) xv[kb][i][a] = 0.f;
+#pragma unroll
+                    for (int b = 0; b < NPL; ++b) bv[kb][i][b] = 0.f;
+                }
+    }
     f32x4 acc[CPL][NPL];
 #pragma unroll
     for (int a = 0; a < CPL; ++a)
@@ -532,6 +544,25 @@ __global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict_
 #pragma unroll
                 for (int i = 0; i < 4; ++i) acc[a][i] *= et;
         }
+        // A weight of 0 takes a later token out of the sum only if its x is finite (0 x inf is NaN): on the diagonal
+        // tile the values that are not are taken out of the operand and added token by token, where there are any.
+        bool odd = false;  // uniform
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j == w) {
+                float z = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int a = 0; a < CPL; ++a) z = fmaf(xv[j][i][a], 0.f, z);
+                odd = __any(z != 0.f);
+                if (odd) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int a = 0; a < CPL; ++a) xv[j][i][a] = finite(xv[j][i][a]) ? xv[j][i][a] : 0.f;
+                }
+            }
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             if (j <= w) {
@@ -540,6 +571,27 @@ __global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict_
 #pragma unroll
                     for (int a = 0; a < CPL; ++a) acc[a] = mfma4(xv[j][i][a], W[j][i], acc[a]);
             }
+        if (odd) {
+            f32x4 wd = W[0];
+#pragma unroll
+            for (int j = 1; j < 4; ++j)
+                if (j == w) wd = W[j];
+#pragma unroll 1
+            for (int u = 0; u < 16; ++u) {
+                const float mine = u & 2 ? (u & 1 ? wd[3] : wd[2]) : (u & 1 ? wd[1] : wd[0]);
+                const float weight = __shfl(mine, 16 * (u >> 2) + lr, kWave);
+                if (u > lr || t >= Tn) continue;
+                const T *xr = x + ((size_t)(t0 + 16 * w + u) * H + h) * P;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int a = 0; a < CPL; ++a) {
+                        const int p = p0 + CPL * (4 * lb + i) + a;
+                        const float val = p < P ? to_f32(xr[p]) : 0.f;
+                        acc[a][i] = finite(val) ? acc[a][i] : fmaf(val, weight, acc[a][i]);
+                    }
+            }
+        }
         if (p0 + 16 * CPL < P) load_block(p0 + 16 * CPL);
         if (t < Tn)
 #pragma unroll

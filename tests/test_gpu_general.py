@@ -215,3 +215,29 @@ def test_attention_keeps_non_finite_rows_to_themselves(T, d, dtype):
         assert bool(torch.isnan(got[s:, 2:]).all())
         got[s:, 2:] = want[s:, 2:]
         assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("T,H,P,G,n", [(20, 2, 32, 1, 16), (64, 2, 64, 1, 64), (100, 2, 20, 1, 40), (130, 2, 33, 2, 7),
+                                       (145, 2, 80, 1, 128)])
+def test_scan_keeps_non_finite_rows_to_themselves(T, H, P, G, n, dtype):
+    """One inf or NaN in x at token s is no business of the tokens before s, of the other channels or of the other
+    head: they have the same bits as with 0 in its place; from s on its channel is not finite, nor is its state.  The
+    last token's inf leaves an infinite state (no row past the end is added to it)."""
+    if dtype == BF16 and n in (64, 128):
+        n -= 4
+    rn, r32 = _draw(T + P, dtype), _draw(T + n, F32)
+    x, B, C = rn(T, H, P).to(DEV), rn(T, G, n).to(DEV), rn(T, G, n).to(DEV)
+    dt, A, D = torch.nn.functional.softplus(r32(T, H)).to(DEV), -0.1 * torch.ones(H, device=DEV), r32(H).to(DEV)
+    p = P // 2 - 1
+    for s in sorted({1, 15, 16, 17, T // 2, T - 2, T - 1}):
+        for bad in (float("inf"), float("nan")):
+            _say("scan T=%d P=%d n=%d %s, %f at %d" % (T, P, n, dtype, bad, s))
+            clean, dirty = x.clone(), x.clone()
+            clean[s, 1, p], dirty[s, 1, p] = 0.0, bad
+            (want, Sw), (got, Sg) = (strd.ssd_prefill(t, dt, A, B, C, D) for t in (clean, dirty))
+            assert not bool(torch.isfinite(got[s:, 1, p]).any()) and not bool(torch.isfinite(Sg[1, p]).any())
+            if s == T - 1 and bad == float("inf"):
+                assert bool((Sg[1, p] == torch.sign(B[s, G - 1].float()) * bad).all())
+            got[s:, 1, p], Sg[1, p] = want[s:, 1, p], Sw[1, p]
+            assert torch.equal(got, want) and torch.equal(Sg, Sw)
