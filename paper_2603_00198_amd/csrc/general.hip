@@ -378,6 +378,13 @@ __device__ __forceinline__ double wave_scan_f64(double v) {
     return v;
 }
 
+// log2 of one token's decay.  2^-4096 is 0 like everything below it, and a sum of such terms has a difference where
+// -inf (A = -inf: a head that forgets at once) has none.  A NaN stays one.
+__device__ __forceinline__ double log2_decay(float dt, float A) {
+    const double v = (double)dt * A * 1.4426950408889634;
+    return v < -4096.0 ? -4096.0 : v;
+}
+
 // One wave per (head, chunk, block of 16 CPL channels x 16 NPL state columns).
 template <typename T, int CPL, int NPL, bool FULL>
 __global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restrict__ x, const float *__restrict__ dt,
@@ -398,7 +405,7 @@ __global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restr
             load_row<CPL, FULL>(x + (t * H + h) * P, p0 + CPL * lr, P, xv[kb][i]);
             load_row<NPL, FULL>(B + (t * G + g) * n, n0 + NPL * lr, n, bv[kb][i]);
         }
-    const double l = wave_scan_f64((double)dtv * A[h] * 1.4426950408889634);
+    const double l = wave_scan_f64(t0 + lane < Tn ? log2_decay(dtv, A[h]) : 0.0);
     const double end = __shfl(l, kWave - 1, kWave);
     wt[lane] = ex2((float)(end - l)) * dtv;  // 0 past the last token
     if (u == 0 && lane == 0) decay[(size_t)h * nc + c] = ex2((float)end);
@@ -513,7 +520,7 @@ __global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict_
     load_block(0);
     if (w == 0) {
         const float dtv = t0 + lane < Tn ? dt[(size_t)(t0 + lane) * H + h] : 0.f;
-        ls[lane] = wave_scan_f64((double)dtv * A[h] * 1.4426950408889634);
+        ls[lane] = wave_scan_f64(t0 + lane < Tn ? log2_decay(dtv, A[h]) : 0.0);
         dts[lane] = dtv;
     }
     __syncthreads();

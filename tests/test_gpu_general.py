@@ -3,6 +3,7 @@ chunk and one more; rows of exactly 16, 64, 128 elements, rows with a padded end
 element; several key slices and row tiles; with and without a carried state.  Against the fp64 oracle at
 a tenth of the fp32 tolerance: sums of at most a few hundred products of 24-bit numbers stay within
 1e-5 of the largest result.  Needs a GPU."""
+import numpy as np
 import pytest
 import torch
 
@@ -241,3 +242,22 @@ def test_scan_keeps_non_finite_rows_to_themselves(T, H, P, G, n, dtype):
                 assert bool((Sg[1, p] == torch.sign(B[s, G - 1].float()) * bad).all())
             got[s:, 1, p], Sg[1, p] = want[s:, 1, p], Sw[1, p]
             assert torch.equal(got, want) and torch.equal(Sg, Sw)
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("T", [1, 63, 64, 65, 200])
+def test_scan_without_memory(T, dtype):
+    """A = -inf: every decay is exp(-inf) = 0, a token sees only itself.  Beside it a head whose decays are below every
+    number (the same result), a usual one, and an incoming state that goes at once."""
+    _say("scan, A = -inf, T=%d %s" % (T, dtype))
+    H, P, n = 3, 20, 12
+    rn, r32 = _draw(T, dtype), _draw(T + 1, F32)
+    x, B, C = rn(T, H, P), rn(T, 1, n), rn(T, 1, n)
+    dt, D, S_in = 0.1 + torch.nn.functional.softplus(r32(T, H)), r32(H), r32(H, P, n)
+    A = torch.tensor([float("-inf"), -1e30, -1.0])
+    dev = lambda t: t.to(DEV)
+    for carry in (False, True):
+        y, S = strd.ssd_prefill(*(dev(t) for t in (x, dt, A, B, C, D)), dev(S_in) if carry else None)
+        y_ref, S_ref = oracle.ssd_seq(f(x), f(dt), np.maximum(f(A), -1e30), f(B), f(C), f(D), f(S_in) if carry else None)
+        assert_close(f(y), y_ref, BOUND[dtype], "y", units=(1,))
+        assert_close(f(S), S_ref, BOUND[dtype], "S", units=(0,))
