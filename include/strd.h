@@ -223,7 +223,7 @@ int strd_compact_batch(const strd_compact_item *items, int n_items, const int32_
  * (32768: one workgroup per sequence), else STRD_EINVAL / STRD_EUNSUPPORTED.
  * The same alignment rules as the single-sequence calls apply to the packed
  * base pointers.  Tie-breaking, NaN handling and error behaviour are those of
- * the single-sequence calls.
+ * the single-sequence calls (a scale that is not > 0: STRD_EINVAL).
  * ------------------------------------------------------------------------- */
 #define STRD_VARLEN_MAX 64
 typedef struct strd_seq {

@@ -189,7 +189,7 @@ size_t strd_score_attn_varlen_workspace(const strd_seq *seqs, int nseq, int Hq, 
 int strd_score_attn_varlen(const void *q_all, const void *k_all, float *scores, int ld, const strd_seq *seqs, int nseq,
                            int Hq, int Hkv, int d, float scale, strd_dtype io, void *ws, size_t ws_bytes, void *stream) {
     SeqPlan p;
-    if (!q_all || !k_all || !scores || Hq < 1 || Hkv < 1 || d < 1 || Hq % Hkv || !io_ok(io) ||
+    if (!q_all || !k_all || !scores || Hq < 1 || Hkv < 1 || d < 1 || Hq % Hkv || !io_ok(io) || !(scale > 0.f) ||
         !plan_seqs(seqs, nseq, false, p) || ld < p.max_n || ld % 4 || (long long)p.max_m * Hq > (1 << 30))
         return STRD_EINVAL;
     const bool mfma = score_attn_mfma_supported(p.max_m, p.max_n, Hq, Hkv, d, io);

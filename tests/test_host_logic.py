@@ -1,6 +1,7 @@
 """CPU-only checks of the host side: the C ABI library loads and exports every symbol the
 header declares, the schedule helpers reproduce the paper's printed arithmetic, and the input
 generator is deterministic."""
+import ctypes
 import os
 import re
 
@@ -315,3 +316,14 @@ def test_scan_rule_for_segments(H, G, steps):
         if T <= 64 * steps:
             assert ws(T) == 0, T
     assert ws(64 * steps + 1) > 0 and ws(64 * steps * 4) > 0
+
+
+@pytest.mark.parametrize("io", [binding.STRD_F32, binding.STRD_BF16])
+@pytest.mark.parametrize("scale", [0.0, -0.125, float("nan"), 0.125])
+def test_scores_of_one_sequence_and_of_a_batch_refuse_the_same_scales(scale, io):
+    """Only scale > 0 gets past the arguments, to the missing workspace (nothing is launched in either case)."""
+    L, at = strd.lib(), 0x10000   # an address that is never read
+    seqs = (binding._Seq * 2)(*[binding._Seq(20, 3, 1), binding._Seq(37, 2, 1)])
+    one = L.strd_score_attn(at, at, at, 3, 20, 4, 2, 64, scale, io, None, 0, None)
+    packed = L.strd_score_attn_varlen(at, at, at, 40, ctypes.cast(seqs, ctypes.c_void_p), 2, 4, 2, 64, scale, io, None, 0, None)
+    assert one == packed == (-3 if scale > 0 else -1)
