@@ -254,9 +254,10 @@ __device__ __forceinline__ float slice_lse(const float2 *stat, size_t step, int 
         float gm = m;
 #pragma unroll
         for (int j = 0; j < kFuseSlices; ++j) gm = fmaxf(gm, v[j].x);
-        tot *= ex2(m - gm);
+        const float ref = gm == -INFINITY ? 0.f : gm;  // no score above -inf yet
+        tot *= ex2(m - ref);
 #pragma unroll
-        for (int j = 0; j < kFuseSlices; ++j) tot += s0 + j < nslice ? v[j].y * ex2(v[j].x - gm) : 0.f;
+        for (int j = 0; j < kFuseSlices; ++j) tot += s0 + j < nslice ? v[j].y * ex2(v[j].x - ref) : 0.f;
         m = gm;
     }
     return m + __log2f(tot);

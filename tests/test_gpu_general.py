@@ -261,3 +261,19 @@ def test_scan_without_memory(T, dtype):
         y_ref, S_ref = oracle.ssd_seq(f(x), f(dt), np.maximum(f(A), -1e30), f(B), f(C), f(D), f(S_in) if carry else None)
         assert_close(f(y), y_ref, BOUND[dtype], "y", units=(1,))
         assert_close(f(S), S_ref, BOUND[dtype], "S", units=(0,))
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("dead", [100, 1024, 1150, 2047])
+@pytest.mark.parametrize("M", [16, 300])
+def test_score_attn_with_keys_no_query_can_see(M, dead, dtype):
+    """The first `dead` keys score -inf with every query: whole slices of the keys (128 of them in the bf16 kernel,
+    eight combined at a time up to 4096 pairs, in a launch of their own beyond) have neither maximum nor sum."""
+    _say("score_attn, %d keys at -inf, M=%d %s" % (dead, M, dtype))
+    rn = _draw(M + dead, dtype)
+    q, k = rn(M, 2, 64).abs() + 0.1, rn(2048, 2, 64)
+    k[:dead] = float("-inf")
+    got = f(strd.score_attn(q.to(DEV), k.to(DEV)))
+    want = oracle.score_attn(f(q), np.where(np.isfinite(f(k)), f(k), -1e30))
+    assert (got[:dead] == 0.0).all()
+    assert_close(got, want, BOUND[dtype], "s", units=(0,))
