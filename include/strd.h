@@ -265,8 +265,11 @@ int strd_compact_varlen(const strd_compact_item *items, int n_items, const int32
  *   ws  [dev] strd_ssd_prefill_workspace(T, ...) bytes.  bf16 matrix-core shapes: 0 for short
  *       sequences; for long ones the sequence is cut into segments that run side by side, and the local end state and total
  *       decay of every segment but the last pass through the workspace ((segments - 1) * H * P * n
- *       + segments * H floats).  Other shapes: the state before every 64-token chunk and the chunks'
- *       decays, (P * n + 1) * H floats per chunk.  Too small or NULL when needed: STRD_EWORKSPACE.
+ *       + segments * H floats); too small or NULL when needed: STRD_EWORKSPACE.  Other shapes: the state
+ *       before every 64-token chunk and the chunks' decays, (P * n + 1) * H floats per chunk, of as many
+ *       chunks as fit 256 MB (one at least), and two states more when that is not all of them.  Here it
+ *       may be smaller or NULL: the call then walks the sequence token by token, which takes 65 times as
+ *       long at 544 tokens.
  * Requires T >= 0, H % G == 0.
  * ------------------------------------------------------------------------- */
 size_t strd_ssd_prefill_workspace(int T, int H, int P, int G, int n, int chunk, strd_dtype io);

@@ -266,12 +266,14 @@ int strd_ssd_prefill(const void *x, const float *dt, const float *A, const void 
     const bool mfma = ssd_mfma_supported(T, T, H, P, G, n, io) || ssd_seg_supported(T, T, H, P, G, n, io);
     if (mfma && !aligned16(x, B, C, S_in, y, S_out, ws)) return STRD_EINVAL;
     const size_t need = strd_ssd_prefill_workspace(T, H, P, G, n, chunk, io);
-    if (need && (!ws || ws_bytes < need)) return STRD_EWORKSPACE;
+    const bool missing = need && (!ws || ws_bytes < need);
+    if (missing && mfma) return STRD_EWORKSPACE;
     if (use_seg(T, T, H, P, G, n, io))
         return ssd_seg(x, dt, A, B, C, D, S_in, y, S_out, nullptr, 0, 0, T, H, P, G, n, ws, as_stream(stream));
     if (mfma) return ssd_mfma(x, dt, A, B, C, D, S_in, y, S_out, nullptr, 0, 0, T, H, P, G, n, as_stream(stream));
     if (!ssd_general_supported(n)) return STRD_EUNSUPPORTED;
-    return ssd_general(x, dt, A, B, C, D, S_in, y, S_out, T, H, P, G, n, io, ws, as_stream(stream));
+    return ssd_general(x, dt, A, B, C, D, S_in, y, S_out, T, H, P, G, n, io, missing || !aligned16(ws) ? nullptr : ws,
+                       as_stream(stream));
 }
 
 int strd_ssd_prefill_gather(const void *x, const float *dt, const float *A, const void *B, const void *C,

@@ -277,3 +277,46 @@ def test_score_attn_with_keys_no_query_can_see(M, dead, dtype):
     want = oracle.score_attn(f(q), np.where(np.isfinite(f(k)), f(k), -1e30))
     assert (got[:dead] == 0.0).all()
     assert_close(got, want, BOUND[dtype], "s", units=(0,))
+
+
+def _scan_inputs(T, H, P, G, n, dtype, seed):
+    rn, r32 = _draw(seed, dtype), _draw(seed + 1, F32)
+    x, B, C = rn(T, H, P), rn(T, G, n), rn(T, G, n)
+    return x, torch.nn.functional.softplus(r32(T, H)), -torch.exp(2 * torch.rand(H, generator=torch.Generator().manual_seed(T))), \
+        B, C, r32(H), r32(H, P, n)
+
+
+@pytest.mark.parametrize("T", [1024, 1025, 2048, 2118])
+def test_scan_in_rounds_of_chunks(T):
+    """64 heads of 64 x 1024: 16 chunks of 64 tokens make a round.  One round, one and a token, two, two and a part;
+    the first and the last head against the recurrence."""
+    _say("general scan in rounds, T=%d" % T)
+    t = _scan_inputs(T, 64, 64, 1, 1024, F32, T)
+    x, dt, A, B, C, D, S_in = (v.to(DEV) for v in t)
+    y, S = strd.ssd_prefill(x, dt, A, B, C, D, S_in)
+    y0, _ = strd.ssd_prefill(x, dt, A, B, C, D, None, want_state=False)
+    for h in (0, 63):
+        hs = slice(h, h + 1)
+        rows = (f(t[0][:, hs]), f(t[1][:, hs]), f(t[2][hs]), f(t[3]), f(t[4]), f(t[5][hs]))
+        y_ref, S_ref = oracle.ssd_seq(*rows, f(t[6][hs]))
+        assert_close(f(y[:, hs]), y_ref, BOUND[F32], "y", units=(1,))
+        assert_close(f(S[hs]), S_ref, BOUND[F32], "S", units=(0,))
+        assert_close(f(y0[:, hs]), oracle.ssd_seq(*rows, None)[0], BOUND[F32], "y from zero", units=(1,))
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("T,H,P,G,n", [(1, 2, 32, 1, 16), (65, 3, 20, 1, 40), (200, 2, 80, 1, 130), (577, 8, 32, 1, 16)])
+def test_scan_without_a_workspace(T, H, P, G, n, dtype):
+    """A caller that brings none, or too little, gets the recurrence."""
+    _say("general scan without a workspace, T=%d P=%d n=%d %s" % (T, P, n, dtype))
+    t = _scan_inputs(T, H, P, G, n, dtype, T + n)
+    dev = [v.to(DEV) for v in t]
+    y_ref, S_ref = oracle.ssd_seq(*(f(v) for v in t))
+    y, S = strd.ssd_prefill(*dev, ws=torch.empty(16, dtype=torch.uint8, device=DEV))
+    y2, S2 = torch.empty_like(y), torch.empty_like(S)
+    ptr = [v.data_ptr() for v in dev]
+    assert strd.lib().strd_ssd_prefill(*ptr, y2.data_ptr(), S2.data_ptr(), T, H, P, G, n, 256,
+                                       0 if dtype == F32 else 1, None, 0, torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(y, y2) and torch.equal(S, S2)
+    assert_close(f(y), y_ref, BOUND[dtype], "y", units=(1,))
+    assert_close(f(S), S_ref, BOUND[dtype], "S", units=(0,))

@@ -327,3 +327,13 @@ def test_scores_of_one_sequence_and_of_a_batch_refuse_the_same_scales(scale, io)
     one = L.strd_score_attn(at, at, at, 3, 20, 4, 2, 64, scale, io, None, 0, None)
     packed = L.strd_score_attn_varlen(at, at, at, 40, ctypes.cast(seqs, ctypes.c_void_p), 2, 4, 2, 64, scale, io, None, 0, None)
     assert one == packed == (-3 if scale > 0 else -1)
+
+
+def test_workspace_of_the_general_scan_is_bounded():
+    """The states of one round of chunks (256 MB, or one chunk) and two states between rounds, whatever the length."""
+    ws = lambda T, H, P, n: strd.lib().strd_ssd_prefill_workspace(T, H, P, 1, n, 256, binding.STRD_F32)
+    state = 128 * 64 * 128 * 4
+    assert ws(64, 128, 64, 128) == state + 512 and ws(65, 128, 64, 128) == 2 * state + 1024
+    assert ws(4096, 128, 64, 128) == 64 * state + 64 * 512
+    assert ws(4097, 128, 64, 128) == ws(1 << 30, 128, 64, 128) == 66 * state + 64 * 512
+    assert ws(1 << 20, 4096, 64, 1024) == 3 * 4096 * 64 * 1024 * 4 + 4096 * 4
