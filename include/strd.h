@@ -143,7 +143,7 @@ int strd_score_mamba_full(const void *B_vis, const void *C_txt, const float *dt_
  *   idx    [dev] [K] int32 output, strictly ascending
  * Requires 1 <= K <= N.  Bit-exact and deterministic.
  *   ws     [dev] strd_select_topk_workspace(N, K) bytes (0 up to 32768 scores and above 2^20;
- *          about 150 KB of histograms, counters and candidates between); contents need not be initialised and
+ *          about 570 KB of histograms, counters, candidates and tables between); contents need not be initialised and
  *          are not preserved; STRD_EWORKSPACE if it is missing or too small
  * ------------------------------------------------------------------------- */
 size_t strd_select_topk_workspace(int N, int K);
@@ -152,8 +152,8 @@ int strd_select_topk(const float *scores, int N, int K, int32_t *idx, void *ws, 
 
 /* select_topk_noalloc -- strd_select_topk for callers that cannot allocate device memory: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same result,
- * bit for bit; no workspace argument: the histograms, counters and candidates of the selection live
- * in a 150 KB array inside the library's image, one copy per GPU, held until the process ends.  The
+ * bit for bit; no workspace argument: the histograms, counters, candidates and tables of the selection
+ * live in a 570 KB array inside the library's image, one copy per GPU, held until the process ends.  The
  * call allocates and frees nothing (no hipMalloc / hipFree, no allocating library routine).
  *   N at most strd_select_topk_noalloc_max_n() = 1 048 576 scores; more gives STRD_EUNSUPPORTED
  *   and nothing is launched.  Other arguments and errors as strd_select_topk.

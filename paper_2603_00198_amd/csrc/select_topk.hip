@@ -391,32 +391,37 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(const float *__re
 }
 
 // ---------------------------------------------------------------------------------------------
-// Wide form, 32768 < N <= kWideMax * 4096: one workgroup per 4096-score tile and a chain of four (above 65536 scores
-// five) short launches instead of one workgroup that streams the scores four times.  At these sizes the time is the
+// Wide form, 32768 < N <= kWideMax * 4096: one workgroup per 4096-score tile and a chain of five short launches
+// instead of one workgroup that streams the scores four times.  At these sizes the time is the
 // launches, so there are as few as the dependences allow without one workgroup waiting for another:
 //   range    smallest and largest key of every tile (and the histograms cleared)
 //   hist     histogram of the first 11-bit digit of key - min(key), one for all tiles
 //   collect  every workgroup picks the bin that holds the K-th key for itself; the keys of that bin ("candidates":
 //            their remaining bits and tile) go into one list, every tile leaves its counts of keys above the bin and
-//            in it.  More candidates than the list holds (zeros beside close scores) are counted by a second digit
-//            instead and the launch is made again for that one; otherwise the second has nothing to do (2 us).
-//            It is left out up to 65536 scores, where half of them would have to share one of 2048 bins.
-//   emit     every workgroup ranks the candidates for itself, counts what the tiles before it keep -- the keys
-//            above the bin from their counts, the others from the list -- and writes its tile in order.
-// Candidates that are all one value need no list.  Should there still be too many, emit streams the scores in the list's
-// place.  (Appends and writes are bounded: calls that overlap on the array of the form without a
+//            in it.  More candidates than the list holds (close scores beside zeros or an outlier) are counted by the
+//            next digit instead, and
+//   collect  is made again for that one (otherwise, 2 us, it has nothing to do).  Still too many: only the last 10 bits
+//            are open then, and every tile leaves a table of how many of its candidates lie at or above each value.
+//   emit     every workgroup ranks the candidates for itself, from the list or by a third digit, counts what the
+//            tiles before it keep -- the keys above the bin from their counts, the others from the list or their
+//            tables -- and writes its tile in order.
+// Candidates that are all one value need neither.  No workgroup reads another's scores, whatever their values, and no
+// more than kWideCand equal keys meet on one counter in emit (a list of 32768 without the tables took 45 us instead of 21 at
+// 65536 close scores and a zero, 343 instead of 33 at 2^20, 51 instead of 16 where half the scores are one value).  (Appends,
+// table reads and writes are bounded: calls that overlap on the array of the form without a
 // workspace race, with wrong results but inside their buffers.)  The list is in no particular order, only the values in it
 // count: the result is bit-exact and deterministic.  Six launches, with a global histogram per digit of the raw
-// keys and the survivors counted in a launch of their own, took 16.7 us at 36864 scores, 19.2 at 131072 and 50 at 2^20
-// (launched back to back from a graph); these take 14.4, 16.4 and 25.
+// keys and the survivors counted in a launch of their own, took 24 us at 36864 to 131072 scores and 52
+// at 2^20 (back to back, workspace from an allocator); these take 16 to 17 (21 where a second digit is needed), 24 to 33.
 constexpr int kWideMax = 256;     // tiles (workgroups) at most
 constexpr int kWideCopies = 4;    // copies of a bin in the local histogram of one tile
-constexpr int kWideCand = 32768;  // candidates the list holds
+constexpr int kWideCand = 4096;   // candidates the list holds
 constexpr int kLowBits = 21;      // a candidate is its bits below the first digit (at most 21) and, above them, its tile
+constexpr int kLastBins = 1024;   // values of the bits below the second digit
 static_assert(kWideMax <= 1 << (32 - kLowBits), "the tile fits above the low bits");
 
 struct WideWs {
-    uint32_t ghist[2][kBins];      // histograms of the first digit and, where it is needed, the second
+    uint32_t ghist[3][kBins];      // histograms of the first digit and, where they are needed, the second and the third
     uint32_t ncand;                // candidates in the list
     uint32_t low_inv, low_max;     // complement of their smallest low bits, their largest; these three follow ghist
     uint32_t kmin;                 // smallest key of all
@@ -427,13 +432,14 @@ struct WideWs {
     uint32_t range[kWideMax][2];   // per tile: smallest and largest key
     uint32_t counts[kWideMax][2];  // per tile: keys above the bin, keys in it
     uint32_t cand[kWideCand];
+    uint16_t from[kWideMax][kLastBins];  // per tile, two digits picked: keys in the bin whose low bits are at least so much
 };
 
 __global__ __launch_bounds__(kThreads) void topk_wide_range_kernel(const float *__restrict__ scores, int N, WideWs *ws) {
     __shared__ uint32_t buf[2][kWaves];
     uint32_t key[4];
     load_tile(scores, N, blockIdx.x, key);
-    for (int i = blockIdx.x * kThreads + threadIdx.x; i < 2 * kBins; i += gridDim.x * kThreads) ws->ghist[i / kBins][i % kBins] = 0u;
+    for (int i = blockIdx.x * kThreads + threadIdx.x; i < 3 * kBins; i += gridDim.x * kThreads) ws->ghist[i / kBins][i % kBins] = 0u;
     if (blockIdx.x == 0 && threadIdx.x == 0) ws->ncand = ws->low_inv = ws->low_max = 0u;
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
 #pragma unroll
@@ -544,12 +550,12 @@ __global__ __launch_bounds__(kThreads) void topk_wide_collect_kernel(const float
             const uint32_t rel = key[u] - kmin;
             if (key[u] && rel >> shift == bin && at < (uint32_t)kWideCand) ws->cand[at++] = (rel & low) | blockIdx.x << kLowBits;
         }
-    } else if constexpr (PASS == 0) {
-        const int next = max(shift - 11, 0);
+    } else if (PASS == 0 || shift > 0) {
+        const int next = PASS == 0 ? max(shift - 11, 0) : 0;
         for (int b = tid * 4; b < kBins * kWideCopies; b += kThreads * 4)  // (all have read their bins: barriers in pick_bin)
             *reinterpret_cast<uint4 *>(&hist[b]) = make_uint4(0, 0, 0, 0);
         block_range(buf, low_min, low_max);  // its barrier publishes the cleared histogram
-        if (tid == 0) {
+        if (PASS == 0 && tid == 0) {
             atomicMax(&ws->low_inv, ~low_min);
             atomicMax(&ws->low_max, low_max);
         }
@@ -559,15 +565,26 @@ __global__ __launch_bounds__(kThreads) void topk_wide_collect_kernel(const float
             hist_add<kWideCopies>(hist, (rel & low) >> next, key[u] != 0 && rel >> shift == bin);
         }
         __syncthreads();
-        for (int b = tid; b < kBins; b += kThreads) {
+        auto bin_count = [&](int b) {
             const uint4 c = *reinterpret_cast<const uint4 *>(&hist[b * kWideCopies]);
-            const uint32_t n = c.x + c.y + c.z + c.w;
-            if (n) atomicAdd(&ws->ghist[1][b], n);
+            return c.x + c.y + c.z + c.w;
+        };
+        for (int b = tid; b < kBins; b += kThreads) {
+            const uint32_t n = bin_count(b);
+            if (n) atomicAdd(&ws->ghist[PASS + 1][b], n);
+        }
+        if constexpr (PASS == 1) {  // thread t: the value kLastBins - 1 - t, so that the scan adds up from the top
+            static_assert(kLastBins == kThreads, "a value per thread");
+            const int b = kLastBins - 1 - tid;
+            const uint32_t at_least = wave_inclusive_scan(bin_count(b));
+            if (lane == kWave - 1) scan.sums[0][wave] = at_least;
+            finish_scans(scan, base, total);
+            ws->from[blockIdx.x][b] = (uint16_t)(base[0] + at_least);
         }
     }
 }
 
-__global__ __launch_bounds__(kThreads) void topk_wide_emit_kernel(const float *__restrict__ scores, int N, int K, int passes,
+__global__ __launch_bounds__(kThreads) void topk_wide_emit_kernel(const float *__restrict__ scores, int N, int K,
                                                                     const WideWs *__restrict__ ws,
                                                                     int32_t *__restrict__ idx) {
     __shared__ __attribute__((aligned(16))) uint32_t hist[kBins * kFewCopies];
@@ -581,34 +598,33 @@ __global__ __launch_bounds__(kThreads) void topk_wide_emit_kernel(const float *_
         before_gt = ws->counts[tid][0];
         before_eq = ws->counts[tid][1];
     }
-    // one digit was enough, or the candidates are one value, or there was no second pass
+    // one digit was enough, or the candidates are one value, or a second was picked
     const bool over = ws->pick[0].count > (uint32_t)kWideCand, one_value = over && ~ws->low_inv == ws->low_max;
-    const int last = passes == 2 && over && !one_value ? 1 : 0;
+    const int last = over && !one_value ? 1 : 0;
     const uint32_t kmin = ws->kmin, bin = ws->pick[last].bin, count = ws->pick[last].count;
     const int shift = (int)ws->pick[last].shift;
-    const uint32_t low = (1u << shift) - 1u;
-    const bool listed = count <= (uint32_t)kWideCand;
     uint32_t k = ws->pick[last].k;                 // -> how many keys equal to the threshold survive
     uint32_t t_low = one_value ? ws->low_max : 0;  // -> the threshold's low bits
     if (tid == 0) ncand = 0u;
-    // f(low bits, tile) of every key in the bin that is in one of the first `tiles` tiles
+    // f(low bits) of every key in the list that is in one of the first `tiles` tiles
     auto for_each_candidate = [&](int tiles, auto &&f) __attribute__((always_inline)) {
-        if (listed) {
-            for (uint32_t i = tid; i < count; i += kThreads) {
-                const uint32_t c = ws->cand[i];
-                if (c >> kLowBits < (uint32_t)tiles) f(c & ((1u << kLowBits) - 1u));
-            }
-        } else {
-            for (int t = 0; t < tiles; ++t) {
-                uint32_t ck[4];
-                load_tile(scores, N, t, ck);
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (ck[u] && (ck[u] - kmin) >> shift == bin) f((ck[u] - kmin) & low);
-            }
+        for (uint32_t i = tid; i < count; i += kThreads) {
+            const uint32_t c = ws->cand[i];
+            if (c >> kLowBits < (uint32_t)tiles) f(c & ((1u << kLowBits) - 1u));
         }
     };
-    if (shift > 0 && !one_value) {  // uniform, as everything below: the low bits decide, by digits until few keys are left
+    // uniform, as everything below: the low bits decide, ...
+    if (shift > 0 && !one_value && count > (uint32_t)kWideCand) {  // ... by one more digit and the tiles' tables
+        for (int b = tid; b < kBins; b += kThreads) hist[b] = ws->ghist[2][b];
+        __syncthreads();
+        pick_bin<1>(hist, scan[0], found[0], k, t_low);
+        if (tid < (int)blockIdx.x) {
+            const uint32_t at = min(t_low, (uint32_t)kLastBins - 1), above = at + 1 < kLastBins ? ws->from[tid][at + 1] : 0u;
+            const bool any = before_eq > 0;  // (a tile without keys in the bin leaves no table)
+            before_gt += any ? above : 0u;
+            before_eq = any ? ws->from[tid][at] - above : 0u;
+        }
+    } else if (shift > 0 && !one_value) {  // ... by digits of the list until few keys are left
         uint32_t left = count;
         int known = shift;  // the bits of t_low from here on are fixed
         for (int pass = 0; pass < 2 && known > 0 && left > (uint32_t)kRankKeys; ++pass) {
@@ -702,9 +718,8 @@ int select_topk_launch(const float *scores, int N, int K, int32_t *idx, void *ws
         topk_wide_range_kernel<<<G, kThreads, 0, s>>>(scores, N, w);
         topk_wide_hist_kernel<<<G, kThreads, 0, s>>>(scores, N, w);
         topk_wide_collect_kernel<0><<<G, kThreads, 0, s>>>(scores, N, K, w);
-        const int passes = N > 2 * kWideCand ? 2 : 1;
-        if (passes == 2) topk_wide_collect_kernel<1><<<G, kThreads, 0, s>>>(scores, N, K, w);
-        topk_wide_emit_kernel<<<G, kThreads, 0, s>>>(scores, N, K, passes, w, idx);
+        topk_wide_collect_kernel<1><<<G, kThreads, 0, s>>>(scores, N, K, w);
+        topk_wide_emit_kernel<<<G, kThreads, 0, s>>>(scores, N, K, w, idx);
         return launch_status();
     }
     return N <= kTile       ? launch_select<1>(scores, N, K, idx, OneSeq(), 0, 1, s)

@@ -320,3 +320,59 @@ def test_scan_without_a_workspace(T, H, P, G, n, dtype):
     assert torch.equal(y, y2) and torch.equal(S, S2)
     assert_close(f(y), y_ref, BOUND[dtype], "y", units=(1,))
     assert_close(f(S), S_ref, BOUND[dtype], "S", units=(0,))
+
+
+# ------------------------------------------------------------------ selection --------------
+@pytest.mark.parametrize("in_bin", [4095, 4096, 4097, 30000])
+@pytest.mark.parametrize("N,low_bits", [(65536, 11), (65537, 12), (131072, 13), (131072 + 5, 21), (1 << 20, 21)])
+def test_select_topk_many_candidates_after_two_digits(N, low_bits, in_bin):
+    """Scores built from their bit patterns so that the first two 11-bit digits of key - min(key) leave `in_bin` keys
+    (the list holds 4096) that differ in the bits below, none to ten: threshold values in and around them."""
+    _say("topk, two digits, N=%d low_bits=%d in_bin=%d" % (N, low_bits, in_bin))
+    r = np.random.default_rng(in_bin + low_bits)
+    third = max(low_bits - 11, 0)
+    off = r.integers(0, 1 << (11 + low_bits), N)
+    off[off >> low_bits == 700] += 1 << low_bits
+    where = r.choice(np.arange(2, N), in_bin + N // 8, replace=False)
+    # an eighth more keys share the first digit only
+    off[where] = (700 << low_bits) + r.integers(0, 1 << low_bits, len(where))
+    same = where[:in_bin]
+    off[same] = (700 << low_bits) + (5 << third) + r.integers(0, 1 << third, in_bin)
+    off[0], off[1] = 0, (1 << (11 + low_bits)) - 1
+    off = np.minimum(off, 0xFF7FFFFF - 0x00800001)    # at 32 bits: the finite floats
+    key = (np.uint64(0x00800001) + off.astype(np.uint64)).astype(np.uint32)
+    s = np.where(key & np.uint32(0x80000000), key ^ np.uint32(0x80000000), ~key).astype(np.uint32).view(np.float32)
+    above = int((off >= (700 << low_bits) + (6 << third)).sum())
+    for K in (above, above + 1, above + in_bin // 2, above + in_bin, above + in_bin + 1):
+        got = strd.select_topk(torch.from_numpy(s).to(DEV), K).cpu().numpy()
+        np.testing.assert_array_equal(got, oracle.select_topk(s.astype(np.float64), K))
+
+
+@pytest.mark.parametrize("N", [49152, 65536, 131072, 1 << 20])
+def test_selection_time_does_not_hang_on_the_values(N):
+    """Close scores beside a zero, and two values: right, and not several times slower than scores that spread out
+    (measured 1.3 times at most; workgroups that read one another's scores, or a list of one value, made it 3 to 12)."""
+    _say("topk, time by values, N=%d" % N)
+    g = torch.Generator().manual_seed(N)
+    u = torch.rand(N, generator=g)
+    close, two = 1e-5 * (1.0 + 1e-4 * u), torch.full((N,), 1e-5)
+    close[7] = 0.0
+    two[::2] = 0.0
+
+    def micros(s):
+        best = float("inf")
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                strd.select_topk(s, N // 4)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 50.0)
+        return best
+
+    base = micros(u.to(DEV))
+    for s in (close, two):
+        got = strd.select_topk(s.to(DEV), N // 4).cpu().numpy()
+        np.testing.assert_array_equal(got, oracle.select_topk(s.numpy().astype(np.float64), N // 4))
+        assert micros(s.to(DEV)) < 2.0 * base
