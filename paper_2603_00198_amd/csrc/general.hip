@@ -147,6 +147,45 @@ __device__ __forceinline__ void products(const Operand<TA, KJ, FULL> (&a)[NT], c
     }
 }
 
+// The same product in double, from chains of at most 16 elements in single precision: in one chain the rounding grows
+// with the row's length (128 elements: twice that of a sum in pieces of 16).
+template <typename TA, typename TB, int KJ, bool FULL>
+__device__ __forceinline__ void product_f64(const Operand<TA, KJ, FULL> &a, const Operand<TB, KJ, FULL> &b, int lb,
+                                            double (&sum)[4]) {
+    constexpr int kChains = KJ > 1 ? 8 : 4;
+    static_assert(KJ <= 8, "16 elements a chain");
+    f32x4 c[kChains];
+#pragma unroll
+    for (int m = 0; m < kChains; ++m) c[m] = zero4();
+    if constexpr (KJ > 0) {
+#pragma unroll
+        for (int j = 0; j < KJ; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c[(4 * j + i) % kChains] = mfma4(a.v[j][i], b.v[j][i], c[(4 * j + i) % kChains]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        sum[e] = 0.0;
+#pragma unroll
+        for (int m = 0; m < kChains; ++m) sum[e] += (double)c[m][e];
+    }
+    if constexpr (KJ == 0) {
+        for (int e0 = 0; e0 < a.len; e0 += 64) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                c[i] = zero4();
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int e = e0 + 16 * i + 4 * u + lb;
+                    c[i] = mfma4(e < a.len ? to_f32(a.row[e]) : 0.f, e < a.len ? to_f32(b.row[e]) : 0.f, c[i]);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += ((double)c[0][e] + (double)c[1][e]) + ((double)c[2][e] + (double)c[3][e]);
+        }
+    }
+}
+
 // Query row r of kv head kvh (r = m * rep + j) is row m * Hq + kvh * rep + j of q.
 __device__ __forceinline__ size_t qrow_index(int r, int rep, int Hq, int kvh) {
     return (size_t)(r / rep) * Hq + kvh * rep + r % rep;
@@ -357,7 +396,7 @@ __global__ __launch_bounds__(kColThreads) void mamba_score_kernel(const T *__res
 
 // ------------------------------------------------------------------ ssd ---------------------
 // The scan in chunks of 64 tokens, all chunks side by side (the token-by-token recurrence is a serial
-// chain of T steps: 830 us at 544 tokens, 8 heads of 32, n = 16; this form 4.5 + 3.3 + 6.2 us).  Three launches:
+// chain of T steps: 830 us at 544 tokens, 8 heads of 32, n = 16; this form 13.9 in all).  Three launches:
 //   state: per (head, chunk) what the chunk adds to the state, L = sum_s 2^(l_end - l_s) dt_s x_s b_s^T,
 //          and its total decay,
 //   pass:  per state element the recurrence over the chunks, leaving the state BEFORE every chunk in
@@ -365,6 +404,10 @@ __global__ __launch_bounds__(kColThreads) void mamba_score_kernel(const T *__res
 //   out:   y_t = sum_{s<=t} 2^(l_t - l_s) dt_s (c_t.b_s) x_s + 2^(l_t) S_before c_t + D x_t.
 // l is the running sum of dt A log2(e) inside the chunk, in double: it reaches several hundred, and a
 // difference of two such numbers decides weights near 1 (in fp32 they would be off by 1e-5).
+// The weights are products in double, rounded once, and the products c.b and S c sums of short chains: y is 5 to 40 %
+// nearer to 64 bits than the recurrence's and S 2 to 40 %, at 16 to 256 state entries and decays of 1 to 0.01 (with all
+// of it in single precision y was 1.0 to 2.8 times as far off).  That costs 4 to 8 % (544 tokens 13.2 -> 13.9 us, 4096
+// tokens of 128 heads 636 -> 676; rows of 256 entries, read per product, 105 -> 118).
 constexpr int kChunk = 64;
 
 // Inclusive sum over the lanes of a wave.
@@ -385,13 +428,19 @@ __device__ __forceinline__ double log2_decay(float dt, float A) {
     return v < -4096.0 ? -4096.0 : v;
 }
 
+// 2^v without the rounding of v to single precision (v is at least -64 x 4096).
+__device__ __forceinline__ double ex2_f64(double v) {
+    const double whole = rint(v);
+    return (double)ldexpf(ex2((float)(v - whole)), (int)whole);
+}
+
 // One wave per (head, chunk, block of 16 CPL channels x 16 NPL state columns).
 template <typename T, int CPL, int NPL, bool FULL>
 __global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restrict__ x, const float *__restrict__ dt,
                                                                 const float *__restrict__ A, const T *__restrict__ B,
                                                                 float *__restrict__ L, float *__restrict__ decay, int Tn,
                                                                 int H, int P, int G, int n, int nc, int nst, int pblocks) {
-    __shared__ float wt[kChunk];
+    __shared__ double wt[kChunk];  // (in single precision the states were 1 to 8 % further from 64 bits than the recurrence's)
     const int lane = threadIdx.x, lr = lane & 15, lb = lane >> 4;
     const int c = blockIdx.x % nst, h = (blockIdx.x / nst) % H, u = blockIdx.x / nst / H;
     const int p0 = (u % pblocks) * 16 * CPL, n0 = (u / pblocks) * 16 * NPL, g = h / (H / G), t0 = c * kChunk;
@@ -407,8 +456,8 @@ __global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restr
         }
     const double l = wave_scan_f64(t0 + lane < Tn ? log2_decay(dtv, A[h]) : 0.0);
     const double end = __shfl(l, kWave - 1, kWave);
-    wt[lane] = ex2((float)(end - l)) * dtv;  // 0 past the last token
-    if (u == 0 && lane == 0) decay[(size_t)h * nc + c] = ex2((float)end);
+    wt[lane] = ex2_f64(end - l) * dtv;  // 0 past the last token
+    if (u == 0 && lane == 0) decay[(size_t)h * nc + c] = (float)ex2_f64(end);
     __syncthreads();
     if (t0 + kChunk > Tn) {  // uniform: the rows past the end are the last one again, which 0 does not take out if it is not finite
 #pragma unroll
@@ -431,11 +480,11 @@ __global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restr
     for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float wv = wt[16 * kb + 4 * lb + i];
+            const double wv = wt[16 * kb + 4 * lb + i];
 #pragma unroll
             for (int a = 0; a < CPL; ++a)
 #pragma unroll
-                for (int b = 0; b < NPL; ++b) acc[a][b] = mfma4(xv[kb][i][a] * wv, bv[kb][i][b], acc[a][b]);
+                for (int b = 0; b < NPL; ++b) acc[a][b] = mfma4((float)(xv[kb][i][a] * wv), bv[kb][i][b], acc[a][b]);
         }
 #pragma unroll
     for (int a = 0; a < CPL; ++a)
@@ -531,25 +580,28 @@ __global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict_
 #pragma unroll
     for (int j = 0; j < 4; ++j)
         if (j <= w) {
-            W[j] = product(bf[j], cf, lb, zero4());
+            double bc[4];
+            product_f64(bf[j], cf, lb, bc);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int sl = 16 * j + 4 * lb + i;
-                W[j][i] = sl <= tl ? W[j][i] * (ex2((float)(lt - ls[sl])) * dts[sl]) : 0.f;
-                if (D && sl == tl) W[j][i] += D[h];  // the skip term rides on the diagonal
+                const double skip = D && sl == tl ? D[h] : 0.f;  // the skip term rides on the diagonal
+                W[j][i] = sl <= tl ? (float)fma(bc[i], (double)ex2((float)(lt - ls[sl])) * dts[sl], skip) : 0.f;
             }
         }
     for (int p0 = 0; p0 < P; p0 += 16 * CPL) {
-        f32x4 acc[CPL];
+        f32x4 acc[CPL], from_state[CPL];
 #pragma unroll
-        for (int a = 0; a < CPL; ++a) acc[a] = zero4();
+        for (int a = 0; a < CPL; ++a) acc[a] = from_state[a] = zero4();
         if (carried) {
             if (!kEarlyState) load_state(p0);
-            products(sf, cf, lb, acc);
 #pragma unroll
-            for (int a = 0; a < CPL; ++a)
+            for (int a = 0; a < CPL; ++a) {
+                double sc[4];
+                product_f64(sf[a], cf, lb, sc);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[a][i] *= et;
+                for (int i = 0; i < 4; ++i) from_state[a][i] = (float)sc[i];
+            }
         }
         // A weight of 0 takes a later token out of the sum only if its x is finite (0 x inf is NaN): on the diagonal
         // tile the values that are not are taken out of the operand and added token by token, where there are any.
@@ -599,6 +651,12 @@ __global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict_
                     }
             }
         }
+        if (carried) {
+#pragma unroll
+            for (int a = 0; a < CPL; ++a)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[a][i] = fmaf(from_state[a][i], et, acc[a][i]);
+        }
         if (p0 + 16 * CPL < P) load_block(p0 + 16 * CPL);
         if (t < Tn)
 #pragma unroll
@@ -613,7 +671,7 @@ __global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict_
 
 // The recurrence itself, for callers that bring no workspace (and for no tokens): a state column (h, p) is held by
 // `lanes` adjacent lanes, each with kSlice consecutive state entries in registers; y_t is reduced across those
-// lanes.  A serial chain of T steps: 830 us at 544 tokens, 8 heads of 32, n = 16, where the chunks take 12.7.
+// lanes.  A serial chain of T steps: 830 us at 544 tokens, 8 heads of 32, n = 16, where the chunks take 13.4.
 constexpr int kSlice = 16, kRecThreads = 256;
 
 template <typename T>
