@@ -17,6 +17,7 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <climits>
 #include <cmath>
 #include <string>
 
@@ -78,18 +79,27 @@ strd_dtype io_of(const Tensor &t) {
 }
 bool is_f32(const Tensor &t) { return t.scalar_type() == at::kFloat; }
 
-int integer(PyObject *o) {
-    const long v = PyLong_AsLong(o);
-    if (v == -1 && PyErr_Occurred()) {
-        PyErr_Clear();
-        PyObject *n = PyNumber_Long(o);
-        if (!n) throw python_error();
-        const long u = PyLong_AsLong(n);
-        Py_DECREF(n);
-        if (u == -1 && PyErr_Occurred()) throw python_error();
-        return (int)u;
-    }
+// Values that the library takes as int: one that does not fit is refused, not cut.
+int narrow(long long v, const char *what) {
+    if (v < INT_MIN || v > INT_MAX) fail(std::string(what) + " does not fit 32 bits: " + std::to_string(v));
     return (int)v;
+}
+int whole(PyObject *v, const char *what) {  // takes over v
+    if (!v) throw python_error();
+    int over = 0;
+    const long long n = PyLong_AsLongLongAndOverflow(v, &over);
+    Py_DECREF(v);
+    if (over) fail(std::string(what) + " does not fit 32 bits");
+    return narrow(n, what);
+}
+int integer(PyObject *o, const char *what = "a number") { return whole(PyNumber_Index(o), what); }
+// Fields of a sequence descriptor: whatever Python's int() takes.
+int integer_of(PyObject *o, const char *what) { return whole(PyNumber_Long(o), what); }
+int size(const Tensor &t, int dim) { return narrow(t.size(dim), "a tensor's size"); }
+bool truth(PyObject *o) {
+    const int v = PyObject_IsTrue(o);
+    if (v < 0) throw python_error();
+    return v;
 }
 double number(PyObject *o) {
     const double v = PyFloat_AsDouble(o);
@@ -159,7 +169,7 @@ PyObject *score_attn(Args a) {  // q_txt, k_vis, scale, out, ws
     const Tensor &q = dev(a[0]), &k = dev(a[1]);
     if (q.dim() != 3 || k.dim() != 3 || q.size(2) != k.size(2) || q.scalar_type() != k.scalar_type()) fail("q/k mismatch");
     const strd_dtype io = io_of(q);
-    const int M = q.size(0), Hq = q.size(1), d = q.size(2), N = k.size(0), Hkv = k.size(1);
+    const int M = size(q, 0), Hq = size(q, 1), d = size(q, 2), N = size(k, 0), Hkv = size(k, 1);
     const float scale = scale_or_default(a[2], d);
     Tensor s = out_or(a[3], {N}, at::kFloat, q);
     const hipStream_t st = stream();
@@ -177,7 +187,7 @@ PyObject *score_mamba(Args a) {  // B_vis, C_txt, dt_vis, out, ws
         dt.size(0) != B.size(0) || !is_f32(dt) || B.scalar_type() != C.scalar_type())
         fail("B/C/dt mismatch");
     const strd_dtype io = io_of(B);
-    const int N = B.size(0), G = B.size(1), n = B.size(2), M = C.size(0), H = dt.size(1);
+    const int N = size(B, 0), G = size(B, 1), n = size(B, 2), M = size(C, 0), H = size(dt, 1);
     Tensor s = out_or(a[3], {N}, at::kFloat, B);
     const hipStream_t st = stream();
     Workspace ws(a[4], a[4] == Py_None ? strd_score_mamba_workspace(M, N, H, G, n, io) : 0, B, st);
@@ -192,7 +202,7 @@ PyObject *score_mamba(Args a) {  // B_vis, C_txt, dt_vis, out, ws
 PyObject *select_topk(Args a) {  // scores, K, out, ws
     const Tensor &s = dev(a[0]);
     if (!is_f32(s) || s.dim() != 1) fail("scores must be a 1-D fp32 tensor");
-    const int N = s.size(0), K = integer(a[1]);
+    const int N = size(s, 0), K = integer(a[1]);
     if (a[2] == Py_None && K < 0) fail("select_topk failed: K is negative");
     Tensor idx = out_or(a[2], {K}, at::kInt, s);
     const hipStream_t st = stream();
@@ -237,7 +247,7 @@ PyObject *compact_batch(Args a) {  // srcs, idx, N, M, pos_in, want_pos, outs
     const int N = integer(a[2]), M = integer(a[3]);
     const Tensor *pos_in = opt(a[4]);
     if (idx.scalar_type() != at::kInt || idx.dim() != 1) fail("idx must be int32");
-    const int K = idx.size(0), n = (int)srcs.size();
+    const int K = size(idx, 0), n = (int)srcs.size();
     if (n > STRD_COMPACT_MAX) fail("compact_batch failed: " + std::string(strd_status_string(STRD_EINVAL)));
     strd_compact_item items[STRD_COMPACT_MAX];
     Tensor dst[STRD_COMPACT_MAX];
@@ -248,16 +258,14 @@ PyObject *compact_batch(Args a) {  // srcs, idx, N, M, pos_in, want_pos, outs
     }
     for (int i = 0; i < n; ++i) {
         const Tensor &t = dev(srcs[i]);
-        const Sizes sz(K + M, t);
+        const Sizes sz((int64_t)K + M, t);
         if (a[6] == Py_None) dst[i] = empty(sz, t.scalar_type(), t);
-        if (t.size(0) != N + M || dst[i].scalar_type() != t.scalar_type() || dst[i].sizes() != at::IntArrayRef(sz))
+        if (t.size(0) != (int64_t)N + M || dst[i].scalar_type() != t.scalar_type() || dst[i].sizes() != at::IntArrayRef(sz))
             fail("compact_batch: tensor " + std::to_string(i) + " has the wrong shape");
         items[i] = {t.data_ptr(), dst[i].data_ptr(), sz.row() * (int64_t)t.element_size()};
     }
     Tensor pos;
-    const int want = PyObject_IsTrue(a[5]);
-    if (want < 0) throw python_error();
-    if (want || pos_in) pos = empty({K + M}, at::kInt, idx);
+    if (truth(a[5]) || pos_in) pos = empty({(int64_t)K + M}, at::kInt, idx);
     const hipStream_t st = stream();
     check(call([&] {
               return strd_compact_batch(items, n, i32(&idx), N, M, K, i32(pos_in),
@@ -282,16 +290,16 @@ struct Seqs {
         for (int i = 0; i < n; ++i) {
             Sequence t(list[i]);
             if (t.size() != 3) fail("a sequence is described by (N, M, K)");
-            s[i].N = integer(t[0]);
-            s[i].M = integer(t[1]);
-            s[i].K = integer(t[2]);
+            s[i].N = integer_of(t[0], "N");
+            s[i].M = integer_of(t[1], "M");
+            s[i].K = integer_of(t[2], "K");
             rows += (int64_t)s[i].N + s[i].M;
             kept += s[i].K;
             out_rows += (int64_t)s[i].K + s[i].M;
             max_n = std::max(max_n, s[i].N);
         }
     }
-    int ld(PyObject *o) const { return o == Py_None ? (max_n + 3) / 4 * 4 : integer(o); }
+    int ld(PyObject *o) const { return o == Py_None ? narrow(((int64_t)max_n + 3) / 4 * 4, "ld") : integer_of(o, "ld"); }
 };
 
 Tensor scores_or_zeros(PyObject *o, int n, int ld, const Tensor &like) {
@@ -307,7 +315,7 @@ PyObject *score_attn_varlen(Args a) {  // q_all, k_all, seqs, scale, ld, out
         q.scalar_type() != k.scalar_type() || q.size(0) != sq.rows)
         fail("score_attn_varlen: q/k/seqs mismatch");
     const strd_dtype io = io_of(q);
-    const int Hq = q.size(1), d = q.size(2), Hkv = k.size(1), ld = sq.ld(a[4]);
+    const int Hq = size(q, 1), d = size(q, 2), Hkv = size(k, 1), ld = sq.ld(a[4]);
     const float scale = scale_or_default(a[3], d);
     Tensor s = scores_or_zeros(a[5], sq.n, ld, q);
     const hipStream_t st = stream();
@@ -327,7 +335,7 @@ PyObject *score_mamba_varlen(Args a) {  // B_all, C_all, dt_all, seqs, ld, out
         B.scalar_type() != C.scalar_type() || B.size(0) != sq.rows)
         fail("score_mamba_varlen: B/C/dt/seqs mismatch");
     const strd_dtype io = io_of(B);
-    const int G = B.size(1), n = B.size(2), H = dt.size(1), ld = sq.ld(a[4]);
+    const int G = size(B, 1), n = size(B, 2), H = size(dt, 1), ld = sq.ld(a[4]);
     Tensor s = scores_or_zeros(a[5], sq.n, ld, B);
     const hipStream_t st = stream();
     Workspace ws(Py_None, strd_score_mamba_varlen_workspace(sq.s, sq.n, H, G, n, io), B, st);
@@ -344,7 +352,7 @@ PyObject *select_topk_varlen(Args a) {  // scores, seqs, out
     const Seqs sq(a[1]);
     if (!is_f32(s) || s.dim() != 2 || s.size(0) != sq.n) fail("select_topk_varlen: scores must be fp32 [nseq, ld]");
     Tensor idx = out_or(a[2], {sq.kept}, at::kInt, s);
-    const int ld = s.size(1);
+    const int ld = size(s, 1);
     const hipStream_t st = stream();
     check(call([&] { return strd_select_topk_varlen(f32(s), ld, sq.s, sq.n, (int32_t *)idx.data_ptr(), st); }),
           "select_topk_varlen");
@@ -370,9 +378,7 @@ PyObject *compact_varlen(Args a) {  // srcs, idx, seqs, pos_in, want_pos
         items[i] = {t.data_ptr(), dst[i].data_ptr(), sz.row() * (int64_t)t.element_size()};
     }
     Tensor pos;
-    const int want = PyObject_IsTrue(a[4]);
-    if (want < 0) throw python_error();
-    if (want || pos_in) pos = empty({sq.out_rows}, at::kInt, idx);
+    if (truth(a[4]) || pos_in) pos = empty({sq.out_rows}, at::kInt, idx);
     const hipStream_t st = stream();
     check(call([&] {
               return strd_compact_varlen(items, n, i32(&idx), sq.s, sq.n, i32(pos_in),
@@ -392,7 +398,7 @@ struct Scan {
     Scan(Args a, const char *what) : x(dev(a[0])), dt(dev(a[1])), A(dev(a[2])), B(dev(a[3])), C(dev(a[4])) {
         bool ok = x.dim() == 3 && B.dim() == 3 && dt.dim() == 2 && A.dim() == 1;
         if (ok) {
-            rows = x.size(0), H = x.size(1), P = x.size(2), G = B.size(1), n = B.size(2);
+            rows = size(x, 0), H = size(x, 1), P = size(x, 2), G = size(B, 1), n = size(B, 2);
             ok = dt.size(0) == rows && dt.size(1) == H && A.size(0) == H && B.size(0) == rows && C.sizes() == B.sizes() &&
                  is_f32(dt) && is_f32(A) && B.scalar_type() == x.scalar_type() && C.scalar_type() == x.scalar_type();
         }
@@ -413,7 +419,7 @@ PyObject *ssd_prefill(Args a) {  // x, dt, A, B, C, D, S_in, chunk, want_state, 
     t.optional(D, S_in, "ssd_prefill");
     const int chunk = integer(a[7]), T = t.rows;
     Tensor y = out_or(a[9], t.x.sizes(), t.x.scalar_type(), t.x), S;
-    if (PyObject_IsTrue(a[8])) S = empty({t.H, t.P, t.n}, at::kFloat, t.x);
+    if (truth(a[8])) S = empty({t.H, t.P, t.n}, at::kFloat, t.x);
     const hipStream_t st = stream();
     Workspace ws(a[10], a[10] == Py_None ? strd_ssd_prefill_workspace(T, t.H, t.P, t.G, t.n, chunk, t.io) : 0, t.x, st);
     check(call([&] {
@@ -430,13 +436,13 @@ PyObject *ssd_prefill_gather(Args a) {  // x, dt, A, B, C, idx, N, M, D, S_in, c
     const Tensor &idx = dev(a[5]);
     const int N = integer(a[6]), M = integer(a[7]), chunk = integer(a[10]);
     const Tensor *D = opt(a[8]), *S_in = opt(a[9]);
-    if (t.rows != N + M || idx.scalar_type() != at::kInt || idx.dim() != 1)
+    if (t.rows != (int64_t)N + M || idx.scalar_type() != at::kInt || idx.dim() != 1)
         fail("ssd_prefill_gather: inconsistent shapes or dtypes");
-    const int K = idx.size(0);
-    Tensor y = out_or(a[12], {K + M, t.H, t.P}, t.x.scalar_type(), t.x), S;
-    if (PyObject_IsTrue(a[11])) S = empty({t.H, t.P, t.n}, at::kFloat, t.x);
+    const int K = size(idx, 0);
+    Tensor y = out_or(a[12], {(int64_t)K + M, t.H, t.P}, t.x.scalar_type(), t.x), S;
+    if (truth(a[11])) S = empty({t.H, t.P, t.n}, at::kFloat, t.x);
     const hipStream_t st = stream();
-    Workspace ws(a[13], a[13] == Py_None ? strd_ssd_prefill_workspace(K + M, t.H, t.P, t.G, t.n, chunk, t.io) : 0, t.x, st);
+    Workspace ws(a[13], a[13] == Py_None ? strd_ssd_prefill_workspace(narrow((int64_t)K + M, "K + M"), t.H, t.P, t.G, t.n, chunk, t.io) : 0, t.x, st);
     check(call([&] {
               return strd_ssd_prefill_gather(t.x.data_ptr(), f32(t.dt), f32(t.A), t.B.data_ptr(), t.C.data_ptr(), f32(D),
                                              f32(S_in), i32(&idx), y.data_ptr(), S.defined() ? f32(&S) : nullptr, N, M, K,
@@ -452,7 +458,7 @@ PyObject *attn_prefill(Args a) {  // q, k, v, scale, out, ws
         k.scalar_type() != q.scalar_type() || v.scalar_type() != q.scalar_type())
         fail("attn_prefill: inconsistent shapes or dtypes");
     const strd_dtype io = io_of(q);
-    const int T = q.size(0), Hq = q.size(1), d = q.size(2), Hkv = k.size(1);
+    const int T = size(q, 0), Hq = size(q, 1), d = size(q, 2), Hkv = size(k, 1);
     const float scale = scale_or_default(a[3], d);
     Tensor o = out_or(a[4], q.sizes(), q.scalar_type(), q);
     const hipStream_t st = stream();
@@ -477,7 +483,7 @@ PyObject *ssd_decode_step(Args a) {  // x, dt, A, B, C, D, S
     }
     if (!ok) fail("ssd_decode_step: inconsistent shapes or dtypes");
     const strd_dtype io = io_of(x);
-    const int H = x.size(0), P = x.size(1), G = B.size(0), n = B.size(1);
+    const int H = size(x, 0), P = size(x, 1), G = size(B, 0), n = size(B, 1);
     Tensor y = empty(x.sizes(), x.scalar_type(), x);
     const hipStream_t st = stream();
     check(call([&] {
@@ -494,7 +500,7 @@ PyObject *attn_decode_step(Args a) {  // q, k_cache, v_cache, scale, ws
         k.scalar_type() != q.scalar_type() || v.scalar_type() != q.scalar_type())
         fail("attn_decode_step: inconsistent shapes or dtypes");
     const strd_dtype io = io_of(q);
-    const int Hq = q.size(0), d = q.size(1), T = k.size(0), Hkv = k.size(1);
+    const int Hq = size(q, 0), d = size(q, 1), T = size(k, 0), Hkv = size(k, 1);
     const float scale = scale_or_default(a[3], d);
     Tensor o = empty(q.sizes(), q.scalar_type(), q);
     const hipStream_t st = stream();
@@ -512,7 +518,7 @@ PyObject *attn_decode_step(Args a) {  // q, k_cache, v_cache, scale, ws
 int pitch(const Tensor &t, const char *what) {
     if (!t.is_cuda()) fail("tensors must live on the GPU");
     if (t.dim() != 2 || t.stride(1) != 1) fail(std::string(what) + ": rows must be contiguous");
-    return (int)t.stride(0);
+    return narrow(t.stride(0), "a row pitch");
 }
 
 PyObject *linear(Args a) {  // x, w, residual, out
@@ -523,7 +529,7 @@ PyObject *linear(Args a) {  // x, w, residual, out
                  res->scalar_type() != x.scalar_type())))
         fail("linear: x [T,Kd], w [Kd,Nd], residual [T,Nd], one dtype");
     const strd_dtype io = io_of(x);
-    const int T = x.size(0), Kd = x.size(1), Nd = w.size(1);
+    const int T = size(x, 0), Kd = size(x, 1), Nd = size(w, 1);
     Tensor out = out_or(a[3], {T, Nd}, x.scalar_type(), x);
     const hipStream_t st = stream();
     check(call([&] { return strd_linear(x.data_ptr(), w.data_ptr(), ptr(res), out.data_ptr(), T, Kd, Nd, io, st); }), "linear");
@@ -535,7 +541,7 @@ PyObject *rmsnorm(Args a) {  // x, w, eps, out
     if (x.dim() != 2 || w.dim() != 1 || w.size(0) != x.size(1) || w.scalar_type() != x.scalar_type())
         fail("rmsnorm: x [T,d] contiguous, w [d] of the same dtype");
     const strd_dtype io = io_of(x);
-    const int T = x.size(0), d = x.size(1);
+    const int T = size(x, 0), d = size(x, 1);
     const float eps = (float)number(a[2]);
     Tensor out = out_or(a[3], x.sizes(), x.scalar_type(), x);
     const hipStream_t st = stream();
@@ -549,7 +555,7 @@ PyObject *gated_rmsnorm(Args a) {  // y, z, w, groups, eps, out
         z.scalar_type() != y.scalar_type() || w.scalar_type() != y.scalar_type())
         fail("gated_rmsnorm: y, z [T,D], w [D], one dtype");
     const strd_dtype io = io_of(y);
-    const int T = y.size(0), D = y.size(1), groups = integer(a[3]), ldz = pitch(z, "z");
+    const int T = size(y, 0), D = size(y, 1), groups = integer(a[3]), ldz = pitch(z, "z");
     const float eps = (float)number(a[4]);
     Tensor out = out_or(a[5], y.sizes(), y.scalar_type(), y);
     const hipStream_t st = stream();
@@ -563,12 +569,12 @@ PyObject *gated_rmsnorm(Args a) {  // y, z, w, groups, eps, out
 PyObject *conv1d_silu(Args a) {  // xbc, w, b, Cx, Cb
     const Tensor &in = tensor(a[0]), &w = dev(a[1]);
     const Tensor *b = opt(a[2]);
-    const int Cx = integer(a[3]), Cb = integer(a[4]), Ct = Cx + 2 * Cb;
+    const int Cx = integer(a[3]), Cb = integer(a[4]), Ct = narrow((int64_t)Cx + 2 * (int64_t)Cb, "Cx + 2 Cb");
     if (in.dim() != 2 || in.size(1) < Ct || w.dim() != 2 || w.size(0) != Ct || w.scalar_type() != in.scalar_type() ||
         (b && (b->dim() != 1 || b->size(0) != Ct || b->scalar_type() != in.scalar_type())))
         fail("conv1d_silu: xbc [T, >=Cx+2Cb], w [Cx+2Cb, W], b [Cx+2Cb], one dtype");
     const strd_dtype io = io_of(in);
-    const int T = in.size(0), W = w.size(1), ld = pitch(in, "xbc");
+    const int T = size(in, 0), W = size(w, 1), ld = pitch(in, "xbc");
     Tensor x = empty({T, Cx}, in.scalar_type(), in), B = empty({T, Cb}, in.scalar_type(), in),
            C = empty({T, Cb}, in.scalar_type(), in);
     const hipStream_t st = stream();
@@ -588,7 +594,7 @@ PyObject *softplus_dt(Args a) {  // raw, bias
     const Tensor &raw = tensor(a[0]);
     const Tensor *bias = opt(a[1]);
     if (raw.dim() != 2) fail("softplus_dt: raw [T,H]");
-    const int T = raw.size(0), H = raw.size(1);
+    const int T = size(raw, 0), H = size(raw, 1);
     if (bias && (bias->dim() != 1 || bias->size(0) != H || !is_f32(*bias))) fail("softplus_dt: bias [H] fp32");
     const strd_dtype io = io_of(raw);
     const int ld = pitch(raw, "raw");

@@ -395,3 +395,25 @@ def test_selection_time_does_not_hang_on_the_values(N):
         got = strd.select_topk(s.to(DEV), N // 4).cpu().numpy()
         np.testing.assert_array_equal(got, oracle.select_topk(s.numpy().astype(np.float64), N // 4))
         assert micros(s.to(DEV)) < 2.0 * base
+
+
+# ------------------------------------------------------------------ binding ----------------
+def test_numbers_that_are_not_whole_or_do_not_fit_are_refused():
+    """The binding takes what has __index__ and fits 32 bits, as torch and ctypes do: nothing is cut to size."""
+    _say("binding, numbers")
+    s, idx = torch.rand(64, device=DEV), torch.arange(4, dtype=torch.int32, device=DEV)
+    t, x = torch.zeros(8, 2, device=DEV), torch.zeros(8, 2, 4, device=DEV)
+    dt, A, bc = torch.zeros(8, 2, device=DEV), torch.zeros(2, device=DEV), torch.zeros(8, 1, 4, device=DEV)
+    for K in (2.7, "2", 2 ** 32 + 5, 2 ** 70, None):
+        with pytest.raises((strd.StrdError, TypeError)):
+            strd.select_topk(s, K)
+        with pytest.raises((strd.StrdError, TypeError)):
+            strd.compact_batch([t], idx, K, 4)
+        with pytest.raises((strd.StrdError, TypeError)):
+            strd.ssd_prefill(x, dt, A, bc, bc, chunk=K)
+    with pytest.raises((strd.StrdError, TypeError)):
+        strd.compact_batch([t], idx, 2 ** 32 + 4, 4)
+    with pytest.raises((strd.StrdError, TypeError)):
+        strd.select_topk_varlen(torch.rand(1, 8, device=DEV), [(2 ** 32 + 8, 1, 2)])
+    assert strd.select_topk(s, np.int64(3)).shape == (3,) and strd.select_topk(s, torch.tensor(3)).shape == (3,)
+    assert strd.select_topk_varlen(s[None], [(64.0, 1, np.float64(3))]).shape == (3,)   # descriptors go through int()
