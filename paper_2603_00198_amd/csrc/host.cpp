@@ -211,20 +211,17 @@ PyObject *select_topk(Args a) {  // scores, K, out, ws
     return wrap(std::move(idx));
 }
 
-constexpr int kMaxDim = 8;
-// Sizes of `t` with `rows` in place of its first dimension.
+// Sizes of `t`, of any number of dimensions, with `rows` in place of the first one.
 struct Sizes {
-    int64_t v[kMaxDim];
-    int n;
-    Sizes(int64_t rows, const Tensor &t) : n((int)t.dim()) {
-        if (n < 1 || n > kMaxDim) fail("a tensor of 1 to 8 dimensions is needed");
+    at::DimVector v;
+    Sizes(int64_t rows, const Tensor &t) : v(t.sizes().begin(), t.sizes().end()) {
+        if (v.empty()) fail("a tensor with rows is needed");
         v[0] = rows;
-        for (int i = 1; i < n; ++i) v[i] = t.size(i);
     }
-    operator at::IntArrayRef() const { return at::IntArrayRef(v, n); }
+    operator at::IntArrayRef() const { return v; }
     int64_t row() const {
         int64_t r = 1;
-        for (int i = 1; i < n; ++i) r *= v[i];
+        for (size_t i = 1; i < v.size(); ++i) r *= v[i];
         return r;
     }
 };
@@ -246,7 +243,7 @@ PyObject *compact_batch(Args a) {  // srcs, idx, N, M, pos_in, want_pos, outs
     const Tensor &idx = dev(a[1]);
     const int N = integer(a[2]), M = integer(a[3]);
     const Tensor *pos_in = opt(a[4]);
-    if (idx.scalar_type() != at::kInt || idx.dim() != 1) fail("idx must be int32");
+    if (idx.scalar_type() != at::kInt || idx.dim() < 1) fail("idx must be int32");
     const int K = size(idx, 0), n = (int)srcs.size();
     if (n > STRD_COMPACT_MAX) fail("compact_batch failed: " + std::string(strd_status_string(STRD_EINVAL)));
     strd_compact_item items[STRD_COMPACT_MAX];
@@ -272,8 +269,10 @@ PyObject *compact_batch(Args a) {  // srcs, idx, N, M, pos_in, want_pos, outs
                                         pos.defined() ? (int32_t *)pos.data_ptr() : nullptr, st);
           }),
           "compact_batch");
-    PyObject *list = PyList_New(n);
-    for (int i = 0; i < n; ++i) PyList_SET_ITEM(list, i, wrap(std::move(dst[i])));
+    PyObject *list = a[6] == Py_None ? PyList_New(n) : PySequence_List(a[6]);  // the caller's outputs, all of them
+    if (!list) throw python_error();
+    if (a[6] == Py_None)
+        for (int i = 0; i < n; ++i) PyList_SET_ITEM(list, i, wrap(std::move(dst[i])));
     return pair(list, pos.defined() ? wrap(std::move(pos)) : none());
 }
 
@@ -364,7 +363,7 @@ PyObject *compact_varlen(Args a) {  // srcs, idx, seqs, pos_in, want_pos
     const Tensor &idx = dev(a[1]);
     const Seqs sq(a[2]);
     const Tensor *pos_in = opt(a[3]);
-    if (idx.scalar_type() != at::kInt || idx.dim() != 1 || idx.size(0) != sq.kept)
+    if (idx.scalar_type() != at::kInt || idx.dim() < 1 || idx.size(0) != sq.kept)
         fail("compact_varlen: idx must be int32 [sum K]");
     const int n = (int)srcs.size();
     if (n > STRD_COMPACT_MAX) fail("compact_varlen failed: " + std::string(strd_status_string(STRD_EINVAL)));
@@ -436,7 +435,7 @@ PyObject *ssd_prefill_gather(Args a) {  // x, dt, A, B, C, idx, N, M, D, S_in, c
     const Tensor &idx = dev(a[5]);
     const int N = integer(a[6]), M = integer(a[7]), chunk = integer(a[10]);
     const Tensor *D = opt(a[8]), *S_in = opt(a[9]);
-    if (t.rows != (int64_t)N + M || idx.scalar_type() != at::kInt || idx.dim() != 1)
+    if (t.rows != (int64_t)N + M || idx.scalar_type() != at::kInt || idx.dim() < 1)
         fail("ssd_prefill_gather: inconsistent shapes or dtypes");
     const int K = size(idx, 0);
     Tensor y = out_or(a[12], {(int64_t)K + M, t.H, t.P}, t.x.scalar_type(), t.x), S;

@@ -417,3 +417,20 @@ def test_numbers_that_are_not_whole_or_do_not_fit_are_refused():
         strd.select_topk_varlen(torch.rand(1, 8, device=DEV), [(2 ** 32 + 8, 1, 2)])
     assert strd.select_topk(s, np.int64(3)).shape == (3,) and strd.select_topk(s, torch.tensor(3)).shape == (3,)
     assert strd.select_topk_varlen(s[None], [(64.0, 1, np.float64(3))]).shape == (3,)   # descriptors go through int()
+
+
+def test_compaction_takes_tensors_of_any_number_of_dimensions():
+    """Rows of nine and ten dimensions, an index column, and more outputs than tensors (all of them come back)."""
+    _say("binding, dimensions")
+    idx = torch.tensor([1, 4], dtype=torch.int32, device=DEV)
+    keep = torch.tensor([1, 4, 6, 7], device=DEV)
+    a = torch.randn(8, *[1, 2] * 4, device=DEV)
+    b = torch.randn(8, *[2, 1, 1] * 3, device=DEV).to(BF16)
+    for index in (idx, idx[:, None]):
+        (ca, cb), none = strd.compact_batch([a, b], index, 6, 2)
+        assert none is None and torch.equal(ca, a[keep]) and torch.equal(cb, b[keep])
+        (ca,), _ = strd.compact_varlen([a], index, [(6, 2, 2)])
+        assert torch.equal(ca, a[keep])
+    outs = [torch.empty(4, *a.shape[1:], device=DEV), torch.zeros(3, device=DEV)]
+    got, _ = strd.compact_batch([a], idx, 6, 2, outs=outs)
+    assert len(got) == 2 and got[0] is outs[0] and got[1] is outs[1] and torch.equal(got[0], a[keep])
