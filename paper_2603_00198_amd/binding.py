@@ -393,13 +393,7 @@ def linear_mfma_supported(T: int, Kd: int, Nd: int, dtype: torch.dtype) -> bool:
 
 
 def rmsnorm(x: torch.Tensor, w: torch.Tensor, eps: float = 1e-5, out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    _dev(x, w, out)
-    T, d = x.shape
-    if not x.is_contiguous() or w.shape != (d,) or w.dtype != x.dtype:
-        raise StrdError("rmsnorm: x [T,d] contiguous, w [d] of the same dtype")
-    out = out if out is not None else torch.empty_like(x)
-    _check(lib().strd_rmsnorm(_ptr(x), _ptr(w), _ptr(out), T, d, eps, _io(x), _stream()), "rmsnorm")
-    return out
+    return (_host or host()).rmsnorm(x, w, eps, out)
 
 
 def gated_rmsnorm(y: torch.Tensor, z: torch.Tensor, w: torch.Tensor, groups: int = 1, eps: float = 1e-5,

@@ -1,4 +1,6 @@
 """The binding's native half refuses what it cannot hand to the library with the binding's own error."""
+import inspect
+
 import pytest
 import torch
 
@@ -23,3 +25,19 @@ def test_other_objects_and_bad_descriptors_are_refused():
         strd.compact_batch(None, torch.zeros(1, dtype=torch.int32), 1, 1)
     with pytest.raises(strd.StrdError):
         strd.select_topk_varlen(torch.zeros(1, 4), [(4, 1)])
+
+
+def test_every_native_entry_is_the_one_its_call_runs(monkeypatch):
+    """Each entry of the native half is behind the public function of its name."""
+    names = [n for n in dir(strd.binding.host()) if not n.startswith("_") and n != "set_error"]
+    assert len(names) >= 18
+
+    class Spy:
+        def __getattr__(self, name):
+            return lambda *args: (name, len(args))
+
+    monkeypatch.setattr(strd.binding, "_host", Spy())
+    for name in names:
+        fn = getattr(strd, name)
+        required = [p for p in inspect.signature(fn).parameters.values() if p.default is p.empty]
+        assert fn(*[None] * len(required)) == (name, len(inspect.signature(fn).parameters))
