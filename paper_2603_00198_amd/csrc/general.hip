@@ -205,6 +205,7 @@ __device__ __forceinline__ size_t qrow_index(int r, int rep, int Hq, int kvh) {
 constexpr int kStatRows = 64;      // query rows per workgroup of pass 1 (4 waves)
 constexpr int kColThreads = 512;   // pass 2 and score_mamba: 8 waves
 constexpr int kColRows = 2048;     // rows whose log-sum-exp are in LDS at a time
+constexpr int kMaxScoreRow = 14992;  // longest row taken
 
 template <typename T, int KJ, bool FULL, class SEQ>
 __global__ __launch_bounds__(256) void attn_stats_kernel(const T *__restrict__ q, const T *__restrict__ k,
@@ -722,7 +723,7 @@ __global__ __launch_bounds__(kRecThreads) void ssd_recurrence_kernel(
 // alone 30 (16 KB per trip and wave from L2, the rate of a CU's path).  Four waves per SIMD overlap the
 // two; a register set for the next trip in two waves per SIMD, two query tiles a wave (half the loads, but
 // too few workgroups for the causal sweep to balance) and 4 or 16 waves were not faster.
-template <typename T, bool VEC, bool FULL, int DJ, int NW>
+template <typename T, bool VEC, bool FULL, int DJ, int NW, bool WIDE>
 __global__ __launch_bounds__(NW *kWave) __attribute__((amdgpu_waves_per_eu(DJ == 1 ? 4 : 1))) void attn_tile_kernel(
     const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, T *__restrict__ o, int Tn, int Hq, int Hkv,
     int d, float scale2) {
@@ -742,10 +743,12 @@ __global__ __launch_bounds__(NW *kWave) __attribute__((amdgpu_waves_per_eu(DJ ==
         for (int e = 0; e < 4; ++e) acc[b][e] = zero4();
     float run_m = -INFINITY, run_l = 0.f;
     // Rows of a trip: one address per workgroup and trip plus a 24-bit product per row (they lie within 32
-    // rows of each other); rows past the end of the sequence re-read its last one.
-    const unsigned stride = (unsigned)(Hkv * d) * sizeof(T);
+    // rows of each other; WIDE, for rows of 16 MB and more: a full product); rows past the end of the sequence
+    // re-read its last one.
+    const size_t stride = (size_t)Hkv * d * sizeof(T);
     auto row_of = [&](const T *base, int r, int last) {
-        return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + __umul24((unsigned)min(r, last), stride));
+        const size_t off = WIDE ? (unsigned)min(r, last) * stride : __umul24((unsigned)min(r, last), (unsigned)stride);
+        return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + off);
     };
     auto body = [&](auto edge, int trip) __attribute__((always_inline)) {
         const int key0 = trip * KT * 16, last = Tn - 1 - key0;  // uniform
@@ -943,6 +946,7 @@ size_t score_attn_general_ws(int M, int N, int Hq, int Hkv, int nseq) {
 template <typename T, class SEQ>
 static int score_attn_launch(const void *q, const void *k, float *s, int M, int N, int Hq, int Hkv, int d, float scale,
                              void *ws, const SEQ &seq, int nseq, int ld, hipStream_t st) {
+    if (d > kMaxScoreRow) return STRD_EUNSUPPORTED;
     const StatPlan p = stat_plan(M, N, Hq, Hkv, nseq);
     const long long grid1 = (long long)p.nrb * Hkv * p.nslice;
     if (grid1 > 0x7FFFFFFFLL) return STRD_EUNSUPPORTED;
@@ -1002,6 +1006,9 @@ bool ssd_general_supported(int n) { return n >= 1 && n <= 1024; }
 // sequences go through it in rounds of as many chunks as fit kRoundBytes (at 128 heads of 64 x 128: 4096 tokens, 8192
 // workgroups a launch), the state handed on in two more buffers that take turns: 131072 tokens take 276 MB, not 8.6 GB.
 constexpr size_t kRoundBytes = (size_t)256 << 20;
+// The chunked form's launches count 32-bit threads per grid: states of up to 2^28 entries (1 GB) in fewer than 2^24
+// heads.  Beyond, there are channels enough to fill the chip with the recurrence.
+static bool ssd_in_chunks(int H, int P, int n) { return H < 1 << 24 && (long long)H * P <= (1 << 28) / n; }
 struct ScanRounds {
     int chunks;  // per round
     size_t states, decays, carry;  // bytes
@@ -1011,13 +1018,13 @@ static ScanRounds ssd_rounds(int T, int H, int P, int n) {
     const size_t state = (size_t)H * P * n * sizeof(float);
     const int nc = ceil_div(T, kChunk);
     ScanRounds r;
-    r.chunks = (int)std::min<size_t>(nc, std::max<size_t>(1, kRoundBytes / state));
+    r.chunks = (int)std::min<size_t>(nc, std::max<size_t>(1, kRoundBytes / std::max(state, (size_t)H * 64)));
     r.states = align_up(r.chunks * state, 256);
     r.decays = align_up((size_t)H * r.chunks * sizeof(float), 256);
     r.carry = nc > r.chunks ? align_up(state, 256) : 0;
     return r;
 }
-size_t ssd_general_ws(int T, int H, int P, int n) { return ssd_rounds(T, H, P, n).total(); }
+size_t ssd_general_ws(int T, int H, int P, int n) { return ssd_in_chunks(H, P, n) ? ssd_rounds(T, H, P, n).total() : 0; }
 
 template <typename T>
 static int ssd_launch(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D,
@@ -1028,10 +1035,7 @@ static int ssd_launch(const void *x, const float *dt, const float *A, const void
     const int cpl = !vec ? 1 : P > 32 ? 4 : 2, npl = vec && n >= 64 ? 4 : 1;
     const int pblocks = ceil_div(P, 16 * cpl), nblocks = ceil_div(n, 16 * npl);
     const long long grid1 = (long long)nst * H * pblocks * nblocks, total = (long long)H * P * n, grid3 = (long long)nc * H;
-    if (grid1 > 0x7FFFFFFFLL || grid3 > 0x7FFFFFFFLL || (long long)P * n > 0x7FFFFFFFLL)
-        return STRD_EUNSUPPORTED;
     const long long grid2 = (total + kWave - 1) / kWave;
-    if (grid2 > 0x7FFFFFFFLL) return STRD_EUNSUPPORTED;
 #define STRD_SSD_STATE(CC, NN, FF)                                                                                   \
     ssd_chunk_state_kernel<T, CC, NN, FF><<<(unsigned)grid1, kWave, 0, st>>>((const T *)x, dt, A, (const T *)B, L, decay, \
                                                                              Tn, H, P, G, n, nc, nst, pblocks)
@@ -1087,11 +1091,11 @@ static int ssd_in_rounds(const void *x, const float *dt, const float *A, const v
     return STRD_OK;
 }
 
-// ws = nullptr: a caller without a workspace gets the recurrence.
+// ws = nullptr: a caller without a workspace gets the recurrence, and so does a state too large for the chunks' launches.
 int ssd_general(const void *x, const float *dt, const float *A, const void *B, const void *C,
                 const float *D, const float *S_in, void *y, float *S_out, int T, int H, int P, int G,
                 int n, strd_dtype io, void *ws, hipStream_t st) {
-    if (T == 0 || !ws) {
+    if (T == 0 || !ws || !ssd_in_chunks(H, P, n)) {
         int lanes = 1;
         while (lanes * kSlice < n) lanes <<= 1;  // power of two <= 64, so a column never straddles a wave
         const long long threads = (long long)H * P * lanes;
@@ -1116,11 +1120,17 @@ template <typename T>
 static int attn_launch(const void *q, const void *k, const void *v, void *o, int Tn, int Hq, int Hkv, int d, float scale,
                        hipStream_t st) {
     const long long grid = (long long)ceil_div(Tn, 16) * Hq;
-    if (grid > 0x7FFFFFFFLL || (long long)Hkv * d * (long long)sizeof(T) >= 1 << 24) return STRD_EUNSUPPORTED;
-#define STRD_ATTN(VV, FF, DD, NN)                                                                                      \
-    attn_tile_kernel<T, VV, FF, DD, NN><<<(unsigned)grid, NN * kWave, 0, st>>>((const T *)q, (const T *)k, (const T *)v, \
-                                                                               (T *)o, Tn, Hq, Hkv, d, scale * kLog2e)
-    if (!vec4<T>(d, (const T *)q, (const T *)k, (const T *)v)) {
+    if ((long long)Tn * Hq > 0x7FFFFFFFLL) return STRD_EUNSUPPORTED;
+    const bool wide = (long long)Hkv * d * (long long)sizeof(T) >= 1 << 24;  // rows that a 24-bit product does not reach
+#define STRD_ATTN_W(VV, FF, DD, NN, WW)                                                                                  \
+    attn_tile_kernel<T, VV, FF, DD, NN, WW><<<(unsigned)grid, NN * kWave, 0, st>>>(                                      \
+        (const T *)q, (const T *)k, (const T *)v, (T *)o, Tn, Hq, Hkv, d, scale * kLog2e)
+#define STRD_ATTN(VV, FF, DD, NN) STRD_ATTN_W(VV, FF, DD, NN, false)
+    if (wide) {
+        if (d <= 64) STRD_ATTN_W(false, false, 1, 8, true);
+        else if (d <= 128) STRD_ATTN_W(false, false, 2, 4, true);
+        else STRD_ATTN_W(false, false, 4, 2, true);
+    } else if (!vec4<T>(d, (const T *)q, (const T *)k, (const T *)v)) {
         if (d <= 64) STRD_ATTN(false, false, 1, 8);
         else if (d <= 128) STRD_ATTN(false, false, 2, 4);
         else STRD_ATTN(false, false, 4, 2);
@@ -1131,6 +1141,7 @@ static int attn_launch(const void *q, const void *k, const void *v, void *o, int
     else if (d == 256) STRD_ATTN(true, true, 4, 2);
     else STRD_ATTN(true, false, 4, 2);
 #undef STRD_ATTN
+#undef STRD_ATTN_W
     return launch_status();
 }
 

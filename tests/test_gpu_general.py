@@ -341,6 +341,30 @@ def test_scan_without_a_workspace(T, H, P, G, n, dtype):
     assert_close(f(S), S_ref, BOUND[dtype], "S", units=(0,))
 
 
+def test_attention_with_rows_of_16_megabytes():
+    """65536 heads of 64: rows past what a 24-bit product reaches (and one head less: rows just below it)."""
+    T, d = 35, 64
+    for H in (65535, 65536):
+        _say("attn, %d heads" % H)
+        q, k, v = (torch.randn(T, H, d, device=DEV, generator=torch.Generator(device=DEV).manual_seed(H + i)) for i in range(3))
+        o = strd.attn_prefill(q, k, v)
+        for h in (0, H // 2, H - 1):
+            hs = slice(h, h + 1)
+            assert_close(f(o[:, hs]), oracle.attn(f(q[:, hs]), f(k[:, hs]), f(v[:, hs])), BOUND[F32], "o", units=(0,))
+
+
+def test_scan_with_a_state_of_a_gigabyte():
+    """4097 heads of 64 x 1024, one more than the chunks' launches take: the recurrence, with or without a workspace."""
+    _say("general scan, 4097 heads of 64 x 1024")
+    t = _scan_inputs(3, 4097, 64, 1, 1024, F32, 5)[:-1]
+    y, S = strd.ssd_prefill(*(v.to(DEV) for v in t))
+    for h in (0, 4096):
+        hs = slice(h, h + 1)
+        y_ref, S_ref = oracle.ssd_seq(f(t[0][:, hs]), f(t[1][:, hs]), f(t[2][hs]), f(t[3]), f(t[4]), f(t[5][hs]), None)
+        assert_close(f(y[:, hs]), y_ref, BOUND[F32], "y", units=(1,))
+        assert_close(f(S[hs]), S_ref, BOUND[F32], "S", units=(0,))
+
+
 # ------------------------------------------------------------------ selection --------------
 @pytest.mark.parametrize("in_bin", [4095, 4096, 4097, 30000])
 @pytest.mark.parametrize("N,low_bits", [(65536, 11), (65537, 12), (131072, 13), (131072 + 5, 21), (1 << 20, 21)])

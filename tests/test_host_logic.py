@@ -337,3 +337,18 @@ def test_workspace_of_the_general_scan_is_bounded():
     assert ws(4096, 128, 64, 128) == 64 * state + 64 * 512
     assert ws(4097, 128, 64, 128) == ws(1 << 30, 128, 64, 128) == 66 * state + 64 * 512
     assert ws(1 << 20, 4096, 64, 1024) == 3 * 4096 * 64 * 1024 * 4 + 4096 * 4
+
+
+def test_sizes_the_general_kernels_take():
+    """Nothing is launched: rows of scores of up to 14992 elements, 2^31 rows of queries, scans of up to 2^30 lanes; states
+    of more than 2^28 entries need no workspace (the recurrence takes them)."""
+    L, at, F32 = strd.lib(), 0x10000, binding.STRD_F32   # an address that is never read
+    seqs = (binding._Seq * 1)(binding._Seq(20, 3, 1))
+    big = 1 << 40
+    assert L.strd_score_attn(at, at, at, 3, 20, 2, 1, 14993, 0.1, F32, at, big, None) == -2
+    assert L.strd_score_attn_varlen(at, at, at, 20, ctypes.cast(seqs, ctypes.c_void_p), 1, 2, 1, 14993, 0.1, F32, at, big, None) == -2
+    assert L.strd_attn_prefill(at, at, at, at, 1 << 20, 1 << 11, 1, 40, 0.1, F32, None, 0, None) == -2
+    scan = lambda H, P, n, ws: L.strd_ssd_prefill(at, at, at, at, at, None, None, at, at, 1, H, P, 1, n, 256, F32, ws, big, None)
+    assert scan(1 << 20, 1025, 16, at) == scan(1 << 20, 1025, 16, None) == scan(1 << 16, 257, 1024, at) == -2
+    ws = lambda H, P, n: L.strd_ssd_prefill_workspace(1000, H, P, 1, n, 256, F32)
+    assert ws(4096, 64, 1024) > 0 and ws(4097, 64, 1024) == 0 and ws((1 << 24) - 1, 1, 1) > 0 and ws(1 << 24, 1, 1) == 0
