@@ -769,20 +769,20 @@ __global__ __launch_bounds__(threads_for(NC, NH)) void ssd_seg_kernel(SegArgs a,
 }
 
 // ---- the contribution of the incoming state to the first tokens of segments 1.. and S_out -----
-// grid = (boundary b = 1..nseg, head); b < nseg: y of segment b; b == nseg: S_out.
-// One workgroup per (boundary, head), a wave per 16-channel tile.  At the decay rates of a trained layer
-// the incoming state is gone after two or three 64-token tiles, so the kernel is a chain of loads: dt, the
-// state E and the rows of the first tile travel together.  The rows of the next tile are fetched when their
-// turn comes: held beside the current ones they cost the second workgroup of a CU.  (Four workgroups per
-// (boundary, head), a tile each, read dt and E four times over and take four rounds of the chip; this form
-// takes one, and the scan 2 to 6 us less at 2500 to 33280 tokens.)
+// grid = (boundary b = 1..nseg, head, share z); b < nseg: y of segment b; b == nseg: S_out.
+// One workgroup per (boundary, head), or a few that take its 64-token tiles in turn (see fix_shares), a wave per 16-channel
+// tile.  At the decay rates of a trained layer the incoming state is gone after two or three tiles, so the kernel is
+// a chain of loads: dt, the state E and the rows of the first tile travel together.  The rows of the next tile are fetched when their
+// turn comes: held beside the current ones they cost the second workgroup of a CU.  (Always four workgroups per
+// (boundary, head) read dt and E four times over and take four rounds of the chip at 128 heads; one takes one, and the scan
+// 2 to 6 us less at 2500 to 33280 tokens.)
 constexpr int kFixThreads = 256;
 constexpr int kFixBatch = 4;  // tiles whose dt is read at once
 
 template <int NS, bool GATHER>
 __global__ __launch_bounds__(kFixThreads) void ssd_fix_kernel(SegArgs a) {
     constexpr int KS = NS / 32;
-    const int b = 1 + blockIdx.x, h = blockIdx.y;
+    const int b = 1 + blockIdx.x, h = blockIdx.y, z = blockIdx.z, nz = gridDim.z;
     const int lane = threadIdx.x & 63, lr = lane & 15, lb = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const size_t seg_elems = (size_t)a.H * a.P * NS;
@@ -795,7 +795,7 @@ __global__ __launch_bounds__(kFixThreads) void ssd_fix_kernel(SegArgs a) {
         for (int s = b - 2; s >= 0 && f != 0.f; --s) {
             const float *src = a.lend + (size_t)s * seg_elems + (size_t)h * a.P * NS;
             float *dst = a.S_out + (size_t)h * a.P * NS;
-            for (int e = threadIdx.x; e < per; e += kFixThreads) {
+            for (int e = z * kFixThreads + threadIdx.x; e < per; e += nz * kFixThreads) {
                 f32x4 v = reinterpret_cast<const f32x4 *>(src)[e], o = reinterpret_cast<f32x4 *>(dst)[e];
                 reinterpret_cast<f32x4 *>(dst)[e] = o + f * v;
             }
@@ -807,7 +807,7 @@ __global__ __launch_bounds__(kFixThreads) void ssd_fix_kernel(SegArgs a) {
     const int tok0 = b * a.seg_steps * kQ;
     const int tend = min(a.T, (b + 1) * a.seg_steps * kQ);
     const int npt = a.P / 16;
-    if (wave >= npt) return;
+    if (wave >= npt || tok0 + z * kQ >= tend) return;
     const float Al2 = a.A[h] * kLog2e;
     auto row_of = [&](int t) -> size_t {
         t = min(t, a.T - 1);
@@ -842,7 +842,7 @@ __global__ __launch_bounds__(kFixThreads) void ssd_fix_kernel(SegArgs a) {
     for (int pt = wave; pt < npt; pt += kFixThreads / 64) {
         load_dt(0);
         Rows r;
-        load_rows(0, pt, r);
+        load_rows(z, pt, r);
         // E = state at the start of segment b, as A-operand fragments (rows p = 16 pt + lr, k slots
         // n = 32 ks + 8 lb + s)
         bf16x8 ef[KS];
@@ -888,7 +888,8 @@ __global__ __launch_bounds__(kFixThreads) void ssd_fix_kernel(SegArgs a) {
             for (int q = 0; q < kFixBatch; ++q) {
                 if (q >= alive || tok0 + (k0 + q) * kQ >= tend) break;
                 const int k = k0 + q;
-                if (k > 0) load_rows(k, pt, r);
+                if ((k & (nz - 1)) != z) continue;
+                if (k != z) load_rows(k, pt, r);
 #pragma unroll
                 for (int tt = 0; tt < 4; ++tt) {
                     const int tq = tok0 + k * kQ + 16 * tt + lr;  // this lane's token of the query block
@@ -908,13 +909,24 @@ __global__ __launch_bounds__(kFixThreads) void ssd_fix_kernel(SegArgs a) {
     }
 }
 
+// Workgroups that share the tiles of a (boundary, head): as many as still find a CU to themselves, where the state may
+// live through all tiles of a segment (us of a scan whose decays are slow, with 1 / 2 / 4: 24 heads of 64, 1000 tokens,
+// 48 pairs 45.8 / 36.6 / 32.2; 2000, 96 pairs 50.5 / 42.2 / 45.4; 4000, 168 pairs 58.7 / 62.1 / 65.1), two where a few
+// CUs would have two workgroups and the others wait for them (6000, 264 pairs 87.1 / 71.8 / 84.2), and four where heads of
+// more than 64 channels take a wave two turns (30 heads of 128, 4000 tokens, 150 pairs 122 / 125 / 101).  With fast decays the
+// shares cost 1 us at most.  The bits are the same.
+int fix_shares(int nseg, int H, int P) {
+    const long long pairs = (long long)nseg * H;
+    return pairs <= 64 ? 4 : pairs <= 128 ? 2 : pairs <= 256 ? (P > 64 ? 4 : 1) : pairs <= 320 ? 2 : 1;
+}
+
 template <int NS, int NC, int NH, bool GATHER>
 int launch(const SegArgs &a, hipStream_t st) {
     const int nunits = a.nseg * a.wg_per_seg;
     const size_t smem = sizeof(LdsS<NS, NC, NH>);
     if (!allow_dynamic_lds(reinterpret_cast<const void *>(&ssd_seg_kernel<NS, NC, NH, GATHER>), smem)) return STRD_EHIP;
     ssd_seg_kernel<NS, NC, NH, GATHER><<<xcd_grid(nunits), threads_for(NC, NH), smem, st>>>(a, nunits);
-    if (a.nseg > 1) ssd_fix_kernel<NS, GATHER><<<dim3(a.nseg, a.H), kFixThreads, 0, st>>>(a);
+    if (a.nseg > 1) ssd_fix_kernel<NS, GATHER><<<dim3(a.nseg, a.H, fix_shares(a.nseg, a.H, a.P)), kFixThreads, 0, st>>>(a);
     return launch_status();
 }
 

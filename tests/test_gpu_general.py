@@ -365,6 +365,30 @@ def test_scan_with_a_state_of_a_gigabyte():
         assert_close(f(S[hs]), S_ref, BOUND[F32], "S", units=(0,))
 
 
+@pytest.mark.parametrize("H,P,G,n,T", [(8, 64, 1, 128, 1000), (24, 64, 1, 128, 1990), (24, 64, 1, 64, 4000), (30, 128, 2, 128, 3001),
+                                       (60, 64, 2, 128, 3000), (60, 64, 2, 64, 5999), (4, 32, 1, 64, 1100)])
+def test_scan_with_few_heads_and_slow_decays(H, P, G, n, T):
+    """The incoming state lives through every tile of its segment; one, two or four workgroups repair it.  The first and
+    the last head against the recurrence, through the index list bit for bit."""
+    _say("scan, seams, H=%d P=%d n=%d T=%d" % (H, P, n, T))
+    assert strd.lib().strd_ssd_prefill_workspace(T, H, P, G, n, 256, 1) > 0
+    g = torch.Generator().manual_seed(T)
+    x = torch.randn(T, H, P, generator=g).to(BF16)
+    B, C = (torch.randn(T, G, n, generator=g) / n ** 0.5).to(BF16), torch.randn(T, G, n, generator=g).to(BF16)
+    dt, A = torch.rand(T, H, generator=g), -0.002 * (0.5 + torch.rand(H, generator=g))
+    D, S_in = torch.randn(H, generator=g), torch.randn(H, P, n, generator=g)
+    dev = [t.to(DEV) for t in (x, dt, A, B, C)]
+    y, S = strd.ssd_prefill(*dev, D.to(DEV), S_in.to(DEV))
+    N = T - 40
+    yg, Sg = strd.ssd_prefill_gather(*dev, torch.arange(N, dtype=torch.int32, device=DEV), N, 40, D.to(DEV), S_in.to(DEV))
+    assert torch.equal(yg, y) and torch.equal(Sg, S)
+    for h in (0, H - 1):
+        hs, gs = slice(h, h + 1), slice(h * G // H, h * G // H + 1)
+        y_ref, S_ref = oracle.ssd_seq(f(x[:, hs]), f(dt[:, hs]), f(A[hs]), f(B[:, gs]), f(C[:, gs]), f(D[hs]), f(S_in[hs]))
+        assert_close(f(y[:, hs]), y_ref, TOL[BF16], "y", units=(1,))
+        assert_close(f(S[hs]), S_ref, TOL[BF16], "S", units=(0,))
+
+
 # ------------------------------------------------------------------ selection --------------
 @pytest.mark.parametrize("in_bin", [4095, 4096, 4097, 30000])
 @pytest.mark.parametrize("N,low_bits", [(65536, 11), (65537, 12), (131072, 13), (131072 + 5, 21), (1 << 20, 21)])
