@@ -27,6 +27,7 @@ constexpr int kRows = 128;  // rows (keys in pass 1, queries in pass 2) per LDS 
 constexpr int kTW = 2;      // 32-wide register tiles per wave (queries in pass 1, keys in pass 2)
 constexpr int kNarrowBlocks = 128;  // see make_plan
 constexpr long long kFusedStats = 4096;
+constexpr int kFusedSlices = 48;
 constexpr int kFuseSlices = 8;  // slices whose statistics a thread has in flight
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -480,8 +481,10 @@ Plan make_plan(int M, int N, int Hq, int Hkv, int nseq) {
     p.tw = (long long)ceil_div(N, 4 * 32 * kTW) * Hkv * nseq <= kNarrowBlocks ? 1 : 2;
     // Every workgroup of pass 2 combines the slices of its head's rows by itself while that is less than
     // the launch it saves (1024 keys, 16 text rows, 512 pairs per head: 16.0 us -> 13.7; 4000 keys, 20 rows,
-    // 2560 pairs: 18.0 -> 16.6; 2304 keys, 100 rows, 7200 pairs: 27.3 -> 30.1).
-    p.fuse = (long long)R * p.nslice <= kFusedStats;
+    // 2560 pairs: 18.0 -> 16.6; 2304 keys, 100 rows, 7200 pairs: 27.3 -> 30.1).  The slices of a row are a chain, however few
+    // rows there are: 4 rows of 8 heads, 4000 keys in 32 slices 16.8 -> 16.0; 6000 in 47 21.0 -> 20.0; 8000 in 63 21.7 ->
+    // 21.4 (one head 13.6 -> 14.2); 20000 in 128 39.0 -> 43.5.
+    p.fuse = (long long)R * p.nslice <= kFusedStats && p.nslice <= kFusedSlices;
     return p;
 }
 

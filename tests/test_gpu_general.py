@@ -389,6 +389,16 @@ def test_scan_with_few_heads_and_slow_decays(H, P, G, n, T):
         assert_close(f(S[hs]), S_ref, TOL[BF16], "S", units=(0,))
 
 
+@pytest.mark.parametrize("M,Hq,Hkv,d", [(1, 1, 1, 64), (4, 8, 2, 128), (85, 1, 1, 64), (86, 1, 1, 64)])
+@pytest.mark.parametrize("N", [5888, 6016, 6144, 6145, 6300])
+def test_score_attn_around_the_rule_for_combined_slices(N, M, Hq, Hkv, d):
+    """Up to 48 slices of 128 keys (and 4096 pairs of a slice and a row) combined in pass 2, more in a launch."""
+    _say("score_attn, slices, M=%d N=%d" % (M, N))
+    rn = _draw(N + M, BF16)
+    q, k = rn(M, Hq, d), rn(N, Hkv, d)
+    assert_close(f(strd.score_attn(q.to(DEV), k.to(DEV))), oracle.score_attn(f(q), f(k)), BOUND[BF16], "s", units=(0,))
+
+
 # ------------------------------------------------------------------ selection --------------
 @pytest.mark.parametrize("in_bin", [4095, 4096, 4097, 30000])
 @pytest.mark.parametrize("N,low_bits", [(65536, 11), (65537, 12), (131072, 13), (131072 + 5, 21), (1 << 20, 21)])
