@@ -905,6 +905,80 @@ __global__ __launch_bounds__(NW *kWave) __attribute__((amdgpu_waves_per_eu(DJ ==
     }
 }
 
+// Short sequences: one workgroup per (query row, query head).  Keys are walked in tiles of kRowThreads, a thread each,
+// with an online softmax; lane c < d accumulates output channel c.  A row's work is one short chain, where a tile's
+// waves read 32 rows of K and V at a time, element by element if d is odd; see attn_by_rows.
+constexpr int kRowThreads = 256;
+
+__device__ __forceinline__ float wave_max(float v) {
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
+    return v;
+}
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    return v;
+}
+
+template <typename T>
+__global__ __launch_bounds__(kRowThreads) void attn_row_kernel(const T *__restrict__ q, const T *__restrict__ k,
+                                                               const T *__restrict__ v, T *__restrict__ o, int Hq, int Hkv,
+                                                               int d, float scale2) {
+    extern __shared__ float smem[];  // d (q) + kRowThreads (p) + waves (red)
+    float *qs = smem, *ps = smem + d, *red = smem + d + kRowThreads;
+    const int t = blockIdx.x / Hq, h = blockIdx.x % Hq, hk = h / (Hq / Hkv);
+    for (int c = threadIdx.x; c < d; c += kRowThreads) qs[c] = to_f32(q[((size_t)t * Hq + h) * d + c]);
+    __syncthreads();
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    float m_run = -INFINITY, l_run = 0.f, acc = 0.f;  // acc: channel threadIdx.x (< d)
+    for (int j0 = 0; j0 <= t; j0 += kRowThreads) {
+        const int j = j0 + threadIdx.x;
+        float z = -INFINITY;
+        if (j <= t) {
+            const T *kv = k + ((size_t)j * Hkv + hk) * d;
+            float dot[4] = {0.f, 0.f, 0.f, 0.f};  // four chains: less rounding, and a quarter of the wait
+            int c = 0;
+            for (; c + 4 <= d; c += 4)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dot[i] = fmaf(qs[c + i], to_f32(kv[c + i]), dot[i]);
+            for (; c < d; ++c) dot[0] = fmaf(qs[c], to_f32(kv[c]), dot[0]);
+            z = scale2 * ((dot[0] + dot[1]) + (dot[2] + dot[3]));
+        }
+        const float wm = wave_max(z);
+        if (lane == 0) red[wave] = wm;
+        __syncthreads();
+        float tm = -INFINITY;
+        for (int w = 0; w < kRowThreads / kWave; ++w) tm = fmaxf(tm, red[w]);
+        const float m_new = fmaxf(m_run, tm), ref = m_new == -INFINITY ? 0.f : m_new;
+        const float pj = j <= t ? ex2(z - ref) : 0.f;
+        ps[threadIdx.x] = pj;
+        const float wsum = wave_sum(pj);
+        __syncthreads();  // ps complete, red (max) consumed
+        if (lane == 0) red[wave] = wsum;
+        __syncthreads();
+        float tsum = 0.f;
+        for (int w = 0; w < kRowThreads / kWave; ++w) tsum += red[w];
+        const float corr = ex2(m_run - ref);  // 0 on the first tile (m_run = -inf)
+        l_run = l_run * corr + tsum;
+        m_run = m_new;
+        if (threadIdx.x < d) {
+            const int cnt = min(kRowThreads, t + 1 - j0);
+            const T *vc = v + ((size_t)j0 * Hkv + hk) * d + threadIdx.x;
+            const size_t pitch = (size_t)Hkv * d;
+            float sum[4] = {0.f, 0.f, 0.f, 0.f};
+            int jj = 0;
+            for (; jj + 4 <= cnt; jj += 4)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum[i] = fmaf(ps[jj + i], to_f32(vc[(jj + i) * pitch]), sum[i]);
+            for (; jj < cnt; ++jj) sum[0] = fmaf(ps[jj], to_f32(vc[jj * pitch]), sum[0]);
+            acc = fmaf(acc, corr, (sum[0] + sum[1]) + (sum[2] + sum[3]));
+        }
+        __syncthreads();  // before ps / red are overwritten
+    }
+    if (threadIdx.x < d) o[((size_t)t * Hq + h) * d + threadIdx.x] = from_f32<T>(acc / l_run);
+}
+
 // Rows of `len` elements from bases `p...` can be read 4 elements at a time.
 template <typename T, typename... Ptr>
 inline bool vec4(int len, const Ptr *...p) {
@@ -1116,11 +1190,30 @@ int ssd_general(const void *x, const float *dt, const float *A, const void *B, c
 
 bool attn_general_supported(int d) { return d >= 1 && d <= 256; }
 
+// Short sequences go row by row.  The tiles' time is a chain that grows with T (and with d: 2 waves a workgroup above
+// 128; and with every element of a row that vectors cannot read), the rows' with T * T * Hq, so the line lies at about
+// T * (Hq + a few): us as tiles / as rows, fp32, 4 query heads: d = 200, 200 tokens 43 / 18, 600 113 / 113; d = 130, 600
+// 109 / 92, 1000 177 / 230; d = 100, 100 10.3 / 8.1, 200 15.5 / 13.5, 300 20 / 22; d = 65, 300 25 / 20, 600 40 / 50; d = 33,
+// 64 7.0 / 6.1, 100 7.4 / 7.3; bf16: d = 130, 1000 370 / 180, 1500 562 / 400; d = 33 200 12.1 / 12.7.  (Rows of up to 64
+// elements that vectors read: equal within 0.7 us up to 16 tokens, tiles from there on.)
+static bool attn_by_rows(int T, int Hq, int d, bool vec, bool half) {
+    auto below = [&](int extra, int line) { return (long long)T * (Hq + extra) <= line; };
+    if (d <= 64) return !vec && below(4, half ? 2320 : 450);
+    if (d <= 128) return vec ? below(4, d == 128 ? 640 : 1300) : below(1, half ? 4960 : 2560);
+    if (d == 256 && vec) return below(1, half ? 2200 : 1300);
+    return vec ? below(0, half ? 3300 : 3000) : below(0, half ? 6600 : 3300);
+}
+
 template <typename T>
 static int attn_launch(const void *q, const void *k, const void *v, void *o, int Tn, int Hq, int Hkv, int d, float scale,
                        hipStream_t st) {
     const long long grid = (long long)ceil_div(Tn, 16) * Hq;
     if ((long long)Tn * Hq > 0x7FFFFFFFLL) return STRD_EUNSUPPORTED;
+    if (attn_by_rows(Tn, Hq, d, vec4<T>(d, (const T *)q, (const T *)k, (const T *)v), sizeof(T) == 2)) {
+        attn_row_kernel<T><<<Tn * Hq, kRowThreads, (size_t)(d + kRowThreads + kRowThreads / kWave) * sizeof(float), st>>>(
+            (const T *)q, (const T *)k, (const T *)v, (T *)o, Hq, Hkv, d, scale * kLog2e);
+        return launch_status();
+    }
     const bool wide = (long long)Hkv * d * (long long)sizeof(T) >= 1 << 24;  // rows that a 24-bit product does not reach
 #define STRD_ATTN_W(VV, FF, DD, NN, WW)                                                                                  \
     attn_tile_kernel<T, VV, FF, DD, NN, WW><<<(unsigned)grid, NN * kWave, 0, st>>>(                                      \

@@ -341,6 +341,30 @@ def test_scan_without_a_workspace(T, H, P, G, n, dtype):
     assert_close(f(S), S_ref, BOUND[dtype], "S", units=(0,))
 
 
+@pytest.mark.parametrize("d,dtype,Hq,T", [(33, F32, 16, 22), (33, BF16, 16, 116), (72, F32, 16, 65), (128, F32, 16, 32),
+                                          (65, F32, 16, 150), (127, BF16, 16, 291), (200, F32, 16, 187), (136, BF16, 16, 206),
+                                          (256, F32, 16, 76), (256, BF16, 16, 129), (130, F32, 16, 206), (255, BF16, 16, 412),
+                                          (130, F32, 2, 600), (250, BF16, 1, 1025)])
+def test_attention_by_rows_and_by_tiles(d, dtype, Hq, T):
+    """The longest sequence that goes row by row, and one token more, in tiles.  One NaN in v stays with its own and
+    later queries, its channel and its kv head: the rest has the same bits as with 0 in its place."""
+    for n in (T, T + 1):
+        _say("attn, rows and tiles, d=%d %s Hq=%d T=%d" % (d, dtype, Hq, n))
+        rn, Hkv = _draw(n + d, dtype), 1 if Hq == 1 else 2
+        q, k, v = rn(n, Hq, d), rn(n, Hkv, d), rn(n, Hkv, d)
+        q, k, v, v_host = q.to(DEV), k.to(DEV), v.to(DEV), v
+        o = strd.attn_prefill(q, k, v)
+        assert_close(f(o), oracle.attn(f(q), f(k), f(v_host)), BOUND[dtype], "o", units=(0, 1))
+        for s in (n // 2, n - 2):
+            clean, dirty = v.clone(), v.clone()
+            clean[s, -1, d - 1], dirty[s, -1, d - 1] = 0.0, float("nan")
+            want, got = strd.attn_prefill(q, k, clean), strd.attn_prefill(q, k, dirty)
+            mine = slice(Hq - Hq // Hkv, Hq)
+            assert bool(torch.isnan(got[s:, mine, d - 1]).all())
+            got[s:, mine, d - 1] = want[s:, mine, d - 1]
+            assert torch.equal(got, want)
+
+
 def test_attention_with_rows_of_16_megabytes():
     """65536 heads of 64: rows past what a 24-bit product reaches (and one head less: rows just below it)."""
     T, d = 35, 64
