@@ -670,7 +670,7 @@ __global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict_
     }
 }
 
-// The recurrence itself, for callers that bring no workspace (and for no tokens): a state column (h, p) is held by
+// The recurrence itself, for a few tokens, very large states and callers that bring no workspace: a state column (h, p) is held by
 // `lanes` adjacent lanes, each with kSlice consecutive state entries in registers; y_t is reduced across those
 // lanes.  A serial chain of T steps: 830 us at 544 tokens, 8 heads of 32, n = 16, where the chunks take 13.4.
 constexpr int kSlice = 16, kRecThreads = 256;
@@ -1081,8 +1081,18 @@ bool ssd_general_supported(int n) { return n >= 1 && n <= 1024; }
 // workgroups a launch), the state handed on in two more buffers that take turns: 131072 tokens take 276 MB, not 8.6 GB.
 constexpr size_t kRoundBytes = (size_t)256 << 20;
 // The chunked form's launches count 32-bit threads per grid: states of up to 2^28 entries (1 GB) in fewer than 2^24
-// heads.  Beyond, there are channels enough to fill the chip with the recurrence.
-static bool ssd_in_chunks(int H, int P, int n) { return H < 1 << 24 && (long long)H * P <= (1 << 28) / n; }
+// heads.  Beyond, there are channels enough to fill the chip with the recurrence.  And it is two or three launches, of
+// 10 us for the shortest sequence (16 state entries) to 40 to 55 (1024, whose rows are read per product), where a
+// token of the recurrence takes 1.2 to 3.7: us in chunks / as a recurrence, 1 and 5 and 8 tokens: 8 heads of 32, n = 16
+// 10.5 / 5.9, 10.6 / 10.7, 10.6 / 14.5; 128 heads of 64, n = 124 23.2 / 9.9, 23.4 / 18.5, 23.5 / 24.3; n = 256 34 / 20, 35 / 47
+// (every CU has its share of the lanes there: 3 tokens 35 / 33); n = 1024, 8 heads 42 / 10, 46 / 25, 48 / 36, 12 tokens
+// 52 / 51; in bf16, where a round of 16 tokens takes 50 either way, 20 111 / 80, 40 167 / 151.
+static bool ssd_in_chunks(int T, int H, int P, int n, strd_dtype io) {
+    if (H >= 1 << 24 || (long long)H * P > (1 << 28) / n) return false;
+    if (n > 128 && (long long)H * P * ceil_div(n, kSlice) > 1 << 16) return T > 3;
+    if (n > 512 && T < kChunk) return T * (io == STRD_F32 ? 100 : 64) > n * ceil_div(T, 16);
+    return T > (n < 32 ? 5 : n > 256 || H >= 256 ? 8 : 6);
+}
 struct ScanRounds {
     int chunks;  // per round
     size_t states, decays, carry;  // bytes
@@ -1098,7 +1108,9 @@ static ScanRounds ssd_rounds(int T, int H, int P, int n) {
     r.carry = nc > r.chunks ? align_up(state, 256) : 0;
     return r;
 }
-size_t ssd_general_ws(int T, int H, int P, int n) { return ssd_in_chunks(H, P, n) ? ssd_rounds(T, H, P, n).total() : 0; }
+size_t ssd_general_ws(int T, int H, int P, int n, strd_dtype io) {
+    return ssd_in_chunks(T, H, P, n, io) ? ssd_rounds(T, H, P, n).total() : 0;
+}
 
 template <typename T>
 static int ssd_launch(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D,
@@ -1165,11 +1177,11 @@ static int ssd_in_rounds(const void *x, const float *dt, const float *A, const v
     return STRD_OK;
 }
 
-// ws = nullptr: a caller without a workspace gets the recurrence, and so does a state too large for the chunks' launches.
+// ws = nullptr: a caller without a workspace gets the recurrence.
 int ssd_general(const void *x, const float *dt, const float *A, const void *B, const void *C,
                 const float *D, const float *S_in, void *y, float *S_out, int T, int H, int P, int G,
                 int n, strd_dtype io, void *ws, hipStream_t st) {
-    if (T == 0 || !ws || !ssd_in_chunks(H, P, n)) {
+    if (T == 0 || !ws || !ssd_in_chunks(T, H, P, n, io)) {
         int lanes = 1;
         while (lanes * kSlice < n) lanes <<= 1;  // power of two <= 64, so a column never straddles a wave
         const long long threads = (long long)H * P * lanes;

@@ -389,6 +389,23 @@ def test_scan_with_a_state_of_a_gigabyte():
         assert_close(f(S[hs]), S_ref, BOUND[F32], "S", units=(0,))
 
 
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("H,P,G,n,last", [(8, 32, 1, 16, 5), (3, 33, 1, 7, 5), (8, 64, 1, 130, 6), (256, 20, 1, 40, 8), (128, 64, 8, 256, 3),
+                                          (2, 20, 1, 700, {F32: 7, BF16: 10}), (2, 20, 1, 1024, {F32: 10, BF16: 63})])
+def test_scan_of_a_few_tokens(H, P, G, n, last, dtype):
+    """Token by token up to `last` (no workspace), in chunks from one more."""
+    last = last[dtype] if isinstance(last, dict) else last
+    for T in (1, last, last + 1):
+        _say("general scan, T=%d H=%d P=%d n=%d %s" % (T, H, P, n, dtype))
+        ws = strd.lib().strd_ssd_prefill_workspace(T, H, P, G, n, 256, 0 if dtype == F32 else 1)
+        assert (ws == 0) == (T <= last)
+        t = _scan_inputs(T, H, P, G, n, dtype, T + n)
+        y, S = strd.ssd_prefill(*(v.to(DEV) for v in t))
+        y_ref, S_ref = oracle.ssd_seq(*(f(v) for v in t))
+        assert_close(f(y), y_ref, BOUND[dtype], "y", units=(1,))
+        assert_close(f(S), S_ref, BOUND[dtype], "S", units=(0,))
+
+
 @pytest.mark.parametrize("H,P,G,n,T", [(8, 64, 1, 128, 1000), (24, 64, 1, 128, 1990), (24, 64, 1, 64, 4000), (30, 128, 2, 128, 3001),
                                        (60, 64, 2, 128, 3000), (60, 64, 2, 64, 5999), (4, 32, 1, 64, 1100)])
 def test_scan_with_few_heads_and_slow_decays(H, P, G, n, T):
