@@ -269,7 +269,7 @@ int strd_compact_varlen(const strd_compact_item *items, int n_items, const int32
  *       before every 64-token chunk and the chunks' decays, (P * n + 1) * H floats per chunk, of as many
  *       chunks as fit 256 MB (one at least), and two states more when that is not all of them.  Here it
  *       may be smaller or NULL: the call then walks the sequence token by token, which takes 65 times as
- *       long at 544 tokens; a few tokens (up to 3 to 63, by size) and states of more than 2^28 entries
+ *       long at 544 tokens; a few tokens (up to 2 to 8, by size) and states of more than 2^28 entries
  *       are always walked so, and need 0 bytes.
  * Requires T >= 0, H % G == 0.
  * ------------------------------------------------------------------------- */

@@ -255,7 +255,7 @@ size_t strd_ssd_prefill_workspace(int T, int H, int P, int G, int n, int chunk, 
     (void)chunk;
     if (T < 1 || H < 1 || P < 1 || G < 1 || n < 1 || H % G) return 0;
     if (use_seg(T, T, H, P, G, n, io)) return ssd_seg_ws(T, H, P, G, n);
-    return ssd_mfma_supported(T, T, H, P, G, n, io) || !ssd_general_supported(n) ? 0 : ssd_general_ws(T, H, P, n, io);
+    return ssd_mfma_supported(T, T, H, P, G, n, io) || !ssd_general_supported(n) ? 0 : ssd_general_ws(T, H, P, n);
 }
 
 int strd_ssd_prefill(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D,

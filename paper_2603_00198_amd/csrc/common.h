@@ -249,7 +249,7 @@ int score_attn_general(const void *q, const void *k, float *s, int M, int N, int
 int score_mamba_general(const void *B, const void *C, const float *dt, float *s, int M, int N, int H,
                         int G, int n, strd_dtype io, hipStream_t st);
 bool ssd_general_supported(int n);
-size_t ssd_general_ws(int T, int H, int P, int n, strd_dtype io);
+size_t ssd_general_ws(int T, int H, int P, int n);
 int ssd_general(const void *x, const float *dt, const float *A, const void *B, const void *C,
                 const float *D, const float *S_in, void *y, float *S_out, int T, int H, int P, int G,
                 int n, strd_dtype io, void *ws, hipStream_t st);

@@ -152,37 +152,54 @@ __device__ __forceinline__ void products(const Operand<TA, KJ, FULL> (&a)[NT], c
 template <typename TA, typename TB, int KJ, bool FULL>
 __device__ __forceinline__ void product_f64(const Operand<TA, KJ, FULL> &a, const Operand<TB, KJ, FULL> &b, int lb,
                                             double (&sum)[4]) {
-    constexpr int kChains = KJ > 1 ? 8 : 4;
-    static_assert(KJ <= 8, "16 elements a chain");
-    f32x4 c[kChains];
-#pragma unroll
-    for (int m = 0; m < kChains; ++m) c[m] = zero4();
     if constexpr (KJ > 0) {
+        constexpr int kChains = KJ > 4 ? KJ : 4;  // (a chain of one element's four products waits for each of them)
+        f32x4 c[kChains];
+#pragma unroll
+        for (int m = 0; m < kChains; ++m) c[m] = zero4();
 #pragma unroll
         for (int j = 0; j < KJ; ++j)
 #pragma unroll
             for (int i = 0; i < 4; ++i) c[(4 * j + i) % kChains] = mfma4(a.v[j][i], b.v[j][i], c[(4 * j + i) % kChains]);
-    }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        sum[e] = 0.0;
+        for (int e = 0; e < 4; ++e) {
+            sum[e] = 0.0;
 #pragma unroll
-        for (int m = 0; m < kChains; ++m) sum[e] += (double)c[m][e];
-    }
-    if constexpr (KJ == 0) {
-        for (int e0 = 0; e0 < a.len; e0 += 64) {
+            for (int m = 0; m < kChains; ++m) sum[e] += (double)c[m][e];
+        }
+    } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                c[i] = zero4();
+        for (int e = 0; e < 4; ++e) sum[e] = 0.0;
+        // `M` chains at a time, all their elements requested before the first product
+        auto step = [&](auto chains, int e0) __attribute__((always_inline)) {
+            constexpr int M = decltype(chains)::value;
+            float av[M][4], bv[M][4];
+#pragma unroll
+            for (int m = 0; m < M; ++m)
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int e = e0 + 16 * i + 4 * u + lb;
-                    c[i] = mfma4(e < a.len ? to_f32(a.row[e]) : 0.f, e < a.len ? to_f32(b.row[e]) : 0.f, c[i]);
+                    const int at = min(e0 + 16 * m + 4 * u + lb, a.len - 1);
+                    av[m][u] = to_f32(a.row[at]);
+                    bv[m][u] = to_f32(b.row[at]);
                 }
-            }
+            f32x4 c[M];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sum[e] += ((double)c[0][e] + (double)c[1][e]) + ((double)c[2][e] + (double)c[3][e]);
-        }
+            for (int m = 0; m < M; ++m) c[m] = zero4();
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const bool in = e0 + 16 * m + 4 * u + lb < a.len;
+                    c[m] = mfma4(in ? av[m][u] : 0.f, in ? bv[m][u] : 0.f, c[m]);
+                }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int m = 0; m < M; ++m) sum[e] += (double)c[m][e];
+        };
+        int e0 = 0;
+        for (; e0 + 48 < a.len; e0 += 64) step(std::integral_constant<int, 4>(), e0);
+        for (; e0 < a.len; e0 += 16) step(std::integral_constant<int, 1>(), e0);
     }
 }
 
@@ -406,9 +423,9 @@ __global__ __launch_bounds__(kColThreads) void mamba_score_kernel(const T *__res
 // l is the running sum of dt A log2(e) inside the chunk, in double: it reaches several hundred, and a
 // difference of two such numbers decides weights near 1 (in fp32 they would be off by 1e-5).
 // The weights are products in double, rounded once, and the products c.b and S c sums of short chains: y is 5 to 40 %
-// nearer to 64 bits than the recurrence's and S 2 to 40 %, at 16 to 256 state entries and decays of 1 to 0.01 (with all
-// of it in single precision y was 1.0 to 2.8 times as far off).  That costs 4 to 8 % (544 tokens 13.2 -> 13.9 us, 4096
-// tokens of 128 heads 636 -> 676; rows of 256 entries, read per product, 105 -> 118).
+// nearer to 64 bits than the recurrence's and S 2 to 50 %, at 16 to 1024 state entries and decays of 1 to 0.01 (with all
+// of it in single precision y was 1.0 to 5 times as far off).  That costs 2 to 8 % (544 tokens 13.2 -> 13.9 us, 4096
+// tokens of 128 heads 636 -> 676), and up to a quarter where many heads have a few chunks each.
 constexpr int kChunk = 64;
 
 // Inclusive sum over the lanes of a wave.
@@ -441,7 +458,9 @@ __global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restr
                                                                 const float *__restrict__ A, const T *__restrict__ B,
                                                                 float *__restrict__ L, float *__restrict__ decay, int Tn,
                                                                 int H, int P, int G, int n, int nc, int nst, int pblocks) {
-    __shared__ double wt[kChunk];  // (in single precision the states were 1 to 8 % further from 64 bits than the recurrence's)
+    // weights in two parts: their product with x is rounded once (in one, the states were 1 to 8 % further from 64 bits than
+    // the recurrence's)
+    __shared__ float2 wt[kChunk];
     const int lane = threadIdx.x, lr = lane & 15, lb = lane >> 4;
     const int c = blockIdx.x % nst, h = (blockIdx.x / nst) % H, u = blockIdx.x / nst / H;
     const int p0 = (u % pblocks) * 16 * CPL, n0 = (u / pblocks) * 16 * NPL, g = h / (H / G), t0 = c * kChunk;
@@ -457,7 +476,9 @@ __global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restr
         }
     const double l = wave_scan_f64(t0 + lane < Tn ? log2_decay(dtv, A[h]) : 0.0);
     const double end = __shfl(l, kWave - 1, kWave);
-    wt[lane] = ex2_f64(end - l) * dtv;  // 0 past the last token
+    const double weight = ex2_f64(end - l) * dtv;  // 0 past the last token
+    const float most = (float)weight;
+    wt[lane] = make_float2(most, fabsf(most) < INFINITY ? (float)(weight - most) : 0.f);
     if (u == 0 && lane == 0) decay[(size_t)h * nc + c] = (float)ex2_f64(end);
     __syncthreads();
     if (t0 + kChunk > Tn) {  // uniform: the rows past the end are the last one again, which 0 does not take out if it is not finite
@@ -481,11 +502,14 @@ __global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restr
     for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const double wv = wt[16 * kb + 4 * lb + i];
+            const float2 wv = wt[16 * kb + 4 * lb + i];
 #pragma unroll
-            for (int a = 0; a < CPL; ++a)
+            for (int a = 0; a < CPL; ++a) {
+                const float rest = xv[kb][i][a] * wv.y;
+                const float wx = fmaf(xv[kb][i][a], wv.x, finite(rest) ? rest : 0.f);
 #pragma unroll
-                for (int b = 0; b < NPL; ++b) acc[a][b] = mfma4((float)(xv[kb][i][a] * wv), bv[kb][i][b], acc[a][b]);
+                for (int b = 0; b < NPL; ++b) acc[a][b] = mfma4(wx, bv[kb][i][b], acc[a][b]);
+            }
         }
 #pragma unroll
     for (int a = 0; a < CPL; ++a)
@@ -1082,16 +1106,15 @@ bool ssd_general_supported(int n) { return n >= 1 && n <= 1024; }
 constexpr size_t kRoundBytes = (size_t)256 << 20;
 // The chunked form's launches count 32-bit threads per grid: states of up to 2^28 entries (1 GB) in fewer than 2^24
 // heads.  Beyond, there are channels enough to fill the chip with the recurrence.  And it is two or three launches, of
-// 10 us for the shortest sequence (16 state entries) to 40 to 55 (1024, whose rows are read per product), where a
-// token of the recurrence takes 1.2 to 3.7: us in chunks / as a recurrence, 1 and 5 and 8 tokens: 8 heads of 32, n = 16
-// 10.5 / 5.9, 10.6 / 10.7, 10.6 / 14.5; 128 heads of 64, n = 124 23.2 / 9.9, 23.4 / 18.5, 23.5 / 24.3; n = 256 34 / 20, 35 / 47
-// (every CU has its share of the lanes there: 3 tokens 35 / 33); n = 1024, 8 heads 42 / 10, 46 / 25, 48 / 36, 12 tokens
-// 52 / 51; in bf16, where a round of 16 tokens takes 50 either way, 20 111 / 80, 40 167 / 151.
-static bool ssd_in_chunks(int T, int H, int P, int n, strd_dtype io) {
+// 10 us for the shortest sequence (16 state entries) to 32 (1024, whose rows are read per product), where a token of the
+// recurrence takes 1.2 to 3.7: us in chunks / as a recurrence, 1 and 5 and 8 tokens: 8 heads of 32, n = 16 10.7 / 5.9,
+// 10.7 / 10.7, 10.7 / 14.3; 128 heads of 64, n = 124 23.5 / 10.0, 23.7 / 18.4, 23.8 / 24.5; n = 1024, 8 heads 32 / 10, 34 / 25,
+// 37 / 37; 128 heads of 64, n = 256, where every CU has its share of the lanes, 32 / 20, 32 / 47 and at 2 tokens 32 / 27.
+static bool ssd_in_chunks(int T, int H, int P, int n) {
     if (H >= 1 << 24 || (long long)H * P > (1 << 28) / n) return false;
-    if (n > 128 && (long long)H * P * ceil_div(n, kSlice) > 1 << 16) return T > 3;
-    if (n > 512 && T < kChunk) return T * (io == STRD_F32 ? 100 : 64) > n * ceil_div(T, 16);
-    return T > (n < 32 ? 5 : n > 256 || H >= 256 ? 8 : 6);
+    if (n <= 128) return T > (n < 32 ? 5 : H < 256 ? 6 : 8);
+    if ((long long)H * P * ceil_div(n, kSlice) > 1 << 16) return T > 2;
+    return T > (n <= 256 ? 4 : n <= 512 ? 6 : 8);
 }
 struct ScanRounds {
     int chunks;  // per round
@@ -1108,9 +1131,7 @@ static ScanRounds ssd_rounds(int T, int H, int P, int n) {
     r.carry = nc > r.chunks ? align_up(state, 256) : 0;
     return r;
 }
-size_t ssd_general_ws(int T, int H, int P, int n, strd_dtype io) {
-    return ssd_in_chunks(T, H, P, n, io) ? ssd_rounds(T, H, P, n).total() : 0;
-}
+size_t ssd_general_ws(int T, int H, int P, int n) { return ssd_in_chunks(T, H, P, n) ? ssd_rounds(T, H, P, n).total() : 0; }
 
 template <typename T>
 static int ssd_launch(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D,
@@ -1181,7 +1202,7 @@ static int ssd_in_rounds(const void *x, const float *dt, const float *A, const v
 int ssd_general(const void *x, const float *dt, const float *A, const void *B, const void *C,
                 const float *D, const float *S_in, void *y, float *S_out, int T, int H, int P, int G,
                 int n, strd_dtype io, void *ws, hipStream_t st) {
-    if (T == 0 || !ws || !ssd_in_chunks(T, H, P, n, io)) {
+    if (T == 0 || !ws || !ssd_in_chunks(T, H, P, n)) {
         int lanes = 1;
         while (lanes * kSlice < n) lanes <<= 1;  // power of two <= 64, so a column never straddles a wave
         const long long threads = (long long)H * P * lanes;
