@@ -346,6 +346,9 @@ int strd_linear_mfma(const void *x, const void *w, const void *residual, void *o
 int strd_linear_library(const void *x, const void *w, const void *residual, void *out, int T, int Kd, int Nd,
                         strd_dtype io, void *stream);
 int strd_linear_mfma_supported(int T, int Kd, int Nd, strd_dtype io);
+/* How that kernel cuts the 256 x 256 tiles of its last round over the chip: 0 not at all, 1 into halves of 128
+ * tokens, 2 into quarters of 128 x 128.  Host-only. */
+int strd_linear_mfma_cut(int T, int Nd);
 int strd_rmsnorm(const void *x, const void *w, void *out, int T, int d, float eps, strd_dtype io, void *stream);
 int strd_gated_rmsnorm(const void *y, const void *z, int ldz, const void *w, void *out, int T, int D,
                        int groups, float eps, strd_dtype io, void *stream);

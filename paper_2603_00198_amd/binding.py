@@ -56,6 +56,7 @@ _SIGNATURES = {
     "strd_linear_mfma": (_int, [_vp, _vp, _vp, _vp, _int, _int, _int, _int, _vp]),
     "strd_linear_library": (_int, [_vp, _vp, _vp, _vp, _int, _int, _int, _int, _vp]),
     "strd_linear_mfma_supported": (_int, [_int, _int, _int, _int]),
+    "strd_linear_mfma_cut": (_int, [_int, _int]),
     "strd_rmsnorm": (_int, [_vp, _vp, _vp, _int, _int, _f32, _int, _vp]),
     "strd_gated_rmsnorm": (_int, [_vp, _vp, _int, _vp, _vp, _int, _int, _int, _f32, _int, _vp]),
     "strd_conv1d_silu": (_int, [_vp, _int, _vp, _vp, _vp, _vp, _vp] + [_int] * 4 + [_int, _vp]),

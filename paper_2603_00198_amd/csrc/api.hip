@@ -408,6 +408,8 @@ int strd_linear_library(const void *x, const void *w, const void *residual, void
 
 int strd_linear_mfma_supported(int T, int Kd, int Nd, strd_dtype io) { return linear_mfma_supported(T, Kd, Nd, io) ? 1 : 0; }
 
+int strd_linear_mfma_cut(int T, int Nd) { return linear_mfma_cut(T, Nd); }
+
 int strd_linear_mfma(const void *x, const void *w, const void *residual, void *out, int T, int Kd, int Nd, strd_dtype io,
                      void *stream) {
     if (T < 0 || Kd < 1 || Nd < 1 || !io_ok(io) || !w || (T > 0 && (!x || !out))) return STRD_EINVAL;

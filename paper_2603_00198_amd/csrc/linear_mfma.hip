@@ -392,6 +392,8 @@ bool linear_mfma_supported(int T, int Kd, int Nd, strd_dtype io) {
            (long long)ceil_div(T, kBT) * ceil_div(Nd, kBN) < (1LL << 30);
 }
 
+int linear_mfma_cut(int T, int Nd) { return T >= 1 && Nd >= 1 ? linear_plan(T, Nd).cut : kFull; }
+
 int linear_mfma(const void *x, const void *w, const void *residual, void *out, int T, int Kd, int Nd, hipStream_t st) {
     const size_t smem = (size_t)Shape<kBT, kBN>::kLdsBytes;  // the largest of the three
     if (!allow_dynamic_lds(reinterpret_cast<const void *>(&linear_mfma_kernel), smem)) return STRD_EHIP;

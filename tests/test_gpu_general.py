@@ -139,8 +139,12 @@ def test_scan_around_the_switch_to_segments(T):
         assert_close(f(S[hs]), S_ref, TOL[BF16], "S", units=(0,))
 
 
-# token rows x columns whose last round of 256 tiles is cut: into quarters (a whole tile; an edge row of tiles
-# with one token; an edge column; the corner), into halves, with an edge row inside a half cut; and one left whole
+WHOLE, HALVES, QUARTERS = 0, 1, 2   # strd_linear_mfma_cut
+
+
+# token rows x columns whose last round of 256 tiles is cut into quarters: one tile; an edge row of one token; a row of
+# tiles; edge row, edge column and corner; a column just over half full (not an edge); 155 tiles, left whole; 48 tiles of an
+# edge row; an edge column of 8
 @pytest.mark.parametrize("T,Nd", [(256, 256), (4097, 4096), (4096 + 256, 4096), (4096 + 100, 4096 + 64), (4096, 4096 + 136),
                                   (5 * 256, 31 * 256), (9 * 256 + 5, 56 * 256), (12 * 256, 44 * 256 + 8)])
 def test_projection_with_a_cut_last_round(T, Nd):
@@ -157,6 +161,29 @@ def test_projection_with_a_cut_last_round(T, Nd):
     ref = x.float() @ w.float() + res.float()
     err = (out[:T].float() - ref).abs()
     assert bool((err <= ref.abs() * 2.0 ** -8 + 1e-4).all()), float(err.max())
+    assert bool((out[T] == 7.0).all()), "wrote past the last row"
+
+
+@pytest.mark.parametrize("Kd", [64, 128, 192, 1088])
+@pytest.mark.parametrize("T,Nd,cut", [(1280, 4096, HALVES), (1273, 4096 - 8, HALVES), (3000, 8192, HALVES), (2176, 10368, HALVES),
+                                      (2049, 10248, HALVES), (1280 - 7, 7936 - 24, WHOLE), (4096 - 3, 4096 - 40, WHOLE),
+                                      (4096 + 100, 4096 + 64, QUARTERS), (300, 1000, QUARTERS)])
+def test_projection_by_kind_of_cut_and_depth(T, Nd, cut, Kd):
+    """Whole tiles, halves (alone, ragged, with an edge row and an edge column of tiles) and quarters; two, four and six
+    stages of the copy ring, and many.  Every element against 64 bits: half a bf16 step of the result (and of the sum
+    without the residual) and Kd roundings of 2^-24 of the sum of magnitudes, 0.64 Kd."""
+    _say("projection T=%d Nd=%d Kd=%d cut=%d" % (T, Nd, Kd, cut))
+    assert strd.lib().strd_linear_mfma_cut(T, Nd) == cut
+    g = torch.Generator(device=DEV).manual_seed(T + Nd + Kd)
+    x = torch.randn(T, Kd, generator=g, device=DEV).to(BF16)
+    w = torch.randn(Kd, Nd, generator=g, device=DEV).to(BF16)
+    res = torch.randn(T, Nd, generator=g, device=DEV).to(BF16)
+    out = torch.full((T + 1, Nd), 7.0, device=DEV, dtype=BF16)
+    out[:T] = res
+    strd.linear_mfma(x, w, residual=out[:T], out=out[:T])
+    ref = x.double() @ w.double() + res.double()
+    err = (out[:T].double() - ref).abs() - (ref.abs() * 2.0 ** -8 + Kd * 2.0 ** -24 * Kd)
+    assert bool((err <= 0).all()), float(err.max())
     assert bool((out[T] == 7.0).all()), "wrote past the last row"
 
 
