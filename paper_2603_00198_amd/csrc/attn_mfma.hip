@@ -62,7 +62,7 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// G groups of NW computing waves, and NC copy waves (G = 1); NC = 0: the computing waves request the copies of
+// G groups of NW computing waves, and NC copy waves that serve all groups; NC = 0: the computing waves request the copies of
 // their group themselves.  Group g takes chunks g, g + G, ...
 template <int D, int NW, int NC, int KC, int G>
 __global__ __launch_bounds__((G * NW + NC) * kWave) __attribute__((amdgpu_waves_per_eu(2, NC ? 3 : 2))) void attn_mfma_kernel(

@@ -2,7 +2,7 @@
 // and state size.  They serve fp32 I/O (whose 1e-4 tolerance rules out bf16 matrix cores) and the
 // shapes the bf16 kernels of the *_mfma.hip files are not tiled for.
 //
-// Every contraction runs on v_mfma_f32_16x16x4_f32: fp32 products and sums, so nothing is lost
+// Every contraction (but those of a few tokens: the recurrence, and attention row by row) runs on v_mfma_f32_16x16x4_f32: fp32 products and sums, so nothing is lost
 // against vector arithmetic, while a wave owns a 16 x 16 tile and reads each operand row once per
 // tile instead of once per element.  An operand lane (row r = lane % 16, lane group lb = lane / 16)
 // holds the four elements 16 j + 4 lb .. + 3 of its row as one 16-byte load and feeds them to four
