@@ -63,6 +63,9 @@ struct AsyncTile {
     static constexpr int kSlots = ROWS * kVP;
     static constexpr int kIssues = (kSlots + 64 * NW - 1) / (64 * NW);  // instructions per wave
     static constexpr int kBytes = kSlots * 16;
+    // Instructions that wave `wave` really issues: one whose slots all lie past the tile is branched around, so a wait
+    // that counts outstanding copies has to count these.
+    static constexpr int issued(int wave) { return (kSlots - 64 * wave + 64 * NW - 1) / (64 * NW); }
 
     // Row and vector of the slot this lane fills with its i-th instruction.
     __device__ static __forceinline__ void slot(int wave, int lane, int i, int &row, int &cv) {

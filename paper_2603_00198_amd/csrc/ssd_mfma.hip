@@ -549,10 +549,10 @@ __device__ __forceinline__ void copy_wave(Lds<NS> &lds, const bf16_t *__restrict
         }
         ++next_bc;
     };
-    // Copies issued per step; everything older has landed once at most that many are outstanding
-    // (vector-memory operations complete in order).  s_waitcnt immediate, gfx9 layout:
+    // Copies this wave issues per step (n = 64: 8, 6 and 6 of the 4 rounds); everything older has landed once at most
+    // that many are outstanding (vector-memory operations complete in order).  s_waitcnt immediate, gfx9 layout:
     // vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] << 14
-    constexpr int kNewest = 2 * BC::kIssues;
+    constexpr int kNewest = 2 * BC::issued(CW);
     static_assert(kNewest < 64, "vmcnt has 6 bits");
     constexpr int kWaitOlder = (kNewest & 15) | (7 << 4) | (15 << 8) | ((kNewest >> 4) << 14);
 

@@ -691,3 +691,26 @@ def test_invalid_arguments_are_refused_without_launching():
     with pytest.raises(strd.StrdError):
         strd.score_attn(q, k)          # 3 query heads over 2 kv heads
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("T,H,P,G", [(3000, 72, 64, 8), (1500, 48, 96, 4)])
+def test_whole_sequence_scan_of_64_state_entries_gives_the_same_bits_every_time(T, H, P, G):
+    """Beside copies that keep the memory busy, so that a tile read before it has landed shows."""
+    _say("ssd_prefill repeated T=%d H=%d P=%d G=%d n=64" % (T, H, P, G))
+    g = torch.Generator().manual_seed(T)
+    x, B, C = (torch.randn(T, *s, generator=g).to(torch.bfloat16).to(DEV) for s in ((H, P), (G, 64), (G, 64)))
+    dt = torch.nn.functional.softplus(torch.randn(T, H, generator=g)).to(DEV)
+    A = (-torch.exp(2 * torch.rand(H, generator=g))).to(DEV)
+    f = synth.np64
+    y, S = strd.ssd_prefill(x, dt, A, B, C)
+    h, hg = H // 2, H // 2 // (H // G)
+    y_ref, S_ref = oracle.ssd_seq(f(x[:, h:h + 1]), f(dt[:, h:h + 1]), f(A[h:h + 1]), f(B[:, hg:hg + 1]), f(C[:, hg:hg + 1]))
+    assert_close(f(y[:, h:h + 1]), y_ref, TOL[torch.bfloat16], "y", units=(1,))
+    busy, other = torch.zeros(1 << 27, dtype=torch.uint8, device=DEV), torch.cuda.Stream()
+    other.wait_stream(torch.cuda.current_stream())
+    for _ in range(40):
+        with torch.cuda.stream(other):
+            busy.add_(1)
+        y2, S2 = strd.ssd_prefill(x, dt, A, B, C)
+        assert torch.equal(y2, y) and torch.equal(S2, S)
+    torch.cuda.synchronize()

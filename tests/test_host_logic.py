@@ -352,3 +352,21 @@ def test_sizes_the_general_kernels_take():
     assert scan(1 << 20, 1025, 16, at) == scan(1 << 20, 1025, 16, None) == scan(1 << 16, 257, 1024, at) == -2
     ws = lambda H, P, n: L.strd_ssd_prefill_workspace(1000, H, P, 1, n, 256, F32)
     assert ws(4096, 64, 1024) > 0 and ws(4097, 64, 1024) == 0 and ws((1 << 24) - 1, 1, 1) > 0 and ws(1 << 24, 1, 1) == 0
+
+
+def test_copies_that_a_wave_issues_are_counted_wave_by_wave(tmp_path):
+    """A tile of 64 rows of 64 bf16 (two pad vectors) is 640 slots: of the four rounds that three copy waves share, the last
+    has slots for one of them.  A wait for older copies that counts four per wave would leave two in flight."""
+    import subprocess
+    from paper_2603_00198_amd import build as strd_build
+    rounds = {(64, 8, 3, 2): (4, 3, 3), (64, 16, 3, 2): (6, 6, 6), (64, 4, 1, 1): (5,), (128, 16, 4, 2): (9, 9, 9, 9)}
+    src = tmp_path / "issued.hip"
+    src.write_text('#include "common.h"\n' + "".join(
+        "static_assert(strd::AsyncTile<%d, %d, %d, %d, true>::issued(%d) == %d, \"\");\n" % (r, v, w, p, i, n)
+        for (r, v, w, p), per in rounds.items() for i, n in enumerate(per)))
+    for (r, v, w, p), per in rounds.items():   # the slots of wave i's last round start inside the tile
+        for i, n in enumerate(per):
+            assert ((n - 1) * w + i) * 64 < r * (v + p) <= (n * w + i) * 64
+    cmd = [strd_build.HIPCC] + strd_build.FLAGS + ["--cuda-host-only", "-fsyntax-only", str(src)]
+    run = subprocess.run(cmd, capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr[-2000:]
