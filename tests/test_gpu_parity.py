@@ -714,3 +714,66 @@ def test_whole_sequence_scan_of_64_state_entries_gives_the_same_bits_every_time(
         y2, S2 = strd.ssd_prefill(x, dt, A, B, C)
         assert torch.equal(y2, y) and torch.equal(S2, S)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("case", ["fast", "slow head", "four steps", "five steps", "no decay", "alternating"])
+@pytest.mark.parametrize("T,H,G,n", [(64 * 13 + 1, 64, 4, 128), (64 * 20, 128, 8, 64), (64 * 21 - 63, 128, 8, 128), (64 * 31 - 1, 80, 4, 128)])
+def test_ssd_prefill_pairs_of_heads_in_segments(T, H, G, n, case):
+    """Sequences of middle length: segments that start a few steps early where the decays of a pair of heads allow it (four
+    steps at most), one walk over the sequence where they do not; dense with D and a carried-in state, and through an
+    index list."""
+    _say("ssd_prefill pairs T=%d H=%d G=%d n=%d %s" % (T, H, G, n, case))
+    P, M = 64, 21
+    K = T - M
+    N = K + K // 2 + 3
+    rows = N + M
+    g = torch.Generator().manual_seed(T + n)
+    x = torch.randn(rows, H, P, generator=g).to(torch.bfloat16)
+    B = (torch.randn(rows, G, n, generator=g) / n ** 0.5).to(torch.bfloat16)
+    C = torch.randn(rows, G, n, generator=g).to(torch.bfloat16)
+    dt = torch.nn.functional.softplus(torch.randn(rows, H, generator=g))
+    A = -torch.exp(2 * torch.rand(H, generator=g))
+    watch = [0, 1, H // 2, H - 1]
+    if case == "slow head":
+        A[[1, H - 2]] = -0.01
+    elif case in ("four steps", "five steps"):   # 126 / 1.4427 / 64 = 1.365 of decay per token for one step
+        dt[:] = 1.0
+        A[:] = -1.365 / (3.5 if case == "four steps" else 4.5)
+    elif case == "no decay":
+        A[:] = 0.0
+    elif case == "alternating":                  # short and long memory inside one head
+        dt = torch.where((torch.arange(rows) // 150 % 2 == 0)[:, None], dt, dt * 1e-3)
+    D, S_in = torch.randn(H, generator=g), torch.randn(H, P, n, generator=g)
+    idx = torch.sort(torch.randperm(N, generator=g)[:K]).values.to(torch.int32)
+    keep = torch.cat([idx.long(), torch.arange(N, rows)])
+    f, dev = synth.np64, lambda t: t.to(DEV)
+    xk, dtk, Bk, Ck = (dev(t[keep].contiguous()) for t in (x, dt, B, C))
+    y, S = strd.ssd_prefill(xk, dtk, dev(A), Bk, Ck, D=dev(D), S_in=dev(S_in))
+    y_g, S_g = strd.ssd_prefill_gather(dev(x), dev(dt), dev(A), dev(B), dev(C), dev(idx), N, M, D=dev(D), S_in=dev(S_in))
+    assert torch.equal(y_g, y) and torch.equal(S_g, S), "the gathering scan must give the bits of compact + scan"
+    y2, none = strd.ssd_prefill(xk, dtk, dev(A), Bk, Ck, D=dev(D), S_in=dev(S_in), want_state=False)
+    assert none is None and torch.equal(y2, y)
+    for h in watch:
+        q = h // (H // G)
+        y_ref, S_ref = oracle.ssd_seq(f(x[keep, h:h + 1]), f(dt[keep, h:h + 1]), f(A[h:h + 1]), f(B[keep, q:q + 1]),
+                                      f(C[keep, q:q + 1]), f(D[h:h + 1]), f(S_in[h:h + 1]))
+        assert_close(f(y[:, h:h + 1]), y_ref, TOL[torch.bfloat16], "y of head %d" % h, units=(1,))
+        assert_close(f(S[h:h + 1]), S_ref, TOL[torch.bfloat16], "state of head %d" % h, units=(0,))
+
+
+def test_ssd_prefill_pairs_of_heads_values_that_are_not_finite():
+    """An infinite x stays infinite in its own output and reaches no step before its own, no other channel and no other head."""
+    T, H, P, G, n = 64 * 24, 128, 64, 8, 128
+    g = torch.Generator().manual_seed(5)
+    x, B, C = (torch.rand(T, *s, generator=g).add_(0.5).to(torch.bfloat16).to(DEV) for s in ((H, P), (G, n), (G, n)))
+    dt = torch.nn.functional.softplus(torch.randn(T, H, generator=g)).to(DEV)
+    A = (-torch.exp(2 * torch.rand(H, generator=g))).to(DEV)
+    y, _ = strd.ssd_prefill(x, dt, A, B, C)
+    x2 = x.clone()
+    t, h = 700, 37
+    x2[t, h, 3] = float("inf")
+    y2, _ = strd.ssd_prefill(x2, dt, A, B, C)
+    assert y2[t, h, 3] == float("inf")
+    same = torch.ones(T, H, P, dtype=torch.bool, device=DEV)
+    same[t // 64 * 64:, h, 3] = False     # a step's products take its later tokens with weight 0
+    assert torch.equal(y2[same], y[same])
