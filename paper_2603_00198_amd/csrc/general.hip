@@ -452,18 +452,14 @@ __device__ __forceinline__ double ex2_f64(double v) {
     return (double)ldexpf(ex2((float)(v - whole)), (int)whole);
 }
 
-// One wave per (head, chunk, block of 16 CPL channels x 16 NPL state columns).
+// What chunk c of head h adds to a block of 16 CPL channels x 16 NPL state columns, by one wave, into L[P][n], and (where
+// `decay` is given) the chunk's total decay.  The weights go through LDS (`wt`, 64 entries) in two parts: their product with x is
+// rounded once (in one, the states were 1 to 8 % further from 64 bits than the recurrence's).
 template <typename T, int CPL, int NPL, bool FULL>
-__global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restrict__ x, const float *__restrict__ dt,
-                                                                const float *__restrict__ A, const T *__restrict__ B,
-                                                                float *__restrict__ L, float *__restrict__ decay, int Tn,
-                                                                int H, int P, int G, int n, int nc, int nst, int pblocks) {
-    // weights in two parts: their product with x is rounded once (in one, the states were 1 to 8 % further from 64 bits than
-    // the recurrence's)
-    __shared__ float2 wt[kChunk];
-    const int lane = threadIdx.x, lr = lane & 15, lb = lane >> 4;
-    const int c = blockIdx.x % nst, h = (blockIdx.x / nst) % H, u = blockIdx.x / nst / H;
-    const int p0 = (u % pblocks) * 16 * CPL, n0 = (u / pblocks) * 16 * NPL, g = h / (H / G), t0 = c * kChunk;
+__device__ __forceinline__ void chunk_state(const T *__restrict__ x, const float *__restrict__ dt, const float *__restrict__ A,
+                                            const T *__restrict__ B, float *L, float *decay, float2 *wt, int Tn, int H, int P, int G,
+                                            int n, int h, int c, int p0, int n0) {
+    const int lane = threadIdx.x & 63, lr = lane & 15, lb = lane >> 4, g = h / (H / G), t0 = c * kChunk;
     const float dtv = t0 + lane < Tn ? dt[(size_t)(t0 + lane) * H + h] : 0.f;
     float xv[4][4][CPL], bv[4][4][NPL];
 #pragma unroll
@@ -479,8 +475,8 @@ __global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restr
     const double weight = ex2_f64(end - l) * dtv;  // 0 past the last token
     const float most = (float)weight;
     wt[lane] = make_float2(most, fabsf(most) < INFINITY ? (float)(weight - most) : 0.f);
-    if (u == 0 && lane == 0) decay[(size_t)h * nc + c] = (float)ex2_f64(end);
-    __syncthreads();
+    if (decay && lane == 0) *decay = (float)ex2_f64(end);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (LDS operations of a wave keep their order)
     if (t0 + kChunk > Tn) {  // uniform: the rows past the end are the last one again, which 0 does not take out if it is not finite
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
@@ -519,8 +515,20 @@ __global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restr
             float v[NPL];
 #pragma unroll
             for (int b = 0; b < NPL; ++b) v[b] = acc[a][b][i];
-            if (p < P) store_row<NPL>(L + (((size_t)h * nc + c) * P + p) * n, n0 + NPL * lr, n, v);
+            if (p < P) store_row<NPL>(L + p * n, n0 + NPL * lr, n, v);
         }
+}
+
+// One wave per (head, chunk, block of 16 CPL channels x 16 NPL state columns).
+template <typename T, int CPL, int NPL, bool FULL>
+__global__ __launch_bounds__(kWave) void ssd_chunk_state_kernel(const T *__restrict__ x, const float *__restrict__ dt,
+                                                                const float *__restrict__ A, const T *__restrict__ B,
+                                                                float *__restrict__ L, float *__restrict__ decay, int Tn,
+                                                                int H, int P, int G, int n, int nc, int nst, int pblocks) {
+    __shared__ float2 wt[kChunk];
+    const int c = blockIdx.x % nst, h = (blockIdx.x / nst) % H, u = blockIdx.x / nst / H;
+    chunk_state<T, CPL, NPL, FULL>(x, dt, A, B, L + ((size_t)h * nc + c) * P * n, u == 0 ? decay + (size_t)h * nc + c : nullptr, wt,
+                                   Tn, H, P, G, n, h, c, u % pblocks * 16 * CPL, u / pblocks * 16 * NPL);
 }
 
 __global__ __launch_bounds__(kWave) void ssd_pass_kernel(float *__restrict__ L, const float *__restrict__ decay,
@@ -551,36 +559,33 @@ __global__ __launch_bounds__(kWave) void ssd_pass_kernel(float *__restrict__ L, 
     if (S_out) S_out[e] = run;
 }
 
-// One workgroup per (head, chunk); wave w owns tokens 16 w .. 16 w + 15 of the chunk as accumulator
+// Outputs of the 64 tokens of chunk c of head h, by four waves: wave w owns tokens 16 w .. 16 w + 15 of the chunk as accumulator
 // columns: weights W[s, t] = 2^(l_t - l_s) dt_s (c_t.b_s) for s <= t from the products b.c, then
-// y^T[p, t] = sum_s x[s, p] W[s, t], a block of 16 CPL channels at a time.
-template <typename T, int CPL, int KN, bool FULL>
-__global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict__ x, const float *__restrict__ dt,
-                                                            const float *__restrict__ A, const T *__restrict__ B,
-                                                            const T *__restrict__ C, const float *__restrict__ D,
-                                                            const float *__restrict__ S, T *__restrict__ y, int Tn, int H,
-                                                            int P, int G, int n, int nc, int first_carried) {
-    __shared__ double ls[kChunk];
-    __shared__ float dts[kChunk];
-    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lb = lane >> 4, w = wave_index();
-    const int h = blockIdx.x % H, c = blockIdx.x / H, g = h / (H / G), t0 = c * kChunk;
+// y^T[p, t] = sum_s x[s, p] W[s, t], a block of 16 CPL channels at a time.  `S`: the state before the chunk, [P][n] (`carried`:
+// there is one), read with the first operands (EARLY) or after `publish`, which meets the other waves and makes the decays (ls: running
+// sums, dts: dt) and the state theirs.
+template <typename T, int CPL, int KN, bool FULL, bool EARLY, typename Publish>
+__device__ __forceinline__ void chunk_out(const T *__restrict__ x, const T *__restrict__ B, const T *__restrict__ C,
+                                          const float *__restrict__ D, const float *S, T *__restrict__ y, int Tn, int H, int P, int G,
+                                          int n, int h, int c, int w, bool carried, const double *ls, const float *dts,
+                                          Publish publish) {
+    const int lane = threadIdx.x & 63, lr = lane & 15, lb = lane >> 4, g = h / (H / G), t0 = c * kChunk;
     const int tl = 16 * w + lr, t = t0 + tl;  // this lane's token (a column)
     Operand<T, KN, FULL> cf, bf[4];
     cf.load(C + ((size_t)min(t, Tn - 1) * G + g) * n, lb, n);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
         if (j <= w) bf[j].load(B + ((size_t)min(t0 + 16 * j + lr, Tn - 1) * G + g) * n, lb, n);
-    const bool carried = c >= first_carried;
     // x and, where they are short enough for the registers, the state rows of a channel block: those of the
     // first block are on their way while the decays are scanned, those of the next while a block is summed
     float xv[4][4][CPL];
     Operand<float, KN, FULL> sf[CPL];
-    constexpr bool kEarlyState = CPL * KN <= 16;
+    constexpr bool kEarlyState = EARLY && CPL * KN <= 16;
     auto load_state = [&](int p0) {
         if (carried)
 #pragma unroll
             for (int a = 0; a < CPL; ++a)
-                sf[a].load(S + (((size_t)h * nc + c) * P + min(p0 + CPL * lr + a, P - 1)) * n, lb, n);
+                sf[a].load(S + min(p0 + CPL * lr + a, P - 1) * n, lb, n);
     };
     auto load_block = [&](int p0) {
         if (kEarlyState) load_state(p0);
@@ -592,13 +597,8 @@ __global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict_
                     load_row<CPL, FULL>(x + ((size_t)min(t0 + 16 * j + 4 * lb + i, Tn - 1) * H + h) * P, p0 + CPL * lr, P, xv[j][i]);
     };
     load_block(0);
-    if (w == 0) {
-        const float dtv = t0 + lane < Tn ? dt[(size_t)(t0 + lane) * H + h] : 0.f;
-        ls[lane] = wave_scan_f64(t0 + lane < Tn ? log2_decay(dtv, A[h]) : 0.0);
-        dts[lane] = dtv;
-    }
-    __syncthreads();
-    if (t0 + 16 * w >= Tn) return;  // uniform per wave, after the only barrier
+    publish();
+    if (t0 + 16 * w >= Tn) return;  // uniform per wave, after the last barrier
     const double lt = ls[tl];
     const float et = ex2((float)lt);
     f32x4 W[4];
@@ -692,6 +692,75 @@ __global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict_
                 store_row<CPL>(y + ((size_t)t * H + h) * P, p0 + CPL * (4 * lb + i), P, v);
             }
     }
+}
+
+// l and dt of a chunk's tokens, by one wave.
+__device__ __forceinline__ void chunk_decays(const float *__restrict__ dt, const float *__restrict__ A, int Tn, int H, int h, int t0,
+                                             double *ls, float *dts) {
+    const int lane = threadIdx.x & 63;
+    const float dtv = t0 + lane < Tn ? dt[(size_t)(t0 + lane) * H + h] : 0.f;
+    ls[lane] = wave_scan_f64(t0 + lane < Tn ? log2_decay(dtv, A[h]) : 0.0);
+    dts[lane] = dtv;
+}
+
+// One workgroup per (head, chunk).
+template <typename T, int CPL, int KN, bool FULL>
+__global__ __launch_bounds__(256) void ssd_chunk_out_kernel(const T *__restrict__ x, const float *__restrict__ dt,
+                                                            const float *__restrict__ A, const T *__restrict__ B,
+                                                            const T *__restrict__ C, const float *__restrict__ D,
+                                                            const float *__restrict__ S, T *__restrict__ y, int Tn, int H,
+                                                            int P, int G, int n, int nc, int first_carried) {
+    __shared__ double ls[kChunk];
+    __shared__ float dts[kChunk];
+    const int w = wave_index(), h = blockIdx.x % H, c = blockIdx.x / H;
+    chunk_out<T, CPL, KN, FULL, true>(x, B, C, D, S + ((size_t)h * nc + c) * P * n, y, Tn, H, P, G, n, h, c, w, c >= first_carried, ls, dts, [&] {
+        if (w == 0) chunk_decays(dt, A, Tn, H, h, c * kChunk, ls, dts);
+        __syncthreads();
+    });
+}
+
+// All three in one launch, for a few chunks of small states: a workgroup per (head, chunk) works out what every chunk before its own
+// adds to the state (8 waves, a chunk each at a time), folds them up in the order of the pass, and has its four other waves' outputs.  The
+// states of the chunks are made over and over, but none of it waits for another launch.
+constexpr int kOnceChunks = 17;  // at most
+constexpr int kOnceStateWaves = 8, kOnceThreads = (4 + kOnceStateWaves) * kWave;
+
+template <typename T, int CPL, int KN, bool FULL>
+__global__ __launch_bounds__(kOnceThreads) void ssd_once_kernel(const T *__restrict__ x, const float *__restrict__ dt,
+                                                                const float *__restrict__ A, const T *__restrict__ B,
+                                                                const T *__restrict__ C, const float *__restrict__ D,
+                                                                const float *__restrict__ S_in, T *__restrict__ y,
+                                                                float *__restrict__ S_out, int Tn, int H, int P, int G, int n, int nc) {
+    extern __shared__ __attribute__((aligned(16))) float added[];  // [chunk][P][n]; chunk 0's place then holds the state before c
+    __shared__ double ls[kChunk];
+    __shared__ float dts[kChunk], decay[kOnceChunks];
+    __shared__ float2 wt[kOnceStateWaves][kChunk];
+    const int w = wave_index(), h = blockIdx.x % H, c = nc - 1 - (int)(blockIdx.x / H), pn = P * n;  // longest first
+    const int want = c == nc - 1 && S_out ? c + 1 : c;  // chunks whose contribution is needed
+    auto fold = [&] {
+        __syncthreads();
+        for (int e = threadIdx.x; e < pn; e += kOnceThreads) {
+            float run = S_in ? S_in[(size_t)h * pn + e] : 0.f;
+            for (int j = 0; j < c; ++j) run = fmaf(run, decay[j], added[j * pn + e]);
+            if (want > c) S_out[(size_t)h * pn + e] = fmaf(run, decay[c], added[c * pn + e]);
+            added[e] = run;
+        }
+        __syncthreads();
+    };
+    if (w >= 4) {
+        const int v = w - 4, pblocks = (P + 16 * CPL - 1) / (16 * CPL), units = pblocks * ((n + 15) / 16);
+        for (int u = v; u < want * units; u += kOnceStateWaves) {
+            const int j = u / units, b = u % units;
+            chunk_state<T, CPL, 1, FULL>(x, dt, A, B, added + j * pn, b == 0 ? &decay[j] : nullptr, wt[v], Tn, H, P, G, n, h, j,
+                                         b % pblocks * 16 * CPL, b / pblocks * 16);
+        }
+        fold();
+        return;
+    }
+    chunk_out<T, CPL, KN, FULL, false>(x, B, C, D, added, y, Tn, H, P, G, n, h, c, w, S_in || c > 0, ls, dts, [&] {
+        if (w == 0) chunk_decays(dt, A, Tn, H, h, c * kChunk, ls, dts);
+        fold();
+    });
 }
 
 // The recurrence itself, for a few tokens, very large states and callers that bring no workspace: a state column (h, p) is held by
@@ -1133,6 +1202,15 @@ static ScanRounds ssd_rounds(int T, int H, int P, int n) {
 }
 size_t ssd_general_ws(int T, int H, int P, int n) { return ssd_in_chunks(T, H, P, n) ? ssd_rounds(T, H, P, n).total() : 0; }
 
+// Few chunks of small states go in one launch: while no state wave has more than two chunk states to make, and all workgroups
+// together not many more than the chip has waves for.  us, three launches -> one (fp32, 16 state entries): 8 heads of 32, 65 tokens
+// 11.9 -> 6.8, 544 13.5 -> 10.1, 800 13.8 -> 12.4 (1088 14.4 either way, 1600 15.3 / 18.3); 32 heads, 544 tokens 14.5 -> 13.2 (800
+// 16.3 / 17.8); 64 heads of 64, 200 tokens 16.3 -> 10.8 (544 23.7 / 30.0); 256 of 32, 128 tokens 15.5 -> 14.1 (200 20.7 / 27.6).
+static bool ssd_at_once(int nc, int nst, int H, int P, int n) {
+    const long long states = (long long)nst * ceil_div(P, 32);  // blocks of 32 channels x 16 state entries, 2 KB of LDS each
+    return n <= 16 && nc <= kOnceChunks && states <= 2 * kOnceStateWaves && states * nc * H <= 3000;
+}
+
 template <typename T>
 static int ssd_launch(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D,
                       const float *S_in, void *y, float *S_out, int Tn, int H, int P, int G, int n, float *L, float *decay,
@@ -1140,6 +1218,16 @@ static int ssd_launch(const void *x, const float *dt, const float *A, const void
     const int nc = ceil_div(Tn, kChunk), nst = S_out ? nc : nc - 1;  // chunks whose contribution to the state is needed
     const bool vec = vec4<T>(P, (const T *)x, (const T *)y) && vec4<T>(n, (const T *)B, (const T *)C);
     const int cpl = !vec ? 1 : P > 32 ? 4 : 2, npl = vec && n >= 64 ? 4 : 1;
+    if (vec && ssd_at_once(nc, nst, H, P, n)) {
+        const size_t lds = (size_t)std::max(nst, 1) * P * n * sizeof(float);
+#define STRD_SSD_ONCE(FF)                                                                                                    \
+    ssd_once_kernel<T, 2, 1, FF><<<(unsigned)(nc * H), kOnceThreads, lds, st>>>((const T *)x, dt, A, (const T *)B, (const T *)C, D, \
+                                                                               S_in, (T *)y, S_out, Tn, H, P, G, n, nc)
+        if (P % 32 == 0 && n == 16) STRD_SSD_ONCE(true);
+        else STRD_SSD_ONCE(false);
+#undef STRD_SSD_ONCE
+        return launch_status();
+    }
     const int pblocks = ceil_div(P, 16 * cpl), nblocks = ceil_div(n, 16 * npl);
     const long long grid1 = (long long)nst * H * pblocks * nblocks, total = (long long)H * P * n, grid3 = (long long)nc * H;
     const long long grid2 = (total + kWave - 1) / kWave;

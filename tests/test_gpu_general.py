@@ -559,3 +559,29 @@ def test_compaction_takes_tensors_of_any_number_of_dimensions():
     outs = [torch.empty(4, *a.shape[1:], device=DEV), torch.zeros(3, device=DEV)]
     got, _ = strd.compact_batch([a], idx, 6, 2, outs=outs)
     assert len(got) == 2 and got[0] is outs[0] and got[1] is outs[1] and torch.equal(got[0], a[keep])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,H,P,G,n", [(9, 8, 32, 1, 16), (64 * 16, 8, 32, 1, 16), (64 * 16 + 1, 8, 32, 1, 16), (64 * 9 - 5, 32, 32, 4, 16),
+                                       (64 * 8, 8, 64, 2, 16), (130, 6, 20, 3, 4), (64 * 5 + 3, 3, 40, 1, 12)])
+@pytest.mark.parametrize("carry", [False, True])
+def test_scan_of_a_few_chunks_in_one_launch(T, H, P, G, n, carry, dtype):
+    """The same bits as the first tokens of a scan too long for one launch (outputs depend on earlier tokens alone), the state
+    against the oracle; with and without a state output."""
+    long = 64 * 40
+    g = torch.Generator().manual_seed(T + H)
+    x, B, C = (torch.randn(long, *s, generator=g).to(dtype).to(DEV) for s in ((H, P), (G, n), (G, n)))
+    dt = torch.nn.functional.softplus(torch.randn(long, H, generator=g)).to(DEV)
+    A = (-0.3 * torch.exp(2 * torch.rand(H, generator=g))).to(DEV)
+    D, S_in = (torch.randn(H, generator=g).to(DEV), torch.randn(H, P, n, generator=g).to(DEV)) if carry else (None, None)
+    y_long, _ = strd.ssd_prefill(x, dt, A, B, C, D=D, S_in=S_in)
+    short = [t[:T].contiguous() for t in (x, dt, B, C)]
+    y, S = strd.ssd_prefill(short[0], short[1], A, short[2], short[3], D=D, S_in=S_in)
+    assert torch.equal(y, y_long[:T])
+    y2, none = strd.ssd_prefill(short[0], short[1], A, short[2], short[3], D=D, S_in=S_in, want_state=False)
+    assert none is None and torch.equal(y2, y)
+    f = synth.np64
+    opt = lambda t: None if t is None else f(t)
+    y_ref, S_ref = oracle.ssd_seq(f(short[0]), f(short[1]), f(A), f(short[2]), f(short[3]), opt(D), opt(S_in))
+    assert_close(f(y), y_ref, TOL[dtype], "y", units=(1,))
+    assert_close(f(S), S_ref, TOL[torch.float32], "state", units=(0,))
