@@ -14,6 +14,8 @@
 // query rows of its kv head through LDS and accumulates 2^(z-lse) per (lane, key) over all
 // query tiles before a single butterfly reduction over the 32 lanes.  All reductions run in a
 // fixed order: the scores are bit-reproducible.
+#include <algorithm>
+
 #include "common.h"
 
 namespace strd {
@@ -28,7 +30,6 @@ constexpr int kTW = 2;      // 32-wide register tiles per wave (queries in pass 
 constexpr int kNarrowBlocks = 128;  // see make_plan
 constexpr long long kFusedStats = 4096;
 constexpr int kFusedSlices = 48;
-constexpr int kFuseSlices = 8;  // slices whose statistics a thread has in flight
 constexpr float kLog2e = 1.4426950408889634f;
 
 template <int D>
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     int row[kTW];
 #pragma unroll
     for (int qt = 0; qt < kTW; ++qt) {
-        row[qt] = rb * (4 * 32 * kTW) + w * (32 * kTW) + 32 * qt + lc;
+        row[qt] = rb * (4 * 32 * kTW) + 32 * (4 * qt + w) + lc;  // tiles dealt in turn: all four SIMDs have their share of few rows
         const bf16_t *qp = q + qrow_index(min(row[qt], R - 1), rep, Hq, kvh) * D;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) bq[qt][ks] = *reinterpret_cast<const bf16x8 *>(qp + 16 * ks + 8 * half);
@@ -116,13 +117,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     float run_m[kTW], run_s[kTW];
 #pragma unroll
     for (int qt = 0; qt < kTW; ++qt) { run_m[qt] = -INFINITY; run_s[qt] = 0.f; }
+    // Tiles of this wave that hold a row at all: the others are no work (uniform).  (With that, no copy of a next chunk where there is
+    // none, and the log-sum-exps at once in pass 2: 131072 keys, 16 text rows 141 -> 105 us; 32768, 20 55 -> 44; 2304, 37 19.0 -> 16.2;
+    // 12 clips of 1500, 48 45 -> 40; 40 of 600, 30 60 -> 51.)
+    const int ntile = min(2, max(0, (R - rb * (4 * 32 * kTW) - 32 * w + 127) / 128));
 
     stage(0, 0);
     async_tile_wait();
     __syncthreads();
     for (int chunk = 0; chunk < nchunk; ++chunk) {
         const int cur = chunk & 1;
-        stage(min(chunk + 1, nchunk - 1), cur ^ 1);
+        if (chunk + 1 < nchunk) stage(chunk + 1, cur ^ 1);
         const int kbase = key0 + chunk * kRows;
         // Units of work: (key tile kt, query tile qt): 8 products, then the online (max, sum) update
         // with 16 exponentials.  In a full chunk the products of the next unit are issued with the
@@ -163,7 +168,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         };
         static_assert(kTW == 2, "two query tiles per wave");
         bf16x8 kf[KS];
-        if (kbase + kRows <= key1) {  // uniform: every key of the chunk belongs to the slice -- one straight block
+        if (ntile == 0) {  // (all branches on it are uniform)
+        } else if (ntile == 1 && kbase + kRows <= key1) {  // the products of the next key tile under the exponentials of this one
+            load_k(0, kf);
+            f32x16 acc0 = products(0, kf), acc1;
+#pragma unroll
+            for (int kt = 0; kt < kRows / 32; ++kt) {
+                if (kt + 1 < kRows / 32) {
+                    load_k(kt + 1, kf);
+                    acc1 = products(0, kf);
+                }
+                fold(0, acc0);
+                if (kt + 1 < kRows / 32) interleave();
+                acc0 = acc1;
+            }
+        } else if (kbase + kRows <= key1) {  // uniform: every key of the chunk belongs to the slice -- one straight block
             load_k(0, kf);
             f32x16 acc0 = products(0, kf), acc1;
 #pragma unroll
@@ -179,7 +198,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         } else {
             for (int kt = 0; kbase + 32 * kt < key1; ++kt) {  // ragged last chunk: tile by tile, keys past the slice masked
                 load_k(kt, kf);
-                f32x16 acc[kTW] = {products(0, kf), products(1, kf)};
+                f32x16 acc[kTW] = {products(0, kf), ntile > 1 ? products(1, kf) : zero16()};
                 if (kbase + 32 * kt + 32 > key1) {
 #pragma unroll
                     for (int qt = 0; qt < kTW; ++qt)
@@ -188,7 +207,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                             if (kbase + 32 * kt + 8 * (i / 4) + 4 * half + (i % 4) >= key1) acc[qt][i] = -INFINITY;
                 }
                 fold(0, acc[0]);
-                fold(1, acc[1]);
+                if (ntile > 1) fold(1, acc[1]);
             }
         }
         async_tile_wait();
@@ -245,20 +264,21 @@ __global__ __launch_bounds__(kThreads) void attn_lse_kernel(const float2 *__rest
     }
 }
 
-// The same for one row, in one thread; the pairs of its slices are `step` apart.
+// The same for one row, in one thread, `FLIGHT` slices in flight; the pairs of its slices are `step` apart.
+template <int FLIGHT>
 __device__ __forceinline__ float slice_lse(const float2 *stat, size_t step, int nslice) {
     float m = -INFINITY, tot = 0.f;
-    for (int s0 = 0; s0 < nslice; s0 += kFuseSlices) {
-        float2 v[kFuseSlices];
+    for (int s0 = 0; s0 < nslice; s0 += FLIGHT) {
+        float2 v[FLIGHT];
 #pragma unroll
-        for (int j = 0; j < kFuseSlices; ++j) v[j] = stat[min(s0 + j, nslice - 1) * step];
+        for (int j = 0; j < FLIGHT; ++j) v[j] = stat[min(s0 + j, nslice - 1) * step];
         float gm = m;
 #pragma unroll
-        for (int j = 0; j < kFuseSlices; ++j) gm = fmaxf(gm, v[j].x);
+        for (int j = 0; j < FLIGHT; ++j) gm = fmaxf(gm, v[j].x);
         const float ref = gm == -INFINITY ? 0.f : gm;  // no score above -inf yet
         tot *= ex2(m - ref);
 #pragma unroll
-        for (int j = 0; j < kFuseSlices; ++j) tot += s0 + j < nslice ? v[j].y * ex2(v[j].x - ref) : 0.f;
+        for (int j = 0; j < FLIGHT; ++j) tot += s0 + j < nslice ? v[j].y * ex2(v[j].x - ref) : 0.f;
         m = gm;
     }
     return m + __log2f(tot);
@@ -309,6 +329,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     float stage_lse = 0.f;
     // rows per kv head are usually a power of two: shift and mask instead of a division per copy
     const int rep_shift = (rep & (rep - 1)) == 0 ? __builtin_ctz(rep) : -1;  // uniform
+    auto row_lse = [&](int rr) {
+        // rows past the end get lse = +inf, so their probabilities are exactly 0
+        const int rc = min(rr, R - 1);
+        float v;
+        if constexpr (FUSE) {
+            const float2 *at = stat + (size_t)kvh * R + rc;
+            if (TW == 1 && nslice > 8) v = slice_lse<24>(at, (size_t)Hkv * R, nslice);  // uniform
+            else v = slice_lse<8>(at, (size_t)Hkv * R, nslice);
+        } else {
+            v = lse2[(size_t)kvh * R + rc];
+        }
+        return rr < R ? v : INFINITY;
+    };
     auto stage = [&](int chunk, int b, bool with_lse) {
         int lane_now = lane;
         asm volatile("" : "+v"(lane_now));  // keeps the slot arithmetic here instead of in registers across the loop
@@ -321,17 +354,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                                              : qrow_index(rr, rep, Hq, kvh);
             AT::issue(q + qi * D + st_col * 8, &lds.t[b], w, i);
         }
-        if (with_lse && tid < kRows) {
-            const int rr = chunk * kRows + tid;
-            // rows past the end get lse = +inf, so their probabilities are exactly 0
-            const int rc = min(rr, R - 1);
-            if constexpr (FUSE) {
-                stage_lse = slice_lse(stat + (size_t)kvh * R + rc, (size_t)Hkv * R, nslice);
-            } else {
-                stage_lse = lse2[(size_t)kvh * R + rc];
-            }
-            if (rr >= R) stage_lse = INFINITY;
-        }
+        if (with_lse && tid < kRows) stage_lse = row_lse(chunk * kRows + tid);
     };
     auto stage_lse_store = [&](int b) {
         if (tid < kRows) lds.lse[b][tid] = stage_lse;
@@ -341,13 +364,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
     for (int j = 0; j < TW * 16; ++j) col[j] = 0.f;
 
-    stage(0, 0, true);
-    stage_lse_store(0);
+    // the first two chunks' log-sum-exps by all threads at once (2304 keys, 148 rows per head in 18 slices: 10.8 -> 8.6 us)
+    static_assert(kThreads == 2 * kRows, "a thread per row of two chunks");
+    stage(0, 0, false);
+    lds.lse[tid / kRows][tid % kRows] = row_lse(tid);
     async_tile_wait();
     __syncthreads();
     for (int chunk = 0; chunk < nchunk; ++chunk) {
         const int cur = chunk & 1;
-        stage(min(chunk + 1, nchunk - 1), cur ^ 1, chunk + 1 < nchunk);
+        const bool more_lse = chunk > 0 && chunk + 1 < nchunk;
+        if (chunk + 1 < nchunk) stage(chunk + 1, cur ^ 1, more_lse);
         // Units of work: (query tile qt, key tile kt), 8 products each, then 16 exponentials folded
         // into the column sums.  The products of the next unit are issued before the exponentials
         // of the current one (two accumulators), so the matrix pipe works while the wave does its
@@ -411,7 +437,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                 fold(1, acc1, lse);
             }
         }
-        stage_lse_store(cur ^ 1);
+        if (more_lse) stage_lse_store(cur ^ 1);
         async_tile_wait();
         __syncthreads();
     }
@@ -470,6 +496,21 @@ Plan make_plan(int M, int N, int Hq, int Hkv, int nseq) {
     // tile each (20 sequences of 1500 keys, 128 text rows: 161 us with slices as for one sequence, 139 with these)
     const long long per_slice = (long long)p.nrb * Hkv * nseq;
     int want = (int)((1024 + per_slice - 1) / per_slice);
+    if (nseq == 1) {
+        // One sequence: as few whole rounds of the chip (two workgroups per CU) as are nearly full -- a round costs its start, rows and
+        // keys on their way, and a few workgroups more than a round cost another (1024 workgroups and more, us -> one round:
+        // 20000 keys, 300 rows 135 -> 135 in 12 slices, 152 in 13; 16384, 128 rows 54.3 -> 52.4; 131072, 16 rows 108 -> 105).
+        constexpr int kRound = 512;
+        double best = 0.0;
+        for (int r = 1; r <= 4 && best < 0.85; ++r) {
+            const long long cut = std::max(1LL, kRound * r / per_slice);
+            const double full = (double)(cut * per_slice) / ((cut * per_slice + kRound - 1) / kRound * kRound);
+            if (full > best) {
+                best = full;
+                want = (int)cut;
+            }
+        }
+    }
     const int max_slices = ceil_div(N, kRows);
     if (want > max_slices) want = max_slices;
     if (want < 1) want = 1;

@@ -585,3 +585,15 @@ def test_scan_of_a_few_chunks_in_one_launch(T, H, P, G, n, carry, dtype):
     y_ref, S_ref = oracle.ssd_seq(f(short[0]), f(short[1]), f(A), f(short[2]), f(short[3]), opt(D), opt(S_in))
     assert_close(f(y), y_ref, TOL[dtype], "y", units=(1,))
     assert_close(f(S), S_ref, TOL[torch.float32], "state", units=(0,))
+
+
+@pytest.mark.parametrize("N", [700, 4096 + 33])
+@pytest.mark.parametrize("M,Hq,Hkv,d", [(1, 1, 1, 64), (8, 8, 2, 128), (33, 2, 2, 64), (97, 4, 4, 128), (32, 8, 2, 128), (43, 3, 1, 64),
+                                        (129, 1, 1, 128), (65, 4, 1, 128), (100, 3, 1, 64)])
+def test_score_attn_rows_that_leave_waves_without_a_tile(N, M, Hq, Hkv, d):
+    """1 to 300 query rows of a kv head: none, one or two tiles of 32 rows in a wave of pass 1, one to three chunks of 128 in
+    pass 2 (the log-sum-exps of the first two at once), keys that end inside a chunk."""
+    _say("score_attn rows N=%d M=%d Hq=%d Hkv=%d d=%d" % (N, M, Hq, Hkv, d))
+    rn = _draw(N + M, BF16)
+    q, k = rn(M, Hq, d), rn(N, Hkv, d)
+    assert_close(f(strd.score_attn(q.to(DEV), k.to(DEV))), oracle.score_attn(f(q), f(k)), BOUND[BF16], "s", units=(0,))
