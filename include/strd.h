@@ -235,11 +235,17 @@ size_t strd_score_attn_varlen_workspace(const strd_seq *seqs, int nseq, int Hq, 
 int strd_score_attn_varlen(const void *q_all /* [dev] [rows, Hq, d] */, const void *k_all /* [dev] [rows, Hkv, d] */,
                            float *scores, int ld, const strd_seq *seqs, int nseq, int Hq, int Hkv, int d,
                            float scale, strd_dtype io, void *ws, size_t ws_bytes, void *stream);
+/* The same, and the ld - N_b floats behind the scores of sequence b become 0. */
+int strd_score_attn_varlen_padded(const void *q_all, const void *k_all, float *scores, int ld, const strd_seq *seqs, int nseq,
+                                  int Hq, int Hkv, int d, float scale, strd_dtype io, void *ws, size_t ws_bytes, void *stream);
 size_t strd_score_mamba_varlen_workspace(const strd_seq *seqs, int nseq, int H, int G, int n, strd_dtype io);
 int strd_score_mamba_varlen(const void *B_all /* [dev] [rows, G, n] */, const void *C_all /* [dev] [rows, G, n] */,
                             const float *dt_all /* [dev] [rows, H] */, float *scores, int ld,
                             const strd_seq *seqs, int nseq, int H, int G, int n, strd_dtype io, void *ws,
                             size_t ws_bytes, void *stream);
+int strd_score_mamba_varlen_padded(const void *B_all, const void *C_all, const float *dt_all, float *scores, int ld,
+                                   const strd_seq *seqs, int nseq, int H, int G, int n, strd_dtype io, void *ws, size_t ws_bytes,
+                                   void *stream);
 int strd_select_topk_varlen_max_n(void);
 int strd_select_topk_varlen(const float *scores, int ld, const strd_seq *seqs, int nseq, int32_t *idx,
                             void *stream);

@@ -186,8 +186,9 @@ size_t strd_score_attn_varlen_workspace(const strd_seq *seqs, int nseq, int Hq, 
     return score_attn_general_ws(p.max_m, p.max_n, Hq, Hkv, nseq);
 }
 
-int strd_score_attn_varlen(const void *q_all, const void *k_all, float *scores, int ld, const strd_seq *seqs, int nseq,
-                           int Hq, int Hkv, int d, float scale, strd_dtype io, void *ws, size_t ws_bytes, void *stream) {
+static int score_attn_packed(const void *q_all, const void *k_all, float *scores, int ld, const strd_seq *seqs, int nseq,
+                             int Hq, int Hkv, int d, float scale, strd_dtype io, void *ws, size_t ws_bytes, bool pad,
+                             void *stream) {
     SeqPlan p;
     if (!q_all || !k_all || !scores || Hq < 1 || Hkv < 1 || d < 1 || Hq % Hkv || !io_ok(io) || !(scale > 0.f) ||
         !plan_seqs(seqs, nseq, false, p) || ld < p.max_n || ld % 4 || (long long)p.max_m * Hq > (1 << 30))
@@ -197,10 +198,20 @@ int strd_score_attn_varlen(const void *q_all, const void *k_all, float *scores, 
     const size_t need = strd_score_attn_varlen_workspace(seqs, nseq, Hq, Hkv, d, io);
     if (!ws || ws_bytes < need) return STRD_EWORKSPACE;
     if (mfma)
-        return score_attn_mfma_varlen(q_all, k_all, scores, ld, p.tab, nseq, p.max_m, p.max_n, Hq, Hkv, d, scale, ws,
+        return score_attn_mfma_varlen(q_all, k_all, scores, ld, p.tab, nseq, p.max_m, p.max_n, Hq, Hkv, d, scale, ws, pad,
                                       as_stream(stream));
+    if (pad && scores_pad(scores, ld, p.tab, nseq, as_stream(stream)) != STRD_OK) return STRD_EHIP;
     return score_attn_general_varlen(q_all, k_all, scores, ld, p.tab, nseq, p.max_m, p.max_n, Hq, Hkv, d, scale, io, ws,
                                      as_stream(stream));
+}
+
+int strd_score_attn_varlen(const void *q_all, const void *k_all, float *scores, int ld, const strd_seq *seqs, int nseq,
+                           int Hq, int Hkv, int d, float scale, strd_dtype io, void *ws, size_t ws_bytes, void *stream) {
+    return score_attn_packed(q_all, k_all, scores, ld, seqs, nseq, Hq, Hkv, d, scale, io, ws, ws_bytes, false, stream);
+}
+int strd_score_attn_varlen_padded(const void *q_all, const void *k_all, float *scores, int ld, const strd_seq *seqs, int nseq,
+                                  int Hq, int Hkv, int d, float scale, strd_dtype io, void *ws, size_t ws_bytes, void *stream) {
+    return score_attn_packed(q_all, k_all, scores, ld, seqs, nseq, Hq, Hkv, d, scale, io, ws, ws_bytes, true, stream);
 }
 
 size_t strd_score_mamba_varlen_workspace(const strd_seq *seqs, int nseq, int H, int G, int n, strd_dtype io) {
@@ -209,9 +220,9 @@ size_t strd_score_mamba_varlen_workspace(const strd_seq *seqs, int nseq, int H, 
     return score_mamba_mfma_supported(p.max_m, p.max_n, H, G, n, io) ? align_up((size_t)p.rows * G * sizeof(float), 256) : 0;
 }
 
-int strd_score_mamba_varlen(const void *B_all, const void *C_all, const float *dt_all, float *scores, int ld,
+static int score_mamba_packed(const void *B_all, const void *C_all, const float *dt_all, float *scores, int ld,
                             const strd_seq *seqs, int nseq, int H, int G, int n, strd_dtype io, void *ws, size_t ws_bytes,
-                            void *stream) {
+                              bool pad, void *stream) {
     SeqPlan p;
     // b and c are one packed tensor each; the library reads vision rows of B_all and text rows of C_all
     if (!B_all || !C_all || !dt_all || !scores || H < 1 || G < 1 || n < 1 || H % G || !io_ok(io) ||
@@ -222,11 +233,23 @@ int strd_score_mamba_varlen(const void *B_all, const void *C_all, const float *d
     const size_t need = strd_score_mamba_varlen_workspace(seqs, nseq, H, G, n, io);
     if (need && (!ws || ws_bytes < need)) return STRD_EWORKSPACE;
     if (mfma)
-        return score_mamba_mfma_varlen(B_all, C_all, dt_all, scores, ld, p.tab, nseq, p.max_n, H, G, n, ws,
+        return score_mamba_mfma_varlen(B_all, C_all, dt_all, scores, ld, p.tab, nseq, p.max_n, H, G, n, ws, pad,
                                        as_stream(stream));
+    if (pad && scores_pad(scores, ld, p.tab, nseq, as_stream(stream)) != STRD_OK) return STRD_EHIP;
     return score_mamba_general_varlen(B_all, C_all, dt_all, scores, ld, p.tab, nseq, p.max_n, H, G, n, io,
                                       as_stream(stream));
 }
+int strd_score_mamba_varlen(const void *B_all, const void *C_all, const float *dt_all, float *scores, int ld,
+                            const strd_seq *seqs, int nseq, int H, int G, int n, strd_dtype io, void *ws, size_t ws_bytes,
+                            void *stream) {
+    return score_mamba_packed(B_all, C_all, dt_all, scores, ld, seqs, nseq, H, G, n, io, ws, ws_bytes, false, stream);
+}
+int strd_score_mamba_varlen_padded(const void *B_all, const void *C_all, const float *dt_all, float *scores, int ld,
+                                   const strd_seq *seqs, int nseq, int H, int G, int n, strd_dtype io, void *ws, size_t ws_bytes,
+                                   void *stream) {
+    return score_mamba_packed(B_all, C_all, dt_all, scores, ld, seqs, nseq, H, G, n, io, ws, ws_bytes, true, stream);
+}
+
 
 int strd_select_topk_varlen_max_n(void) { return select_topk_varlen_max_n(); }
 

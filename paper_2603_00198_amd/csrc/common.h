@@ -234,12 +234,13 @@ int select_topk_varlen_launch(const float *scores, int ld, const SeqTab &tab, in
 int score_mamba_general_varlen(const void *B, const void *C, const float *dt, float *s, int ld, const SeqTab &tab, int nseq, int max_n,
                                int H, int G, int n, strd_dtype io, hipStream_t st);
 int score_mamba_mfma_varlen(const void *B, const void *C, const float *dt, float *s, int ld, const SeqTab &tab, int nseq, int max_n,
-                            int H, int G, int n, void *ws, hipStream_t st);
+                            int H, int G, int n, void *ws, bool pad, hipStream_t st);
 int score_attn_general_varlen(const void *q, const void *k, float *s, int ld, const SeqTab &tab, int nseq, int max_m,
                               int max_n, int Hq, int Hkv, int d, float scale, strd_dtype io, void *ws, hipStream_t st);
 size_t score_attn_mfma_varlen_ws(int nseq, int max_m, int max_n, int Hq, int Hkv);
 int score_attn_mfma_varlen(const void *q, const void *k, float *s, int ld, const SeqTab &tab, int nseq, int max_m,
-                           int max_n, int Hq, int Hkv, int d, float scale, void *ws, hipStream_t st);
+                           int max_n, int Hq, int Hkv, int d, float scale, void *ws, bool pad, hipStream_t st);
+int scores_pad(float *s, int ld, const SeqTab &tab, int nseq, hipStream_t st);
 size_t select_topk_ws(int N);
 int select_topk_launch(const float *scores, int N, int K, int32_t *idx, void *ws, hipStream_t s);
 int select_topk_static_max_n();

@@ -1155,6 +1155,17 @@ static int score_mamba_launch(const void *B, const void *C, const float *dt, flo
     return launch_status();
 }
 
+// The floats behind every sequence's scores, `ld` apart, become 0.
+static __global__ __launch_bounds__(256) void scores_pad_kernel(float *__restrict__ s, SeqTab seq, int ld) {
+    const int i = seq.N[blockIdx.y] + blockIdx.x * 256 + threadIdx.x;
+    if (i < ld) s[(size_t)blockIdx.y * ld + i] = 0.f;
+}
+int scores_pad(float *s, int ld, const SeqTab &tab, int nseq, hipStream_t st) {
+    int most = 0;
+    for (int b = 0; b < nseq; ++b) most = std::max(most, ld - tab.N[b]);
+    if (most > 0) scores_pad_kernel<<<dim3(ceil_div(most, 256), nseq), 256, 0, st>>>(s, tab, ld);
+    return launch_status();
+}
 int score_mamba_general(const void *B, const void *C, const float *dt, float *s, int M, int N, int H,
                         int G, int n, strd_dtype io, hipStream_t st) {
     if (io == STRD_F32) return score_mamba_launch<float>(B, C, dt, s, M, N, H, G, n, OneSeq(), 1, 0, st);

@@ -301,12 +301,6 @@ struct Seqs {
     int ld(PyObject *o) const { return o == Py_None ? narrow(((int64_t)max_n + 3) / 4 * 4, "ld") : integer_of(o, "ld"); }
 };
 
-Tensor scores_or_zeros(PyObject *o, int n, int ld, const Tensor &like) {
-    if (o != Py_None) return dev(o);
-    Tensor s = empty({n, ld}, at::kFloat, like);
-    return s.zero_();
-}
-
 PyObject *score_attn_varlen(Args a) {  // q_all, k_all, seqs, scale, ld, out
     const Tensor &q = dev(a[0]), &k = dev(a[1]);
     const Seqs sq(a[2]);
@@ -316,11 +310,12 @@ PyObject *score_attn_varlen(Args a) {  // q_all, k_all, seqs, scale, ld, out
     const strd_dtype io = io_of(q);
     const int Hq = size(q, 1), d = size(q, 2), Hkv = size(k, 1), ld = sq.ld(a[4]);
     const float scale = scale_or_default(a[3], d);
-    Tensor s = scores_or_zeros(a[5], sq.n, ld, q);
+    const bool mine = a[5] == Py_None;  // a matrix made here has zeros behind the scores
+    Tensor s = out_or(a[5], {sq.n, ld}, at::kFloat, q);
     const hipStream_t st = stream();
     Workspace ws(Py_None, strd_score_attn_varlen_workspace(sq.s, sq.n, Hq, Hkv, d, io), q, st);
     check(call([&] {
-              return strd_score_attn_varlen(q.data_ptr(), k.data_ptr(), f32(&s), ld, sq.s, sq.n, Hq, Hkv, d, scale, io, ws.p,
+              return (mine ? strd_score_attn_varlen_padded : strd_score_attn_varlen)(q.data_ptr(), k.data_ptr(), f32(&s), ld, sq.s, sq.n, Hq, Hkv, d, scale, io, ws.p,
                                             ws.bytes, st);
           }),
           "score_attn_varlen");
@@ -335,11 +330,12 @@ PyObject *score_mamba_varlen(Args a) {  // B_all, C_all, dt_all, seqs, ld, out
         fail("score_mamba_varlen: B/C/dt/seqs mismatch");
     const strd_dtype io = io_of(B);
     const int G = size(B, 1), n = size(B, 2), H = size(dt, 1), ld = sq.ld(a[4]);
-    Tensor s = scores_or_zeros(a[5], sq.n, ld, B);
+    const bool mine = a[5] == Py_None;
+    Tensor s = out_or(a[5], {sq.n, ld}, at::kFloat, B);
     const hipStream_t st = stream();
     Workspace ws(Py_None, strd_score_mamba_varlen_workspace(sq.s, sq.n, H, G, n, io), B, st);
     check(call([&] {
-              return strd_score_mamba_varlen(B.data_ptr(), C.data_ptr(), f32(dt), f32(&s), ld, sq.s, sq.n, H, G, n, io, ws.p,
+              return (mine ? strd_score_mamba_varlen_padded : strd_score_mamba_varlen)(B.data_ptr(), C.data_ptr(), f32(dt), f32(&s), ld, sq.s, sq.n, H, G, n, io, ws.p,
                                              ws.bytes, st);
           }),
           "score_mamba_varlen");

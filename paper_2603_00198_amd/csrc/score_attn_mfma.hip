@@ -343,6 +343,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         return rr < R ? v : INFINITY;
     };
     auto stage = [&](int chunk, int b, bool with_lse) {
+        const int slots = (min(kRows, R - chunk * kRows) + 31) / 32 * 32 * AT::kVP;  // of the 32-row tiles that hold a row
         int lane_now = lane;
         asm volatile("" : "+v"(lane_now));  // keeps the slot arithmetic here instead of in registers across the loop
 #pragma unroll
@@ -352,7 +353,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             const int rr = min(chunk * kRows + st_row, R - 1);
             const size_t qi = rep_shift >= 0 ? (size_t)(rr >> rep_shift) * Hq + kvh * rep + (rr & (rep - 1))
                                              : qrow_index(rr, rep, Hq, kvh);
-            AT::issue(q + qi * D + st_col * 8, &lds.t[b], w, i);
+            if (i * kThreads < slots) AT::issue(q + qi * D + st_col * 8, &lds.t[b], w, i);  // uniform
         }
         if (with_lse && tid < kRows) stage_lse = row_lse(chunk * kRows + tid);
     };
@@ -468,7 +469,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 template <class SEQ>
 __global__ __launch_bounds__(kThreads) void attn_score_reduce_kernel(const float *__restrict__ part, float *__restrict__ s,
                                                                      int N, int Hkv, float norm, SEQ seq, int Hq,
-                                                                     size_t part_stride, int ld) {
+                                                                     size_t part_stride, int ld, bool pad) {
     if constexpr (is_varlen<SEQ>()) {
         const int b = blockIdx.y;
         N = seq.N[b];
@@ -477,7 +478,10 @@ __global__ __launch_bounds__(kThreads) void attn_score_reduce_kernel(const float
         s += (size_t)b * ld;
     }
     const int i = blockIdx.x * kThreads + threadIdx.x;
-    if (i >= N) return;
+    if (i >= N) {
+        if (pad && i < ld) s[i] = 0.f;  // what lies behind a sequence's scores
+        return;
+    }
     float t = 0.f;
     for (int h = 0; h < Hkv; ++h) t += part[(size_t)h * N + i];
     s[i] = t * norm;
@@ -533,7 +537,7 @@ Plan make_plan(int M, int N, int Hq, int Hkv, int nseq) {
 // vision counts of the batch, and every sequence has a plan's worth of workspace of its own.
 template <int D, class SEQ>
 int run(const void *q, const void *k, float *s, int M, int N, int Hq, int Hkv, float scale, void *ws, const SEQ &seq,
-        int nseq, int ld, hipStream_t st) {
+        int nseq, int ld, bool pad, hipStream_t st) {
     const Plan p = make_plan(M, N, Hq, Hkv, nseq);
     const size_t smem = sizeof(Tile<D>);
     const auto colsum = p.tw == 1 ? (p.fuse ? &attn_colsum_kernel<D, SEQ, 1, true> : &attn_colsum_kernel<D, SEQ, 1, false>)
@@ -556,8 +560,8 @@ int run(const void *q, const void *k, float *s, int M, int N, int Hq, int Hkv, f
     colsum<<<dim3(ceil_div(N, 4 * 32 * p.tw) * Hkv, nseq), kThreads, smem, st>>>(
         (const bf16_t *)q, (const bf16_t *)k, lse2, stat, part, M, N, Hq, Hkv, scale2, p.nslice, seq, (int)rows, stat_stride,
         part_stride);
-    attn_score_reduce_kernel<SEQ><<<dim3(ceil_div(N, kThreads), nseq), kThreads, 0, st>>>(
-        part, s, N, Hkv, 1.f / ((float)M * (float)Hq), seq, Hq, part_stride, ld);
+    attn_score_reduce_kernel<SEQ><<<dim3(ceil_div(pad ? ld : N, kThreads), nseq), kThreads, 0, st>>>(
+        part, s, N, Hkv, 1.f / ((float)M * (float)Hq), seq, Hq, part_stride, ld, pad);
     return launch_status();
 }
 
@@ -583,15 +587,15 @@ size_t score_attn_mfma_varlen_ws(int nseq, int max_m, int max_n, int Hq, int Hkv
 
 int score_attn_mfma(const void *q, const void *k, float *s, int M, int N, int Hq, int Hkv, int d, float scale, void *ws,
                     hipStream_t st) {
-    if (d == 128) return run<128>(q, k, s, M, N, Hq, Hkv, scale, ws, OneSeq(), 1, 0, st);
-    if (d == 64) return run<64>(q, k, s, M, N, Hq, Hkv, scale, ws, OneSeq(), 1, 0, st);
+    if (d == 128) return run<128>(q, k, s, M, N, Hq, Hkv, scale, ws, OneSeq(), 1, 0, false, st);
+    if (d == 64) return run<64>(q, k, s, M, N, Hq, Hkv, scale, ws, OneSeq(), 1, 0, false, st);
     return STRD_EUNSUPPORTED;
 }
 
 int score_attn_mfma_varlen(const void *q, const void *k, float *s, int ld, const SeqTab &tab, int nseq, int max_m,
-                           int max_n, int Hq, int Hkv, int d, float scale, void *ws, hipStream_t st) {
-    if (d == 128) return run<128>(q, k, s, max_m, max_n, Hq, Hkv, scale, ws, tab, nseq, ld, st);
-    if (d == 64) return run<64>(q, k, s, max_m, max_n, Hq, Hkv, scale, ws, tab, nseq, ld, st);
+                           int max_n, int Hq, int Hkv, int d, float scale, void *ws, bool pad, hipStream_t st) {
+    if (d == 128) return run<128>(q, k, s, max_m, max_n, Hq, Hkv, scale, ws, tab, nseq, ld, pad, st);
+    if (d == 64) return run<64>(q, k, s, max_m, max_n, Hq, Hkv, scale, ws, tab, nseq, ld, pad, st);
     return STRD_EUNSUPPORTED;
 }
 

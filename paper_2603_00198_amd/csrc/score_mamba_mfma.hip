@@ -71,6 +71,7 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
         Bv += (size_t)seq.row0[b] * G * NS;
         Ct += (size_t)(seq.row0[b] + N) * G * NS;
         part += (size_t)seq.row0[b] * G;
+        if (!FULL) U += (size_t)seq.row0[b] * H;
     }
 
     const int tid = threadIdx.x, lane = tid & 63, lc = lane & 31, half = lane >> 5;
@@ -86,10 +87,11 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
 #pragma unroll
     for (int i = 0; i < AT::kIssues; ++i) AT::slot(w, lane, i, st_row[i], st_col[i]);
     auto stage = [&](int mc, int b) {
+        const int slots = (min(kMC, M - mc * kMC) + 31) / 32 * 32 * AT::kVP;  // of the 32-row tiles that hold a row
 #pragma unroll
         for (int i = 0; i < AT::kIssues; ++i) {
             const int m = min(mc * kMC + st_row[i], M - 1);
-            AT::issue(Ct + ((size_t)m * G + g) * NS + st_col[i] * 8, &lds.c[b], w, i);
+            if (i * kThreads < slots) AT::issue(Ct + ((size_t)m * G + g) * NS + st_col[i] * 8, &lds.c[b], w, i);  // uniform
         }
     };
     stage(0, 0);
@@ -103,7 +105,24 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
         for (int ks = 0; ks < KS; ++ks) bfr[ct][ks] = *reinterpret_cast<const bf16x8 *>(bp + 16 * ks);
     }
     // u fragments of this wave's tokens (B operand: lane = token column, k = head 8*half + j of the group)
-    const int hpg = FULL ? H / G : 0;
+    const int hpg = H / G;
+    // Without FULL, U is dt: the sum of the group's heads per token, half of them per lane half, beside the b fragments
+    // (in a launch of its own, which also adds up the groups, dt cost 10 us for 16 clips of 2048 tokens and 128 heads, 5 without).
+    float dts[CT];
+    if (!FULL) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            const float *dp = U + (size_t)min(tok0 + 32 * ct + lc, N - 1) * H + g * hpg;
+            float t = 0.f;
+            if (hpg == 16) {  // uniform
+                const float4 a = *reinterpret_cast<const float4 *>(dp + 8 * half), b = *reinterpret_cast<const float4 *>(dp + 8 * half + 4);
+                t = ((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w));
+            } else {
+                for (int h = half; h < hpg; h += 2) t += dp[h];
+            }
+            dts[ct] = t + __shfl_xor(t, 32, kWave);
+        }
+    }
     bf16x8 u_hi[CT], u_lo[CT];
     if (FULL) {
 #pragma unroll
@@ -190,43 +209,27 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
     for (int ct = 0; ct < CT; ++ct) {
         const float col = part_sum[ct] + __shfl_xor(part_sum[ct], 32, kWave);
         const int t = tok0 + 32 * ct + lc;
-        if (half == 0 && t < N) part[(size_t)g * N + t] = col;
+        if (half == 0 && t < N) part[(size_t)g * N + t] = FULL ? col : col * dts[ct];
     }
 }
 
-// s_i = 1/(M*H) * sum_h dt_i^h * a[g(h)][i].  16 adjacent lanes share a token and read its dt
-// row in 64-byte pieces (coalesced); their partial sums meet in a fixed butterfly order.
+// Adds up the group partials, in which the per-token factors are already.  SeqTab: blockIdx.y = sequence, `s` has `ld` floats per
+// sequence; `pad`: those behind the sequence's scores become 0.
 template <class SEQ = OneSeq>
-__global__ __launch_bounds__(kThreads) void score_mamba_reduce_kernel(const float *__restrict__ part,
-                                                                      const float *__restrict__ dtv,
-                                                                      float *__restrict__ s, int N, int H, int G,
-                                                                      float norm, SEQ seq, int ld) {
-    if constexpr (is_varlen<SEQ>()) {  // blockIdx.y = sequence; dtv is the packed tensor, s has `ld` floats per sequence
+__global__ __launch_bounds__(kThreads) void score_mamba_reduce_kernel(const float *__restrict__ part, float *__restrict__ s, int N,
+                                                                      int H, int G, float norm, SEQ seq, int ld, bool pad) {
+    if constexpr (is_varlen<SEQ>()) {
         const int b = blockIdx.y;
         N = seq.N[b];
         norm = 1.f / ((float)seq.M[b] * (float)H);
         part += (size_t)seq.row0[b] * G;
-        dtv += (size_t)seq.row0[b] * H;
         s += (size_t)b * ld;
     }
-    const int i = blockIdx.x * (kThreads / 16) + threadIdx.x / 16, j = threadIdx.x & 15;
-    const int hpg = H / G;
-    float tot = 0.f;
-    if (i < N) {
-        const float *dr = dtv + (size_t)i * H;
-        for (int h = j; h < H; h += 16) tot = fmaf(dr[h], part[(size_t)(h / hpg) * N + i], tot);
-    }
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) tot += __shfl_xor(tot, o, kWave);
-    if (i < N && j == 0) s[i] = tot * norm;
-}
-
-// Full score: the per-token factors are already inside the group partials.
-__global__ __launch_bounds__(kThreads) void score_mamba_full_reduce_kernel(const float *__restrict__ part,
-                                                                           float *__restrict__ s, int N, int G,
-                                                                           float norm) {
     const int i = blockIdx.x * kThreads + threadIdx.x;
-    if (i >= N) return;
+    if (i >= N) {
+        if (pad && i < ld) s[i] = 0.f;
+        return;
+    }
     float tot = 0.f;
     for (int g = 0; g < G; ++g) tot += part[(size_t)g * N + i];
     s[i] = tot * norm;
@@ -456,8 +459,8 @@ int launch_res(const void *B, const void *C, const float *dt, float *s, int M, i
     float *part = (float *)ws;
     score_mamba_res_kernel<NS, CT><<<slices * G, kResThreads, smem, st>>>((const bf16_t *)B, (const bf16_t *)C, dt, part,
                                                                          M, N, G, H, slices, slice_len);
-    score_mamba_full_reduce_kernel<<<ceil_div(N, kThreads), kThreads, 0, st>>>(part, s, N, G,
-                                                                             1.f / ((float)M * (float)H));
+    score_mamba_reduce_kernel<<<ceil_div(N, kThreads), kThreads, 0, st>>>(part, s, N, H, G, 1.f / ((float)M * (float)H), OneSeq(), 0,
+                                                                          false);
     return launch_status();
 }
 
@@ -471,37 +474,44 @@ int launch_full(const void *B, const void *C, const float *U, const float *V, fl
     const dim3 grid(ceil_div(N, 128 * CT), G);
     score_mamba_mfma_kernel<NS, CT, true><<<grid, kThreads, smem, st>>>((const bf16_t *)B, (const bf16_t *)C, U, V, part,
                                                                         M, N, G, H, OneSeq());
-    score_mamba_full_reduce_kernel<<<ceil_div(N, kThreads), kThreads, 0, st>>>(part, s, N, G,
-                                                                             1.f / ((float)M * (float)H));
+    score_mamba_reduce_kernel<<<ceil_div(N, kThreads), kThreads, 0, st>>>(part, s, N, H, G, 1.f / ((float)M * (float)H), OneSeq(), 0,
+                                                                          false);
     return launch_status();
+}
+
+// LDS of the tile kernel: one tile, of the rows that there are, where one holds them all (four workgroups and more per CU then).
+template <int NS>
+size_t tile_lds(int M) {
+    return M > kMC ? sizeof(Tile<NS>) : (size_t)(M + 31) / 32 * 32 * Tile<NS>::A::kVP * 16;
 }
 
 template <int NS, int CT>
 int launch(const void *B, const void *C, const float *dt, float *s, int M, int N, int H, int G, void *ws,
            hipStream_t st) {
-    const size_t smem = sizeof(Tile<NS>);
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&score_mamba_mfma_kernel<NS, CT, false>), smem))
+    const size_t smem = tile_lds<NS>(M);
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&score_mamba_mfma_kernel<NS, CT, false>), sizeof(Tile<NS>)))
         return STRD_EHIP;
     float *part = (float *)ws;
     const dim3 grid(ceil_div(N, 128 * CT), G);
-    score_mamba_mfma_kernel<NS, CT, false><<<grid, kThreads, smem, st>>>((const bf16_t *)B, (const bf16_t *)C, nullptr,
+    score_mamba_mfma_kernel<NS, CT, false><<<grid, kThreads, smem, st>>>((const bf16_t *)B, (const bf16_t *)C, dt,
                                                                          nullptr, part, M, N, G, H, OneSeq());
-    score_mamba_reduce_kernel<<<ceil_div(N, kThreads / 16), kThreads, 0, st>>>(part, dt, s, N, H, G,
-                                                                          1.f / ((float)M * (float)H), OneSeq(), 0);
+    score_mamba_reduce_kernel<<<ceil_div(N, kThreads), kThreads, 0, st>>>(part, s, N, H, G, 1.f / ((float)M * (float)H), OneSeq(), 0,
+                                                                          false);
     return launch_status();
 }
 
 template <int NS>
 int launch_varlen(const void *B, const void *C, const float *dt, float *s, int ld, const SeqTab &tab, int nseq, int max_n, int H, int G,
-                  void *ws, hipStream_t st) {
-    const size_t smem = sizeof(Tile<NS>);
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&score_mamba_mfma_kernel<NS, 1, false, SeqTab>), smem))
+                  void *ws, bool pad, hipStream_t st) {
+    int max_m = 0;
+    for (int b = 0; b < nseq; ++b) max_m = std::max(max_m, tab.M[b]);
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&score_mamba_mfma_kernel<NS, 1, false, SeqTab>), sizeof(Tile<NS>)))
         return STRD_EHIP;
     float *part = (float *)ws;
-    score_mamba_mfma_kernel<NS, 1, false, SeqTab><<<dim3(ceil_div(max_n, 128), G, nseq), kThreads, smem, st>>>(
-        (const bf16_t *)B, (const bf16_t *)C, nullptr, nullptr, part, 0, 0, G, H, tab);
-    score_mamba_reduce_kernel<SeqTab><<<dim3(ceil_div(max_n, kThreads / 16), nseq), kThreads, 0, st>>>(part, dt, s, 0, H, G,
-                                                                                               0.f, tab, ld);
+    score_mamba_mfma_kernel<NS, 1, false, SeqTab><<<dim3(ceil_div(max_n, 128), G, nseq), kThreads, tile_lds<NS>(max_m), st>>>(
+        (const bf16_t *)B, (const bf16_t *)C, dt, nullptr, part, 0, 0, G, H, tab);
+    score_mamba_reduce_kernel<SeqTab><<<dim3(ceil_div(pad ? ld : max_n, kThreads), nseq), kThreads, 0, st>>>(part, s, 0, H, G, 0.f, tab,
+                                                                                                            ld, pad);
     return launch_status();
 }
 
@@ -509,9 +519,9 @@ int launch_varlen(const void *B, const void *C, const float *dt, float *s, int l
 
 // Packed batch on the matrix-core tile kernel: partials of sequence b at ws + row0[b] * G floats.
 int score_mamba_mfma_varlen(const void *B, const void *C, const float *dt, float *s, int ld, const SeqTab &tab, int nseq, int max_n,
-                            int H, int G, int n, void *ws, hipStream_t st) {
-    if (n == 128) return launch_varlen<128>(B, C, dt, s, ld, tab, nseq, max_n, H, G, ws, st);
-    if (n == 64) return launch_varlen<64>(B, C, dt, s, ld, tab, nseq, max_n, H, G, ws, st);
+                            int H, int G, int n, void *ws, bool pad, hipStream_t st) {
+    if (n == 128) return launch_varlen<128>(B, C, dt, s, ld, tab, nseq, max_n, H, G, ws, pad, st);
+    if (n == 64) return launch_varlen<64>(B, C, dt, s, ld, tab, nseq, max_n, H, G, ws, pad, st);
     return STRD_EUNSUPPORTED;
 }
 

@@ -169,3 +169,25 @@ def test_random_packed_batches(seed):
         k0 += k
         want_rows += [v0 + int(i) for i in want] + list(range(t0, t1))
     assert torch.equal(h2, hid[torch.tensor(want_rows, device=DEV)])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("ld", [None, 1000])
+def test_scores_of_a_packed_batch_have_zeros_behind_them(dtype, ld):
+    """In a matrix that the call makes; one that is passed in keeps what lies there."""
+    _say("varlen padding %s ld=%s" % (dtype, ld))
+    seqs = [(1, 2, 1), (300, 33, 5), (77, 1, 3), (512, 65, 9)]
+    rows = sum(n + m for n, m, _ in seqs)
+    g = torch.Generator().manual_seed(3)
+    rn = lambda *s: torch.randn(*s, generator=g).to(dtype).to(DEV)
+    q, k, B, C = rn(rows, 4, 64), rn(rows, 2, 64), rn(rows, 2, 64), rn(rows, 2, 64)
+    dt = torch.rand(rows, 8, generator=g).to(DEV)
+    for call in (lambda **kw: strd.score_attn_varlen(q, k, seqs, **kw), lambda **kw: strd.score_mamba_varlen(B, C, dt, seqs, **kw)):
+        for _ in range(3):                      # the memory of a freed matrix comes back
+            junk = torch.full((4, ld or 512), 7.0, device=DEV)
+            del junk
+            s = call(ld=ld)
+            mine = call(ld=ld, out=torch.full_like(s, 5.0))
+            for b, (n, _, _) in enumerate(seqs):
+                assert torch.equal(s[b, :n], mine[b, :n])
+                assert (s[b, n:] == 0).all() and (mine[b, n:] == 5).all()
