@@ -94,12 +94,20 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
             if (i * kThreads < slots) AT::issue(Ct + ((size_t)m * G + g) * NS + st_col[i] * 8, &lds.c[b], w, i);  // uniform
         }
     };
-    stage(0, 0);
+    // The b rows of 128 tokens come through LDS, in the place of the second text tile: a load that gives every lane its own token
+    // touches 32 rows with 32 bytes each, a copy whole rows.
+    constexpr bool kRows = CT == 1 && !FULL;
+    if constexpr (kRows) {
+#pragma unroll
+        for (int i = 0; i < AT::kIssues; ++i)
+            AT::issue(Bv + ((size_t)min((int)blockIdx.x * 128 + st_row[i], N - 1) * G + g) * NS + st_col[i] * 8, &lds.c[0], w, i);
+    }
+    stage(0, 1);
 
     // b fragments of this wave's tokens: lane = token column, 8 consecutive k (tail lanes repeat the last token)
     bf16x8 bfr[CT][KS];
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
+    for (int ct = 0; ct < CT && !kRows; ++ct) {
         const bf16_t *bp = Bv + ((size_t)min(tok0 + 32 * ct + lc, N - 1) * G + g) * NS + 8 * half;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) bfr[ct][ks] = *reinterpret_cast<const bf16x8 *>(bp + 16 * ks);
@@ -138,13 +146,18 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
     }
     async_tile_wait();
     __syncthreads();
+    if constexpr (kRows) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) bfr[0][ks] = *reinterpret_cast<const bf16x8 *>(lds.c[0].at(32 * w + lc, 16 * ks + 8 * half));
+        if (nmc > 1) __syncthreads();  // uniform: before the second text tile takes their place
+    }
 
     float part_sum[CT];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) part_sum[ct] = 0.f;
 
     for (int mc = 0; mc < nmc; ++mc) {
-        const int cur = mc & 1;
+        const int cur = ~mc & 1;
         if (mc + 1 < nmc) stage(mc + 1, cur ^ 1);  // uniform
         const int mrows = M - mc * kMC;            // valid text rows of this tile (may exceed kMC)
 #pragma unroll
@@ -479,10 +492,10 @@ int launch_full(const void *B, const void *C, const float *U, const float *V, fl
     return launch_status();
 }
 
-// LDS of the tile kernel: one tile, of the rows that there are, where one holds them all (four workgroups and more per CU then).
+// LDS of the tile kernel: the b rows and one text tile, of the rows that there are, where one holds them all.
 template <int NS>
 size_t tile_lds(int M) {
-    return M > kMC ? sizeof(Tile<NS>) : (size_t)(M + 31) / 32 * 32 * Tile<NS>::A::kVP * 16;
+    return M > kMC ? sizeof(Tile<NS>) : sizeof(typename Tile<NS>::Buf) + (size_t)(M + 31) / 32 * 32 * Tile<NS>::A::kVP * 16;
 }
 
 template <int NS, int CT>
