@@ -777,3 +777,14 @@ def test_ssd_prefill_pairs_of_heads_values_that_are_not_finite():
     same = torch.ones(T, H, P, dtype=torch.bool, device=DEV)
     same[t // 64 * 64:, h, 3] = False     # a step's products take its later tokens with weight 0
     assert torch.equal(y2[same], y[same])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d", [8, 520, 2048, 2056, 4096, 4104, 8192])
+def test_rmsnorm_rows_in_registers_and_longer_ones(d, dtype):
+    """Rows of up to 8 KB are held in registers, longer ones read twice; both sides of the line and a ragged last vector."""
+    _say("rmsnorm d=%d %s" % (d, dtype))
+    g = torch.Generator().manual_seed(d)
+    x, w = torch.randn(7, d, generator=g).to(dtype).to(DEV), torch.randn(d, generator=g).to(dtype).to(DEV)
+    got = strd.rmsnorm(x, w, 1e-5)
+    assert_close(synth.np64(got), oracle.rmsnorm(synth.np64(x), synth.np64(w), 1e-5), TOL[dtype], "rmsnorm")
