@@ -42,8 +42,10 @@ _SIGNATURES = {
     "strd_mfma_rate_probe": (_int, [_vp, _int, _int, _int, _vp]),
     "strd_score_attn_varlen_workspace": (_sz, [_vp, _int, _int, _int, _int, _int]),
     "strd_score_attn_varlen": (_int, [_vp, _vp, _vp, _int, _vp, _int, _int, _int, _int, _f32, _int, _vp, _sz, _vp]),
+    "strd_score_attn_varlen_padded": (_int, [_vp, _vp, _vp, _int, _vp, _int, _int, _int, _int, _f32, _int, _vp, _sz, _vp]),
     "strd_score_mamba_varlen_workspace": (_sz, [_vp, _int, _int, _int, _int, _int]),
     "strd_score_mamba_varlen": (_int, [_vp, _vp, _vp, _vp, _int, _vp, _int, _int, _int, _int, _int, _vp, _sz, _vp]),
+    "strd_score_mamba_varlen_padded": (_int, [_vp, _vp, _vp, _vp, _int, _vp, _int, _int, _int, _int, _int, _vp, _sz, _vp]),
     "strd_select_topk_varlen_max_n": (_int, []),
     "strd_select_topk_varlen": (_int, [_vp, _int, _vp, _int, _vp, _vp]),
     "strd_compact_varlen": (_int, [_vp, _int, _vp, _vp, _int, _vp, _vp, _vp]),
