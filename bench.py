@@ -32,13 +32,16 @@ KERNEL_STEP = 64               # tokens per step of the scan kernel, whatever `c
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "hbm_traffic.md")
 
 
-def source_hash(file_name):
+def source_hash(file_names):
+    """Of the named source files together ("kernel.hip" or "kernel.hip + roles.h")."""
     import hashlib
-    path = os.path.join(ROOT, "paper_2603_00198_amd", "csrc", file_name)
+    h = hashlib.sha1()
     try:
-        return hashlib.sha1(open(path, "rb").read()).hexdigest()[:12]
+        for name in file_names.split("+"):
+            h.update(open(os.path.join(ROOT, "paper_2603_00198_amd", "csrc", name.strip()), "rb").read())
     except OSError:
         return None
+    return h.hexdigest()[:12]
 
 
 def measured_traffic(workload, budget, kernel):
