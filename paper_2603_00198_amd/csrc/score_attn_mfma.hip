@@ -343,17 +343,24 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         return rr < R ? v : INFINITY;
     };
     auto stage = [&](int chunk, int b, bool with_lse) {
-        const int slots = (min(kRows, R - chunk * kRows) + 31) / 32 * 32 * AT::kVP;  // of the 32-row tiles that hold a row
         int lane_now = lane;
         asm volatile("" : "+v"(lane_now));  // keeps the slot arithmetic here instead of in registers across the loop
-#pragma unroll
-        for (int i = 0; i < AT::kIssues; ++i) {
+        auto copy = [&](int i) {
             int st_row, st_col;
             AT::slot(w, lane_now, i, st_row, st_col);
             const int rr = min(chunk * kRows + st_row, R - 1);
             const size_t qi = rep_shift >= 0 ? (size_t)(rr >> rep_shift) * Hq + kvh * rep + (rr & (rep - 1))
                                              : qrow_index(rr, rep, Hq, kvh);
-            if (i * kThreads < slots) AT::issue(q + qi * D + st_col * 8, &lds.t[b], w, i);  // uniform
+            AT::issue(q + qi * D + st_col * 8, &lds.t[b], w, i);
+        };
+        const int slots = (min(kRows, R - chunk * kRows) + 31) / 32 * 32 * AT::kVP;  // of the 32-row tiles that hold a row
+        if (slots == kRows * AT::kVP) {  // uniform, as the one below
+#pragma unroll
+            for (int i = 0; i < AT::kIssues; ++i) copy(i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < AT::kIssues; ++i)
+                if (i * kThreads < slots) copy(i);
         }
         if (with_lse && tid < kRows) stage_lse = row_lse(chunk * kRows + tid);
     };
@@ -505,13 +512,12 @@ Plan make_plan(int M, int N, int Hq, int Hkv, int nseq) {
         // keys on their way, and a few workgroups more than a round cost another (1024 workgroups and more, us -> one round:
         // 20000 keys, 300 rows 135 -> 135 in 12 slices, 152 in 13; 16384, 128 rows 54.3 -> 52.4; 131072, 16 rows 108 -> 105).
         constexpr int kRound = 512;
-        double best = 0.0;
-        for (int r = 1; r <= 4 && best < 0.85; ++r) {
-            const long long cut = std::max(1LL, kRound * r / per_slice);
-            const double full = (double)(cut * per_slice) / ((cut * per_slice + kRound - 1) / kRound * kRound);
-            if (full > best) {
-                best = full;
+        const int most = want;  // never more slices, hence never more scratch, than those 1024 workgroups take
+        for (int r = 1; r <= 2 && kRound * r / per_slice <= most; ++r) {
+            const long long cut = kRound * r / per_slice;
+            if (cut * per_slice * 100 >= 85 * kRound * r) {
                 want = (int)cut;
+                break;
             }
         }
     }

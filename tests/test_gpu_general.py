@@ -597,3 +597,13 @@ def test_score_attn_rows_that_leave_waves_without_a_tile(N, M, Hq, Hkv, d):
     rn = _draw(N + M, BF16)
     q, k = rn(M, Hq, d), rn(N, Hkv, d)
     assert_close(f(strd.score_attn(q.to(DEV), k.to(DEV))), oracle.score_attn(f(q), f(k)), BOUND[BF16], "s", units=(0,))
+
+
+@pytest.mark.parametrize("M,Hq,Hkv", [(8213, 8, 1), (600, 24, 2), (1280, 2, 2)])
+def test_score_attn_of_many_rows(M, Hq, Hkv):
+    """257, 58 and 10 workgroups per slice of keys: no whole number of the chip's rounds, nearly one, and one of more than its slices;
+    chunks of 128 rows copied whole and, in the first two, a last one of 40 and 32 rows."""
+    _say("score_attn many rows M=%d Hq=%d Hkv=%d" % (M, Hq, Hkv))
+    rn = _draw(M + Hq, BF16)
+    q, k = rn(M, Hq, 64), rn(700, Hkv, 64)
+    assert_close(f(strd.score_attn(q.to(DEV), k.to(DEV))), oracle.score_attn(f(q), f(k)), BOUND[BF16], "s", units=(0,))

@@ -329,6 +329,19 @@ def test_scores_of_one_sequence_and_of_a_batch_refuse_the_same_scales(scale, io)
     assert one == packed == (-3 if scale > 0 else -1)
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(32, 8), (28, 4), (8, 1)])
+def test_scores_need_no_more_scratch_than_1024_workgroups_take(Hq, Hkv):
+    """Two floats per query row and key slice, one per row (their number to 64) and one per key and kv head, to 256 bytes; the slices
+    at most those that 1024 workgroups of 256 rows and one kv head need, from one text row to more rows than that."""
+    need = binding.lib().strd_score_attn_workspace
+    for M in [1, 16, 100, 512, 1200, 3000, 8213, 12000]:
+        rows = M * Hq
+        slices = -(-1024 // (-(-(rows // Hkv) // 256) * Hkv))
+        for N in [1, 130, 2000, 5013, 16384, 131072]:
+            most = 4 * (2 * rows * min(slices, -(-N // 128)) + -(-rows // 64) * 64 + Hkv * N)
+            assert need(M, N, Hq, Hkv, 128, 1) <= -(-most // 256) * 256, (M, N)
+
+
 def test_workspace_of_the_general_scan_is_bounded():
     """The states of one round of chunks (256 MB, or one chunk) and two states between rounds, whatever the length."""
     ws = lambda T, H, P, n: strd.lib().strd_ssd_prefill_workspace(T, H, P, 1, n, 256, binding.STRD_F32)
