@@ -607,3 +607,13 @@ def test_score_attn_of_many_rows(M, Hq, Hkv):
     rn = _draw(M + Hq, BF16)
     q, k = rn(M, Hq, 64), rn(700, Hkv, 64)
     assert_close(f(strd.score_attn(q.to(DEV), k.to(DEV))), oracle.score_attn(f(q), f(k)), BOUND[BF16], "s", units=(0,))
+
+
+@pytest.mark.parametrize("H,G,n", [(64, 1, 128), (8, 1, 64), (48, 2, 128), (80, 1, 64), (20, 1, 128), (70, 1, 64), (32, 2, 64)])
+def test_score_mamba_heads_of_a_group(H, G, n):
+    """dt of 8 to 80 heads of a group added up beside the products: 16 bytes at a time (8, 16, 20, 24, 64, 80 heads) and one by one (70)."""
+    _say("score_mamba heads H=%d G=%d n=%d" % (H, G, n))
+    rn = _draw(H + n, BF16)
+    B, C, dt = rn(300, G, n), rn(37, G, n), rn(300, H).float().abs()
+    got = strd.score_mamba(B.to(DEV), C.to(DEV), dt.to(DEV))
+    assert_close(f(got), oracle.score_mamba(f(B), f(C), f(dt)), BOUND[BF16], "s", units=(0,))
