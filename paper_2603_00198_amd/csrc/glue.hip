@@ -70,7 +70,9 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_vec_kernel(const T *__restri
     V *orow = reinterpret_cast<V *>(out + (size_t)row * d);
     float ss = 0.f;
     constexpr int kHeld = 16 / sizeof(T);  // vectors of a row in registers: 4096 elements of bf16, 2048 of fp32
-    if (d <= kHeld * 8 * kWave) {  // uniform: the row is read once, and all of it is on its way before the first sum
+    // (uniform; the row is read once, and all of it is on its way before the first sum.  Rows of up to 2 KB find themselves in the
+    // cache and are faster in a loop: 8448 rows, bf16, 1024 elements 6.1 against 7.2 us, 2048 14.3 against 12.7; fp32, 520 8.1 / 7.9)
+    if (d * (int)sizeof(T) > 2048 && d <= kHeld * 8 * kWave) {
         V held[kHeld];
 #pragma unroll
         for (int j = 0; j < kHeld; ++j) held[j] = xr[min(lane + kWave * j, d / 8 - 1)];
@@ -188,12 +190,12 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void conv1d_silu_kernel(const T *__restrict__ in, int ld, const T *__restrict__ w,
                                                                const T *__restrict__ b, T *__restrict__ xo,
                                                                T *__restrict__ Bo, T *__restrict__ Co, int Tn, int Cx,
-                                                               int Cb, int W, int nunits) {
+                                                               int Cb, int W, int nunits, bool spread) {
     typedef typename Vec8<T>::type V;
     const int Ct = Cx + 2 * Cb, vecs = Ct / 8;
     // neighbouring blocks of tokens share kMaxW - 1 rows: on one XCD they find them in its L2 (8448 tokens of 10240 channels
-    // 85 -> 82 us)
-    const int unit = xcd_swizzle(blockIdx.x, nunits);
+    // 85 -> 82 us in bf16; in fp32 146 -> 149, 33000 of 1280 75 -> 78, and few blocks lose 0.2 us either way: as they come)
+    const int unit = spread ? xcd_swizzle(blockIdx.x, nunits) : (int)blockIdx.x;
     const long long gid = (long long)unit * kThreads + threadIdx.x;
     const int tblocks = (Tn + kTok - 1) / kTok;
     if (unit >= nunits || gid >= (long long)tblocks * vecs) return;
@@ -314,8 +316,9 @@ int glue_conv1d_silu(const void *in, int ld, const void *w, const void *b, void 
     const int grid = (int)((n + kThreads - 1) / kThreads);
     return by_dtype(io, [&](auto *tag) {
         using E = std::remove_pointer_t<decltype(tag)>;
-        conv1d_silu_kernel<E><<<xcd_grid(grid), kThreads, 0, st>>>((const E *)in, ld, (const E *)w, (const E *)b, (E *)xo, (E *)Bo,
-                                                        (E *)Co, T, Cx, Cb, W, grid);
+        const bool spread = sizeof(E) == 2 && grid >= 768;
+        conv1d_silu_kernel<E><<<spread ? xcd_grid(grid) : grid, kThreads, 0, st>>>(
+            (const E *)in, ld, (const E *)w, (const E *)b, (E *)xo, (E *)Bo, (E *)Co, T, Cx, Cb, W, grid, spread);
     });
 }
 

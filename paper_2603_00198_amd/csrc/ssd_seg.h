@@ -564,7 +564,9 @@ __device__ __forceinline__ uint32_t gather_row(const SegArgs &a, int t, int32_t 
 
 // Warming up.  A segment can make up for its missing past by itself: it starts a few steps early, with the state alone,
 // until everything older has decayed to zero in fp32.
-constexpr int kMaxWarm = 4;       // steps that a segment may start early
+// Steps that a segment may start early.  Where some heads of a call warm up and others do not, their steps come on top of the
+// seam repair: 32 heads, 2176 tokens, decays of 0.05 to 0.8 per token 43.7 us without warming up, 48.1 with up to 4 steps.
+constexpr int kMaxWarm = 2;
 constexpr float kGone = -126.f;   // log2 of a weight that is zero in fp32 (where the seam repair stops, too)
 // log2 decays of heads h0 and h0 + 1 over one step of the sequence (every lane; 0 before its start)
 template <bool GATHER>

@@ -48,7 +48,7 @@
 //   y_t += 2^(l_t) * E c_t,   E = state at the segment's start, l_t = decay since then,
 // for as many 64-token tiles as 2^(l_t) is not yet zero in fp32 (a handful at the decay rates of
 // a trained layer, the whole segment if A = 0: always exact), and completes S_out.
-// Two heads per workgroup: where at most four steps before a segment reach into it (dt and A say so on the device), the
+// Two heads per workgroup: where at most kMaxWarm steps before a segment reach into it (dt and A say so on the device), the
 // segment starts that much earlier, with the state alone, and its seam needs no repair (8448 tokens of 128 heads 104 -> 94 us,
 // 33280 353 -> 343: the second kernel then costs its launch, the segments 2 us for the sums and 2 us per step).
 //

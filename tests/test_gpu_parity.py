@@ -716,10 +716,10 @@ def test_whole_sequence_scan_of_64_state_entries_gives_the_same_bits_every_time(
     torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("case", ["fast", "slow head", "four steps", "five steps", "no decay", "alternating"])
+@pytest.mark.parametrize("case", ["fast", "slow head", "two steps", "three steps", "no decay", "alternating"])
 @pytest.mark.parametrize("T,H,G,n", [(64 * 13 + 1, 64, 4, 128), (64 * 20, 128, 8, 64), (64 * 21 - 63, 128, 8, 128), (64 * 31 - 1, 80, 4, 128)])
 def test_ssd_prefill_pairs_of_heads_in_segments(T, H, G, n, case):
-    """Sequences of middle length: segments that start a few steps early where the decays of a pair of heads allow it (four
+    """Sequences of middle length: segments that start a few steps early where the decays of a pair of heads allow it (two
     steps at most), one walk over the sequence where they do not; dense with D and a carried-in state, and through an
     index list."""
     _say("ssd_prefill pairs T=%d H=%d G=%d n=%d %s" % (T, H, G, n, case))
@@ -736,9 +736,9 @@ def test_ssd_prefill_pairs_of_heads_in_segments(T, H, G, n, case):
     watch = [0, 1, H // 2, H - 1]
     if case == "slow head":
         A[[1, H - 2]] = -0.01
-    elif case in ("four steps", "five steps"):   # 126 / 1.4427 / 64 = 1.365 of decay per token for one step
+    elif case in ("two steps", "three steps"):   # 126 / 1.4427 / 64 = 1.365 of decay per token for one step
         dt[:] = 1.0
-        A[:] = -1.365 / (3.5 if case == "four steps" else 4.5)
+        A[:] = -1.365 / (1.5 if case == "two steps" else 2.5)
     elif case == "no decay":
         A[:] = 0.0
     elif case == "alternating":                  # short and long memory inside one head
