@@ -56,10 +56,14 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_kernel(const T *__restrict__
     for (int c = threadIdx.x; c < d; c += kThreads) orow[c] = from_f32<T>(to_f32(xr[c]) * inv * to_f32(w[c]));
 }
 
+// vectors of a row that a lane holds: 4096 elements of bf16, 2048 of fp32 in a wave
+template <typename T>
+constexpr int held_vecs() { return 16 / sizeof(T); }
+
 // Same, one wave per row with 8-element vectors (d % 8 == 0, 16-byte aligned rows): no barrier.  Rows of up to 8 KB stay in
 // registers, all of a row requested at once (8448 rows of 4096 in bf16 37.5 -> 28 us, 4.9 TB/s; 33 -> 26 at best); of longer ones
 // the second pass re-reads the row from the cache.
-template <typename T>
+template <typename T, bool HELD>
 __global__ __launch_bounds__(kThreads) void rmsnorm_vec_kernel(const T *__restrict__ x, const T *__restrict__ w,
                                                                T *__restrict__ out, int Tn, int d, float eps) {
     typedef typename Vec8<T>::type V;
@@ -69,10 +73,8 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_vec_kernel(const T *__restri
     const V *wr = reinterpret_cast<const V *>(w);
     V *orow = reinterpret_cast<V *>(out + (size_t)row * d);
     float ss = 0.f;
-    constexpr int kHeld = 16 / sizeof(T);  // vectors of a row in registers: 4096 elements of bf16, 2048 of fp32
-    // (uniform; the row is read once, and all of it is on its way before the first sum.  Rows of up to 2 KB find themselves in the
-    // cache and are faster in a loop: 8448 rows, bf16, 1024 elements 6.1 against 7.2 us, 2048 14.3 against 12.7; fp32, 520 8.1 / 7.9)
-    if (d * (int)sizeof(T) > 2048 && d <= kHeld * 8 * kWave) {
+    constexpr int kHeld = held_vecs<T>();
+    if constexpr (HELD) {  // the row is read once, and all of it is on its way before the first sum
         V held[kHeld];
 #pragma unroll
         for (int j = 0; j < kHeld; ++j) held[j] = xr[min(lane + kWave * j, d / 8 - 1)];
@@ -283,8 +285,13 @@ int glue_rmsnorm(const void *x, const void *w, void *out, int T, int d, float ep
     const bool vec = d % 8 == 0 && !((uintptr_t)x % (8 * es)) && !((uintptr_t)w % (8 * es)) && !((uintptr_t)out % (8 * es));
     return by_dtype(io, [&](auto *tag) {
         using E = std::remove_pointer_t<decltype(tag)>;
-        if (vec)
-            rmsnorm_vec_kernel<E><<<ceil_div(T, kThreads / kWave), kThreads, 0, st>>>((const E *)x, (const E *)w, (E *)out, T,
+        // Rows of up to 2 KB come faster in the loop, with more waves in flight than the held row's registers leave: 8448 rows, bf16, 1024
+        // elements 6.1 us (held 7.2), 2048 14.3 (12.7); fp32, 64 elements 4.2 (5.0), 520 8.1 (7.9); 33000 rows of 64, bf16, 7.8 (12.2).
+        if (vec && d * (int)es > 2048 && d <= held_vecs<E>() * 8 * kWave)
+            rmsnorm_vec_kernel<E, true><<<ceil_div(T, kThreads / kWave), kThreads, 0, st>>>((const E *)x, (const E *)w, (E *)out, T,
+                                                                                          d, eps);
+        else if (vec)
+            rmsnorm_vec_kernel<E, false><<<ceil_div(T, kThreads / kWave), kThreads, 0, st>>>((const E *)x, (const E *)w, (E *)out, T,
                                                                                     d, eps);
         else
             rmsnorm_kernel<E><<<T, kThreads, 0, st>>>((const E *)x, (const E *)w, (E *)out, d, eps);
