@@ -628,10 +628,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 3))
 // makes up for its missing past by itself: it starts `warm` steps early, with the state alone, as many as it takes for
 // everything older to have decayed to zero in fp32 (or to reach the start of the sequence), so no second launch and no
 // workspace are needed and no output is touched twice.  How many that are, dt says, on the device: every workgroup of a
-// pair of heads adds up the steps before each seam, and where one of them needs more than seg::kMaxWarm all of them walk the
+// pair of heads adds up the steps before each seam, and where one of them needs more than kMaxWarm all of them walk the
 // whole sequence instead, as 2 heads x 2 slabs.  (As everywhere in this library, a weight that is zero in fp32 is no
 // weight: a value of x that is not finite reaches the later tokens of its own segment and of those that warm up on it.)
 constexpr int kMidSegs = 8;   // segments at most
+constexpr int kMaxWarm = 2;   // steps that a segment may start early
+constexpr float kGone = -126.f;  // log2 of a weight that is zero in fp32 (the rule of the seam repair in ssd_seg_mfma.hip)
 
 template <int NS, bool GATHER>
 __global__ __launch_bounds__(kThreads) void ssd_mid_kernel(seg::SegArgs a, int first_steps, int nunits) {
@@ -641,14 +643,34 @@ __global__ __launch_bounds__(kThreads) void ssd_mid_kernel(seg::SegArgs a, int f
     const int pair = unit / a.nseg, part = unit % a.nseg, h0 = 2 * pair, lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int seams = a.nseg - 1;
-    float2(*decay)[seg::kMaxWarm] = reinterpret_cast<float2(*)[seg::kMaxWarm]>(smem_raw);  // of the steps before each seam
-    for (int t = wave; t < seams * seg::kMaxWarm; t += kThreads / 64) {
-        const int s = t / seg::kMaxWarm, k = t % seg::kMaxWarm;
-        const float2 v = seg::step_decay<GATHER>(a, h0, first_steps + s * a.seg_steps - (1 + k));
-        if (lane == 0) decay[s][k] = v;
+    const float al0 = a.A[h0] * kLog2e, al1 = a.A[h0 + 1] * kLog2e;
+    float2(*sums)[kMaxWarm] = reinterpret_cast<float2(*)[kMaxWarm]>(smem_raw);  // log2 decays of both heads over one step
+    for (int t = wave; t < seams * kMaxWarm; t += kThreads / 64) {
+        const int step = first_steps + t / kMaxWarm * a.seg_steps - (1 + t % kMaxWarm);
+        float v0 = 0.f, v1 = 0.f;
+        if (step >= 0) {
+            const int tok = step * kQ + lane;
+            const size_t row = GATHER ? seg::gather_row(a, tok, a.idx[min(tok, a.K - 1)]) : (size_t)tok;
+            v0 = a.dt[row * a.H + h0];
+            v1 = a.dt[row * a.H + h0 + 1];
+        }
+        v0 = read_lane_f32(wave_inclusive_scan_f32(v0), 63);
+        v1 = read_lane_f32(wave_inclusive_scan_f32(v1), 63);
+        if (lane == 0) sums[t / kMaxWarm][t % kMaxWarm] = make_float2(v0 * al0, v1 * al1);
     }
     __syncthreads();
-    const int need = lane < seams ? seg::warm_steps(decay[lane], first_steps + lane * a.seg_steps) : 0;  // of segment lane + 1
+    int need = lane < seams ? -1 : 0;  // lane s: steps that segment s + 1 starts early, -1: more than there may be
+    if (need < 0) {
+        float c0 = 0.f, c1 = 0.f;
+        for (int k = 0; k < kMaxWarm && need < 0; ++k) {
+            c0 += sums[lane][k].x;
+            c1 += sums[lane][k].y;
+            if (k + 1 >= first_steps + lane * a.seg_steps)
+                need = k + 1;  // the start of the sequence
+            else if (c0 < kGone && c1 < kGone)
+                need = k + 1;
+        }
+    }
     __syncthreads();
     if (!__all(need >= 0)) {
         if (part < 4)
@@ -666,7 +688,7 @@ __global__ __launch_bounds__(kThreads) void ssd_mid_kernel(seg::SegArgs a, int f
     const float *s_src = s0 == warm ? a.S_in : nullptr;
     float *s_dst = part == a.nseg - 1 ? a.S_out : nullptr;
     if (wave < 4) {
-        seg::compute_wave<NS, 2, 2, GATHER>(lds, a, wave >> 1, wave & 1, h0 + (wave >> 1), 0, nloc, s_src, s_dst, warm);
+        seg::compute_wave<NS, 2, 2, GATHER, true>(lds, a, wave >> 1, wave & 1, h0 + (wave >> 1), 0, nloc, s_src, s_dst, warm);
         return;
     }
     switch (wave) {

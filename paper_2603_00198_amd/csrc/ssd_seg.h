@@ -154,8 +154,8 @@ __device__ __forceinline__ void settle_c_pieces(strd_s16x4 (&r)[2 * KS]) {
 }
 
 // ---- compute wave: the slab of 32 channels at column 32 * cw of the workgroup's x tile: (d), (e) ----
-// `warm`: steps at the start that only bring the state up to date -- (e) alone, no outputs.
-template <int NS, int NC, int NH, bool GATHER>
+// WARM: the first `warm` steps only bring the state up to date -- (e) alone, no outputs.
+template <int NS, int NC, int NH, bool GATHER, bool WARM = false>
 __device__ __forceinline__ void compute_wave(LdsS<NS, NC, NH> &lds, const SegArgs &a, int hh, int cw, int h, int pin, int nloc,
                                              const float *s_src, float *s_dst, int warm = 0) {
     using L = LdsS<NS, NC, NH>;
@@ -215,7 +215,7 @@ __device__ __forceinline__ void compute_wave(LdsS<NS, NC, NH> &lds, const SegArg
         // 32 ks + 16 + 4 lb + s - 4 (s >= 4) of row p; the c fragments are read in the same slot order
         // (two 8-byte reads).  Once the bf16 copy exists the accumulators are free: their decay, which
         // (e) needs, is interleaved with the products of (d), so that vector and matrix pipe overlap.
-        if (NH == 1 || i >= warm) {
+        if (!WARM || i >= warm) {
             bf16x8 sb[2][KS];
 #pragma unroll
             for (int pt = 0; pt < 2; ++pt)
@@ -301,11 +301,11 @@ __device__ __forceinline__ void compute_wave(LdsS<NS, NC, NH> &lds, const SegArg
 // ---- G wave GW: (a), (b), (c) and the outputs of the query blocks {0, 3} (GW = 0) or {1, 2} (GW = 1) ----
 // The outputs of a step leave one step late: (a)-(c) of step i are summed up in registers during step i,
 // the carried part arrives from the compute waves with the barrier that ends the step.
-// `warm`: steps at the start in which there is nothing to do.  FINE: the weights of the diagonal blocks keep 16 bits: what
-// their truncation to bf16 leaves behind goes through (c) as a second operand.  A decay of a few tokens puts nearly all
+// WARM: nothing to do in the first `warm` steps; and the weights of the diagonal blocks keep 16 bits: what their
+// truncation to bf16 leaves behind goes through (c) as a second operand.  A decay of a few tokens puts nearly all
 // weight there, so this takes 0.28 of the error out (2.32e-3 -> 1.67e-3 at the decays of a trained layer), which more
 // than pays for the rounding of the carried part (2.327e-3) down to a decay of 2^(-0.05) per token.
-template <int NS, int NC, int NH, int GW, bool GATHER, bool FINE = false>
+template <int NS, int NC, int NH, int GW, bool GATHER, bool WARM = false>
 __device__ __forceinline__ void g_wave(LdsS<NS, NC, NH> &lds, const SegArgs &a, int hh, int h, int chan0, int tok0, int nloc,
                                        int warm = 0) {
     using L = LdsS<NS, NC, NH>;
@@ -341,12 +341,12 @@ __device__ __forceinline__ void g_wave(LdsS<NS, NC, NH> &lds, const SegArgs &a, 
     auto emit_read = [&](int j) __attribute__((always_inline)) {
 #pragma unroll
         for (int pt = 0; pt < PT; ++pt) {
-            ia[pt] = lds.yin[(j + warm) & 1][hh][TA * PT + pt][lane];
-            ib[pt] = lds.yin[(j + warm) & 1][hh][TB * PT + pt][lane];
+            ia[pt] = lds.yin[j & 1][hh][TA * PT + pt][lane];
+            ib[pt] = lds.yin[j & 1][hh][TB * PT + pt][lane];
         }
     };
     auto emit_turn = [&](int j) __attribute__((always_inline)) {
-        char *sta = reinterpret_cast<char *>(&lds.yin[(j + warm) & 1][hh][TA * PT][0]), *stb = reinterpret_cast<char *>(&lds.yin[(j + warm) & 1][hh][TB * PT][0]);
+        char *sta = reinterpret_cast<char *>(&lds.yin[j & 1][hh][TA * PT][0]), *stb = reinterpret_cast<char *>(&lds.yin[j & 1][hh][TB * PT][0]);
 #pragma unroll
         for (int pt = 0; pt < PT; ++pt) {
             bf16x4 oa, ob;
@@ -362,7 +362,7 @@ __device__ __forceinline__ void g_wave(LdsS<NS, NC, NH> &lds, const SegArgs &a, 
         }
     };
     auto emit_back = [&](int j) __attribute__((always_inline)) {
-        const char *sta = reinterpret_cast<const char *>(&lds.yin[(j + warm) & 1][hh][TA * PT][0]), *stb = reinterpret_cast<const char *>(&lds.yin[(j + warm) & 1][hh][TB * PT][0]);
+        const char *sta = reinterpret_cast<const char *>(&lds.yin[j & 1][hh][TA * PT][0]), *stb = reinterpret_cast<const char *>(&lds.yin[j & 1][hh][TB * PT][0]);
 #pragma unroll
         for (int k = 0; k < 16 / RPI; ++k) {
             const int r = srow + RPI * k;
@@ -386,14 +386,13 @@ __device__ __forceinline__ void g_wave(LdsS<NS, NC, NH> &lds, const SegArgs &a, 
     __syncthreads();
     __syncthreads();
 
-    for (int i = 0; i < warm; ++i) lds_barrier();
-    nloc -= warm;  // from here on steps count from the first one with outputs
-    tok0 += warm * kQ;
-    for (int i = 0; i < nloc; ++i) {
-        const typename L::Scan &sc = lds.scan[hh][(i + warm) & 1];
-        const typename L::TileBC &tb = lds.bc[(i + warm) % L::kRB];
-        const bf16_t *xt = lds.xr[(i + warm) % L::kRX].x;
-        const bool prev = i > 0;  // uniform: the step before has outputs waiting
+    if (WARM)
+        for (int i = 0; i < warm; ++i) lds_barrier();
+    for (int i = WARM ? warm : 0; i < nloc; ++i) {
+        const typename L::Scan &sc = lds.scan[hh][i & 1];
+        const typename L::TileBC &tb = lds.bc[i % L::kRB];
+        const bf16_t *xt = lds.xr[i % L::kRX].x;
+        const bool prev = i > (WARM ? warm : 0);  // uniform: the step before has outputs waiting
         // fragments: b rows of key blocks 0..TB, c rows of the two query blocks
         strd_s16x4 xr8[NC][8];
         f32x4 ga[TA + 1], gb[TB + 1];
@@ -484,7 +483,7 @@ __device__ __forceinline__ void g_wave(LdsS<NS, NC, NH> &lds, const SegArgs &a, 
                 for (int e = 0; e < 4; ++e) {
                     float val = g[e] * fast_exp2(el_t - elj[e]) * dtj[e] + dskip[e];
                     val = (4 * lb + e <= lr) ? val : 0.f;  // causal mask
-                    if constexpr (FINE) {
+                    if constexpr (WARM) {
                         const uint32_t bits = __builtin_bit_cast(uint32_t, val) & 0xFFFF0000u;  // towards 0: never an overflow
                         mv[e] = __builtin_bit_cast(bf16_t, (uint16_t)(bits >> 16));
                         rest[e] = (bf16_t)(val - __builtin_bit_cast(float, bits));
@@ -504,7 +503,7 @@ __device__ __forceinline__ void g_wave(LdsS<NS, NC, NH> &lds, const SegArgs &a, 
             if (jt <= TA) ma[jt] = weigh(TA, jt, ga[jt <= TA ? jt : 0], el_a, era, fja[jt < TA ? jt : 0], elj_a, dtj_a, resta);
             if (jt <= TB) mb[jt] = weigh(TB, jt, gb[jt <= TB ? jt : 0], el_b, erb, fjb[jt < TB ? jt : 0], elj_b, dtj_b, restb);
         }
-        if constexpr (FINE) {  // a weight that is not finite has no rest (inf - inf would make an output NaN that is inf)
+        if constexpr (WARM) {  // a weight that is not finite has no rest (inf - inf would make an output NaN that is inf)
             float big = 0.f;
 #pragma unroll
             for (int e = 0; e < 4; ++e) big = fmaxf(big, fmaxf(fabsf((float)ma[TA][e]), fabsf((float)mb[TB][e])));
@@ -540,7 +539,7 @@ __device__ __forceinline__ void g_wave(LdsS<NS, NC, NH> &lds, const SegArgs &a, 
                 if (2 * kr <= TA) ya[pt] = mfma16(xf[pt >> 1][kr][pt & 1], cat8(ma[2 * kr], ma[2 * kr + 1]), ya[pt]);
                 if (2 * kr <= TB) yb[pt] = mfma16(xf[pt >> 1][kr][pt & 1], cat8(mb[2 * kr], mb[2 * kr + 1]), yb[pt]);
             }
-            if constexpr (FINE) {
+            if constexpr (WARM) {
                 ya[pt] = mfma16(xf[pt >> 1][TA / 2][pt & 1], TA % 2 ? cat8(zero4, resta) : cat8(resta, zero4), ya[pt]);
                 yb[pt] = mfma16(xf[pt >> 1][TB / 2][pt & 1], TB % 2 ? cat8(zero4, restb) : cat8(restb, zero4), yb[pt]);
             }
@@ -562,40 +561,9 @@ __device__ __forceinline__ uint32_t gather_row(const SegArgs &a, int t, int32_t 
     return min((uint32_t)(t < a.K ? kept : a.N + (t - a.K)), last_row);
 }
 
-// Warming up.  A segment can make up for its missing past by itself: it starts a few steps early, with the state alone,
-// until everything older has decayed to zero in fp32.
-// Steps that a segment may start early.  Where some heads of a call warm up and others do not, their steps come on top of the
-// seam repair: 32 heads, 2176 tokens, decays of 0.05 to 0.8 per token 43.7 us without warming up, 48.1 with up to 4 steps.
-constexpr int kMaxWarm = 2;
-constexpr float kGone = -126.f;   // log2 of a weight that is zero in fp32 (where the seam repair stops, too)
-// log2 decays of heads h0 and h0 + 1 over one step of the sequence (every lane; 0 before its start)
-template <bool GATHER>
-__device__ __forceinline__ float2 step_decay(const SegArgs &a, int h0, int step) {
-    const int tok = step * kQ + (int)(threadIdx.x & 63);
-    float v0 = 0.f, v1 = 0.f;
-    if (step >= 0) {
-        const size_t row = GATHER ? gather_row(a, tok, a.idx[min(tok, a.K - 1)]) : (size_t)tok;
-        v0 = a.dt[row * a.H + h0];
-        v1 = a.dt[row * a.H + h0 + 1];
-    }
-    v0 = read_lane_f32(wave_inclusive_scan_f32(v0), 63);
-    v1 = read_lane_f32(wave_inclusive_scan_f32(v1), 63);
-    return make_float2(v0 * (a.A[h0] * kLog2e), v1 * (a.A[h0 + 1] * kLog2e));
-}
-// The steps to start early by, from the decays of the kMaxWarm steps before a seam at step `first`; -1: more than that.
-__device__ __forceinline__ int warm_steps(const float2 *decay, int first) {
-    float c0 = 0.f, c1 = 0.f;
-    for (int k = 0; k < kMaxWarm; ++k) {
-        c0 += decay[k].x;
-        c1 += decay[k].y;
-        if (k + 1 >= first || (c0 < kGone && c1 < kGone)) return k + 1;  // (or the start of the sequence)
-    }
-    return -1;
-}
-
 // ---- helper wave: dt copies, the scans of the workgroup's heads, the row tables of the gather form ----
 template <int NS, int NC, int NH, bool GATHER>
-__device__ __forceinline__ void helper_wave(LdsS<NS, NC, NH> &lds, const SegArgs &a, int h0, int tok0, int nloc, int seg, int warm = 0) {
+__device__ __forceinline__ void helper_wave(LdsS<NS, NC, NH> &lds, const SegArgs &a, int h0, int tok0, int nloc, int seg) {
     using L = LdsS<NS, NC, NH>;
     const int lane = threadIdx.x & 63;
     float Al2[NH];
@@ -678,9 +646,9 @@ __device__ __forceinline__ void helper_wave(LdsS<NS, NC, NH> &lds, const SegArgs
             async_tile_wait();
         lds_barrier();
     }
-    if (lane == 0 && a.ltot) {  // (a segment that has warmed up keeps nothing of what is older)
+    if (lane == 0 && a.ltot) {
 #pragma unroll
-        for (int hh = 0; hh < NH; ++hh) a.ltot[(size_t)seg * a.H + h0 + hh] = warm ? -INFINITY : ltot[hh];
+        for (int hh = 0; hh < NH; ++hh) a.ltot[(size_t)seg * a.H + h0 + hh] = ltot[hh];
     }
 }
 

@@ -48,9 +48,6 @@
 //   y_t += 2^(l_t) * E c_t,   E = state at the segment's start, l_t = decay since then,
 // for as many 64-token tiles as 2^(l_t) is not yet zero in fp32 (a handful at the decay rates of
 // a trained layer, the whole segment if A = 0: always exact), and completes S_out.
-// Two heads per workgroup: where at most kMaxWarm steps before a segment reach into it (dt and A say so on the device), the
-// segment starts that much earlier, with the state alone, and its seam needs no repair (8448 tokens of 128 heads 104 -> 94 us,
-// 33280 353 -> 343: the second kernel then costs its launch, the segments 2 us for the sums and 2 us per step).
 //
 // GATHER: token t of the sequence is row idx[t] (t < K) or N + t - K of the tensors, i.e. the
 // kernel reads the uncompacted x, dt, B, C through the kept-index list instead of a compacted copy.
@@ -74,47 +71,33 @@ __global__ __launch_bounds__(threads_for(NC, NH)) void ssd_seg_kernel(SegArgs a,
     const int h0 = chan0 / a.P, pin = chan0 % a.P, g = h0 / (a.H / a.G);
     const int nsteps = (a.T + kQ - 1) / kQ;
     const int s0 = seg * a.seg_steps;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    // Two heads: a segment warms up where a few steps are enough for that, and its seam needs no repair.
-    int warm = 0;
-    if constexpr (NH == 2) {
-        if (seg > 0) {
-            float2 *decay = reinterpret_cast<float2 *>(smem_raw);
-            if (wave < kMaxWarm) {
-                const float2 v = step_decay<GATHER>(a, h0, s0 - 1 - wave);
-                if ((threadIdx.x & 63) == 0) decay[wave] = v;
-            }
-            __syncthreads();
-            warm = __builtin_amdgcn_readfirstlane(max(warm_steps(decay, s0), 0));
-            __syncthreads();
-        }
-    }
-    const int nloc = warm + min(a.seg_steps, nsteps - s0);
-    const int tok0 = (s0 - warm) * kQ;
+    const int nloc = min(a.seg_steps, nsteps - s0);
+    const int tok0 = s0 * kQ;
     // where the segment's state comes from and goes to
-    const float *s_src = s0 == warm ? a.S_in : nullptr;
+    const float *s_src = seg == 0 ? a.S_in : nullptr;
     float *s_dst = seg == a.nseg - 1 ? a.S_out : a.lend + (size_t)seg * a.H * a.P * NS;
     // Wave i runs on SIMD i % 4.  NH = 1, NC = 2: the compute waves have SIMDs 0 and 1, the G waves 2 and 3, each
     // with one copy wave beside it.  NH = 2: every SIMD has one compute wave, one G wave and one copy wave, so
     // the vector work of one overlaps the matrix products of the other.
+    const int wave = threadIdx.x >> 6;
     if (wave < NH * NC) {
         const int hh = NH == 1 ? 0 : wave / NC, cw = NH == 1 ? wave : wave % NC;
-        compute_wave<NS, NC, NH, GATHER>(lds, a, hh, cw, h0 + hh, pin, nloc, s_src, s_dst, warm);
+        compute_wave<NS, NC, NH, GATHER>(lds, a, hh, cw, h0 + hh, pin, nloc, s_src, s_dst);
         return;
     }
     const int r = wave - NH * NC;
     if (r < 2 * NH) {
         const int hh = NH == 1 ? 0 : r >> 1;
         if (r & 1)
-            g_wave<NS, NC, NH, 1, GATHER>(lds, a, hh, h0 + hh, chan0 + hh * 32 * NC, tok0, nloc, warm);
+            g_wave<NS, NC, NH, 1, GATHER>(lds, a, hh, h0 + hh, chan0 + hh * 32 * NC, tok0, nloc);
         else
-            g_wave<NS, NC, NH, 0, GATHER>(lds, a, hh, h0 + hh, chan0 + hh * 32 * NC, tok0, nloc, warm);
+            g_wave<NS, NC, NH, 0, GATHER>(lds, a, hh, h0 + hh, chan0 + hh * 32 * NC, tok0, nloc);
         return;
     }
     switch (r - 2 * NH) {
         case 0: copy_wave<NS, NC, NH, 1, GATHER>(lds, a, g * NS * 2, tok0, nloc); break;
         case 1: copy_wave<NS, NC, NH, 2, GATHER>(lds, a, g * NS * 2, tok0, nloc); break;
-        case 2: helper_wave<NS, NC, NH, GATHER>(lds, a, h0, tok0, nloc, seg, warm); break;
+        case 2: helper_wave<NS, NC, NH, GATHER>(lds, a, h0, tok0, nloc, seg); break;
         default: copy_wave<NS, NC, NH, 0, GATHER>(lds, a, chan0 * 2, tok0, nloc); break;
     }
 }
@@ -154,7 +137,6 @@ __global__ __launch_bounds__(kFixThreads) void ssd_fix_kernel(SegArgs a) {
         }
         return;
     }
-    if (a.ltot[(size_t)b * a.H + h] == -INFINITY) return;  // the segment has warmed up
     const int HP = a.H * a.P, g = h / (a.H / a.G);
     const int tok0 = b * a.seg_steps * kQ;
     const int tend = min(a.T, (b + 1) * a.seg_steps * kQ);

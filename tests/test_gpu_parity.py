@@ -788,3 +788,29 @@ def test_rmsnorm_rows_in_registers_and_longer_ones(d, dtype):
     x, w = torch.randn(7, d, generator=g).to(dtype).to(DEV), torch.randn(d, generator=g).to(dtype).to(DEV)
     got = strd.rmsnorm(x, w, 1e-5)
     assert_close(synth.np64(got), oracle.rmsnorm(synth.np64(x), synth.np64(w), 1e-5), TOL[dtype], "rmsnorm")
+
+
+@pytest.mark.parametrize("H,G", [(32, 2), (31, 1)])   # two heads per workgroup, one
+@pytest.mark.parametrize("where", ["x", "dt", "S_in"])
+def test_ssd_prefill_values_that_are_not_finite_reach_over_a_seam(H, G, where):
+    """Segments of 8 steps: what is not finite in the state at a segment's end reaches the tokens behind the seam, however fast
+    the decays are, and every later token of its own segment."""
+    T, P, n, seg = 64 * 32, 64, 128, 64 * 8
+    g = torch.Generator().manual_seed(H)
+    x, B, C = (torch.randn(T, *s, generator=g).to(torch.bfloat16).to(DEV) for s in ((H, P), (G, n), (G, n)))
+    dt = torch.nn.functional.softplus(torch.randn(T, H, generator=g)).to(DEV)
+    A = (-torch.exp(2 * torch.rand(H, generator=g))).to(DEV)
+    S_in = torch.randn(H, P, n, generator=g).to(DEV)
+    h, p, t = H - 2, 3, 0 if where == "S_in" else 70
+    if where == "x":
+        x[t, h, p] = float("inf")
+    elif where == "dt":
+        dt[t, h] = float("nan")
+    else:
+        S_in[h, p, 5] = float("nan")
+    y, _ = strd.ssd_prefill(x, dt, A, B, C, S_in=S_in)
+    bad = ~torch.isfinite(y[:, h, p].float())
+    assert bad[t:seg].all() and bad[seg], "lost %s" % where
+    assert torch.isfinite(torch.cat([y[:, :h], y[:, h + 1:]], 1).float()).all()
+    if where != "dt":
+        assert torch.isfinite(torch.cat([y[:, h, :p], y[:, h, p + 1:]], 1).float()).all()
