@@ -37,11 +37,7 @@
 // state copy is double-buffered.  One workgroup barrier per step.  Rows past T are copies of the
 // last row with dt = 0, which makes them inert in (b)-(e); their y rows are not stored.  Each wave
 // runs a straight-line specialisation (compile-time trip counts).
-//
-// From about 20 steps on, pairs of heads walk segments of the sequence side by side where their decays are fast enough
-// (ssd_mid_kernel, below).
 #include "common.h"
-#include "ssd_seg.h"
 
 namespace strd {
 namespace {
@@ -580,14 +576,21 @@ __device__ __forceinline__ void copy_wave(Lds<NS> &lds, const bf16_t *__restrict
     }
 }
 
-// One workgroup's walk over a sequence: channels p0 .. p0 + 31 of head h.
 template <int NS, bool GATHER>
-__device__ __forceinline__ void walk(Lds<NS> &lds, const bf16_t *__restrict__ x, const float *__restrict__ dt,
-                                     const float *__restrict__ A, const bf16_t *__restrict__ B, const bf16_t *__restrict__ C,
-                                     const float *__restrict__ D, const float *__restrict__ S_in, bf16_t *__restrict__ y,
-                                     float *__restrict__ S_out, const int32_t *__restrict__ idx, int N, int K, int T, int H,
-                                     int P, int G, int h, int p0) {
-    const int g = h / (H / G), nsteps = (T + kQ - 1) / kQ;
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 3))) void ssd_mfma_kernel(
+    const bf16_t *__restrict__ x, const float *__restrict__ dt, const float *__restrict__ A,
+    const bf16_t *__restrict__ B, const bf16_t *__restrict__ C, const float *__restrict__ D,
+    const float *__restrict__ S_in, bf16_t *__restrict__ y, float *__restrict__ S_out,
+    const int32_t *__restrict__ idx, int N, int K, int T, int H, int P, int G, int nunits) {
+    using L = Lds<NS>;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    L &lds = *reinterpret_cast<L *>(smem_raw);
+
+    const int unit = xcd_swizzle(blockIdx.x, nunits);
+    if (unit >= nunits) return;
+    const int nslab = P / kPB;
+    const int h = unit / nslab, p0 = (unit % nslab) * kPB, g = h / (H / G);
+    const int nsteps = (T + kQ - 1) / kQ;
     switch (threadIdx.x >> 6) {
         case 0: output_wave<NS, 0, GATHER>(lds, D, y, T, H, P, h, p0, nsteps); break;
         case 1: output_wave<NS, 1, GATHER>(lds, D, y, T, H, P, h, p0, nsteps); break;
@@ -607,103 +610,6 @@ __device__ __forceinline__ void walk(Lds<NS> &lds, const bf16_t *__restrict__ x,
 }
 
 template <int NS, bool GATHER>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 3))) void ssd_mfma_kernel(
-    const bf16_t *__restrict__ x, const float *__restrict__ dt, const float *__restrict__ A,
-    const bf16_t *__restrict__ B, const bf16_t *__restrict__ C, const float *__restrict__ D,
-    const float *__restrict__ S_in, bf16_t *__restrict__ y, float *__restrict__ S_out,
-    const int32_t *__restrict__ idx, int N, int K, int T, int H, int P, int G, int nunits) {
-    using L = Lds<NS>;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    L &lds = *reinterpret_cast<L *>(smem_raw);
-
-    const int unit = xcd_swizzle(blockIdx.x, nunits);
-    if (unit >= nunits) return;
-    const int nslab = P / kPB;
-    walk<NS, GATHER>(lds, x, dt, A, B, C, D, S_in, y, S_out, idx, N, K, T, H, P, G, unit / nslab, (unit % nslab) * kPB);
-}
-
-// ---- sequences of middle length: pairs of heads in segments, where decays let them ----
-// The walk above takes a SIMD's time for 32 channels of one head; the waves of the segmented kernel (ssd_seg.h) take
-// about the same step for 64 channels of two, but need the sequence cut into segments to fill the chip.  Here a segment
-// makes up for its missing past by itself: it starts `warm` steps early, with the state alone, as many as it takes for
-// everything older to have decayed to zero in fp32 (or to reach the start of the sequence), so no second launch and no
-// workspace are needed and no output is touched twice.  How many that are, dt says, on the device: every workgroup of a
-// pair of heads adds up the steps before each seam, and where one of them needs more than kMaxWarm all of them walk the
-// whole sequence instead, as 2 heads x 2 slabs.  (As everywhere in this library, a weight that is zero in fp32 is no
-// weight: a value of x that is not finite reaches the later tokens of its own segment and of those that warm up on it.)
-constexpr int kMidSegs = 8;   // segments at most
-constexpr int kMaxWarm = 2;   // steps that a segment may start early
-constexpr float kGone = -126.f;  // log2 of a weight that is zero in fp32 (the rule of the seam repair in ssd_seg_mfma.hip)
-
-template <int NS, bool GATHER>
-__global__ __launch_bounds__(kThreads) void ssd_mid_kernel(seg::SegArgs a, int first_steps, int nunits) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    const int unit = xcd_swizzle(blockIdx.x, nunits);
-    if (unit >= nunits) return;
-    const int pair = unit / a.nseg, part = unit % a.nseg, h0 = 2 * pair, lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int seams = a.nseg - 1;
-    const float al0 = a.A[h0] * kLog2e, al1 = a.A[h0 + 1] * kLog2e;
-    float2(*sums)[kMaxWarm] = reinterpret_cast<float2(*)[kMaxWarm]>(smem_raw);  // log2 decays of both heads over one step
-    for (int t = wave; t < seams * kMaxWarm; t += kThreads / 64) {
-        const int step = first_steps + t / kMaxWarm * a.seg_steps - (1 + t % kMaxWarm);
-        float v0 = 0.f, v1 = 0.f;
-        if (step >= 0) {
-            const int tok = step * kQ + lane;
-            const size_t row = GATHER ? seg::gather_row(a, tok, a.idx[min(tok, a.K - 1)]) : (size_t)tok;
-            v0 = a.dt[row * a.H + h0];
-            v1 = a.dt[row * a.H + h0 + 1];
-        }
-        v0 = read_lane_f32(wave_inclusive_scan_f32(v0), 63);
-        v1 = read_lane_f32(wave_inclusive_scan_f32(v1), 63);
-        if (lane == 0) sums[t / kMaxWarm][t % kMaxWarm] = make_float2(v0 * al0, v1 * al1);
-    }
-    __syncthreads();
-    int need = lane < seams ? -1 : 0;  // lane s: steps that segment s + 1 starts early, -1: more than there may be
-    if (need < 0) {
-        float c0 = 0.f, c1 = 0.f;
-        for (int k = 0; k < kMaxWarm && need < 0; ++k) {
-            c0 += sums[lane][k].x;
-            c1 += sums[lane][k].y;
-            if (k + 1 >= first_steps + lane * a.seg_steps)
-                need = k + 1;  // the start of the sequence
-            else if (c0 < kGone && c1 < kGone)
-                need = k + 1;
-        }
-    }
-    __syncthreads();
-    if (!__all(need >= 0)) {
-        if (part < 4)
-            walk<NS, GATHER>(*reinterpret_cast<Lds<NS> *>(smem_raw), a.x, a.dt, a.A, a.B, a.C, a.D, a.S_in, a.y, a.S_out, a.idx, a.N, a.K, a.T, a.H,
-                             a.P, a.G, h0 + part / 2, part % 2 * kPB);
-        return;
-    }
-    using L = seg::LdsS<NS, 2, 2>;
-    L &lds = *reinterpret_cast<L *>(smem_raw);
-    const int warm = part == 0 ? 0 : __builtin_amdgcn_readlane(need, part - 1);
-    const int s0 = part == 0 ? 0 : first_steps + (part - 1) * a.seg_steps;  // first step of the segment
-    const int nsteps = (a.T + kQ - 1) / kQ;
-    const int nloc = warm + min(part == 0 ? first_steps : a.seg_steps, nsteps - s0);
-    const int tok0 = (s0 - warm) * kQ, chan0 = h0 * 64, g = h0 / (a.H / a.G);
-    const float *s_src = s0 == warm ? a.S_in : nullptr;
-    float *s_dst = part == a.nseg - 1 ? a.S_out : nullptr;
-    if (wave < 4) {
-        seg::compute_wave<NS, 2, 2, GATHER, true>(lds, a, wave >> 1, wave & 1, h0 + (wave >> 1), 0, nloc, s_src, s_dst, warm);
-        return;
-    }
-    switch (wave) {
-        case 4: seg::g_wave<NS, 2, 2, 0, GATHER, true>(lds, a, 0, h0, chan0, tok0, nloc, warm); break;
-        case 5: seg::g_wave<NS, 2, 2, 1, GATHER, true>(lds, a, 0, h0, chan0, tok0, nloc, warm); break;
-        case 6: seg::g_wave<NS, 2, 2, 0, GATHER, true>(lds, a, 1, h0 + 1, chan0 + 64, tok0, nloc, warm); break;
-        case 7: seg::g_wave<NS, 2, 2, 1, GATHER, true>(lds, a, 1, h0 + 1, chan0 + 64, tok0, nloc, warm); break;
-        case 8: seg::copy_wave<NS, 2, 2, 1, GATHER>(lds, a, g * NS * 2, tok0, nloc); break;
-        case 9: seg::copy_wave<NS, 2, 2, 2, GATHER>(lds, a, g * NS * 2, tok0, nloc); break;
-        case 10: seg::helper_wave<NS, 2, 2, GATHER>(lds, a, h0, tok0, nloc, part); break;
-        default: seg::copy_wave<NS, 2, 2, 0, GATHER>(lds, a, chan0 * 2, tok0, nloc); break;
-    }
-}
-
-template <int NS, bool GATHER>
 int launch(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D,
            const float *S_in, void *y, float *S_out, const int32_t *idx, int N, int K, int T, int H, int P, int G,
            hipStream_t st) {
@@ -714,41 +620,6 @@ int launch(const void *x, const float *dt, const float *A, const void *B, const 
     ssd_mfma_kernel<NS, GATHER><<<xcd_grid(nunits), kThreads, smem, st>>>(
         (const bf16_t *)x, dt, A, (const bf16_t *)B, (const bf16_t *)C, D, S_in, (bf16_t *)y, S_out, idx, N, K, T, H, P,
         G, nunits);
-    return launch_status();
-}
-
-struct MidPlan {
-    int nseg, first_steps, seg_steps;  // nseg = 0: the walk over the whole sequence instead
-};
-MidPlan mid_plan(int T, int H, int P, int G) {
-    constexpr int kCUs = 256;
-    MidPlan p = {0, 0, 0};
-    const int nsteps = (T + kQ - 1) / kQ, pairs = H / 2;
-    if (P != 2 * kPB || (H / G) % 2 != 0) return p;  // two heads of 64 channels with the same B and C
-    // One workgroup per CU.  (Two segments of 96 pairs leave CUs idle and were slower: 192 heads, 2752 tokens 104 us, 92 in one walk.)
-    const int nseg = min(kCUs / pairs, kMidSegs);
-    if (nseg < 4) return p;
-    // Two steps of every segment but the first go into warming up, as a rule: the first is that much longer.
-    const int per = (nsteps + 2 * (nseg - 1) + nseg - 1) / nseg;
-    // us: about 2.3 per step and 7 to start in segments, 1.0 and 4 in one walk.  Measured, walk -> segments: 128 heads, 1024 tokens 21.1 -> 20.8,
-    // 1280 24.7 -> 22.6, 2176 37.2 -> 29.8, 5630 98 -> 67, 7936 157 -> 93; 64 heads, 768 tokens 14.8 -> 14.3, 1024 18.1 -> 15.4.
-    // Where a slow head makes its pair take the walk after all, adding up dt has cost 2 to 3 us.
-    if (23 * per + 40 > 10 * nsteps) return p;
-    p.first_steps = per;
-    p.seg_steps = per - 2;
-    const int cut = 1 + (nsteps - per + p.seg_steps - 1) / p.seg_steps;
-    if (cut >= 4) p.nseg = cut;  // a walk of the pair takes four workgroups
-    return p;
-}
-
-template <int NS, bool GATHER>
-int launch_mid(const MidPlan &p, seg::SegArgs &a, hipStream_t st) {
-    a.nseg = p.nseg;
-    a.seg_steps = p.seg_steps;
-    const int nunits = a.H / 2 * p.nseg;
-    constexpr size_t smem = sizeof(Lds<NS>) > sizeof(seg::LdsS<NS, 2, 2>) ? sizeof(Lds<NS>) : sizeof(seg::LdsS<NS, 2, 2>);
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&ssd_mid_kernel<NS, GATHER>), smem)) return STRD_EHIP;
-    ssd_mid_kernel<NS, GATHER><<<xcd_grid(nunits), kThreads, smem, st>>>(a, p.first_steps, nunits);
     return launch_status();
 }
 
@@ -765,14 +636,6 @@ bool ssd_mfma_supported(int T, int rows, int H, int P, int G, int n, strd_dtype 
 int ssd_mfma(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D,
              const float *S_in, void *y, float *S_out, const int32_t *idx, int N, int K, int T, int H, int P, int G,
              int n, hipStream_t st) {
-    const MidPlan mid = mid_plan(T, H, P, G);
-    if (mid.nseg) {
-        seg::SegArgs a = {};
-        a.x = (const bf16_t *)x; a.dt = dt; a.A = A; a.B = (const bf16_t *)B; a.C = (const bf16_t *)C; a.D = D; a.S_in = S_in;
-        a.y = (bf16_t *)y; a.S_out = S_out; a.idx = idx; a.N = N; a.K = K; a.T = T; a.H = H; a.P = P; a.G = G;
-        if (n == 128) return idx ? launch_mid<128, true>(mid, a, st) : launch_mid<128, false>(mid, a, st);
-        if (n == 64) return idx ? launch_mid<64, true>(mid, a, st) : launch_mid<64, false>(mid, a, st);
-    }
     if (idx) {
         if (n == 128) return launch<128, true>(x, dt, A, B, C, D, S_in, y, S_out, idx, N, K, T, H, P, G, st);
         if (n == 64) return launch<64, true>(x, dt, A, B, C, D, S_in, y, S_out, idx, N, K, T, H, P, G, st);

@@ -718,11 +718,10 @@ def test_whole_sequence_scan_of_64_state_entries_gives_the_same_bits_every_time(
 
 @pytest.mark.parametrize("case", ["fast", "slow head", "two steps", "three steps", "no decay", "alternating"])
 @pytest.mark.parametrize("T,H,G,n", [(64 * 13 + 1, 64, 4, 128), (64 * 20, 128, 8, 64), (64 * 21 - 63, 128, 8, 128), (64 * 31 - 1, 80, 4, 128)])
-def test_ssd_prefill_pairs_of_heads_in_segments(T, H, G, n, case):
-    """Sequences of middle length: segments that start a few steps early where the decays of a pair of heads allow it (two
-    steps at most), one walk over the sequence where they do not; dense with D and a carried-in state, and through an
-    index list."""
-    _say("ssd_prefill pairs T=%d H=%d G=%d n=%d %s" % (T, H, G, n, case))
+def test_ssd_prefill_sequences_of_middle_length(T, H, G, n, case):
+    """14 to 31 steps of 64 to 128 heads, of decays that reach over one step, two, three or the whole sequence; dense with D and a
+    carried-in state, and through an index list."""
+    _say("ssd_prefill middle length T=%d H=%d G=%d n=%d %s" % (T, H, G, n, case))
     P, M = 64, 21
     K = T - M
     N = K + K // 2 + 3
@@ -761,7 +760,7 @@ def test_ssd_prefill_pairs_of_heads_in_segments(T, H, G, n, case):
         assert_close(f(S[h:h + 1]), S_ref, TOL[torch.bfloat16], "state of head %d" % h, units=(0,))
 
 
-def test_ssd_prefill_pairs_of_heads_values_that_are_not_finite():
+def test_ssd_prefill_middle_length_value_that_is_not_finite():
     """An infinite x stays infinite in its own output and reaches no step before its own, no other channel and no other head."""
     T, H, P, G, n = 64 * 24, 128, 64, 8, 128
     g = torch.Generator().manual_seed(5)
@@ -814,3 +813,32 @@ def test_ssd_prefill_values_that_are_not_finite_reach_over_a_seam(H, G, where):
     assert torch.isfinite(torch.cat([y[:, :h], y[:, h + 1:]], 1).float()).all()
     if where != "dt":
         assert torch.isfinite(torch.cat([y[:, h, :p], y[:, h, p + 1:]], 1).float()).all()
+
+
+@pytest.mark.parametrize("a_scale", [1.0, 0.01])
+@pytest.mark.parametrize("where", ["x", "dt", "S_in"])
+@pytest.mark.parametrize("T,H,G,n", [(64 * 24, 128, 8, 128), (64 * 40, 64, 4, 64)])
+def test_ssd_prefill_middle_length_loses_no_value_that_is_not_finite(T, H, G, n, where, a_scale):
+    """Where one workgroup walks the sequence, every later output of the channel (of the head, for dt) shows it, and so does the
+    state at the end, whether the decays are fast or slow."""
+    P, h, p, t = 64, H - 3, 3, 0 if where == "S_in" else 70
+    g = torch.Generator().manual_seed(T)
+    x, B, C = (torch.randn(T, *s, generator=g).to(torch.bfloat16).to(DEV) for s in ((H, P), (G, n), (G, n)))
+    dt = torch.nn.functional.softplus(torch.randn(T, H, generator=g)).to(DEV)
+    A = (-a_scale * torch.exp(2 * torch.rand(H, generator=g))).to(DEV)
+    S_in = torch.randn(H, P, n, generator=g).to(DEV)
+    if where == "x":
+        x[t, h, p] = float("inf")
+    elif where == "dt":
+        dt[t, h] = float("nan")
+    else:
+        S_in[h, p, 5] = float("nan")
+    y, S = strd.ssd_prefill(x, dt, A, B, C, S_in=S_in)
+    which = slice(None) if where == "dt" else p
+    assert (~torch.isfinite(y[t:, h, which].float())).all(), "lost %s" % where
+    # one entry of a carried-in state stays in its column n = 5; a token's x and dt go to all columns
+    lost = S[h, which, 5] if where == "S_in" else S[h, which]
+    assert (~torch.isfinite(lost)).all()
+    ok = torch.ones(H, P, dtype=torch.bool, device=DEV)
+    ok[h, which] = False
+    assert torch.isfinite(y.float()[:, ok]).all() and torch.isfinite(S[ok]).all()
