@@ -53,7 +53,8 @@ template <class SEQ> constexpr bool is_varlen() { return std::is_same<SEQ, SeqTa
 // global_load_lds writes lane l of a wave to (uniform LDS base) + 16 * l, so the tile is filled
 // slot by slot: slot s = row * (VR + PAD) + cv; pad slots (cv >= VR) re-read the row's last vector.
 // Slots are dealt to the NW waves of the workgroup 64 at a time; lanes whose slot lies past the
-// end of the tile copy nothing, so the tile occupies exactly ROWS * (VR + PAD) * 16 bytes.
+// end of the tile copy nothing, so the tile occupies exactly ROWS * (VR + PAD) * 16 bytes -- or, where only its
+// first `slots` slots are copied, slots * 16.
 // SKIP_PAD: lanes on pad slots copy nothing either (the pad bytes stay unwritten and must never
 // be read into a result), which saves PAD / (VR + PAD) of the copy traffic.
 template <int ROWS, int VR, int NW, int PAD = 1, bool SKIP_PAD = false>
@@ -73,12 +74,21 @@ struct AsyncTile {
         row = min(s / kVP, ROWS - 1);
         cv = min(s % kVP, VR - 1);
     }
+    // Whether slot s is copied to a tile of which there are `slots`.
+    static constexpr bool copied(int s, int slots) { return s < slots && (!SKIP_PAD || s % kVP < VR); }
     // Issue this lane's i-th copy: 16 bytes from `src` to its slot of the tile at `lds_tile`.
     __device__ static __forceinline__ void issue(const void *src, void *lds_tile, int wave, int i) {
         char *dst = reinterpret_cast<char *>(lds_tile) + (i * NW + wave) * 1024;
         const int s = (i * NW + wave) * 64 + (int)(threadIdx.x & 63);
         if (((i + 1) * NW * 64 <= kSlots || s < kSlots) &&  // only the last round can run past the tile
             (!SKIP_PAD || s % kVP < VR))
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                             (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+    }
+    // The same into a tile of which there are the first `slots` slots only.
+    __device__ static __forceinline__ void issue_part(const void *src, void *lds_tile, int wave, int i, int slots) {
+        char *dst = reinterpret_cast<char *>(lds_tile) + (i * NW + wave) * 1024;
+        if (copied((i * NW + wave) * 64 + (int)(threadIdx.x & 63), slots))
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
                                              (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
     }

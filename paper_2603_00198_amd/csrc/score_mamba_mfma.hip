@@ -45,6 +45,17 @@ struct Tile {
     Buf c[2];
 };
 
+// 16-byte slots of the 32-row tiles that hold one of `rows` text rows; no more of a text tile is copied, and where one tile holds all
+// rows there is LDS for no more.
+template <int NS>
+constexpr int text_slots(int rows) { return (rows + 31) / 32 * 32 * Tile<NS>::A::kVP; }
+
+// LDS of the tile kernel: the b rows and one text tile, of the rows that there are, where one holds them all.
+template <int NS>
+constexpr size_t tile_lds(int M) {
+    return M > kMC ? sizeof(Tile<NS>) : sizeof(typename Tile<NS>::Buf) + (size_t)text_slots<NS>(M) * 16;
+}
+
 // FULL (the Full Mamba Dynamic score, |w_{t,j}| of paper Eq. "ssm_weight", Sec. "Why the Full Mamba Dynamic Fails"): every |b_i . c_m| is
 // weighted by sum_{h in g} u_i^h v_m^h, u_i^h = dt_i^h * decay from token i to the last vision
 // token, v_m^h = decay from there to text row m (both <= dt resp. 1, made by the prep kernels).
@@ -87,11 +98,12 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
 #pragma unroll
     for (int i = 0; i < AT::kIssues; ++i) AT::slot(w, lane, i, st_row[i], st_col[i]);
     auto stage = [&](int mc, int b) {
-        const int slots = (min(kMC, M - mc * kMC) + 31) / 32 * 32 * AT::kVP;  // of the 32-row tiles that hold a row
+        const int slots = text_slots<NS>(min(kMC, M - mc * kMC));
 #pragma unroll
         for (int i = 0; i < AT::kIssues; ++i) {
             const int m = min(mc * kMC + st_row[i], M - 1);
-            if (i * kThreads < slots) AT::issue(Ct + ((size_t)m * G + g) * NS + st_col[i] * 8, &lds.c[b], w, i);  // uniform
+            if (i * kThreads < slots)  // uniform
+                AT::issue_part(Ct + ((size_t)m * G + g) * NS + st_col[i] * 8, &lds.c[b], w, i, slots);
         }
     };
     // The b rows of 128 tokens come through LDS, in the place of the second text tile: a load that gives every lane its own token
@@ -499,12 +511,6 @@ int launch_full(const void *B, const void *C, const float *U, const float *V, fl
     score_mamba_reduce_kernel<<<ceil_div(N, kThreads), kThreads, 0, st>>>(part, s, N, H, G, 1.f / ((float)M * (float)H), OneSeq(), 0,
                                                                           false);
     return launch_status();
-}
-
-// LDS of the tile kernel: the b rows and one text tile, of the rows that there are, where one holds them all.
-template <int NS>
-size_t tile_lds(int M) {
-    return M > kMC ? sizeof(Tile<NS>) : sizeof(typename Tile<NS>::Buf) + (size_t)(M + 31) / 32 * 32 * Tile<NS>::A::kVP * 16;
 }
 
 template <int NS, int CT>

@@ -383,3 +383,32 @@ def test_copies_that_a_wave_issues_are_counted_wave_by_wave(tmp_path):
     cmd = [strd_build.HIPCC] + strd_build.FLAGS + ["--cuda-host-only", "-fsyntax-only", str(src)]
     run = subprocess.run(cmd, capture_output=True, text=True)
     assert run.returncode == 0, run.stderr[-2000:]
+
+
+def test_copies_of_text_rows_stay_inside_the_lds_that_a_launch_asks_for(tmp_path):
+    """The tile kernel of the Mamba scores: LDS for the b rows and for the 32-row tiles of text that there are.  On both sides of
+    every line between 1 and 300 text rows, every slot that a chunk of 128 copies lies inside that, and every row of those tiles is copied."""
+    import subprocess
+    from paper_2603_00198_amd import build as strd_build
+    src = tmp_path / "text_rows.hip"
+    src.write_text('''#include "score_mamba_mfma.hip"
+namespace strd { namespace {
+template <int NS> constexpr bool inside() {
+    using A = typename Tile<NS>::A;
+    for (int M : {1, 32, 33, 64, 65, 96, 97, 128, 129, 192, 256, 257, 300})
+        for (int mc = 0; mc * kMC < M; ++mc) {
+            const int rows = M - mc * kMC < kMC ? M - mc * kMC : kMC, slots = text_slots<NS>(rows);
+            const size_t tile = (~mc & 1) * sizeof(typename Tile<NS>::Buf);
+            for (int s = 0; s < A::kIssues * kThreads; ++s) {
+                if (A::copied(s, slots) && tile + (s + 1) * 16 > tile_lds<NS>(M)) return false;
+                if (s < (rows + 31) / 32 * 32 * A::kVP && !A::copied(s, slots)) return false;
+            }
+        }
+    return tile_lds<NS>(128) <= sizeof(Tile<NS>);
+}
+static_assert(inside<128>() && inside<64>(), "");
+}}
+''')
+    cmd = [strd_build.HIPCC] + strd_build.FLAGS + ["--cuda-host-only", "-fsyntax-only", "-fconstexpr-steps=100000000", str(src)]
+    run = subprocess.run(cmd, capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr[-2000:]
