@@ -617,3 +617,19 @@ def test_score_mamba_heads_of_a_group(H, G, n):
     B, C, dt = rn(300, G, n), rn(37, G, n), rn(300, H).float().abs()
     got = strd.score_mamba(B.to(DEV), C.to(DEV), dt.to(DEV))
     assert_close(f(got), oracle.score_mamba(f(B), f(C), f(dt)), BOUND[BF16], "s", units=(0,))
+
+
+@pytest.mark.parametrize("T,H,P", [(9, 2, 512), (40, 1, 516), (64, 2, 1024), (30, 3, 4096), (12, 3100, 4)])
+@pytest.mark.parametrize("carry", [False, True])
+def test_scan_of_one_chunk_without_an_end_state(T, H, P, carry):
+    """16 state entries, up to more channels than a launch has LDS for and more heads than one launch is for."""
+    g = torch.Generator().manual_seed(T + P)
+    x, B, C = (torch.randn(T, *s, generator=g).to(DEV) for s in ((H, P), (1, 16), (1, 16)))
+    dt = torch.nn.functional.softplus(torch.randn(T, H, generator=g)).to(DEV)
+    A = (-0.3 * torch.exp(2 * torch.rand(H, generator=g))).to(DEV)
+    S_in = torch.randn(H, P, 16, generator=g).to(DEV) if carry else None
+    y, none = strd.ssd_prefill(x, dt, A, B, C, S_in=S_in, want_state=False)
+    f = synth.np64
+    y_ref, _ = oracle.ssd_seq(f(x), f(dt), f(A), f(B), f(C), None, f(S_in) if carry else None)
+    assert none is None
+    assert_close(f(y), y_ref, TOL[torch.float32], "y", units=(1,))

@@ -412,3 +412,29 @@ static_assert(inside<128>() && inside<64>(), "");
     cmd = [strd_build.HIPCC] + strd_build.FLAGS + ["--cuda-host-only", "-fsyntax-only", "-fconstexpr-steps=100000000", str(src)]
     run = subprocess.run(cmd, capture_output=True, text=True)
     assert run.returncode == 0, run.stderr[-2000:]
+
+
+def test_scans_in_one_launch_fit_the_lds_of_a_launch(tmp_path):
+    """The states that a workgroup holds are 32 KB at most (a launch has 64 KB, the kernel's own arrays 5), with an end state asked for
+    and without, whatever the number of channels; and the small scans that the rule is for are still taken."""
+    import subprocess
+    from paper_2603_00198_amd import build as strd_build
+    src = tmp_path / "once.hip"
+    src.write_text('''#include "general.hip"
+namespace strd {
+constexpr bool fits() {
+    for (int nc = 1; nc <= kOnceChunks + 1; ++nc)
+        for (int nst = nc - 1; nst <= nc; ++nst)
+            for (int H : {1, 8, 1000, 100000})
+                for (int P : {1, 32, 64, 512, 513, 1024, 4096, 1 << 20})
+                    for (int n : {1, 4, 16, 17})
+                        if (ssd_at_once(nc, nst, H, P, n) && once_lds(nst, P, n) > 32768) return false;
+    return true;
+}
+static_assert(fits(), "");
+static_assert(ssd_at_once(1, 0, 8, 32, 16) && ssd_at_once(1, 0, 1, 512, 16) && ssd_at_once(9, 9, 8, 32, 16), "");
+}
+''')
+    cmd = [strd_build.HIPCC] + strd_build.FLAGS + ["--cuda-host-only", "-fsyntax-only", str(src)]
+    run = subprocess.run(cmd, capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr[-2000:]
