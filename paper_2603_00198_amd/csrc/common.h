@@ -22,6 +22,11 @@ template <typename T> __device__ __forceinline__ T from_f32(float v);
 template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
 template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float v) { return static_cast<bf16_t>(v); }
 
+// Whether two arrays of `bytes` bytes share memory (a null one shares none).
+inline bool overlap(const void *a, const void *b, size_t bytes) {
+    const uintptr_t u = (uintptr_t)a, v = (uintptr_t)b;
+    return a && b && (u < v ? v - u : u - v) < bytes;
+}
 __host__ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 __host__ __device__ __forceinline__ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 

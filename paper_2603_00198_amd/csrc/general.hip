@@ -1233,7 +1233,8 @@ static int ssd_launch(const void *x, const float *dt, const float *A, const void
     const int nc = ceil_div(Tn, kChunk), nst = S_out ? nc : nc - 1;  // chunks whose contribution to the state is needed
     const bool vec = vec4<T>(P, (const T *)x, (const T *)y) && vec4<T>(n, (const T *)B, (const T *)C);
     const int cpl = !vec ? 1 : P > 32 ? 4 : 2, npl = vec && n >= 64 ? 4 : 1;
-    if (vec && ssd_at_once(nc, nst, H, P, n)) {
+    // (there every workgroup of a head reads S_in and one writes S_out: not in place)
+    if (vec && ssd_at_once(nc, nst, H, P, n) && !overlap(S_in, S_out, (size_t)H * P * n * sizeof(float))) {
         const size_t lds = once_lds(nst, P, n);
 #define STRD_SSD_ONCE(FF)                                                                                                    \
     ssd_once_kernel<T, 2, 1, FF><<<(unsigned)(nc * H), kOnceThreads, lds, st>>>((const T *)x, dt, A, (const T *)B, (const T *)C, D, \
