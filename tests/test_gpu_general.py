@@ -633,3 +633,32 @@ def test_scan_of_one_chunk_without_an_end_state(T, H, P, carry):
     y_ref, _ = oracle.ssd_seq(f(x), f(dt), f(A), f(B), f(C), None, f(S_in) if carry else None)
     assert none is None
     assert_close(f(y), y_ref, TOL[torch.float32], "y", units=(1,))
+
+
+def _scan_in_place(x, dt, A, B, C, S, chunk=64):
+    """The C call with one buffer for the state carried in and the state at the end; the outputs."""
+    T, H, P = x.shape
+    G, n = B.shape[1:]
+    io = strd.binding.STRD_F32 if x.dtype == F32 else strd.binding.STRD_BF16
+    L = strd.lib()
+    size = L.strd_ssd_prefill_workspace(T, H, P, G, n, chunk, io)
+    ws = torch.empty(max(size, 16), dtype=torch.uint8, device=DEV)
+    y = torch.empty_like(x)
+    rc = L.strd_ssd_prefill(x.data_ptr(), dt.data_ptr(), A.data_ptr(), B.data_ptr(), C.data_ptr(), None, S.data_ptr(), y.data_ptr(),
+                            S.data_ptr(), T, H, P, G, n, chunk, io, ws.data_ptr(), size, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    return y
+
+
+@pytest.mark.parametrize("dtype,T,H,P,G,n", [(F32, 9, 8, 32, 1, 16), (F32, 64 * 16 + 1, 8, 32, 1, 16), (BF16, 500, 6, 20, 3, 4),
+                                            (F32, 3000, 8, 32, 1, 16), (F32, 3, 8, 32, 1, 16), (BF16, 700, 8, 64, 2, 128)])
+def test_scan_with_its_state_in_place(dtype, T, H, P, G, n):
+    """Token by token, in one launch's range, in chunks and in one walk: the same bits as with two buffers."""
+    rn = _draw(T + n, dtype)
+    x, B, C = rn(T, H, P).to(DEV), rn(T, G, n).to(DEV), rn(T, G, n).to(DEV)
+    dt = torch.nn.functional.softplus(rn(T, H).float()).to(DEV)
+    A = -(0.3 + rn(H).float().abs()).to(DEV)
+    S = rn(H, P, n).float().to(DEV)
+    y_ref, S_ref = strd.ssd_prefill(x, dt, A, B, C, S_in=S)
+    y = _scan_in_place(x, dt, A, B, C, S)
+    assert torch.equal(y, y_ref) and torch.equal(S, S_ref)
