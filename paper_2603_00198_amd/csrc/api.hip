@@ -15,10 +15,11 @@ namespace {
 inline bool io_ok(strd_dtype io) { return io == STRD_F32 || io == STRD_BF16; }
 inline hipStream_t as_stream(void *s) { return (hipStream_t)s; }
 // The two matrix-core kernels of the scan: segments of the sequence side by side (ssd_seg) where that
-// pays, one workgroup per (head, 32 channels) over the whole sequence (ssd_mfma) otherwise.
-inline bool use_seg(int T, int rows, int H, int P, int G, int n, strd_dtype io) {
+// pays, one workgroup per (head, 32 channels) over the whole sequence (ssd_mfma) otherwise.  `in_place`: S_out lies over
+// S_in -- the first segment reads the one while the last writes the other, a walk reads its part before it writes it.
+inline bool use_seg(int T, int rows, int H, int P, int G, int n, strd_dtype io, bool in_place = false) {
     return ssd_seg_supported(T, rows, H, P, G, n, io) &&
-           (ssd_seg_preferred(T, H, P, G) || !ssd_mfma_supported(T, rows, H, P, G, n, io));
+           ((ssd_seg_preferred(T, H, P, G) && !in_place) || !ssd_mfma_supported(T, rows, H, P, G, n, io));
 }
 // The kernels read and write 16-byte vectors straight from the caller's pointers.
 template <typename... P>
@@ -291,7 +292,7 @@ int strd_ssd_prefill(const void *x, const float *dt, const float *A, const void 
     const size_t need = strd_ssd_prefill_workspace(T, H, P, G, n, chunk, io);
     const bool missing = need && (!ws || ws_bytes < need);
     if (missing && mfma) return STRD_EWORKSPACE;
-    if (use_seg(T, T, H, P, G, n, io))
+    if (use_seg(T, T, H, P, G, n, io, overlap(S_in, S_out, (size_t)H * P * n * sizeof(float))))
         return ssd_seg(x, dt, A, B, C, D, S_in, y, S_out, nullptr, 0, 0, T, H, P, G, n, ws, as_stream(stream));
     if (mfma) return ssd_mfma(x, dt, A, B, C, D, S_in, y, S_out, nullptr, 0, 0, T, H, P, G, n, as_stream(stream));
     if (!ssd_general_supported(n)) return STRD_EUNSUPPORTED;
@@ -312,7 +313,8 @@ int strd_ssd_prefill_gather(const void *x, const float *dt, const float *A, cons
     if (!ssd_seg_supported((int)T, N + M, H, P, G, n, io) && !ssd_mfma_supported((int)T, N + M, H, P, G, n, io))
         return STRD_EUNSUPPORTED;
     // the same choice of kernel as strd_ssd_prefill makes for K + M tokens: the results must be the same bits
-    const bool old = !use_seg((int)T, (int)T, H, P, G, n, io) || !ssd_seg_supported((int)T, N + M, H, P, G, n, io);
+    const bool in_place = overlap(S_in, S_out, (size_t)H * P * n * sizeof(float)) && ssd_mfma_supported((int)T, N + M, H, P, G, n, io);
+    const bool old = !use_seg((int)T, (int)T, H, P, G, n, io, in_place) || !ssd_seg_supported((int)T, N + M, H, P, G, n, io);
     if (old && !ssd_mfma_supported((int)T, N + M, H, P, G, n, io)) return STRD_EUNSUPPORTED;
     const size_t need = old ? 0 : ssd_seg_ws((int)T, H, P, G, n);
     if (need && (!ws || ws_bytes < need)) return STRD_EWORKSPACE;

@@ -987,6 +987,10 @@ int ssd_seg(const void *x, const float *dt, const float *A, const void *B, const
     a.x = (const bf16_t *)x; a.dt = dt; a.A = A; a.B = (const bf16_t *)B; a.C = (const bf16_t *)C; a.D = D; a.S_in = S_in;
     a.y = (bf16_t *)y; a.S_out = S_out; a.idx = idx; a.N = N; a.K = K; a.T = T; a.H = H; a.P = P; a.G = G;
     ssd_seg_plan(T, H, P, G, &a.nseg, &a.seg_steps);
+    if (overlap(S_in, S_out, (size_t)H * P * n * sizeof(float))) {  // tensors too large for ssd_mfma: one segment reads its state, then writes it
+        a.seg_steps *= a.nseg;
+        a.nseg = 1;
+    }
     const int nc = slabs_per_wg(P), nh = heads_per_wg(H, P, G);
     a.wg_per_seg = H * (P / 32) / nc / nh;
     a.lend = a.ltot = nullptr;

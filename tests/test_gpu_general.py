@@ -662,3 +662,27 @@ def test_scan_with_its_state_in_place(dtype, T, H, P, G, n):
     y_ref, S_ref = strd.ssd_prefill(x, dt, A, B, C, S_in=S)
     y = _scan_in_place(x, dt, A, B, C, S)
     assert torch.equal(y, y_ref) and torch.equal(S, S_ref)
+
+
+@pytest.mark.parametrize("T,H,G,n", [(64 * 32 - 5, 32, 2, 128), (64 * 17, 15, 1, 64)])
+def test_long_scan_with_its_state_in_place(T, H, G, n):
+    """Sequences that are cut into segments (of two heads per workgroup and of one) otherwise: against the call with two buffers and the
+    oracle, a second call going on from the state of the first."""
+    P, first = 64, T - 64 * 9
+    rn = _draw(T + n, BF16)
+    x, B, C = rn(T, H, P).to(DEV), (rn(T, G, n) / n ** 0.5).to(DEV), rn(T, G, n).to(DEV)
+    dt = torch.nn.functional.softplus(rn(T, H).float()).to(DEV)
+    A = -(0.05 + rn(H).float().abs()).to(DEV)
+    S0 = rn(H, P, n).float().to(DEV)
+    y_ref, S_ref = strd.ssd_prefill(x, dt, A, B, C, S_in=S0)
+    S = S0.clone()
+    y = torch.cat([_scan_in_place(*(t[a:b].contiguous() if t is not A else A for t in (x, dt, A, B, C)), S)
+                   for a, b in ((0, first), (first, T))])
+    assert_close(f(y), f(y_ref), BOUND[BF16], "y of one buffer and of two", units=(1,))
+    assert_close(f(S), f(S_ref), BOUND[BF16], "state of one buffer and of two", units=(0,))
+    for h in (0, H - 1):
+        q = h // (H // G)
+        y_o, S_o = oracle.ssd_seq(f(x[:, h:h + 1]), f(dt[:, h:h + 1]), f(A[h:h + 1]), f(B[:, q:q + 1]), f(C[:, q:q + 1]), None,
+                                  f(S0[h:h + 1]))
+        assert_close(f(y[:, h:h + 1]), y_o, BOUND[BF16], "y of head %d" % h, units=(1,))
+        assert_close(f(S[h:h + 1]), S_o, BOUND[BF16], "state of head %d" % h, units=(0,))
