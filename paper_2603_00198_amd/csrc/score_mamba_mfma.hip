@@ -82,7 +82,6 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
         Bv += (size_t)seq.row0[b] * G * NS;
         Ct += (size_t)(seq.row0[b] + N) * G * NS;
         part += (size_t)seq.row0[b] * G;
-        if (!FULL) U += (size_t)seq.row0[b] * H;
     }
 
     const int tid = threadIdx.x, lane = tid & 63, lc = lane & 31, half = lane >> 5;
@@ -125,33 +124,7 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
         for (int ks = 0; ks < KS; ++ks) bfr[ct][ks] = *reinterpret_cast<const bf16x8 *>(bp + 16 * ks);
     }
     // u fragments of this wave's tokens (B operand: lane = token column, k = head 8*half + j of the group)
-    const int hpg = H / G;
-    // Without FULL, U is dt: the sum of the group's heads per token, half of them per lane half, beside the b fragments
-    // (in a launch of its own, which also adds up the groups, dt cost 10 us for 16 clips of 2048 tokens and 128 heads, 5 without).
-    float dts[CT];
-    if (!FULL) {
-        const bool vec = hpg % 4 == 0;  // uniform: 16 bytes at a time, all in flight (one by one -> so: 64 heads of one group, 8192 tokens,
-                                        // 512 rows 13.2 -> 10.9 us; 128, 4096, 64 12.1 -> 7.2; 80, 2000, 128 10.0 -> 7.2)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            const float *dp = U + (size_t)min(tok0 + 32 * ct + lc, N - 1) * H + g * hpg;
-            float t = 0.f;
-            if (hpg == 16) {  // uniform
-                const float4 a = *reinterpret_cast<const float4 *>(dp + 8 * half), b = *reinterpret_cast<const float4 *>(dp + 8 * half + 4);
-                t = ((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w));
-            } else if (vec) {
-#pragma unroll 8
-                for (int h = 4 * half; h < hpg; h += 8) {
-                    const float4 a = *reinterpret_cast<const float4 *>(dp + h);
-                    t += (a.x + a.y) + (a.z + a.w);
-                }
-            } else {
-#pragma unroll 8
-                for (int h = half; h < hpg; h += 2) t += dp[h];
-            }
-            dts[ct] = t + __shfl_xor(t, 32, kWave);
-        }
-    }
+    const int hpg = FULL ? H / G : 0;
     bf16x8 u_hi[CT], u_lo[CT];
     if (FULL) {
 #pragma unroll
@@ -243,30 +216,49 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
     for (int ct = 0; ct < CT; ++ct) {
         const float col = part_sum[ct] + __shfl_xor(part_sum[ct], 32, kWave);
         const int t = tok0 + 32 * ct + lc;
-        if (half == 0 && t < N) part[(size_t)g * N + t] = FULL ? col : col * dts[ct];
+        if (half == 0 && t < N) part[(size_t)g * N + t] = col;
     }
 }
 
-// Adds up the group partials, in which the per-token factors are already.  SeqTab: blockIdx.y = sequence, `s` has `ld` floats per
-// sequence; `pad`: those behind the sequence's scores become 0.
+// Adds up the group partials, in which the per-token factors are already.
+__global__ __launch_bounds__(kThreads) void score_mamba_reduce_kernel(const float *__restrict__ part, float *__restrict__ s, int N, int G,
+                                                                      float norm) {
+    const int i = blockIdx.x * kThreads + threadIdx.x;
+    if (i >= N) return;
+    float tot = 0.f;
+    for (int g = 0; g < G; ++g) tot += part[(size_t)g * N + i];
+    s[i] = tot * norm;
+}
+
+// s_i = 1/(M*H) * sum_h dt_i^h * a[g(h)][i].  16 adjacent lanes share a token and read its dt row in 64-byte pieces (coalesced); their
+// partial sums meet in a fixed order.  SeqTab: blockIdx.y = sequence, dtv is the packed tensor, `s` has `ld` floats per sequence;
+// `pad`: those behind the sequence's scores become 0.  (Summed in the tile kernel, two lanes per token, dt took longer wherever a
+// group has many heads or rows of an odd length and no less elsewhere: us here / there, 300 tokens, 37 rows, 250 heads of one group 7.0 /
+// 14.1; 16000, 60, 8 groups of 7 10.6 / 15.6, of 24 13.6 / 15.3; packed 40 x 600, 100, of 7 21.5 / 30.2, of 16 22.8 / 24.1; it
+// gained 0.4 to 1.1 for 8 groups of 16 or 24 and 4096 tokens or fewer.)
 template <class SEQ = OneSeq>
-__global__ __launch_bounds__(kThreads) void score_mamba_reduce_kernel(const float *__restrict__ part, float *__restrict__ s, int N,
-                                                                      int H, int G, float norm, SEQ seq, int ld, bool pad) {
+__global__ __launch_bounds__(kThreads) void score_mamba_dt_reduce_kernel(const float *__restrict__ part, const float *__restrict__ dtv,
+                                                                         float *__restrict__ s, int N, int H, int G, float norm,
+                                                                         SEQ seq, int ld, bool pad) {
     if constexpr (is_varlen<SEQ>()) {
         const int b = blockIdx.y;
         N = seq.N[b];
         norm = 1.f / ((float)seq.M[b] * (float)H);
         part += (size_t)seq.row0[b] * G;
+        dtv += (size_t)seq.row0[b] * H;
         s += (size_t)b * ld;
     }
-    const int i = blockIdx.x * kThreads + threadIdx.x;
-    if (i >= N) {
-        if (pad && i < ld) s[i] = 0.f;
-        return;
-    }
+    const int i = blockIdx.x * (kThreads / 16) + threadIdx.x / 16, j = threadIdx.x & 15;
+    const int hpg = H / G;
     float tot = 0.f;
-    for (int g = 0; g < G; ++g) tot += part[(size_t)g * N + i];
-    s[i] = tot * norm;
+    if (i < N) {
+        const float *dr = dtv + (size_t)i * H;
+        for (int h = j; h < H; h += 16) tot = fmaf(dr[h], part[(size_t)(h / hpg) * N + i], tot);
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) tot += __shfl_xor(tot, o, kWave);
+    if (j == 0 && i < N) s[i] = tot * norm;
+    if (j == 0 && i >= N && pad && i < ld) s[i] = 0.f;
 }
 
 // ---- long sequences: the text rows of a group stay resident in LDS ------------------------------
@@ -493,8 +485,7 @@ int launch_res(const void *B, const void *C, const float *dt, float *s, int M, i
     float *part = (float *)ws;
     score_mamba_res_kernel<NS, CT><<<slices * G, kResThreads, smem, st>>>((const bf16_t *)B, (const bf16_t *)C, dt, part,
                                                                          M, N, G, H, slices, slice_len);
-    score_mamba_reduce_kernel<<<ceil_div(N, kThreads), kThreads, 0, st>>>(part, s, N, H, G, 1.f / ((float)M * (float)H), OneSeq(), 0,
-                                                                          false);
+    score_mamba_reduce_kernel<<<ceil_div(N, kThreads), kThreads, 0, st>>>(part, s, N, G, 1.f / ((float)M * (float)H));
     return launch_status();
 }
 
@@ -508,8 +499,7 @@ int launch_full(const void *B, const void *C, const float *U, const float *V, fl
     const dim3 grid(ceil_div(N, 128 * CT), G);
     score_mamba_mfma_kernel<NS, CT, true><<<grid, kThreads, smem, st>>>((const bf16_t *)B, (const bf16_t *)C, U, V, part,
                                                                         M, N, G, H, OneSeq());
-    score_mamba_reduce_kernel<<<ceil_div(N, kThreads), kThreads, 0, st>>>(part, s, N, H, G, 1.f / ((float)M * (float)H), OneSeq(), 0,
-                                                                          false);
+    score_mamba_reduce_kernel<<<ceil_div(N, kThreads), kThreads, 0, st>>>(part, s, N, G, 1.f / ((float)M * (float)H));
     return launch_status();
 }
 
@@ -521,10 +511,10 @@ int launch(const void *B, const void *C, const float *dt, float *s, int M, int N
         return STRD_EHIP;
     float *part = (float *)ws;
     const dim3 grid(ceil_div(N, 128 * CT), G);
-    score_mamba_mfma_kernel<NS, CT, false><<<grid, kThreads, smem, st>>>((const bf16_t *)B, (const bf16_t *)C, dt,
+    score_mamba_mfma_kernel<NS, CT, false><<<grid, kThreads, smem, st>>>((const bf16_t *)B, (const bf16_t *)C, nullptr,
                                                                          nullptr, part, M, N, G, H, OneSeq());
-    score_mamba_reduce_kernel<<<ceil_div(N, kThreads), kThreads, 0, st>>>(part, s, N, H, G, 1.f / ((float)M * (float)H), OneSeq(), 0,
-                                                                          false);
+    score_mamba_dt_reduce_kernel<<<ceil_div(N, kThreads / 16), kThreads, 0, st>>>(part, dt, s, N, H, G, 1.f / ((float)M * (float)H),
+                                                                                  OneSeq(), 0, false);
     return launch_status();
 }
 
@@ -537,9 +527,9 @@ int launch_varlen(const void *B, const void *C, const float *dt, float *s, int l
         return STRD_EHIP;
     float *part = (float *)ws;
     score_mamba_mfma_kernel<NS, 1, false, SeqTab><<<dim3(ceil_div(max_n, 128), G, nseq), kThreads, tile_lds<NS>(max_m), st>>>(
-        (const bf16_t *)B, (const bf16_t *)C, dt, nullptr, part, 0, 0, G, H, tab);
-    score_mamba_reduce_kernel<SeqTab><<<dim3(ceil_div(pad ? ld : max_n, kThreads), nseq), kThreads, 0, st>>>(part, s, 0, H, G, 0.f, tab,
-                                                                                                            ld, pad);
+        (const bf16_t *)B, (const bf16_t *)C, nullptr, nullptr, part, 0, 0, G, H, tab);
+    score_mamba_dt_reduce_kernel<SeqTab><<<dim3(ceil_div(pad ? ld : max_n, kThreads / 16), nseq), kThreads, 0, st>>>(
+        part, dt, s, 0, H, G, 0.f, tab, ld, pad);
     return launch_status();
 }
 

@@ -611,7 +611,8 @@ def test_score_attn_of_many_rows(M, Hq, Hkv):
 
 @pytest.mark.parametrize("H,G,n", [(64, 1, 128), (8, 1, 64), (48, 2, 128), (80, 1, 64), (20, 1, 128), (70, 1, 64), (32, 2, 64)])
 def test_score_mamba_heads_of_a_group(H, G, n):
-    """dt of 8 to 80 heads of a group added up beside the products: 16 bytes at a time (8, 16, 20, 24, 64, 80 heads) and one by one (70)."""
+    """dt of 8 to 80 heads of a group, added up by 16 lanes per token: fewer heads than lanes, as many, several times as many with and
+    without a rest, rows of dt that start anywhere in a 64-byte line."""
     _say("score_mamba heads H=%d G=%d n=%d" % (H, G, n))
     rn = _draw(H + n, BF16)
     B, C, dt = rn(300, G, n), rn(37, G, n), rn(300, H).float().abs()
