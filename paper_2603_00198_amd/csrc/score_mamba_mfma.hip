@@ -9,7 +9,7 @@
 // Two kernels make the group partials a[g][i].
 // Short sequences: one workgroup = 4 waves = 128*CT consecutive tokens of ONE group (grid = token
 // tiles x groups, so even 8192 tokens give 512 workgroups); the text tile (128 rows) is
-// double-buffered in LDS, filled by asynchronous global -> LDS copies, shared by the 4 waves.
+// double-buffered in LDS where there are more rows, filled by asynchronous global -> LDS copies, shared by the 4 waves.
 // It writes a[g][i] = sum_m |b_i^g . c_m^g|, and 16 lanes per token then sum dt_i^h * a[g(h)][i]
 // over the heads and scale.
 // Long sequences: one workgroup per CU keeps all text rows of its group in LDS and its 8 waves
@@ -45,15 +45,14 @@ struct Tile {
     Buf c[2];
 };
 
-// 16-byte slots of the 32-row tiles that hold one of `rows` text rows; no more of a text tile is copied, and where one tile holds all
-// rows there is LDS for no more.
+// 16-byte slots of the 32-row tiles that hold one of `rows` text rows (at most kMC).
 template <int NS>
 constexpr int text_slots(int rows) { return (rows + 31) / 32 * 32 * Tile<NS>::A::kVP; }
 
-// LDS of the tile kernel: the b rows and one text tile, of the rows that there are, where one holds them all.
+// LDS of the tile kernel: two text tiles -- or, where one holds all M rows (ONE), the b rows and what there are of it; no more is copied.
 template <int NS>
-constexpr size_t tile_lds(int M) {
-    return M > kMC ? sizeof(Tile<NS>) : sizeof(typename Tile<NS>::Buf) + (size_t)text_slots<NS>(M) * 16;
+constexpr size_t tile_lds(bool one, int M) {
+    return one ? sizeof(typename Tile<NS>::Buf) + (size_t)text_slots<NS>(M) * 16 : sizeof(Tile<NS>);
 }
 
 // FULL (the Full Mamba Dynamic score, |w_{t,j}| of paper Eq. "ssm_weight", Sec. "Why the Full Mamba Dynamic Fails"): every |b_i . c_m| is
@@ -64,7 +63,11 @@ constexpr size_t tile_lds(int M) {
 // bf16 high and low parts (three products) to keep about 16 bits of them.
 // SEQ = SeqTab (packed batch, blockIdx.z = sequence): Bv and Ct point at the packed b and c tensors,
 // the sequence's partials start at part + row0 * G.
-template <int NS, int CT, bool FULL, class SEQ = OneSeq>
+// ONE: one text tile holds all rows (of every sequence).  Then the b rows of 128 tokens come through LDS, in the place of the second text
+// tile: a load that gives every lane its own token touches 32 rows with 32 bytes each, a copy whole rows.  With more text rows the
+// second tile would wait for the b rows, and every copy would be checked.  us, always so / never / here: 4096 tokens, 400 rows, 25 heads of
+// one group 10.5 / 9.7 / 9.5; 16000, 60, 8 groups of 16 - / 14.5 / 12.1; packed 16 x 2048, 64 - / 26.4 / 20.9 (with fewer launches).
+template <int NS, int CT, bool FULL, bool ONE, class SEQ = OneSeq>
 __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t *__restrict__ Bv,
                                                                     const bf16_t *__restrict__ Ct,
                                                                     const float *__restrict__ U,
@@ -97,28 +100,28 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
 #pragma unroll
     for (int i = 0; i < AT::kIssues; ++i) AT::slot(w, lane, i, st_row[i], st_col[i]);
     auto stage = [&](int mc, int b) {
-        const int slots = text_slots<NS>(min(kMC, M - mc * kMC));
+        const int slots = text_slots<NS>(M);
 #pragma unroll
         for (int i = 0; i < AT::kIssues; ++i) {
-            const int m = min(mc * kMC + st_row[i], M - 1);
-            if (i * kThreads < slots)  // uniform
-                AT::issue_part(Ct + ((size_t)m * G + g) * NS + st_col[i] * 8, &lds.c[b], w, i, slots);
+            const bf16_t *src = Ct + ((size_t)min(mc * kMC + st_row[i], M - 1) * G + g) * NS + st_col[i] * 8;
+            if (!ONE)
+                AT::issue(src, &lds.c[b], w, i);
+            else if (i * kThreads < slots)  // uniform
+                AT::issue_part(src, &lds.c[b], w, i, slots);
         }
     };
-    // The b rows of 128 tokens come through LDS, in the place of the second text tile: a load that gives every lane its own token
-    // touches 32 rows with 32 bytes each, a copy whole rows.
-    constexpr bool kRows = CT == 1 && !FULL;
-    if constexpr (kRows) {
+    static_assert(!ONE || (CT == 1 && !FULL), "128 tokens");
+    if constexpr (ONE) {
 #pragma unroll
         for (int i = 0; i < AT::kIssues; ++i)
             AT::issue(Bv + ((size_t)min((int)blockIdx.x * 128 + st_row[i], N - 1) * G + g) * NS + st_col[i] * 8, &lds.c[0], w, i);
     }
-    stage(0, 1);
+    stage(0, ONE);
 
     // b fragments of this wave's tokens: lane = token column, 8 consecutive k (tail lanes repeat the last token)
     bf16x8 bfr[CT][KS];
 #pragma unroll
-    for (int ct = 0; ct < CT && !kRows; ++ct) {
+    for (int ct = 0; ct < CT && !ONE; ++ct) {
         const bf16_t *bp = Bv + ((size_t)min(tok0 + 32 * ct + lc, N - 1) * G + g) * NS + 8 * half;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) bfr[ct][ks] = *reinterpret_cast<const bf16x8 *>(bp + 16 * ks);
@@ -140,19 +143,18 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
     }
     async_tile_wait();
     __syncthreads();
-    if constexpr (kRows) {
+    if constexpr (ONE) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) bfr[0][ks] = *reinterpret_cast<const bf16x8 *>(lds.c[0].at(32 * w + lc, 16 * ks + 8 * half));
-        if (nmc > 1) __syncthreads();  // uniform: before the second text tile takes their place
     }
 
     float part_sum[CT];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) part_sum[ct] = 0.f;
 
-    for (int mc = 0; mc < nmc; ++mc) {
-        const int cur = ~mc & 1;
-        if (mc + 1 < nmc) stage(mc + 1, cur ^ 1);  // uniform
+    for (int mc = 0; mc < (ONE ? 1 : nmc); ++mc) {
+        const int cur = ONE ? 1 : mc & 1;
+        if (!ONE && mc + 1 < nmc) stage(mc + 1, cur ^ 1);  // uniform
         const int mrows = M - mc * kMC;            // valid text rows of this tile (may exceed kMC)
 #pragma unroll
         for (int mt = 0; mt < kMC / 32; ++mt) {
@@ -209,8 +211,10 @@ __global__ __launch_bounds__(kThreads) void score_mamba_mfma_kernel(const bf16_t
                 part_sum[ct] += t;
             }
         }
-        async_tile_wait();
-        __syncthreads();
+        if (!ONE) {
+            async_tile_wait();
+            __syncthreads();
+        }
     }
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
@@ -493,43 +497,27 @@ template <int NS, int CT>
 int launch_full(const void *B, const void *C, const float *U, const float *V, float *s, int M, int N, int H, int G,
                 void *ws, hipStream_t st) {
     const size_t smem = sizeof(Tile<NS>);
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&score_mamba_mfma_kernel<NS, CT, true>), smem))
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&score_mamba_mfma_kernel<NS, CT, true, false>), smem))
         return STRD_EHIP;
     float *part = (float *)ws;
     const dim3 grid(ceil_div(N, 128 * CT), G);
-    score_mamba_mfma_kernel<NS, CT, true><<<grid, kThreads, smem, st>>>((const bf16_t *)B, (const bf16_t *)C, U, V, part,
+    score_mamba_mfma_kernel<NS, CT, true, false><<<grid, kThreads, smem, st>>>((const bf16_t *)B, (const bf16_t *)C, U, V, part,
                                                                         M, N, G, H, OneSeq());
     score_mamba_reduce_kernel<<<ceil_div(N, kThreads), kThreads, 0, st>>>(part, s, N, G, 1.f / ((float)M * (float)H));
     return launch_status();
 }
 
-template <int NS, int CT>
-int launch(const void *B, const void *C, const float *dt, float *s, int M, int N, int H, int G, void *ws,
-           hipStream_t st) {
-    const size_t smem = tile_lds<NS>(M);
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&score_mamba_mfma_kernel<NS, CT, false>), sizeof(Tile<NS>)))
-        return STRD_EHIP;
+// A packed batch (M, N: the most text rows and tokens of a sequence) or one sequence.
+template <int NS, int CT, bool ONE, class SEQ>
+int launch(const void *B, const void *C, const float *dt, float *s, int M, int N, int H, int G, void *ws, const SEQ &seq, int nseq, int ld,
+           bool pad, hipStream_t st) {
+    const auto kernel = &score_mamba_mfma_kernel<NS, CT, false, ONE, SEQ>;
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(kernel), sizeof(Tile<NS>))) return STRD_EHIP;
     float *part = (float *)ws;
-    const dim3 grid(ceil_div(N, 128 * CT), G);
-    score_mamba_mfma_kernel<NS, CT, false><<<grid, kThreads, smem, st>>>((const bf16_t *)B, (const bf16_t *)C, nullptr,
-                                                                         nullptr, part, M, N, G, H, OneSeq());
-    score_mamba_dt_reduce_kernel<<<ceil_div(N, kThreads / 16), kThreads, 0, st>>>(part, dt, s, N, H, G, 1.f / ((float)M * (float)H),
-                                                                                  OneSeq(), 0, false);
-    return launch_status();
-}
-
-template <int NS>
-int launch_varlen(const void *B, const void *C, const float *dt, float *s, int ld, const SeqTab &tab, int nseq, int max_n, int H, int G,
-                  void *ws, bool pad, hipStream_t st) {
-    int max_m = 0;
-    for (int b = 0; b < nseq; ++b) max_m = std::max(max_m, tab.M[b]);
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&score_mamba_mfma_kernel<NS, 1, false, SeqTab>), sizeof(Tile<NS>)))
-        return STRD_EHIP;
-    float *part = (float *)ws;
-    score_mamba_mfma_kernel<NS, 1, false, SeqTab><<<dim3(ceil_div(max_n, 128), G, nseq), kThreads, tile_lds<NS>(max_m), st>>>(
-        (const bf16_t *)B, (const bf16_t *)C, nullptr, nullptr, part, 0, 0, G, H, tab);
-    score_mamba_dt_reduce_kernel<SeqTab><<<dim3(ceil_div(pad ? ld : max_n, kThreads / 16), nseq), kThreads, 0, st>>>(
-        part, dt, s, 0, H, G, 0.f, tab, ld, pad);
+    kernel<<<dim3(ceil_div(N, 128 * CT), G, nseq), kThreads, tile_lds<NS>(ONE, M), st>>>((const bf16_t *)B, (const bf16_t *)C, nullptr,
+                                                                                        nullptr, part, M, N, G, H, seq);
+    score_mamba_dt_reduce_kernel<SEQ><<<dim3(ceil_div(pad ? ld : N, kThreads / 16), nseq), kThreads, 0, st>>>(
+        part, dt, s, N, H, G, 1.f / ((float)M * (float)H), seq, ld, pad);
     return launch_status();
 }
 
@@ -538,8 +526,14 @@ int launch_varlen(const void *B, const void *C, const float *dt, float *s, int l
 // Packed batch on the matrix-core tile kernel: partials of sequence b at ws + row0[b] * G floats.
 int score_mamba_mfma_varlen(const void *B, const void *C, const float *dt, float *s, int ld, const SeqTab &tab, int nseq, int max_n,
                             int H, int G, int n, void *ws, bool pad, hipStream_t st) {
-    if (n == 128) return launch_varlen<128>(B, C, dt, s, ld, tab, nseq, max_n, H, G, ws, pad, st);
-    if (n == 64) return launch_varlen<64>(B, C, dt, s, ld, tab, nseq, max_n, H, G, ws, pad, st);
+    int max_m = 0;
+    for (int b = 0; b < nseq; ++b) max_m = std::max(max_m, tab.M[b]);
+#define STRD_LAUNCH(NS, ONE) return launch<NS, 1, ONE>(B, C, dt, s, max_m, max_n, H, G, ws, tab, nseq, ld, pad, st)
+    if (n == 128 && max_m <= kMC) STRD_LAUNCH(128, true);
+    if (n == 128) STRD_LAUNCH(128, false);
+    if (n == 64 && max_m <= kMC) STRD_LAUNCH(64, true);
+    if (n == 64) STRD_LAUNCH(64, false);
+#undef STRD_LAUNCH
     return STRD_EUNSUPPORTED;
 }
 
@@ -560,10 +554,14 @@ int score_mamba_mfma(const void *B, const void *C, const float *dt, float *s, in
         return n == 128 ? launch_res<128, 1>(B, C, dt, s, M, N, H, G, ws, st) : launch_res<64, 1>(B, C, dt, s, M, N, H, G, ws, st);
     // wide token tiles once there are enough of them to fill 256 CUs several times over
     const bool wide = (long long)N * G >= 256LL * 256 * 8;
-    if (n == 128)
-        return wide ? launch<128, 2>(B, C, dt, s, M, N, H, G, ws, st) : launch<128, 1>(B, C, dt, s, M, N, H, G, ws, st);
-    if (n == 64)
-        return wide ? launch<64, 2>(B, C, dt, s, M, N, H, G, ws, st) : launch<64, 1>(B, C, dt, s, M, N, H, G, ws, st);
+#define STRD_LAUNCH(NS, CT, ONE) return launch<NS, CT, ONE>(B, C, dt, s, M, N, H, G, ws, OneSeq(), 1, 0, false, st)
+    if (n == 128 && wide) STRD_LAUNCH(128, 2, false);
+    if (n == 128 && M <= kMC) STRD_LAUNCH(128, 1, true);
+    if (n == 128) STRD_LAUNCH(128, 1, false);
+    if (n == 64 && wide) STRD_LAUNCH(64, 2, false);
+    if (n == 64 && M <= kMC) STRD_LAUNCH(64, 1, true);
+    if (n == 64) STRD_LAUNCH(64, 1, false);
+#undef STRD_LAUNCH
     return STRD_EUNSUPPORTED;
 }
 

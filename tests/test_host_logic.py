@@ -386,8 +386,9 @@ def test_copies_that_a_wave_issues_are_counted_wave_by_wave(tmp_path):
 
 
 def test_copies_of_text_rows_stay_inside_the_lds_that_a_launch_asks_for(tmp_path):
-    """The tile kernel of the Mamba scores: LDS for the b rows and for the 32-row tiles of text that there are.  On both sides of
-    every line between 1 and 300 text rows, every slot that a chunk of 128 copies lies inside that, and every row of those tiles is copied."""
+    """The tile kernel of the Mamba scores where one text tile holds all rows: LDS for the b rows and, behind them, for the 32-row tiles of text
+    that there are.  On both sides of every line between 1 and 128 text rows, every slot that is copied lies inside that, and
+    every row of those tiles is copied."""
     import subprocess
     from paper_2603_00198_amd import build as strd_build
     src = tmp_path / "text_rows.hip"
@@ -395,16 +396,12 @@ def test_copies_of_text_rows_stay_inside_the_lds_that_a_launch_asks_for(tmp_path
 namespace strd { namespace {
 template <int NS> constexpr bool inside() {
     using A = typename Tile<NS>::A;
-    for (int M : {1, 32, 33, 64, 65, 96, 97, 128, 129, 192, 256, 257, 300})
-        for (int mc = 0; mc * kMC < M; ++mc) {
-            const int rows = M - mc * kMC < kMC ? M - mc * kMC : kMC, slots = text_slots<NS>(rows);
-            const size_t tile = (~mc & 1) * sizeof(typename Tile<NS>::Buf);
-            for (int s = 0; s < A::kIssues * kThreads; ++s) {
-                if (A::copied(s, slots) && tile + (s + 1) * 16 > tile_lds<NS>(M)) return false;
-                if (s < (rows + 31) / 32 * 32 * A::kVP && !A::copied(s, slots)) return false;
-            }
+    for (int M : {1, 32, 33, 64, 65, 96, 97, 128})
+        for (int s = 0; s < A::kIssues * kThreads; ++s) {
+            if (A::copied(s, text_slots<NS>(M)) && sizeof(typename Tile<NS>::Buf) + (s + 1) * 16 > tile_lds<NS>(true, M)) return false;
+            if (s < (M + 31) / 32 * 32 * A::kVP && !A::copied(s, text_slots<NS>(M))) return false;
         }
-    return tile_lds<NS>(128) <= sizeof(Tile<NS>);
+    return tile_lds<NS>(true, 128) <= sizeof(Tile<NS>) && tile_lds<NS>(false, 1) == sizeof(Tile<NS>);
 }
 static_assert(inside<128>() && inside<64>(), "");
 }}
