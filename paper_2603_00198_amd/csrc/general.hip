@@ -1217,13 +1217,16 @@ size_t ssd_general_ws(int T, int H, int P, int n) { return ssd_in_chunks(T, H, P
 // together not many more than the chip has waves for.  us, three launches -> one (fp32, 16 state entries): 8 heads of 32, 65 tokens
 // 11.9 -> 6.8, 544 13.5 -> 10.1, 800 13.8 -> 12.4 (1088 14.4 either way, 1600 15.3 / 18.3); 32 heads, 544 tokens 14.5 -> 13.2 (800
 // 16.3 / 17.8); 64 heads of 64, 200 tokens 16.3 -> 10.8 (544 23.7 / 30.0); 256 of 32, 128 tokens 15.5 -> 14.1 (200 20.7 / 27.6).
+// Of heads with many channels a workgroup has the blocks one after the other, which the separate launches share out: 512 channels, 9
+// tokens 17 / 21, 128 30 / 33; 384, 9 15.6 / 16.3; 256, 128 21.2 / 22.6 (9 14.1 -> 12.3); 192, 128 18.9 -> 17.8.  And one chunk that starts
+// from nothing and leaves nothing is one launch anyway (`carried`: there is a state carried in): 64 channels 5.3 / 5.6, 256 8.8 / 10.8.
 // The workgroup has LDS for one state at least (the one before its chunk), also where no chunk's is asked for.
 constexpr int once_states(int nst) { return nst > 1 ? nst : 1; }
 constexpr size_t once_lds(int nst, int P, int n) { return (size_t)once_states(nst) * P * n * sizeof(float); }
-constexpr bool ssd_at_once(int nc, int nst, int H, int P, int n) {
+constexpr bool ssd_at_once(int nc, int nst, bool carried, int H, int P, int n) {
     // blocks of 32 channels x 16 state entries, 2 KB of LDS each: 32 KB at most
     const long long states = (long long)once_states(nst) * (P / 32 + (P % 32 != 0));
-    return n <= 16 && nc <= kOnceChunks && states <= 2 * kOnceStateWaves && states * nc * H <= 3000;
+    return (nst > 0 || carried) && (P <= 192 || (P <= 256 && nst <= 1)) && n <= 16 && nc <= kOnceChunks && states <= 2 * kOnceStateWaves && states * nc * H <= 3000;
 }
 
 template <typename T>
@@ -1234,7 +1237,7 @@ static int ssd_launch(const void *x, const float *dt, const float *A, const void
     const bool vec = vec4<T>(P, (const T *)x, (const T *)y) && vec4<T>(n, (const T *)B, (const T *)C);
     const int cpl = !vec ? 1 : P > 32 ? 4 : 2, npl = vec && n >= 64 ? 4 : 1;
     // (there every workgroup of a head reads S_in and one writes S_out: not in place)
-    if (vec && ssd_at_once(nc, nst, H, P, n) && !overlap(S_in, S_out, (size_t)H * P * n * sizeof(float))) {
+    if (vec && ssd_at_once(nc, nst, S_in, H, P, n) && !overlap(S_in, S_out, (size_t)H * P * n * sizeof(float))) {
         const size_t lds = once_lds(nst, P, n);
 #define STRD_SSD_ONCE(FF)                                                                                                    \
     ssd_once_kernel<T, 2, 1, FF><<<(unsigned)(nc * H), kOnceThreads, lds, st>>>((const T *)x, dt, A, (const T *)B, (const T *)C, D, \

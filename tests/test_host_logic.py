@@ -425,11 +425,12 @@ constexpr bool fits() {
             for (int H : {1, 8, 1000, 100000})
                 for (int P : {1, 32, 64, 512, 513, 1024, 4096, 1 << 20})
                     for (int n : {1, 4, 16, 17})
-                        if (ssd_at_once(nc, nst, H, P, n) && once_lds(nst, P, n) > 32768) return false;
+                        if (ssd_at_once(nc, nst, true, H, P, n) && once_lds(nst, P, n) > 32768) return false;
     return true;
 }
 static_assert(fits(), "");
-static_assert(ssd_at_once(1, 0, 8, 32, 16) && ssd_at_once(1, 0, 1, 512, 16) && ssd_at_once(9, 9, 8, 32, 16), "");
+static_assert(ssd_at_once(1, 0, true, 8, 32, 16) && ssd_at_once(1, 1, false, 1, 256, 16) && ssd_at_once(9, 9, false, 8, 32, 16), "");
+static_assert(!ssd_at_once(1, 0, false, 8, 32, 16) && !ssd_at_once(2, 2, false, 1, 256, 16) && !ssd_at_once(1, 1, true, 1, 257, 16), "");
 }
 ''')
     cmd = [strd_build.HIPCC] + strd_build.FLAGS + ["--cuda-host-only", "-fsyntax-only", str(src)]
