@@ -286,7 +286,10 @@ __device__ __forceinline__ float slice_lse(const float2 *stat, size_t step, int 
 
 // ---------------------------------------------------------------------------------------------
 // pass 2: grid = kv heads (fastest) x key blocks of 4 waves of 32 TW keys
-template <int D, class SEQ, int TW, bool FUSE>
+// TRIM (trim_rows, below): the log-sum-exps of the first two chunks are there before the loop, from all threads at once (2304 keys, 148
+// rows per head in 18 slices: 10.8 -> 8.6 us), no chunk is requested where there is none, and of a short one only the 32-row tiles that
+// hold a row.  Otherwise every chunk is copied whole by straight code between the products.
+template <int D, class SEQ, int TW, bool FUSE, bool TRIM>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_colsum_kernel(const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                                const float *__restrict__ lse2, const float2 *__restrict__ stat,
                                                                float *__restrict__ part, int M, int N, int Hq, int Hkv,
@@ -335,7 +338,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         float v;
         if constexpr (FUSE) {
             const float2 *at = stat + (size_t)kvh * R + rc;
-            if (TW == 1 && nslice > 8) v = slice_lse<24>(at, (size_t)Hkv * R, nslice);  // uniform
+            // uniform; with 24 in flight instead of 8 (2304 keys in 18 slices, 37 text rows): 32 / 8 heads 16.4 -> 16.0 us, 4 / 4 12.9 -> 12.4,
+            // 3 / 1 13.6 -> 13.2.  (Two key tiles leave no registers for them.)
+            if (TW == 1 && nslice > 8) v = slice_lse<24>(at, (size_t)Hkv * R, nslice);
             else v = slice_lse<8>(at, (size_t)Hkv * R, nslice);
         } else {
             v = lse2[(size_t)kvh * R + rc];
@@ -354,7 +359,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             AT::issue(q + qi * D + st_col * 8, &lds.t[b], w, i);
         };
         const int slots = (min(kRows, R - chunk * kRows) + 31) / 32 * 32 * AT::kVP;  // of the 32-row tiles that hold a row
-        if (slots == kRows * AT::kVP) {  // uniform, as the one below
+        if (!TRIM || slots == kRows * AT::kVP) {  // uniform, as the one below
 #pragma unroll
             for (int i = 0; i < AT::kIssues; ++i) copy(i);
         } else {
@@ -372,16 +377,22 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
     for (int j = 0; j < TW * 16; ++j) col[j] = 0.f;
 
-    // the first two chunks' log-sum-exps by all threads at once (2304 keys, 148 rows per head in 18 slices: 10.8 -> 8.6 us)
-    static_assert(kThreads == 2 * kRows, "a thread per row of two chunks");
-    stage(0, 0, false);
-    lds.lse[tid / kRows][tid % kRows] = row_lse(tid);
+    stage(0, 0, !TRIM);
+    if constexpr (TRIM) {
+        static_assert(kThreads == 2 * kRows, "a thread per row of two chunks");
+        lds.lse[tid / kRows][tid % kRows] = row_lse(tid);
+    } else {
+        stage_lse_store(0);
+    }
     async_tile_wait();
     __syncthreads();
     for (int chunk = 0; chunk < nchunk; ++chunk) {
         const int cur = chunk & 1;
-        const bool more_lse = chunk > 0 && chunk + 1 < nchunk;
-        if (chunk + 1 < nchunk) stage(chunk + 1, cur ^ 1, more_lse);
+        const bool more_lse = (!TRIM || chunk > 0) && chunk + 1 < nchunk;
+        if (!TRIM)
+            stage(min(chunk + 1, nchunk - 1), cur ^ 1, more_lse);
+        else if (chunk + 1 < nchunk)
+            stage(chunk + 1, cur ^ 1, more_lse);
         // Units of work: (query tile qt, key tile kt), 8 products each, then 16 exponentials folded
         // into the column sums.  The products of the next unit are issued before the exponentials
         // of the current one (two accumulators), so the matrix pipe works while the wave does its
@@ -445,7 +456,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                 fold(1, acc1, lse);
             }
         }
-        if (more_lse) stage_lse_store(cur ^ 1);
+        if (!TRIM || more_lse) stage_lse_store(cur ^ 1);
         async_tile_wait();
         __syncthreads();
     }
@@ -539,6 +550,13 @@ Plan make_plan(int M, int N, int Hq, int Hkv, int nseq) {
     return p;
 }
 
+// Whether pass 2 takes the rows with or without branches around their copies (TRIM).  Up to 16 chunks of rows per kv head (10 of
+// 64 elements) they save more than they cost.  With more they lie in the way of the products, the more so where 64 elements leave few of them, or where
+// the query heads per kv head are no power of two and a row is found by a division.  us with / without: 7 heads of one, 700 keys, 1050 rows 35.4 /
+// 36.8, d = 64, 1400 rows 31.7 / 31.1; 28 of 4, d = 64, 700 keys, 56000 rows 854 / 814, d = 128 1190 / 1164; 8 of 1, 64000, d = 64 809 / 788, d = 128 1097 / 1115.
+template <int D>
+constexpr bool trim_rows(int M, int rep) { return (long long)M * rep <= (D == 128 ? 16 : 10) * kRows || (D == 128 && (rep & (rep - 1)) == 0); }
+
 // One sequence (SEQ = OneSeq, nseq = 1) or a packed batch: M and N are then the largest text and
 // vision counts of the batch, and every sequence has a plan's worth of workspace of its own.
 template <int D, class SEQ>
@@ -546,8 +564,10 @@ int run(const void *q, const void *k, float *s, int M, int N, int Hq, int Hkv, f
         int nseq, int ld, bool pad, hipStream_t st) {
     const Plan p = make_plan(M, N, Hq, Hkv, nseq);
     const size_t smem = sizeof(Tile<D>);
-    const auto colsum = p.tw == 1 ? (p.fuse ? &attn_colsum_kernel<D, SEQ, 1, true> : &attn_colsum_kernel<D, SEQ, 1, false>)
-                                  : (p.fuse ? &attn_colsum_kernel<D, SEQ, 2, true> : &attn_colsum_kernel<D, SEQ, 2, false>);
+#define STRD_COLSUM(TW, FUSE) (trim_rows<D>(M, Hq / Hkv) ? &attn_colsum_kernel<D, SEQ, TW, FUSE, true> : &attn_colsum_kernel<D, SEQ, TW, FUSE, false>)
+    const auto colsum = p.tw == 1 ? (p.fuse ? STRD_COLSUM(1, true) : STRD_COLSUM(1, false))
+                                  : (p.fuse ? STRD_COLSUM(2, true) : STRD_COLSUM(2, false));
+#undef STRD_COLSUM
     if (!allow_dynamic_lds(reinterpret_cast<const void *>(&attn_stats_kernel<D, SEQ>), smem) ||
         !allow_dynamic_lds(reinterpret_cast<const void *>(colsum), smem))
         return STRD_EHIP;

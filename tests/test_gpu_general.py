@@ -609,6 +609,17 @@ def test_score_attn_of_many_rows(M, Hq, Hkv):
     assert_close(f(strd.score_attn(q.to(DEV), k.to(DEV))), oracle.score_attn(f(q), f(k)), BOUND[BF16], "s", units=(0,))
 
 
+@pytest.mark.parametrize("M,Hq,Hkv,d,N", [(1280, 1, 1, 64, 300), (1281, 1, 1, 64, 300), (2049, 1, 1, 128, 300), (683, 3, 1, 128, 300),
+                                          (683, 3, 1, 128, 100), (1281, 8, 8, 64, 4400), (37, 8, 8, 64, 4400)])
+def test_score_attn_rows_copied_with_and_without_branches(M, Hq, Hkv, d, N):
+    """Pass 2 on both sides of its lines, 1280 rows per kv head of 64 elements and 2048 of 128 (more of them where the query heads per kv
+    head are a power of two), with one and two key tiles per wave and with the slices combined in it."""
+    _say("score_attn copies M=%d Hq=%d Hkv=%d d=%d N=%d" % (M, Hq, Hkv, d, N))
+    rn = _draw(M + N, BF16)
+    q, k = rn(M, Hq, d), rn(N, Hkv, d)
+    assert_close(f(strd.score_attn(q.to(DEV), k.to(DEV))), oracle.score_attn(f(q), f(k)), BOUND[BF16], "s", units=(0,))
+
+
 @pytest.mark.parametrize("H,G,n", [(64, 1, 128), (8, 1, 64), (48, 2, 128), (80, 1, 64), (20, 1, 128), (70, 1, 64), (32, 2, 64)])
 def test_score_mamba_heads_of_a_group(H, G, n):
     """dt of 8 to 80 heads of a group, added up by 16 lanes per token: fewer heads than lanes, as many, several times as many with and
