@@ -60,9 +60,9 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_kernel(const T *__restrict__
 template <typename T>
 constexpr int held_vecs() { return 16 / sizeof(T); }
 
-// Same, one wave per row with 8-element vectors (d % 8 == 0, 16-byte aligned rows): no barrier.  Rows of up to 8 KB stay in
-// registers, all of a row requested at once (8448 rows of 4096 in bf16 37.5 -> 28 us, 4.9 TB/s; 33 -> 26 at best); of longer ones
-// the second pass re-reads the row from the cache.
+// Same, one wave per row with 8-element vectors (d % 8 == 0, 16-byte aligned rows): no barrier.  HELD: the row stays in registers, all of
+// it requested at once (8448 rows of 4096 in bf16 37.5 -> 28 us, 4.9 TB/s; 33 -> 26 at best); otherwise the second pass re-reads
+// the row from the cache.
 template <typename T, bool HELD>
 __global__ __launch_bounds__(kThreads) void rmsnorm_vec_kernel(const T *__restrict__ x, const T *__restrict__ w,
                                                                T *__restrict__ out, int Tn, int d, float eps) {

@@ -533,6 +533,20 @@ def test_conv1d_silu_parity(T, Cx, Cb, W, extra, dtype):
                  "conv without bias")
 
 
+@pytest.mark.parametrize("T", [1220, 1235])
+def test_conv1d_silu_of_many_workgroups(T):
+    """bf16, 765 workgroups as they come and 775 dealt to the XCDs (no multiple of 8, so padded; the last block of tokens is ragged)."""
+    Cx, Cb, W = 8192, 1024, 4
+    _say("conv1d_silu T=%d Cx=%d Cb=%d" % (T, Cx, Cb))
+    g = torch.Generator(device=DEV).manual_seed(T)
+    x = torch.randn(T, Cx + 2 * Cb, generator=g, device=DEV).to(torch.bfloat16)
+    w = (0.5 * torch.randn(Cx + 2 * Cb, W, generator=g, device=DEV)).to(torch.bfloat16)
+    b = torch.randn(Cx + 2 * Cb, generator=g, device=DEV).to(torch.bfloat16)
+    want = oracle.conv1d_silu(synth.np64(x), synth.np64(w), synth.np64(b))
+    for got, part, name in zip(strd.conv1d_silu(x, w, b, Cx, Cb), np.split(want, [Cx, Cx + Cb], axis=1), "xBC"):
+        assert_close(synth.np64(got), part, TOL[torch.bfloat16], "conv " + name, units=(0,))
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_softplus_dt_parity(dtype):
     _say("softplus_dt %s" % dtype)
@@ -779,9 +793,10 @@ def test_ssd_prefill_middle_length_value_that_is_not_finite():
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("d", [8, 520, 2048, 2056, 4096, 4104, 8192])
+@pytest.mark.parametrize("d", [8, 512, 520, 1024, 1032, 2048, 2056, 4096, 4104, 8192])
 def test_rmsnorm_rows_in_registers_and_longer_ones(d, dtype):
-    """Rows of up to 8 KB are held in registers, longer ones read twice; both sides of the line and a ragged last vector."""
+    """Rows of more than 2 KB and up to 8 are held in registers, shorter and longer ones read twice; both sides of either line (1024 elements
+    in bf16 and 512 in fp32 are the first) and a ragged last vector."""
     _say("rmsnorm d=%d %s" % (d, dtype))
     g = torch.Generator().manual_seed(d)
     x, w = torch.randn(7, d, generator=g).to(dtype).to(DEV), torch.randn(d, generator=g).to(dtype).to(DEV)
