@@ -16,7 +16,7 @@
  *     it allocates) for the life of the process.
  *   - `io` is the element type of the tensors declared `const void*` / `void*`
  *     (STRD_F32 or STRD_BF16); accumulation, exponentials, decay, state and scores
- *     are always fp32.
+ *     are fp32 (strd_ssd_prefill says where a long bf16 sequence is an exception).
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*; NULL = the null
  *     stream) and the call returns without synchronising.
  *   - `ws` is caller-provided scratch [dev] of at least the size the matching
@@ -264,6 +264,12 @@ int strd_compact_varlen(const strd_compact_item *items, int n_items, const int32
  * The bf16 matrix-core kernels add D x_t inside the token product (D joins the bf16 weight of
  * token t on itself), i.e. that term carries a relative rounding error of up to 2^-9, like every
  * other term of the sum and like the bf16 output itself.
+ * Long bf16 sequences are cut into segments: there the part of an output that the state carries is rounded to bf16
+ * before it is added, and the first outputs of a segment are rounded a second time when what the earlier segments left
+ * is added to them.
+ * Values of x, dt or S_in that are not finite stay in the state and show in every later output of their channel (dt: of
+ * their head) and in S_out -- in a sequence cut into segments up to the end of the segment and, behind it, for as long as
+ * the decays since its start are not zero in fp32.
  * `chunk` is the chunk length of the caller's formulation (> 0).  It is validated and
  * otherwise unused: it does NOT select the tiling.  The kernels always cut time into
  * 64-token steps and carry the state across them on chip, so results do not depend on

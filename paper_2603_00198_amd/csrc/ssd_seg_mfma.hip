@@ -46,8 +46,8 @@
 // leaves its final local state and its total decay in the workspace; a second, small kernel adds
 // what the true incoming state contributes to the first tokens of each later segment,
 //   y_t += 2^(l_t) * E c_t,   E = state at the segment's start, l_t = decay since then,
-// for as many 64-token tiles as 2^(l_t) is not yet zero in fp32 (a handful at the decay rates of
-// a trained layer, the whole segment if A = 0: always exact), and completes S_out.
+// for as many 64-token tiles as 2^(l_t) is not yet zero in fp32 (two or three where a head forgets
+// within a hundred tokens, the whole segment if A = 0), and completes S_out.
 //
 // GATHER: token t of the sequence is row idx[t] (t < K) or N + t - K of the tensors, i.e. the
 // kernel reads the uncompacted x, dt, B, C through the kept-index list instead of a compacted copy.
@@ -771,7 +771,7 @@ __global__ __launch_bounds__(threads_for(NC, NH)) void ssd_seg_kernel(SegArgs a,
 // ---- the contribution of the incoming state to the first tokens of segments 1.. and S_out -----
 // grid = (boundary b = 1..nseg, head, share z); b < nseg: y of segment b; b == nseg: S_out.
 // One workgroup per (boundary, head), or a few that take its 64-token tiles in turn (see fix_shares), a wave per 16-channel
-// tile.  At the decay rates of a trained layer the incoming state is gone after two or three tiles, so the kernel is
+// tile.  Where a head forgets within a hundred tokens the incoming state is gone after two or three tiles, and the kernel is
 // a chain of loads: dt, the state E and the rows of the first tile travel together.  The rows of the next tile are fetched when their
 // turn comes: held beside the current ones they cost the second workgroup of a CU.  (Always four workgroups per
 // (boundary, head) read dt and E four times over and take four rounds of the chip at 128 heads; one takes one, and the scan
