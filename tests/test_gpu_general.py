@@ -698,3 +698,26 @@ def test_long_scan_with_its_state_in_place(T, H, G, n):
                                   f(S0[h:h + 1]))
         assert_close(f(y[:, h:h + 1]), y_o, BOUND[BF16], "y of head %d" % h, units=(1,))
         assert_close(f(S[h:h + 1]), S_o, BOUND[BF16], "state of head %d" % h, units=(0,))
+
+
+@pytest.mark.parametrize("K", [64 * 20 + 7, 0])
+def test_gathering_scan_with_its_state_in_place(K):
+    """The bits of the dense call in place, for a sequence that is cut into segments otherwise; and with nothing kept but the text."""
+    N, M, H, P, G, n = 1500, 64 * 17 - 3, 16, 64, 2, 128
+    rn = _draw(K + 1, BF16)
+    x, B, C = rn(N + M, H, P).to(DEV), rn(N + M, G, n).to(DEV), rn(N + M, G, n).to(DEV)
+    dt = torch.nn.functional.softplus(rn(N + M, H).float()).to(DEV)
+    A = -(0.3 + rn(H).float().abs()).to(DEV)
+    S = rn(H, P, n).float().to(DEV)
+    idx = torch.sort(torch.randperm(N, generator=torch.Generator().manual_seed(K))[:K]).values
+    keep = torch.cat([idx, torch.arange(N, N + M)]).to(DEV)
+    S_ref = S.clone()
+    y_ref = _scan_in_place(x[keep], dt[keep], A, B[keep], C[keep], S_ref)
+    idx, y, L = idx.to(torch.int32).to(DEV), torch.empty(K + M, H, P, dtype=BF16, device=DEV), strd.lib()
+    size = L.strd_ssd_prefill_workspace(K + M, H, P, G, n, 64, strd.binding.STRD_BF16)
+    ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+    assert size > 0      # the segments' scratch
+    rc = L.strd_ssd_prefill_gather(x.data_ptr(), dt.data_ptr(), A.data_ptr(), B.data_ptr(), C.data_ptr(), None, S.data_ptr(),
+                                   idx.data_ptr() if K else None, y.data_ptr(), S.data_ptr(), N, M, K, H, P, G, n, 64,
+                                   strd.binding.STRD_BF16, ws.data_ptr(), size, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0 and torch.equal(y, y_ref) and torch.equal(S, S_ref)
