@@ -551,11 +551,14 @@ Plan make_plan(int M, int N, int Hq, int Hkv, int nseq) {
 }
 
 // Whether pass 2 takes the rows with or without branches around their copies (TRIM).  Up to 16 chunks of rows per kv head (10 of
-// 64 elements) they save more than they cost.  With more they lie in the way of the products, the more so where 64 elements leave few of them, or where
-// the query heads per kv head are no power of two and a row is found by a division.  us with / without: 7 heads of one, 700 keys, 1050 rows 35.4 /
-// 36.8, d = 64, 1400 rows 31.7 / 31.1; 28 of 4, d = 64, 700 keys, 56000 rows 854 / 814, d = 128 1190 / 1164; 8 of 1, 64000, d = 64 809 / 788, d = 128 1097 / 1115.
+// 64 elements) they save more than they cost.  With more they lie in the way of the products, the more so where 64 elements leave
+// few of them, or where the query heads per kv head are no power of two and a row is found by a division.  us with / without: 7
+// heads of one, 700 keys, 1050 rows 35.4 / 36.8, d = 64, 1400 rows 31.7 / 31.1; 28 of 4, d = 64, 700 keys, 56000 rows 854 / 814,
+// d = 128 1190 / 1164; 8 of 1, 64000, d = 64 809 / 788, d = 128 1097 / 1115.
 template <int D>
-constexpr bool trim_rows(int M, int rep) { return (long long)M * rep <= (D == 128 ? 16 : 10) * kRows || (D == 128 && (rep & (rep - 1)) == 0); }
+constexpr bool trim_rows(int M, int rep) {
+    return (long long)M * rep <= (D == 128 ? 16 : 10) * kRows || (D == 128 && (rep & (rep - 1)) == 0);
+}
 
 // One sequence (SEQ = OneSeq, nseq = 1) or a packed batch: M and N are then the largest text and
 // vision counts of the batch, and every sequence has a plan's worth of workspace of its own.
@@ -564,7 +567,8 @@ int run(const void *q, const void *k, float *s, int M, int N, int Hq, int Hkv, f
         int nseq, int ld, bool pad, hipStream_t st) {
     const Plan p = make_plan(M, N, Hq, Hkv, nseq);
     const size_t smem = sizeof(Tile<D>);
-#define STRD_COLSUM(TW, FUSE) (trim_rows<D>(M, Hq / Hkv) ? &attn_colsum_kernel<D, SEQ, TW, FUSE, true> : &attn_colsum_kernel<D, SEQ, TW, FUSE, false>)
+    const bool trim = trim_rows<D>(M, Hq / Hkv);
+#define STRD_COLSUM(TW, FUSE) (trim ? &attn_colsum_kernel<D, SEQ, TW, FUSE, true> : &attn_colsum_kernel<D, SEQ, TW, FUSE, false>)
     const auto colsum = p.tw == 1 ? (p.fuse ? STRD_COLSUM(1, true) : STRD_COLSUM(1, false))
                                   : (p.fuse ? STRD_COLSUM(2, true) : STRD_COLSUM(2, false));
 #undef STRD_COLSUM
