@@ -14,9 +14,13 @@ namespace {
 
 inline bool io_ok(strd_dtype io) { return io == STRD_F32 || io == STRD_BF16; }
 inline hipStream_t as_stream(void *s) { return (hipStream_t)s; }
-// The two matrix-core kernels of the scan: segments of the sequence side by side (ssd_seg) where that
-// pays, one workgroup per (head, 32 channels) over the whole sequence (ssd_mfma) otherwise.  `in_place`: S_out lies over
-// S_in -- the first segment reads the one while the last writes the other, a walk reads its part before it writes it.
+// The matrix-core kernels of the scan: segments of the sequence side by side, four heads of a group per workgroup (ssd_quad) where
+// the shape allows and that pays, else fewer heads (ssd_seg), or one workgroup per (head, 32 channels) over the whole sequence (ssd_mfma).
+// `in_place`: S_out lies over S_in -- the first segment reads the one while the last writes the other, a walk reads its part
+// before it writes it.
+inline bool use_quad(int T, int rows, int H, int P, int G, int n, strd_dtype io, bool in_place = false) {
+    return ssd_quad_supported(T, rows, H, P, G, n, io) && ssd_quad_preferred(T, H) && !in_place;
+}
 inline bool use_seg(int T, int rows, int H, int P, int G, int n, strd_dtype io, bool in_place = false) {
     return ssd_seg_supported(T, rows, H, P, G, n, io) &&
            ((ssd_seg_preferred(T, H, P, G) && !in_place) || !ssd_mfma_supported(T, rows, H, P, G, n, io));
@@ -278,6 +282,7 @@ int strd_compact_varlen(const strd_compact_item *items, int n_items, const int32
 size_t strd_ssd_prefill_workspace(int T, int H, int P, int G, int n, int chunk, strd_dtype io) {
     (void)chunk;
     if (T < 1 || H < 1 || P < 1 || G < 1 || n < 1 || H % G) return 0;
+    if (use_quad(T, T, H, P, G, n, io)) return ssd_quad_ws(T, H, n);
     if (use_seg(T, T, H, P, G, n, io)) return ssd_seg_ws(T, H, P, G, n);
     return ssd_mfma_supported(T, T, H, P, G, n, io) || !ssd_general_supported(n) ? 0 : ssd_general_ws(T, H, P, n);
 }
@@ -292,7 +297,10 @@ int strd_ssd_prefill(const void *x, const float *dt, const float *A, const void 
     const size_t need = strd_ssd_prefill_workspace(T, H, P, G, n, chunk, io);
     const bool missing = need && (!ws || ws_bytes < need);
     if (missing && mfma) return STRD_EWORKSPACE;
-    if (use_seg(T, T, H, P, G, n, io, overlap(S_in, S_out, (size_t)H * P * n * sizeof(float))))
+    const bool in_place = overlap(S_in, S_out, (size_t)H * P * n * sizeof(float));
+    if (use_quad(T, T, H, P, G, n, io, in_place))
+        return ssd_quad(x, dt, A, B, C, D, S_in, y, S_out, nullptr, 0, 0, T, H, G, n, ws, as_stream(stream));
+    if (use_seg(T, T, H, P, G, n, io, in_place))
         return ssd_seg(x, dt, A, B, C, D, S_in, y, S_out, nullptr, 0, 0, T, H, P, G, n, ws, as_stream(stream));
     if (mfma) return ssd_mfma(x, dt, A, B, C, D, S_in, y, S_out, nullptr, 0, 0, T, H, P, G, n, as_stream(stream));
     if (!ssd_general_supported(n)) return STRD_EUNSUPPORTED;
@@ -313,13 +321,19 @@ int strd_ssd_prefill_gather(const void *x, const float *dt, const float *A, cons
     if (!ssd_seg_supported((int)T, N + M, H, P, G, n, io) && !ssd_mfma_supported((int)T, N + M, H, P, G, n, io))
         return STRD_EUNSUPPORTED;
     // the same choice of kernel as strd_ssd_prefill makes for K + M tokens: the results must be the same bits
-    const bool in_place = overlap(S_in, S_out, (size_t)H * P * n * sizeof(float)) && ssd_mfma_supported((int)T, N + M, H, P, G, n, io);
+    const bool same = overlap(S_in, S_out, (size_t)H * P * n * sizeof(float));
+    const bool quad = use_quad((int)T, (int)T, H, P, G, n, io, same) && ssd_quad_supported((int)T, N + M, H, P, G, n, io);
+    const bool in_place = same && ssd_mfma_supported((int)T, N + M, H, P, G, n, io);
     const bool old = !use_seg((int)T, (int)T, H, P, G, n, io, in_place) || !ssd_seg_supported((int)T, N + M, H, P, G, n, io);
-    if (old && !ssd_mfma_supported((int)T, N + M, H, P, G, n, io)) return STRD_EUNSUPPORTED;
-    const size_t need = old ? 0 : ssd_seg_ws((int)T, H, P, G, n);
+    if (!quad && old && !ssd_mfma_supported((int)T, N + M, H, P, G, n, io)) return STRD_EUNSUPPORTED;
+    const size_t need = quad ? ssd_quad_ws((int)T, H, n) : old ? 0 : ssd_seg_ws((int)T, H, P, G, n);
     if (need && (!ws || ws_bytes < need)) return STRD_EWORKSPACE;
     if (K == 0) {  // only the text rows survive: a dense scan over the tail of the tensors
         const size_t es = 2;
+        if (quad)
+            return ssd_quad((const char *)x + (size_t)N * H * P * es, dt + (size_t)N * H, A,
+                            (const char *)B + (size_t)N * G * n * es, (const char *)C + (size_t)N * G * n * es, D, S_in, y,
+                            S_out, nullptr, 0, 0, (int)T, H, G, n, ws, as_stream(stream));
         if (old)
             return ssd_mfma((const char *)x + (size_t)N * H * P * es, dt + (size_t)N * H, A,
                             (const char *)B + (size_t)N * G * n * es, (const char *)C + (size_t)N * G * n * es, D, S_in, y,
@@ -328,6 +342,7 @@ int strd_ssd_prefill_gather(const void *x, const float *dt, const float *A, cons
                        (const char *)B + (size_t)N * G * n * es, (const char *)C + (size_t)N * G * n * es, D, S_in, y,
                        S_out, nullptr, 0, 0, (int)T, H, P, G, n, ws, as_stream(stream));
     }
+    if (quad) return ssd_quad(x, dt, A, B, C, D, S_in, y, S_out, idx, N, K, (int)T, H, G, n, ws, as_stream(stream));
     if (old) return ssd_mfma(x, dt, A, B, C, D, S_in, y, S_out, idx, N, K, (int)T, H, P, G, n, as_stream(stream));
     return ssd_seg(x, dt, A, B, C, D, S_in, y, S_out, idx, N, K, (int)T, H, P, G, n, ws, as_stream(stream));
 }
