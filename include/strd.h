@@ -265,11 +265,12 @@ int strd_compact_varlen(const strd_compact_item *items, int n_items, const int32
  * token t on itself), i.e. that term carries a relative rounding error of up to 2^-9, like every
  * other term of the sum and like the bf16 output itself.
  * Long bf16 sequences are cut into segments: there the part of an output that the state carries is rounded to bf16
- * before it is added, and the first outputs of a segment are rounded a second time when what the earlier segments left
- * is added to them.
+ * before it is added (not where four heads of a group and P = 64 go together, from 64 heads on), and the first outputs of
+ * a segment are rounded a second time when what the earlier segments left is added to them (from the 65th token on
+ * where four heads go together).
  * Values of x, dt or S_in that are not finite stay in the state and show in every later output of their channel (dt: of
- * their head) and in S_out -- in a sequence cut into segments up to the end of the segment and, behind it, for as long as
- * the decays since its start are not zero in fp32.
+ * their head) and in S_out -- in a sequence cut into segments of fewer heads up to the end of the segment and, behind it,
+ * for as long as the decays since its start are not zero in fp32.
  * `chunk` is the chunk length of the caller's formulation (> 0).  It is validated and
  * otherwise unused: it does NOT select the tiling.  The kernels always cut time into
  * 64-token steps and carry the state across them on chip, so results do not depend on
@@ -280,7 +281,8 @@ int strd_compact_varlen(const strd_compact_item *items, int n_items, const int32
  *   ws  [dev] strd_ssd_prefill_workspace(T, ...) bytes.  bf16 matrix-core shapes: 0 for short
  *       sequences; for long ones the sequence is cut into segments that run side by side, and the local end state and total
  *       decay of every segment but the last pass through the workspace ((segments - 1) * H * P * n
- *       + segments * H floats); too small or NULL when needed: STRD_EWORKSPACE.  Other shapes: the state
+ *       + segments * H floats; with four heads together also 64 * P floats per head and segment and one per head and
+ *       token); too small or NULL when needed: STRD_EWORKSPACE.  Other shapes: the state
  *       before every 64-token chunk and the chunks' decays, (P * n + 1) * H floats per chunk, of as many
  *       chunks as fit 256 MB (one at least), and two states more when that is not all of them.  Here it
  *       may be smaller or NULL: the call then walks the sequence token by token, which takes 65 times as

@@ -19,7 +19,7 @@ inline hipStream_t as_stream(void *s) { return (hipStream_t)s; }
 // `in_place`: S_out lies over S_in -- the first segment reads the one while the last writes the other, a walk reads its part
 // before it writes it.
 inline bool use_quad(int T, int rows, int H, int P, int G, int n, strd_dtype io, bool in_place = false) {
-    return ssd_quad_supported(T, rows, H, P, G, n, io) && ssd_quad_preferred(T, H) && !in_place;
+    return ssd_quad_supported(T, rows, H, P, G, n, io) && ssd_quad_preferred(T, H, P, G) && !in_place;
 }
 inline bool use_seg(int T, int rows, int H, int P, int G, int n, strd_dtype io, bool in_place = false) {
     return ssd_seg_supported(T, rows, H, P, G, n, io) &&

@@ -319,7 +319,7 @@ int ssd_seg(const void *x, const float *dt, const float *A, const void *B, const
             void *ws, hipStream_t st);
 bool ssd_quad_supported(int T, int rows, int H, int P, int G, int n, strd_dtype io);
 size_t ssd_quad_ws(int T, int H, int n);
-bool ssd_quad_preferred(int T, int H);
+bool ssd_quad_preferred(int T, int H, int P, int G);
 int ssd_quad(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D, const float *S_in,
              void *y, float *S_out, const int32_t *idx, int N, int K, int T, int H, int G, int n, void *ws, hipStream_t st);
 bool ssd_mfma_supported(int T, int rows, int H, int P, int G, int n, strd_dtype io);

@@ -10,25 +10,30 @@
 //   (e) S^T[n,p] = 2^(l_Q) S^T[n,p] + sum_j b_j[n] (w_j x_j[p]),  w_j = dt_j 2^(l_Q-l_j)
 // every product a v_mfma_f32_16x16x32_bf16: 32 tokens are one contraction of (c) and (e).
 //
-// Waves (12, three per SIMD, 168 registers each).  Eight compute waves, two per head, each with a slab of 32
-// channels whose state S^T[n, 32] stays in fp32 accumulator registers for the whole segment; they do (d), (c), (e) and
-// store the outputs, so an output is summed in fp32 from its first term to its last and rounded once.  Two G waves make the weights M of two
-// heads each, one step ahead, and leave them in LDS in the operand layout of (c): (a) is the same for every head of a group.
-// One wave requests the asynchronous global -> LDS copies of the B, C and x tiles (two steps ahead of their first use), one helper wave dt,
-// the scans l_t with everything that follows from them (two steps ahead) and the row tables of the gather form.
-// One LDS-only barrier per step.
+// Waves (12, three per SIMD, 168 registers each).  Eight compute waves, two per head, each with a slab of 32 channels whose state
+// S^T[n, 32] stays in fp32 accumulator registers for the whole segment; they do (d), (c), (e) and store the outputs, so an output is summed
+// in fp32 from its first term to its last and rounded once.  Two G waves make the weights M of two heads each, one step ahead, and leave them
+// in LDS in the operand layout of (c): (a) is the same for every head of a group.  One wave requests the asynchronous global -> LDS copies
+// of the B, C and x tiles (three steps ahead), one helper wave dt, the scans l_t with everything that follows from them (two steps ahead) and
+// the row tables of the gather form.  One LDS-only barrier per step.
 //
 // The accumulator layout of (e) is at the same time the A-operand layout of (d) (the contraction index n runs over the
 // accumulator rows a lane holds), so the state is converted to bf16 in registers and never passes through LDS.  Column m of a
 // slab's 16-channel tile pt is channel 8 (m / 4) + 4 pt + m % 4: a lane then holds 8 consecutive channels of its token and stores 16 bytes.
 //
-// Why four heads and 32 tokens.  Per token and head the tiles of B and C cross the CU's copy path a quarter of a time, every SIMD holds
-// two compute waves whose products and vector instructions fill each other's gaps, and three to four tiles of each stream fit the LDS.
+// Why four heads and 32 tokens.  With two heads per workgroup (ssd_seg) a step of 64 tokens takes 5400 cycles, this one of twice the heads and
+// half the tokens 3400: the tiles of B and C cross the CU's copy path half as often and the b.c products are made for two heads at once
+// instead of for each; every output is added up where its accumulators are, without a way through LDS and back through 16 bits; and each SIMD has two
+// compute waves whose stalls the other fills.  What bounds a step: the vector instructions and products of the two compute waves of a SIMD do
+// not overlap on this machine (36 products and 190 vector instructions each: 576 + 820 cycles of issue, 2600 measured for the pair without any
+// LDS read, 2900 with them, 3160 with the G wave; copies, stores and G waves cost no cycles of a step but clock: 2.2 -> 1.85 GHz).
+// Orders that changed nothing: products and vector work in turn or in blocks, with and without wave priorities, every LDS read a phase earlier, the
+// copies dealt to three waves.
 //
 // Segments.  Each starts from a zero state (the first from S_in) and leaves its final local state and its total decay in the
 // workspace; a second, small kernel adds what the true incoming state contributes to the tokens of each later segment,
 //   y_t += 2^(l_t) * E c_t,   E = state at the segment's start, l_t = decay since then,
-// for as long as 2^(l_t) is not zero in fp32, and completes S_out.  The first kSeamTok outputs of a later segment wait for it in fp32, so that
+// for as long as 2^(l_t) is not zero in fp32, and completes S_out.  The first kSeamTok outputs of a later segment wait for that in fp32, so that
 // where a head forgets within that many tokens no output is rounded twice.  Values that are not finite are never forgotten: a
 // segment whose final state holds one says so, and the later segments then add it to all their tokens.
 //
@@ -53,7 +58,6 @@ constexpr int kRB = 4;      // B / C tiles in LDS: of this step (compute waves),
 constexpr int kRX = 4;      // x tiles in LDS: of this step, three on their way
 constexpr int kRD = 4;      // dt rows in LDS
 constexpr int kSeamTok = 64;   // outputs of a later segment that are kept in fp32 for the seam (a multiple of the fix kernel's tile)
-constexpr int kDecayTok = 128;  // tokens of a later segment whose decays are kept
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct QuadArgs {
@@ -66,7 +70,8 @@ struct QuadArgs {
     float *lend;        // [nseg - 1, H, P, n]: final local state of every segment but the last
     float *ltot;        // [nseg, H]: total log2 decay of every segment
     uint32_t *lost;     // [nseg - 1, H, 2]: 1 where the final local state of a slab holds a value that is not finite
-    float *seam;        // [nseg - 1, H, kDecayTok]: log2 decay since the start of a later segment, of its first tokens
+    float *seam;        // [nseg - 1, H, seg_steps * 32]: log2 decay of the tokens of a later segment since its start, while it is not zero
+    int32_t *life;      // [nseg - 1, H]: for how many steps that is
     float *ybuf;        // [nseg - 1, kSeamTok, H * P]: first outputs of the later segments, before the seam
     const int32_t *idx;
     int N, K, T, H, G;
@@ -178,8 +183,15 @@ __device__ __forceinline__ void issue_b_frags(uint32_t e, uint32_t o, strd_s16x4
         : "memory");
 }
 
-#define SGB1(nv) __builtin_amdgcn_sched_group_barrier(0x8, 1, 0); __builtin_amdgcn_sched_group_barrier(0x2, nv, 0);
-#define SGB_E SGB1(4) SGB1(4) SGB1(4) SGB1(4) SGB1(4) SGB1(4) SGB1(4) SGB1(4)
+// The scheduler's order for the code before it: eight products, four vector instructions behind each (which also keeps the
+// registers of the region within bounds).
+__device__ __forceinline__ void eight_products_with_vector_work() {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x2, 4, 0);
+    }
+}
 
 // Channel (in the head) of column m of tile pt of slab cw.
 __device__ __forceinline__ int chan_of(int cw, int pt, int m) { return 32 * cw + 8 * (m >> 2) + 4 * pt + (m & 3); }
@@ -246,9 +258,8 @@ __device__ __forceinline__ void compute_wave(LdsQ<NS> &lds, const QuadArgs &a, i
         // (d): Y^T[p, t] = sum_n S[p, n] c_t[n].  A operand straight from the accumulators: the lane holds rows
         // 4 lb .. 4 lb + 3 of state tiles 2 ks and 2 ks + 1 for column p = lr, i.e. the k slots n = 32 ks + 4 lb + s (s < 4),
         // 32 ks + 16 + 4 lb + s - 4 (s >= 4); the c fragments are read in the same slot order (two 8-byte reads).
-        // A product takes the matrix pipe 16 cycles and a vector instruction 4 of the other: the vector work of a step is dealt
-        // out between its products, four or five instructions to each -- the state's conversion and the weights of x here, the state's
-        // decay in (e).
+        // The vector work of a step is dealt out between its products, four or five instructions to each: the state's conversion and the
+        // weights of x here, the state's decay in (e).
         f32x4 yacc[2][2];  // [query block][tile]
         bf16x8 xf[2], xwf[2];
         auto decay = [&](int nt, int pt) __attribute__((always_inline)) { sacc[nt][pt] *= dq; };
@@ -318,7 +329,7 @@ __device__ __forceinline__ void compute_wave(LdsQ<NS> &lds, const QuadArgs &a, i
             for (int pt = 0; pt < 2; ++pt) sacc[d][pt] = mfma16(tr_pair(ba[2 * d], ba[2 * d + 1]), xwf[pt], sacc[d][pt]);
             if (d + 2 < NT) decay(d + 2, 0), decay(d + 2, 1);
         }
-        SGB_E
+        eight_products_with_vector_work();
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (NT == 8) {
             lds_settle8_but<2 * KS>(bb);
@@ -330,7 +341,7 @@ __device__ __forceinline__ void compute_wave(LdsQ<NS> &lds, const QuadArgs &a, i
                     sacc[d % NT][pt] = mfma16(tr_pair(bb[2 * (d - 4)], bb[2 * (d - 4) + 1]), xwf[pt], sacc[d % NT][pt]);
                 if (d + 2 < NT) decay(d + 2, 0), decay(d + 2, 1);
             }
-            SGB_E
+            eight_products_with_vector_work();
             __builtin_amdgcn_sched_barrier(0);
         }
         // outputs: 16 bytes of this lane's token
@@ -481,6 +492,7 @@ __device__ __forceinline__ void helper_wave(LdsQ<NS> &lds, const QuadArgs &a, in
                 (__attribute__((address_space(3))) void *)lds.dt[i % kRD][k], 4, 0, 0);
     };
     float ltot[2] = {0.f, 0.f};
+    int life[2] = {0, 0};
     auto make_scan = [&](int k, int i, float raw) __attribute__((always_inline)) {
         const float dv = (tok0 + i * kQ + j < a.T) ? raw : 0.f;
         float inc = dv * Al2[k];  // inclusive prefix sum over the 32 lanes of a head
@@ -500,8 +512,10 @@ __device__ __forceinline__ void helper_wave(LdsQ<NS> &lds, const QuadArgs &a, in
         m.w[slot_of(j)] = dv * fast_exp2(tot - inc);
         m.carry[j] = fast_exp2(inc);
         if (j < 16) m.fw[j] = dv * fast_exp2(l15 - inc);  // the exponent is <= 0 for these
-        if (seg > 0 && i < kDecayTok / kQ)  // uniform
-            a.seam[((size_t)(seg - 1) * a.H + h0 + 2 * k + half) * kDecayTok + i * kQ + j] = ltot[k] + inc;
+        if (seg > 0 && fast_exp2(ltot[k]) != 0.f) {  // for the seam, while anything of what lies before the segment is left
+            a.seam[((size_t)(seg - 1) * a.H + h0 + 2 * k + half) * (a.seg_steps * kQ) + i * kQ + j] = ltot[k] + inc;
+            life[k] = i + 1;
+        }
         ltot[k] += tot;
     };
     constexpr int kNewest = 2 + (GATHER ? 1 : 0);  // copies requested per step
@@ -554,7 +568,10 @@ __device__ __forceinline__ void helper_wave(LdsQ<NS> &lds, const QuadArgs &a, in
     }
     if (j == 0 && a.ltot) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k) a.ltot[(size_t)seg * a.H + h0 + 2 * k + half] = ltot[k];
+        for (int k = 0; k < 2; ++k) {
+            a.ltot[(size_t)seg * a.H + h0 + 2 * k + half] = ltot[k];
+            if (seg > 0) a.life[(size_t)(seg - 1) * a.H + h0 + 2 * k + half] = life[k];
+        }
     }
 }
 
@@ -667,33 +684,35 @@ __global__ __launch_bounds__(kThreads) void ssd_quad_kernel(QuadArgs a, int nuni
 }
 
 // ---- the contribution of the incoming state to the tokens of segments 1.. and S_out -----
-// grid = (boundary b = 1..nseg, four heads of a group, share z); b < nseg: y of segment b; b == nseg: S_out.
-// A wave per head and 16-channel tile; shares take the 64-token tiles of a segment in turn.  Where a head forgets within two tiles the kernel
-// is a launch and one round of loads: what the first tile needs -- the state E, the outputs that wait in fp32, the
-// decays, which the segment's own scan has left -- is requested before anything is waited for, and the c rows of two tiles, which
-// the 16 waves share, go through LDS (each wave with its own copy of them took 23.5 us for 7 boundaries of 128 heads, this
-// takes FIXTIME).
+// One workgroup per (four heads of a group, boundary b = 1..nseg), or a few that take its 64-token tiles in turn (share z); b < nseg: y of
+// segment b; b == nseg: S_out.  A wave per head and 16-channel tile.  Where the heads forget within a tile the kernel is a launch and one
+// round of loads: the state E, the outputs that wait in fp32 and the decays, which the segment's own scan has left, are
+// requested before anything is waited for, and the c rows, which the 16 waves share, go through LDS (each wave with its own copy of
+// them took 23.5 us for 7 boundaries of 128 heads, this 14).  Where they remember for longer, the c rows, outputs and decays of the next
+// tile travel while a tile is corrected.  The boundaries of a head lie on one XCD: their states E are sums over the same final states.
 constexpr int kFixThreads = 1024;
 constexpr int kFixTile = 64;  // tokens per tile: a lane per token
-static_assert(kSeamTok == kFixTile && kDecayTok == 2 * kFixTile, "the outputs of the first tile wait in fp32, the decays of two tiles are there");
+static_assert(kSeamTok == kFixTile, "the outputs of the first tile wait in fp32");
 constexpr float kTiny = 1.17549435e-38f;  // smallest normal number
 
 template <int NS, bool GATHER>
-__global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a) {
+__global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, int nunits) {
     using TB = typename LdsQ<NS>::TB;
     constexpr int KS = NS / 32;
-    __shared__ TB ct[kDecayTok / kQ];  // c rows of the first two tiles
-    const int b = 1 + blockIdx.x, z = blockIdx.z, nz = gridDim.z;
+    __shared__ TB ct[2][kFixTile / kQ];  // c rows of this tile and the next
+    const int unit = xcd_swizzle(blockIdx.x, nunits);
+    if (unit >= nunits) return;
+    const int b = 1 + unit % a.nseg, h0 = unit / a.nseg * kHeads, z = blockIdx.y, nz = gridDim.y;
     const int lane = threadIdx.x & 63, lr = lane & 15, lb = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), pt = wave & 3;  // 16-channel tile of this wave
-    const int h = blockIdx.y * kHeads + (wave >> 2);
+    const int h = h0 + (wave >> 2);
     const size_t seg_elems = (size_t)a.H * kP * NS;
     // A value that is not finite in an earlier segment's state reaches everything behind it, whatever the decays: then no weight below
     // is less than the smallest normal number and no tile is skipped.
-    auto any_lost = [&](int n) {  // in the final states of segments 0 .. n - 1
+    auto any_lost = [&](int head, int n) {  // in the final states of segments 0 .. n - 1
         bool lost = false;
         for (int s0 = 0; s0 < n; s0 += 64) {
-            const uint32_t *p = a.lost + ((size_t)min(s0 + lane, n - 1) * a.H + h) * 2;
+            const uint32_t *p = a.lost + ((size_t)min(s0 + lane, n - 1) * a.H + head) * 2;
             lost |= __ballot((p[0] | p[1]) != 0) != 0;
         }
         return lost;
@@ -703,7 +722,7 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a) {
     // (uniform; the loops below stop at the first segment whose weight is zero)
     if (b == a.nseg) {
         if (!a.S_out) return;
-        const bool lost = any_lost(b - 1);
+        const bool lost = any_lost(h, b - 1);
         float f = weight(lost, fast_exp2(a.ltot[(size_t)(b - 1) * a.H + h]));
         constexpr int per = kP * NS / 4, kStep = kFixThreads / kHeads;  // float4s of the head's state, threads of the head
         f32x4 *dst = reinterpret_cast<f32x4 *>(a.S_out + (size_t)h * kP * NS);
@@ -716,41 +735,70 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a) {
     }
     const uint32_t HP = (uint32_t)a.H * kP;
     const int g = h / (a.H / a.G);
-    const int tok0 = b * a.seg_steps * kQ;
-    const int tend = min(a.T, (b + 1) * a.seg_steps * kQ);
-    if (tok0 + z * kFixTile >= tend) return;
+    const int seg_tok = a.seg_steps * kQ, tok0 = b * seg_tok, tend = min(a.T, tok0 + seg_tok);
+    const int ntiles = (tend - tok0 + kFixTile - 1) / kFixTile;
+    if (z >= ntiles) return;
     auto row_of = [&](int t) -> size_t {
         t = min(t, a.T - 1);
         return GATHER ? (size_t)gather_row(a, t, a.idx[min(t, a.K - 1)]) : (size_t)t;
     };
-    // c rows, 1 KB per instruction, the pieces of a row permuted as in the scan's tiles
-    constexpr int kCopies = sizeof(ct) / sizeof(TB) * TB::kIssues;
-#pragma unroll
-    for (int k = wave; k < kCopies; k += kFixThreads / 64) {
-        const int row0 = lane / (64 / TB::kRows);
-        copy16(reinterpret_cast<const char *>(a.C + (row_of(tok0 + k * TB::kRows + row0) * a.G + g) * NS) + ((lane % (64 / TB::kRows)) ^ (row0 & 3)) * 16,
-               ct[k / TB::kIssues].v + 1088 * (k % TB::kIssues));
-    }
+    // c rows of tile k, 1 KB per instruction, the pieces of a row permuted as in the scan's tiles
+    auto copy_c = [&](int k, TB *dst) __attribute__((always_inline)) {
+        if (wave < kFixTile / TB::kRows) {
+            const int row0 = lane / (64 / TB::kRows);
+            copy16(reinterpret_cast<const char *>(a.C + (row_of(tok0 + k * kFixTile + wave * TB::kRows + row0) * a.G + g) * NS) + ((lane % (64 / TB::kRows)) ^ (row0 & 3)) * 16,
+                   dst[wave / TB::kIssues].v + 1088 * (wave % TB::kIssues));
+        }
+    };
+    static_assert(kFixTile / TB::kRows <= kFixThreads / 64, "one copy per wave");
     // uniform pointers, to which a lane adds an offset of 32 bits
     auto state_of = [&](int s) { return a.lend + (size_t)s * seg_elems + ((size_t)h * kP + 16 * pt) * NS; };
     const uint32_t e_at = lr * NS + 8 * lb;
     const int col = h * kP + 16 * pt;
     auto in_tile = [&](int k, int tt) { return (uint32_t)min(16 * tt + lr, a.T - 1 - (tok0 + k * kFixTile)); };  // tokens past T: the last
     auto y_of = [&](int k) { return a.y + (size_t)(tok0 + k * kFixTile) * HP + col; };
+    const float *seam = a.seam + ((size_t)(b - 1) * a.H + h) * seg_tok;
+    copy_c(z, ct[0]);
     // E = state at the start of segment b, as A-operand fragments (rows p = 16 pt + lr, k slots n = 32 ks + 8 lb + s)
-    f32x4 e[KS][2], y[4];
+    f32x4 e[KS][2];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         e[ks][0] = *reinterpret_cast<const f32x4 *>(state_of(b - 1) + e_at + 32 * ks);
         e[ks][1] = *reinterpret_cast<const f32x4 *>(state_of(b - 1) + e_at + 32 * ks + 4);
     }
-    const float lt = a.ltot[(size_t)(b - 1) * a.H + h];
-    const float *sw = a.seam + ((size_t)(b - 1) * a.H + h) * kDecayTok;
-    float inc = sw[lane], inc1 = sw[kFixTile + lane];  // lane = token: decay since the segment's start
-    const float *yw = a.ybuf + (size_t)(b - 1) * kSeamTok * HP + col;
+    f32x4 y[4];
+    bf16x4 yn[4];
+    auto load_y = [&](int k) __attribute__((always_inline)) {
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt) y[tt] = *reinterpret_cast<const f32x4 *>(yw + ((16 * tt + lr) * HP + 4 * lb));
-    const bool lost = any_lost(b);
+        for (int tt = 0; tt < 4; ++tt) yn[tt] = *reinterpret_cast<const bf16x4 *>(y_of(k) + (in_tile(k, tt) * HP + 4 * lb));
+    };
+    auto take_y = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) y[tt][q] = (float)yn[tt][q];
+    };
+    if (z == 0) {
+        const float *yw = a.ybuf + (size_t)(b - 1) * kSeamTok * HP + col;
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) y[tt] = *reinterpret_cast<const f32x4 *>(yw + ((16 * tt + lr) * HP + 4 * lb));
+    } else {
+        load_y(z);
+        take_y();
+    }
+    float inc = seam[min(z * kFixTile + lane, seg_tok - 1)];  // lane = token: decay since the segment's start
+    const float lt = a.ltot[(size_t)(b - 1) * a.H + h];
+    // tiles that anything of E reaches, for this head and for all four; the outputs of the first tile are written in any case
+    int mine = 1, most = 1;
+    bool lost = false;
+#pragma unroll
+    for (int q = 0; q < kHeads; ++q) {
+        const bool l = any_lost(h0 + q, b);
+        const int n = l ? ntiles : min(ntiles, (a.life[(size_t)(b - 1) * a.H + h0 + q] * kQ + kFixTile - 1) / kFixTile);
+        most = max(most, n);
+        if (h0 + q == h) mine = n, lost = l;
+    }
+    mine = max(mine, 1);
     float f = weight(lost, fast_exp2(lt));
     for (int s = b - 2; s >= 0 && f != 0.f; --s) {
         const float *src = state_of(s) + e_at;
@@ -764,55 +812,49 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a) {
     bf16x8 ef[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) ef[ks] = cat8(to_bf16x4(e[ks][0]), to_bf16x4(e[ks][1]));
-    // the outputs of tile k; those of the first one are written in any case
-    auto correct = [&](int k, float cr, auto c_of) __attribute__((always_inline)) {
+    const int c_at = TB::row_at(lr) + 16 * (lb ^ (lr & 3));
+    const int life_tok = a.life[(size_t)(b - 1) * a.H + h] * kQ;  // tokens whose decays are there; behind them they are zero
+    bf16x4 out[4];
+    auto store = [&](int k) __attribute__((always_inline)) {
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-            const float crt = __shfl(cr, 16 * tt + lr, 64);
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) acc = mfma16(ef[ks], c_of(tt, ks), acc);
-            if (tok0 + k * kFixTile + 16 * tt + lr < tend && (crt != 0.f || k == 0)) {
-                bf16x4 out;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) out[q] = (bf16_t)(crt != 0.f ? y[tt][q] + crt * acc[q] : y[tt][q]);
-                *reinterpret_cast<bf16x4 *>(y_of(k) + (in_tile(k, tt) * HP + 4 * lb)) = out;
+        for (int tt = 0; tt < 4; ++tt)
+            if (tok0 + k * kFixTile + 16 * tt + lr < tend) *reinterpret_cast<bf16x4 *>(y_of(k) + (in_tile(k, tt) * HP + 4 * lb)) = out[tt];
+    };
+    int last = -1;  // the tile whose outputs wait to be stored
+    for (int k = z, par = 0;; par ^= 1) {
+        async_tile_wait();
+        lds_barrier();  // the c rows of this tile are there, and everyone is done with those of the tile before
+        const int next = k + nz;
+        if (last >= 0) store(last);
+        last = -1;
+        float incn = 0.f;
+        if (next < most) {
+            copy_c(next, ct[par ^ 1]);
+            if (next < mine) {
+                load_y(next);
+                incn = seam[min(next * kFixTile + lane, seg_tok - 1)];
             }
         }
-    };
-    auto reached = [&](int k) {  // by anything of E (uniform)
-        return tok0 + k * kFixTile < tend && (lost || fast_exp2(read_lane_f32(inc, kFixTile - 1)) != 0.f);
-    };
-    auto load_y = [&](int k) __attribute__((always_inline)) {
+        if (k < mine) {
+            const float cr = k * kFixTile + lane < life_tok ? weight(lost, fast_exp2(inc)) : lost ? kTiny : 0.f;
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-            const bf16x4 v = *reinterpret_cast<const bf16x4 *>(y_of(k) + (in_tile(k, tt) * HP + 4 * lb));
+            for (int tt = 0; tt < 4; ++tt) {
+                const float crt = __shfl(cr, 16 * tt + lr, 64);
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int q = 0; q < 4; ++q) y[tt][q] = (float)v[q];
+                for (int ks = 0; ks < KS; ++ks)
+                    acc = mfma16(ef[ks], *reinterpret_cast<const bf16x8 *>(ct[par][tt >> 1].v + c_at + (tt & 1) * TB::kBlock + 64 * ks), acc);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) out[tt][q] = (bf16_t)(crt != 0.f ? y[tt][q] + crt * acc[q] : y[tt][q]);
+            }
+            last = k;
         }
-    };
-    async_tile_wait();
-    __syncthreads();
-    const int c_at = TB::row_at(lr) + 16 * (lb ^ (lr & 3));
-    if (z == 0)
-        correct(0, weight(lost, fast_exp2(inc)), [&](int tt, int ks) { return *reinterpret_cast<const bf16x8 *>(ct[tt >> 1].v + c_at + (tt & 1) * TB::kBlock + 64 * ks); });
-    if (!reached(1)) return;
-    inc = inc1;
-    if ((1 & (nz - 1)) == z) {
-        load_y(1);
-        correct(1, weight(lost, fast_exp2(inc)), [&](int tt, int ks) { return *reinterpret_cast<const bf16x8 *>(ct[2 + (tt >> 1)].v + c_at + (tt & 1) * TB::kBlock + 64 * ks); });
+        if (next >= most) break;
+        take_y();
+        inc = incn;
+        k = next;
     }
-    const float Al2 = a.A[h] * kLog2e;
-    for (int k = 2; reached(k); ++k) {
-        const float prefix = read_lane_f32(inc, kFixTile - 1);
-        const int t = tok0 + k * kFixTile + lane;
-        inc = prefix + wave_inclusive_scan_f32(t < tend ? a.dt[row_of(t) * a.H + h] * Al2 : 0.f);
-        if ((k & (nz - 1)) != z) continue;
-        load_y(k);
-        correct(k, weight(lost, fast_exp2(inc)), [&](int tt, int ks) {
-            return *reinterpret_cast<const bf16x8 *>(a.C + (row_of(tok0 + k * kFixTile + 16 * tt + lr) * a.G + g) * NS + 8 * lb + 32 * ks);
-        });
-    }
+    if (last >= 0) store(last);
 }
 
 // Workgroups that share the tiles of a (boundary, four heads), a power of two: where decays are slow the state lives through all tiles of
@@ -828,29 +870,30 @@ int launch(const QuadArgs &a, hipStream_t st) {
     const size_t smem = sizeof(LdsQ<NS>);
     if (!allow_dynamic_lds(reinterpret_cast<const void *>(&ssd_quad_kernel<NS, GATHER>), smem)) return STRD_EHIP;
     ssd_quad_kernel<NS, GATHER><<<xcd_grid(nunits), kThreads, smem, st>>>(a, nunits);
-    if (a.nseg > 1) ssd_quad_fix_kernel<NS, GATHER><<<dim3(a.nseg, a.H / kHeads, fix_shares(a.nseg, a.H)), kFixThreads, 0, st>>>(a);
+    if (a.nseg > 1)  // (as many units again: a boundary per segment, the last one for S_out)
+        ssd_quad_fix_kernel<NS, GATHER><<<dim3(xcd_grid(nunits), fix_shares(a.nseg, a.H)), kFixThreads, 0, st>>>(a, nunits);
     return launch_status();
 }
 
 struct Plan {
     int nseg, seg_steps;
-    size_t lend, ltot, lost, seam, ybuf;  // bytes of the parts of the workspace
-    size_t bytes() const { return nseg > 1 ? lend + ltot + lost + seam + ybuf : 0; }
+    size_t lend, ltot, lost, seam, life, ybuf;  // bytes of the parts of the workspace
+    size_t bytes() const { return nseg > 1 ? lend + ltot + lost + seam + life + ybuf : 0; }
 };
 
 // How the sequence is cut: as many segments as it takes to give every CU a workgroup, each at least kMinSegSteps steps long.
 Plan plan_of(int T, int H, int n) {
     constexpr int kMinSegSteps = 8, kCUs = 256;
     const int nsteps = (T + kQ - 1) / kQ, wg = H / kHeads;
-    int s = wg >= kCUs ? 1 : (kCUs + wg - 1) / wg;
-    s = max(1, min(s, nsteps / kMinSegSteps));
+    const int s = max(1, min(kCUs / wg, nsteps / kMinSegSteps));  // (one round of the chip)
     Plan p;
     p.seg_steps = max(1, (nsteps + s - 1) / s);
     p.nseg = max(1, (nsteps + p.seg_steps - 1) / p.seg_steps);
     p.lend = align_up((size_t)(p.nseg - 1) * H * kP * n * sizeof(float), 256);
     p.ltot = align_up((size_t)p.nseg * H * sizeof(float), 256);
     p.lost = align_up((size_t)(p.nseg - 1) * H * 2 * sizeof(uint32_t), 256);
-    p.seam = align_up((size_t)(p.nseg - 1) * H * kDecayTok * sizeof(float), 256);
+    p.seam = align_up((size_t)(p.nseg - 1) * H * p.seg_steps * kQ * sizeof(float), 256);
+    p.life = align_up((size_t)(p.nseg - 1) * H * sizeof(int32_t), 256);
     p.ybuf = (size_t)(p.nseg - 1) * kSeamTok * H * kP * sizeof(float);
     return p;
 }
@@ -864,9 +907,16 @@ bool ssd_quad_supported(int T, int rows, int H, int P, int G, int n, strd_dtype 
     return P == kP && H / G % kHeads == 0 && ssd_seg_supported(T, rows, H, P, G, n, io);
 }
 
-bool ssd_quad_preferred(int T, int H) {
-    const Plan p = plan_of(T, H, 64);
-    return p.nseg >= 2;
+// Whether this kernel takes the place of ssd_seg's two-head form: where that one would be taken with segments of 32 steps of 64 tokens and
+// more, and the segments here, twice as many, still leave the few CUs that they need (64 heads).  us of a call, ssd_seg / this, n = 128,
+// with decays of one per token and more / with
+// 0.003 of those: 128 heads, 8448 tokens 98.5 -> 89 / 253 -> 180, 33280 tokens 336 -> 277 / 1081 -> 626; 64 heads, 16640 tokens 106 -> 96 / 262 ->
+// 211; 256 heads, 4224 tokens 105 -> 88 / 260 -> 157; 96 heads, 12000 tokens 159 -> 105 / 386 -> 221; n = 64: 128 heads, 8448 tokens 80.7 -> 81.0 /
+// 185 -> 155, 33280 tokens 277 -> 252 / 846 -> 593.  Shorter sequences, which one workgroup per (head, 32 channels) walks, would be faster
+// where heads forget (128 heads, 5630 tokens 87 -> 69) and slower where they do not (85 -> 126: seven eighths of the outputs are read
+// and written again); up to 32 heads neither gains (16 heads, 2176 tokens 31 -> 36).
+bool ssd_quad_preferred(int T, int H, int P, int G) {
+    return H >= 64 && plan_of(T, H, 64).nseg >= 2 && ssd_seg_preferred(T, H, P, G);
 }
 
 int ssd_quad(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D, const float *S_in,
@@ -880,6 +930,7 @@ int ssd_quad(const void *x, const float *dt, const float *A, const void *B, cons
     a.wg_per_seg = H / kHeads;
     a.lend = a.ltot = a.seam = a.ybuf = nullptr;
     a.lost = nullptr;
+    a.life = nullptr;
     if (a.nseg > 1) {
         if (!ws) return STRD_EWORKSPACE;
         char *w = (char *)ws;
@@ -887,7 +938,8 @@ int ssd_quad(const void *x, const float *dt, const float *A, const void *B, cons
         a.ltot = (float *)(w + p.lend);
         a.lost = (uint32_t *)(w + p.lend + p.ltot);
         a.seam = (float *)(w + p.lend + p.ltot + p.lost);
-        a.ybuf = (float *)(w + p.lend + p.ltot + p.lost + p.seam);
+        a.life = (int32_t *)(w + p.lend + p.ltot + p.lost + p.seam);
+        a.ybuf = (float *)(w + p.lend + p.ltot + p.lost + p.seam + p.life);
     }
     if (n == 128) return idx ? launch<128, true>(a, st) : launch<128, false>(a, st);
     return idx ? launch<64, true>(a, st) : launch<64, false>(a, st);

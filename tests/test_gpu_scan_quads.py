@@ -1,0 +1,103 @@
+"""The scan with four heads of a group per workgroup (long bf16 sequences of many heads of 64 channels): segments and steps
+with remainders, what a segment hands to the next for fast, mixed and no decay, both state sizes, gathered rows, values that are not
+finite.  The reference is the oracle on a few heads, since a head depends on no other.  Needs a GPU."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2603_00198_amd as strd
+from paper_2603_00198_amd import synth
+
+pytestmark = pytest.mark.gpu
+f = synth.np64
+H, P = 256, 64          # four segments; from 3969 tokens on
+# 2-norm of the error over that of the result: rounded to 8 bits (2^-9 / sqrt 3 = 1.1e-3 each, in the mean over a binade) are the
+# weights or the state, the weighted x, and the output once, or twice behind a seam: sqrt(4) * 1.1e-3, and as much again as margin
+TOL = 4.5e-3
+
+
+def _inputs(T, G, n, a_scale, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    x, B, C = rn(T, H, P).bfloat16(), (rn(T, G, n) / n ** 0.5).bfloat16(), rn(T, G, n).bfloat16()
+    dt = torch.nn.functional.softplus(rn(T, H))
+    A = -torch.exp(2 * torch.rand(H, generator=g, device="cuda"))
+    if a_scale == "mixed":      # some heads of a workgroup forget at once, others never
+        A[::3] = 0.0
+        A[1::3] *= 0.01
+        dt = dt * 0.05
+    else:
+        A = A * a_scale
+        if a_scale == 0.0:
+            dt = dt * 0.05      # (the state stays of the size of one term's)
+    return x, dt, A, B, C, rn(H), rn(H, P, n)
+
+
+def _sample(t, heads, G):
+    """The oracle's inputs for heads h0 < h1 of two groups: x, dt, A, D, S_in by head, B and C by group."""
+    x, dt, A, B, C, D, S = t
+    gs = [h // (H // G) for h in heads]
+    return f(x[:, heads]), f(dt[:, heads]), f(A[heads]), f(B[:, gs]), f(C[:, gs]), f(D[heads]), f(S[heads])
+
+
+def _rel(got, ref):
+    return np.linalg.norm(f(got) - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("T,G,n,a_scale", [
+    (3969, 8, 128, 1.0),        # the shortest; one token in the last step
+    (4096, 64, 128, "mixed"),   # whole steps and segments, one workgroup per group
+    (4097, 8, 64, 1.0),         # a step of one token more
+    (4131, 1, 128, 0.01),       # one group for all heads; the state lives through a segment
+    (4200, 16, 64, "mixed"),
+    (4159, 32, 128, 0.0),       # no decay: all segments reach every token behind them
+])
+def test_scan_of_four_heads_per_workgroup(T, G, n, a_scale):
+    print("[case] scan quads T=%d G=%d n=%d a=%s" % (T, G, n, a_scale), flush=True)
+    t = _inputs(T, G, n, a_scale, T)
+    x, dt, A, B, C, D, S_in = t
+    y, S = strd.ssd_prefill(x, dt, A, B, C, D, S_in)
+    heads = [0, 5, H - 6, H - 1] if G > 1 else [0, 5]
+    for a, b in zip(heads[::2], heads[1::2]):
+        y_ref, S_ref = oracle.ssd_seq(*_sample(t, [a, b], G))
+        for i, h in enumerate((a, b)):
+            assert _rel(y[:, h], y_ref[:, i]) <= TOL, (h, _rel(y[:, h], y_ref[:, i]))
+            assert _rel(S[h], S_ref[i]) <= TOL, (h, _rel(S[h], S_ref[i]))
+    # the gather form on scattered rows: the same bits
+    N, M = T + 200, 33
+    K = T - M
+    g = torch.Generator(device="cuda").manual_seed(1)
+    idx = torch.sort(torch.randperm(N, generator=g, device="cuda")[:K]).values.int()
+    keep = torch.cat([idx.long(), torch.arange(N, N + M, device="cuda")])
+    wide = []
+    for v in (x, dt, B, C):
+        w = torch.full((N + M,) + v.shape[1:], float("nan"), dtype=v.dtype, device="cuda")
+        w[keep] = v
+        wide.append(w)
+    yg, Sg = strd.ssd_prefill_gather(wide[0], wide[1], A, wide[2], wide[3], idx, N, M, D, S_in)
+    assert torch.equal(yg, y) and torch.equal(Sg, S)
+    # no state asked for, none given, the same outputs where that makes no difference
+    y2, S2 = strd.ssd_prefill(x, dt, A, B, C, D, S_in, want_state=False)
+    assert S2 is None and torch.equal(y2, y)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("where", [0, 1500, 3000])
+def test_scan_of_four_heads_never_forgets_a_value_that_is_not_finite(bad, where):
+    """In x at one token: every later output of that channel and its state are not finite, however fast the heads
+    forget; the other channels of the head and the other heads keep their bits."""
+    T, G, n, h, p = 4100, 8, 128, 70, 37
+    x, dt, A, B, C, D, S_in = _inputs(T, G, n, 1.0, 5)
+    y0, S0 = strd.ssd_prefill(x, dt, A, B, C, None, S_in)
+    x[where, h, p] = bad
+    y, S = strd.ssd_prefill(x, dt, A, B, C, None, S_in)
+    assert not torch.isfinite(y[where:, h, p]).any()
+    assert not torch.isfinite(S[h, p]).any()
+    assert torch.equal(y[:where // 32 * 32], y0[:where // 32 * 32])
+    other = torch.arange(H, device="cuda") != h
+    assert torch.equal(y[:, other], y0[:, other]) and torch.equal(S[other], S0[other])
+    channels = torch.arange(P, device="cuda") != p
+    assert torch.isfinite(y[:, h, channels]).all()
+    # (a seam of that head adds terms of 2^-126 that it leaves out otherwise)
+    assert torch.allclose(y[:, h, channels].float(), y0[:, h, channels].float(), rtol=2 ** -7, atol=1e-30)
