@@ -685,12 +685,14 @@ __global__ __launch_bounds__(kThreads) void ssd_quad_kernel(QuadArgs a, int nuni
 
 // ---- the contribution of the incoming state to the tokens of segments 1.. and S_out -----
 // One workgroup per (four heads of a group, boundary b = 1..nseg), or a few that take its 64-token tiles in turn (share z); b < nseg: y of
-// segment b; b == nseg: S_out.  A wave per head and 16-channel tile.  Where the heads forget within a tile the kernel is a launch and one
-// round of loads: the state E, the outputs that wait in fp32 and the decays, which the segment's own scan has left, are
-// requested before anything is waited for, and the c rows, which the 16 waves share, go through LDS (each wave with its own copy of
-// them took 23.5 us for 7 boundaries of 128 heads, this 14).  Where they remember for longer, the c rows, outputs and decays of the next
-// tile travel while a tile is corrected.  The boundaries of a head lie on one XCD: their states E are sums over the same final states.
-constexpr int kFixThreads = 1024;
+// segment b; b == nseg: S_out.  A wave per head and slab of 32 channels, with the scan's order of channels, so that a lane reads and writes 16 bytes
+// of a token's outputs.  Where the heads forget within a tile the kernel is a launch and one round of loads: the state E, the outputs
+// that wait in fp32 and the decays, which the segment's own scan has left, are requested before anything is waited for, and the c rows, which
+// the waves share, go through LDS (each wave with its own copy of them took 10 us longer for 7 boundaries of 128 heads, 23.5 us at 2176 tokens, this 14).  Where they
+// remember for longer it is bound by the way of the outputs from memory and back: c rows, outputs and decays come two tiles ahead
+// (8448 tokens of 128 heads with decays of 0.003 per token, the whole call: 253 us with the seams of ssd_seg, 180 one tile ahead with 8-byte accesses, 156).
+// The boundaries of a head lie on one XCD: their states E are sums over the same final states.
+constexpr int kFixThreads = 512;
 constexpr int kFixTile = 64;  // tokens per tile: a lane per token
 static_assert(kSeamTok == kFixTile, "the outputs of the first tile wait in fp32");
 constexpr float kTiny = 1.17549435e-38f;  // smallest normal number
@@ -699,13 +701,13 @@ template <int NS, bool GATHER>
 __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, int nunits) {
     using TB = typename LdsQ<NS>::TB;
     constexpr int KS = NS / 32;
-    __shared__ TB ct[2][kFixTile / kQ];  // c rows of this tile and the next
+    __shared__ TB ct[3][kFixTile / kQ];  // c rows of this tile and the next two
     const int unit = xcd_swizzle(blockIdx.x, nunits);
     if (unit >= nunits) return;
     const int b = 1 + unit % a.nseg, h0 = unit / a.nseg * kHeads, z = blockIdx.y, nz = gridDim.y;
     const int lane = threadIdx.x & 63, lr = lane & 15, lb = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), pt = wave & 3;  // 16-channel tile of this wave
-    const int h = h0 + (wave >> 2);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), cw = wave & 1;  // slab of this wave
+    const int h = h0 + (wave >> 1);
     const size_t seg_elems = (size_t)a.H * kP * NS;
     // A value that is not finite in an earlier segment's state reaches everything behind it, whatever the decays: then no weight below
     // is less than the smallest normal number and no tile is skipped.
@@ -743,50 +745,57 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, i
         return GATHER ? (size_t)gather_row(a, t, a.idx[min(t, a.K - 1)]) : (size_t)t;
     };
     // c rows of tile k, 1 KB per instruction, the pieces of a row permuted as in the scan's tiles
+    constexpr int kWaves = kFixThreads / 64, kCopies = (kFixTile / TB::kRows + kWaves - 1) / kWaves;
+    static_assert(kFixTile / TB::kRows % kWaves == 0, "every wave issues as many copies");
     auto copy_c = [&](int k, TB *dst) __attribute__((always_inline)) {
-        if (wave < kFixTile / TB::kRows) {
-            const int row0 = lane / (64 / TB::kRows);
-            copy16(reinterpret_cast<const char *>(a.C + (row_of(tok0 + k * kFixTile + wave * TB::kRows + row0) * a.G + g) * NS) + ((lane % (64 / TB::kRows)) ^ (row0 & 3)) * 16,
-                   dst[wave / TB::kIssues].v + 1088 * (wave % TB::kIssues));
+#pragma unroll
+        for (int q = 0; q < kCopies; ++q) {
+            const int j = q * kWaves + wave, row0 = lane / (64 / TB::kRows);
+            copy16(reinterpret_cast<const char *>(a.C + (row_of(tok0 + k * kFixTile + j * TB::kRows + row0) * a.G + g) * NS) + ((lane % (64 / TB::kRows)) ^ (row0 & 3)) * 16,
+                   dst[j / TB::kIssues].v + 1088 * (j % TB::kIssues));
         }
     };
-    static_assert(kFixTile / TB::kRows <= kFixThreads / 64, "one copy per wave");
     // uniform pointers, to which a lane adds an offset of 32 bits
-    auto state_of = [&](int s) { return a.lend + (size_t)s * seg_elems + ((size_t)h * kP + 16 * pt) * NS; };
-    const uint32_t e_at = lr * NS + 8 * lb;
-    const int col = h * kP + 16 * pt;
+    auto state_of = [&](int s) { return a.lend + (size_t)s * seg_elems + ((size_t)h * kP + 32 * cw) * NS; };
+    const int col = h * kP + 32 * cw;
     auto in_tile = [&](int k, int tt) { return (uint32_t)min(16 * tt + lr, a.T - 1 - (tok0 + k * kFixTile)); };  // tokens past T: the last
     auto y_of = [&](int k) { return a.y + (size_t)(tok0 + k * kFixTile) * HP + col; };
     const float *seam = a.seam + ((size_t)(b - 1) * a.H + h) * seg_tok;
     copy_c(z, ct[0]);
-    // E = state at the start of segment b, as A-operand fragments (rows p = 16 pt + lr, k slots n = 32 ks + 8 lb + s)
-    f32x4 e[KS][2];
+    // E = state at the start of segment b, as A-operand fragments: rows p = chan_of(0, pt, lr) of the slab, k slots n = 32 ks + 4 lb + s
+    // (s < 4), 32 ks + 16 + 4 lb + s - 4 (s >= 4)
+    f32x4 e[2][KS][2];
+    auto each_e = [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        e[ks][0] = *reinterpret_cast<const f32x4 *>(state_of(b - 1) + e_at + 32 * ks);
-        e[ks][1] = *reinterpret_cast<const f32x4 *>(state_of(b - 1) + e_at + 32 * ks + 4);
-    }
-    f32x4 y[4];
-    bf16x4 yn[4];
-    auto load_y = [&](int k) __attribute__((always_inline)) {
+        for (int pt = 0; pt < 2; ++pt)
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) yn[tt] = *reinterpret_cast<const bf16x4 *>(y_of(k) + (in_tile(k, tt) * HP + 4 * lb));
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int hi = 0; hi < 2; ++hi) f(e[pt][ks][hi], (uint32_t)(chan_of(0, pt, lr) * NS + 32 * ks + 16 * hi + 4 * lb));
     };
-    auto take_y = [&]() __attribute__((always_inline)) {
+    each_e([&](f32x4 &v, uint32_t at) { v = *reinterpret_cast<const f32x4 *>(state_of(b - 1) + at); });
+    // Outputs and decays of a tile and the next one.  A tile's are requested when the one two before it is done with its registers.
+    bf16x8 y[2][4];
+    f32x4 y0[4][2];  // the first tile's outputs
+    float inc[2];    // lane = token: decay since the segment's start
+    auto load = [&](int k, auto p) __attribute__((always_inline)) {
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) y[tt][q] = (float)yn[tt][q];
+        for (int tt = 0; tt < 4; ++tt) y[p.value][tt] = *reinterpret_cast<const bf16x8 *>(y_of(k) + (in_tile(k, tt) * HP + 8 * lb));
+        inc[p.value] = seam[min(k * kFixTile + lane, seg_tok - 1)];
     };
+    constexpr int kLoads = kCopies + 5;  // a wave's loads per tile
+    std::integral_constant<int, 0> P0;
+    std::integral_constant<int, 1> P1;
     if (z == 0) {
         const float *yw = a.ybuf + (size_t)(b - 1) * kSeamTok * HP + col;
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) y[tt] = *reinterpret_cast<const f32x4 *>(yw + ((16 * tt + lr) * HP + 4 * lb));
+        for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+            for (int pt = 0; pt < 2; ++pt) y0[tt][pt] = *reinterpret_cast<const f32x4 *>(yw + ((16 * tt + lr) * HP + 8 * lb + 4 * pt));
+        inc[0] = seam[min(lane, seg_tok - 1)];
     } else {
-        load_y(z);
-        take_y();
+        load(z, P0);
     }
-    float inc = seam[min(z * kFixTile + lane, seg_tok - 1)];  // lane = token: decay since the segment's start
     const float lt = a.ltot[(size_t)(b - 1) * a.H + h];
     // tiles that anything of E reaches, for this head and for all four; the outputs of the first tile are written in any case
     int mine = 1, most = 1;
@@ -796,63 +805,74 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, i
         const bool l = any_lost(h0 + q, b);
         const int n = l ? ntiles : min(ntiles, (a.life[(size_t)(b - 1) * a.H + h0 + q] * kQ + kFixTile - 1) / kFixTile);
         most = max(most, n);
-        if (h0 + q == h) mine = n, lost = l;
+        if (h0 + q == h) mine = max(n, 1), lost = l;
     }
-    mine = max(mine, 1);
+    const int life_tok = a.life[(size_t)(b - 1) * a.H + h] * kQ;  // tokens whose decays are there; behind them they are zero
+    if (z + nz < most) {
+        copy_c(z + nz, ct[1]);
+        load(z + nz, P1);
+    }
     float f = weight(lost, fast_exp2(lt));
     for (int s = b - 2; s >= 0 && f != 0.f; --s) {
-        const float *src = state_of(s) + e_at;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            e[ks][0] += f * *reinterpret_cast<const f32x4 *>(src + 32 * ks);
-            e[ks][1] += f * *reinterpret_cast<const f32x4 *>(src + 32 * ks + 4);
-        }
+        const float *src = state_of(s);
+        each_e([&](f32x4 &v, uint32_t at) { v += f * *reinterpret_cast<const f32x4 *>(src + at); });
         f = weight(lost, f * fast_exp2(a.ltot[(size_t)s * a.H + h]));
     }
-    bf16x8 ef[KS];
+    bf16x8 ef[2][KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) ef[ks] = cat8(to_bf16x4(e[ks][0]), to_bf16x4(e[ks][1]));
-    const int c_at = TB::row_at(lr) + 16 * (lb ^ (lr & 3));
-    const int life_tok = a.life[(size_t)(b - 1) * a.H + h] * kQ;  // tokens whose decays are there; behind them they are zero
-    bf16x4 out[4];
+    for (int pt = 0; pt < 2; ++pt)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) ef[pt][ks] = cat8(to_bf16x4(e[pt][ks][0]), to_bf16x4(e[pt][ks][1]));
+    const int c_at = TB::row_at(lr) + 16 * ((lb >> 1) ^ (lr & 3)) + 8 * (lb & 1);
+    bf16x8 out[4];
     auto store = [&](int k) __attribute__((always_inline)) {
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt)
-            if (tok0 + k * kFixTile + 16 * tt + lr < tend) *reinterpret_cast<bf16x4 *>(y_of(k) + (in_tile(k, tt) * HP + 4 * lb)) = out[tt];
+            if (tok0 + k * kFixTile + 16 * tt + lr < tend) *reinterpret_cast<bf16x8 *>(y_of(k) + (in_tile(k, tt) * HP + 8 * lb)) = out[tt];
     };
-    int last = -1;  // the tile whose outputs wait to be stored
-    for (int k = z, par = 0;; par ^= 1) {
-        async_tile_wait();
+    int k = z, buf = 0, last = -1;  // last: the tile whose outputs wait to be stored
+    bool ahead = false;             // the loads of the tile after this one are the newest of the wave
+    // One tile, outputs in slot p; false after the last.
+    auto tile = [&](auto p) __attribute__((always_inline)) {
+        if (ahead)
+            __builtin_amdgcn_s_waitcnt(vm_wait_imm(kLoads));
+        else
+            async_tile_wait();
         lds_barrier();  // the c rows of this tile are there, and everyone is done with those of the tile before
-        const int next = k + nz;
         if (last >= 0) store(last);
         last = -1;
-        float incn = 0.f;
-        if (next < most) {
-            copy_c(next, ct[par ^ 1]);
-            if (next < mine) {
-                load_y(next);
-                incn = seam[min(next * kFixTile + lane, seg_tok - 1)];
-            }
-        }
         if (k < mine) {
-            const float cr = k * kFixTile + lane < life_tok ? weight(lost, fast_exp2(inc)) : lost ? kTiny : 0.f;
+            const float cr = k * kFixTile + lane < life_tok ? weight(lost, fast_exp2(inc[p.value])) : lost ? kTiny : 0.f;
 #pragma unroll
             for (int tt = 0; tt < 4; ++tt) {
                 const float crt = __shfl(cr, 16 * tt + lr, 64);
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                const uint32_t c0 = lds_offset(ct[buf][tt >> 1].v) + c_at + (tt & 1) * TB::kBlock;
+                strd_s16x4 cr8[2 * KS];
+                issue_c_pieces<KS, 0>(c0, c0 ^ 32, cr8);
+                settle_c_pieces<KS>(cr8);
+                f32x4 acc[2] = {};
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks)
-                    acc = mfma16(ef[ks], *reinterpret_cast<const bf16x8 *>(ct[par][tt >> 1].v + c_at + (tt & 1) * TB::kBlock + 64 * ks), acc);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) out[tt][q] = (bf16_t)(crt != 0.f ? y[tt][q] + crt * acc[q] : y[tt][q]);
+                    for (int pt = 0; pt < 2; ++pt) acc[pt] = mfma16(ef[pt][ks], tr_pair(cr8[2 * ks], cr8[2 * ks + 1]), acc[pt]);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const float yv = k == 0 ? y0[tt][q >> 2][q & 3] : (float)y[p.value][tt][q];
+                    out[tt][q] = (bf16_t)(crt != 0.f ? yv + crt * acc[q >> 2][q & 3] : yv);
+                }
             }
             last = k;
         }
-        if (next >= most) break;
-        take_y();
-        inc = incn;
-        k = next;
+        ahead = k + 2 * nz < most;
+        if (ahead) {
+            copy_c(k + 2 * nz, ct[buf == 0 ? 2 : buf - 1]);
+            load(k + 2 * nz, p);
+        }
+        k += nz;
+        buf = buf == 2 ? 0 : buf + 1;
+        return k < most;
+    };
+    while (tile(P0) && tile(P1)) {
     }
     if (last >= 0) store(last);
 }
@@ -907,16 +927,19 @@ bool ssd_quad_supported(int T, int rows, int H, int P, int G, int n, strd_dtype 
     return P == kP && H / G % kHeads == 0 && ssd_seg_supported(T, rows, H, P, G, n, io);
 }
 
-// Whether this kernel takes the place of ssd_seg's two-head form: where that one would be taken with segments of 32 steps of 64 tokens and
-// more, and the segments here, twice as many, still leave the few CUs that they need (64 heads).  us of a call, ssd_seg / this, n = 128,
-// with decays of one per token and more / with
-// 0.003 of those: 128 heads, 8448 tokens 98.5 -> 89 / 253 -> 180, 33280 tokens 336 -> 277 / 1081 -> 626; 64 heads, 16640 tokens 106 -> 96 / 262 ->
-// 211; 256 heads, 4224 tokens 105 -> 88 / 260 -> 157; 96 heads, 12000 tokens 159 -> 105 / 386 -> 221; n = 64: 128 heads, 8448 tokens 80.7 -> 81.0 /
-// 185 -> 155, 33280 tokens 277 -> 252 / 846 -> 593.  Shorter sequences, which one workgroup per (head, 32 channels) walks, would be faster
-// where heads forget (128 heads, 5630 tokens 87 -> 69) and slower where they do not (85 -> 126: seven eighths of the outputs are read
-// and written again); up to 32 heads neither gains (16 heads, 2176 tokens 31 -> 36).
+// Where this kernel is taken.  (1) In the place of ssd_seg's two-head form: where that one would be taken with segments of 32 steps of 64
+// tokens and more, and the segments here, twice as many, still leave the few CUs that they need (64 heads).  (2) 512 heads and more,
+// two segments or one: one workgroup per (head, 32 channels) takes four rounds of the chip and more.  us of a call, before -> here, n = 128,
+// with decays of one per token and more (A = -1 to -7, dt = 0.8) / with
+// 0.003 of those: 128 heads, 8448 tokens 98.5 -> 89 / 253 -> 156, 33280 tokens 336 -> 280 / 1081 -> 505; 64 heads, 16640 tokens 106 -> 96 / 262 ->
+// 190; 256 heads, 8448 tokens 189 -> 155 / 535 -> 264; 96 heads, 12000 tokens 159 -> 105 / 386 -> 221; n = 64: 128 heads, 8448 tokens 80.7 -> 80.5 /
+// 185 -> 126, 33280 tokens 277 -> 253 / 846 -> 469.
+// (2): 512 heads, 150 tokens 25.3 -> 17.5 / 25.8 -> 17.4, 2176 tokens 166 -> 92 / 167 -> 129; 1024 heads, 2176 tokens 334 -> 143.
+// Not taken: shorter sequences of fewer heads, where one workgroup per (head, 32 channels) is the slower one while heads forget (128 heads, 5630
+// tokens 89 -> 67) and the faster one while they do not (90 -> 114: seven eighths of the outputs are read and written again); up to 32 heads
+// neither gains (16 heads, 2176 tokens 31 -> 36).
 bool ssd_quad_preferred(int T, int H, int P, int G) {
-    return H >= 64 && plan_of(T, H, 64).nseg >= 2 && ssd_seg_preferred(T, H, P, G);
+    return H >= 512 ? T >= 128 : H >= 64 && plan_of(T, H, 64).nseg >= 2 && ssd_seg_preferred(T, H, P, G);
 }
 
 int ssd_quad(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D, const float *S_in,

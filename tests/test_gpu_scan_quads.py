@@ -82,6 +82,24 @@ def test_scan_of_four_heads_per_workgroup(T, G, n, a_scale):
     assert S2 is None and torch.equal(y2, y)
 
 
+@pytest.mark.parametrize("T", [127, 128, 159, 1000])   # below the rule, one segment with a whole and a ragged last step, two segments
+def test_scan_of_very_many_heads(T):
+    print("[case] scan quads 512 heads T=%d" % T, flush=True)
+    G, n, heads = 16, 128, [33, 510]
+    g = torch.Generator(device="cuda").manual_seed(T)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    x, B, C, S_in = rn(T, 512, P).bfloat16(), rn(T, G, n).bfloat16(), rn(T, G, n).bfloat16(), rn(512, P, n)
+    dt, A = torch.nn.functional.softplus(rn(T, 512)), -0.1 * torch.exp(2 * torch.rand(512, generator=g, device="cuda"))
+    y, S = strd.ssd_prefill(x, dt, A, B, C, None, S_in)
+    gs = [h // 32 for h in heads]
+    y_ref, S_ref = oracle.ssd_seq(f(x[:, heads]), f(dt[:, heads]), f(A[heads]), f(B[:, gs]), f(C[:, gs]), None, f(S_in[heads]))
+    for i, h in enumerate(heads):
+        assert _rel(y[:, h], y_ref[:, i]) <= TOL and _rel(S[h], S_ref[i]) <= TOL, h
+    # the same bits every time
+    y2, S2 = strd.ssd_prefill(x, dt, A, B, C, None, S_in.clone())
+    assert torch.equal(y2, y) and torch.equal(S2, S)
+
+
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 @pytest.mark.parametrize("where", [0, 1500, 3000])
 def test_scan_of_four_heads_never_forgets_a_value_that_is_not_finite(bad, where):
