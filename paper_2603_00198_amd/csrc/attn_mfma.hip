@@ -39,7 +39,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLazy = 8.f;  // log2 of how far a probability may exceed 1 before the reference moves
+constexpr float kLazySum = 256.f;  // what the probabilities of a lane's 8 keys may add up to before the reference moves
 
 // K rows are read 16 bytes per lane, lane = (row lane % 16, piece lane / 16), V with the transposing load,
 // 8 consecutive rows per half wave: both run fastest at a row pitch of 8 words modulo 32 (two pad
@@ -72,7 +72,6 @@ __global__ __launch_bounds__((G * NW + NC) * kWave) __attribute__((amdgpu_waves_
     using TileT = Tile<D, NC ? NC : NW, KC>;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lb = lane >> 4;
-    const float lazy_raw = kLazy / scale2;  // the slack of the softmax reference, in raw score units
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, in a scalar register
     const int grp = G == 1 ? 0 : wv / NW, w = G == 1 ? wv : wv % NW;
     const bool copies = NC > 0 && wv >= G * NW;              // a copy wave: it serves all groups
@@ -167,6 +166,7 @@ __global__ __launch_bounds__((G * NW + NC) * kWave) __attribute__((amdgpu_waves_
     for (int dt = 0; dt < DT; ++dt) oacc[dt][0] = oacc[dt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     // per query tile; l_run: this lane group's share of the row sum
     float m_run[2] = {-INFINITY, -INFINITY}, m_neg[2] = {0.f, 0.f}, l_run[2] = {0.f, 0.f};
+    bool fresh = true;  // some query of the wave has no reference yet (uniform)
 
     constexpr int kRowB = TileT::kPitch * 2;  // row pitch of the tiles in bytes
     if (NC == 0) {
@@ -222,55 +222,59 @@ __global__ __launch_bounds__((G * NW + NC) * kWave) __attribute__((amdgpu_waves_
                             if (key > tq1) sacc[1][j][r] = -INFINITY;
                         }
                 }
-                float tm[2];  // max of this lane's 8 raw scores per query tile
+                // The probabilities, against the reference as it is.  The row sum is taken of them as they enter the second
+                // product, i.e. rounded to bf16 (numerator and denominator then carry the same rounding), two at a time.
+                bf16x8 pf[2];
+                float ps[2];
+                auto probabilities = [&]() __attribute__((always_inline)) {
 #pragma unroll
-                for (int qt = 0; qt < 2; ++qt) {
-                    float t = sacc[qt][0][0];
+                    for (int qt = 0; qt < 2; ++qt) {
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
+                        for (int j = 0; j < 2; ++j)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) t = fmaxf(t, sacc[qt][j][r]);
-                    tm[qt] = t;
-                }
+                            for (int r = 0; r < 4; ++r)
+                                pf[qt][4 * j + r] = (bf16_t)ex2(fmaf(sacc[qt][j][r], scale2, m_neg[qt]));  // 2^((s - m) * scale * log2 e)
+                        ps[qt] = 0.f;
+#pragma unroll
+                        for (int e = 0; e < 8; e += 2)
+                            ps[qt] = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[qt][e], pf[qt][e + 1]}, bf16x2{(bf16_t)1.f, (bf16_t)1.f}, ps[qt], false);
+                    }
+                };
+                if (!fresh) probabilities();
                 // m_run (raw units) is the reference the exponentials are taken against, common to the four
                 // lane groups of a query.  Softmax does not care which reference is used, so it follows
                 // the running max lazily: it moves (and the accumulators are rescaled, and the groups
-                // talk) only when some lane sees a score more than 2^kLazy above it; until then the
-                // probabilities are merely allowed to reach 2^kLazy instead of 1.
-                if (__any(tm[0] > m_run[0] + lazy_raw || tm[1] > m_run[1] + lazy_raw)) {
+                // talk) only when the 8 probabilities of some lane add up to more than 2^kLazy; until then they
+                // are merely allowed to exceed 1.  The sum says so without a look at the scores' maximum, which is only
+                // taken when the reference moves: vector instructions and products hardly overlap on a SIMD, and the maxima were a
+                // sixth of a block's vector instructions (layers of 33280 and 8448 tokens 8168 -> 7990 and 707 -> 699 us).
+                if (fresh || __any(fmaxf(ps[0], ps[1]) > kLazySum)) {
+                    bool unseen = false;
 #pragma unroll
                     for (int qt = 0; qt < 2; ++qt) {
-                        float t = tm[qt];
+                        float t = sacc[qt][0][0];
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) t = fmaxf(t, sacc[qt][j][r]);
                         t = fmaxf(t, __shfl_xor(t, 16, kWave));
                         t = fmaxf(t, __shfl_xor(t, 32, kWave));
-                        // finite in the first group: key 0 is visible to every query; a query may not see any
-                        // key of the others, whose chunks start later
+                        // (a query may not see any key of the groups behind the first, whose chunks start later)
                         const float nm = fmaxf(m_run[qt], t);
-                        const bool unseen = G > 1 && nm == -INFINITY;
-                        const float corr = unseen ? 1.f : ex2((m_run[qt] - nm) * scale2);
+                        const bool none = nm == -INFINITY;
+                        const float corr = none ? 1.f : ex2((m_run[qt] - nm) * scale2);
                         l_run[qt] *= corr;
 #pragma unroll
                         for (int dt = 0; dt < DT; ++dt) oacc[dt][qt] *= corr;
                         m_run[qt] = nm;
-                        m_neg[qt] = unseen ? 0.f : -nm * scale2;
+                        m_neg[qt] = none ? 0.f : -nm * scale2;
+                        unseen |= none;
                     }
+                    fresh = __any(unseen);
+                    probabilities();
                 }
-                // The row sum is taken of the probabilities as they enter the second product, i.e. rounded to
-                // bf16 (numerator and denominator then carry the same rounding), two at a time.
-                bf16x8 pf[2];
-#pragma unroll
-                for (int qt = 0; qt < 2; ++qt) {
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            pf[qt][4 * j + r] = (bf16_t)ex2(fmaf(sacc[qt][j][r], scale2, m_neg[qt]));  // 2^((s - m) * scale * log2 e)
-                    float ps = l_run[qt];
-#pragma unroll
-                    for (int e = 0; e < 8; e += 2)
-                        ps = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[qt][e], pf[qt][e + 1]}, bf16x2{(bf16_t)1.f, (bf16_t)1.f}, ps, false);
-                    l_run[qt] = ps;
-                }
+                l_run[0] += ps[0];
+                l_run[1] += ps[1];
 #pragma unroll
                 for (int dp = 1; dp < DT / 4; ++dp)
                     lds_issue_tr8<0, 16 * kRowB, 32, 16 * kRowB + 32, 64, 16 * kRowB + 64, 96, 16 * kRowB + 96>(vp + 64 * dp, vr8[dp]);
