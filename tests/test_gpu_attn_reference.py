@@ -31,3 +31,19 @@ def test_attention_scores_that_climb(T, Hq, d, rise, alone):
     kv = [0, Hkv - 1]
     ref = oracle.attn(f(q[:, heads]), f(k[:, kv]), f(v[:, kv]))
     assert_close(f(o[:, heads]), ref, TOL[torch.bfloat16], "o", units=(0, 1))
+
+
+@pytest.mark.parametrize("N,M,Hq,Hkv,d", [(1500, 20, 4, 2, 128), (1500, 70, 8, 2, 64), (40000, 33, 8, 8, 128)])
+@pytest.mark.parametrize("jump", [30.0, 58.0, 75.0, 200.0, -75.0])   # log2 of what later keys have over the first: the sums' limit is 2^60
+def test_importance_scores_of_keys_far_above_the_first(N, M, Hq, Hkv, d, jump):
+    print("[case] score climb N=%d M=%d d=%d jump=%s" % (N, M, d, jump), flush=True)
+    g = torch.Generator().manual_seed(N + d)
+    q, k = torch.randn(M, Hq, d, generator=g), torch.randn(N, Hkv, d, generator=g)
+    q[:, :, 0] = 16.0
+    up = torch.zeros(N)
+    up[N // 3:] = jump / 2          # a step within a slice, and lone keys above it
+    up[N // 2::97] = jump
+    k[:, :, 0] = (up / 1.4426950408889634 * d ** 0.5 / 16.0)[:, None]
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    s = strd.score_attn(q.cuda(), k.cuda())
+    assert_close(s.cpu().numpy(), oracle.score_attn(f(q), f(k)), 1e-4, "scores", units=(0,))
