@@ -272,11 +272,11 @@ int strd_compact_varlen(const strd_compact_item *items, int n_items, const int32
  * their head) and in S_out -- in a sequence cut into segments of fewer heads up to the end of the segment and, behind it,
  * for as long as the decays since its start are not zero in fp32.
  * `chunk` is the chunk length of the caller's formulation (> 0).  It is validated and
- * otherwise unused: it does NOT select the tiling.  The kernels always cut time into
- * 64-token steps and carry the state across them on chip, so results do not depend on
+ * otherwise unused: it does NOT select the tiling.  The kernels always cut time into steps of
+ * 64 or 32 tokens and carry the state across them on chip, so results do not depend on
  * `chunk` at all.  S_out of one call fed as S_in of the next continues the same scan; the two may be one buffer (but
  * not overlap in part).  Such a call runs a kernel in which nobody else reads what a workgroup writes: for long bf16
- * sequences the walk over the whole sequence (1.4 to 1.7 times the time of the segments), for a few small chunks in
+ * sequences the walk over the whole sequence (1.4 to 2.3 times the time of the segments), for a few small chunks in
  * single precision three launches instead of one.
  *   ws  [dev] strd_ssd_prefill_workspace(T, ...) bytes.  bf16 matrix-core shapes: 0 for short
  *       sequences; for long ones the sequence is cut into segments that run side by side, and the local end state and total

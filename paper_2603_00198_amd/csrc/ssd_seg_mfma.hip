@@ -40,6 +40,7 @@
 // products and LDS round trips of the other, and the B and C tiles cross the CU's copy path once
 // for both heads.  That leaves 168 registers per wave and LDS for rings of 2 (tiles one step
 // ahead): reads are requested where they are needed instead of at the start of the step.
+// (Where four heads of a group go together and there are 64 heads and more, ssd_quad_mfma.hip takes the long sequences.)
 //
 // Segments.  A head is a serial chain over time; to fill the chip the sequence is cut into a few
 // long segments that run side by side, each from a zero state (the first from S_in).  A segment
