@@ -512,7 +512,9 @@ __device__ __forceinline__ void helper_wave(LdsQ<NS> &lds, const QuadArgs &a, in
         m.w[slot_of(j)] = dv * fast_exp2(tot - inc);
         m.carry[j] = fast_exp2(inc);
         if (j < 16) m.fw[j] = dv * fast_exp2(l15 - inc);  // the exponent is <= 0 for these
-        if (seg > 0 && fast_exp2(ltot[k]) != 0.f) {  // for the seam, while anything of what lies before the segment is left
+        // for the seam, while anything of what lies before the segment is left: without a gap, since every entry before life * 32 is read
+        // (a dt that is not finite makes exp2(ltot) other than zero again, long after it was)
+        if (seg > 0 && life[k] == i && fast_exp2(ltot[k]) != 0.f) {
             a.seam[((size_t)(seg - 1) * a.H + h0 + 2 * k + half) * (a.seg_steps * kQ) + i * kQ + j] = ltot[k] + inc;
             life[k] = i + 1;
         }

@@ -119,3 +119,20 @@ def test_scan_of_four_heads_never_forgets_a_value_that_is_not_finite(bad, where)
     assert torch.isfinite(y[:, h, channels]).all()
     # (a seam of that head adds terms of 2^-126 that it leaves out otherwise)
     assert torch.allclose(y[:, h, channels].float(), y0[:, h, channels].float(), rtol=2 ** -7, atol=1e-30)
+
+
+@pytest.mark.parametrize("bad", [float("nan"), -float("inf")])
+@pytest.mark.parametrize("where", [1990, 3100])     # in the second segment and in the last (1056 tokens each)
+def test_what_a_seam_reads_was_written(bad, where):
+    """A dt that is not finite, long after the head has forgotten what lies before the segment: outputs before its step keep
+    their bits, whatever the workspace held (2 in every place that a seam could take for a token's decay)."""
+    T, G, n, h = 4100, 8, 128, 70
+    x, dt, A, B, C, D, S_in = _inputs(T, G, n, 1.0, 6)
+    y0, _ = strd.ssd_prefill(x, dt, A, B, C, D, S_in)
+    ws = torch.ones(strd.lib().strd_ssd_prefill_workspace(T, H, P, G, n, 64, 1) // 4, device="cuda").view(torch.uint8)
+    dt[where, h] = bad
+    y, S = strd.ssd_prefill(x, dt, A, B, C, D, S_in, ws=ws)
+    assert torch.equal(y[:where // 32 * 32], y0[:where // 32 * 32])
+    assert not torch.isfinite(y[where:, h]).any() and not torch.isfinite(S[h]).any()
+    other = torch.arange(H, device="cuda") != h
+    assert torch.equal(y[:, other], y0[:, other])
