@@ -929,20 +929,19 @@ bool ssd_quad_supported(int T, int rows, int H, int P, int G, int n, strd_dtype 
     return P == kP && H / G % kHeads == 0 && ssd_seg_supported(T, rows, H, P, G, n, io);
 }
 
-// Where this kernel is taken.  (1) In the place of ssd_seg's two-head form: where that one would be taken with segments of 32 steps of 64
-// tokens and more, and the segments here, twice as many, still leave the few CUs that they need (64 heads).  (2) 512 heads and more,
-// two segments or one: one workgroup per (head, 32 channels) takes four rounds of the chip and more.  us of a call, before -> here, n = 128,
+// Where this kernel is taken: in the place of ssd_seg's two-head form, where that one would be taken with segments of 32 steps of 64
+// tokens and more, and the segments here, twice as many, still leave the few CUs that they need (64 heads).  us of a call, before -> here, n = 128,
 // with decays of one per token and more (A = -1 to -7, dt = 0.8) / with
 // 0.003 of those: 128 heads, 8448 tokens 98.5 -> 89 / 253 -> 156, 33280 tokens 336 -> 280 / 1081 -> 505; 64 heads, 16640 tokens 106 -> 96 / 262 ->
 // 190; 256 heads, 8448 tokens 189 -> 155 / 535 -> 264; 96 heads, 12000 tokens 159 -> 105 / 386 -> 221; n = 64: 128 heads, 8448 tokens 80.7 -> 80.5 /
 // 185 -> 126, 33280 tokens 277 -> 253 / 846 -> 469.
-// (2): 512 heads, 150 tokens 25.3 -> 17.5 / 25.8 -> 17.4, 2176 tokens 166 -> 92 / 167 -> 129; 1024 heads, 2176 tokens 334 -> 143.
 // Not taken: shorter sequences of fewer heads, where one workgroup per (head, 32 channels) is the slower one while heads forget (128 heads, 5630
 // tokens 89 -> 67) and the faster one while they do not (90 -> 114: seven eighths of the outputs are read and written again); up to 32 heads
-// neither gains (16 heads, 2176 tokens 31 -> 36).
-bool ssd_quad_preferred(int T, int H, int P, int G) {
-    return H >= 512 ? T >= 128 : H >= 64 && plan_of(T, H, 64).nseg >= 2 && ssd_seg_preferred(T, H, P, G);
-}
+// neither gains (16 heads, 2176 tokens 31 -> 36).  512 heads and more, where ssd_seg is not taken either: here they are faster, 2176 tokens of
+// 512 heads 172 -> 97, of 1024 345 -> 146, but further from 64 bits than the kernel that adds up 64 tokens of every output from unrounded x: steps of 32
+// leave more of an output to the state and its weighted x, both rounded (2176 tokens of 512 heads in two segments 2.334 -> 2.335e-3, with slow
+// decays 2.73 -> 2.98e-3; in one segment, of 1024 heads, 2.347 -> 2.348 and 2.73 -> 2.79e-3).
+bool ssd_quad_preferred(int T, int H, int P, int G) { return H >= 64 && ssd_seg_preferred(T, H, P, G); }
 
 int ssd_quad(const void *x, const float *dt, const float *A, const void *B, const void *C, const float *D, const float *S_in,
              void *y, float *S_out, const int32_t *idx, int N, int K, int T, int H, int G, int n, void *ws, hipStream_t st) {
