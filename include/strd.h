@@ -282,7 +282,7 @@ int strd_compact_varlen(const strd_compact_item *items, int n_items, const int32
  *       sequences; for long ones the sequence is cut into segments that run side by side, and the local end state and total
  *       decay of every segment but the last pass through the workspace ((segments - 1) * H * P * n
  *       + segments * H floats; with four heads together also 64 * P floats per head and segment and one per head and
- *       token); too small or NULL when needed: STRD_EWORKSPACE.  Other shapes: the state
+ *       token); too small or NULL when needed: STRD_EWORKSPACE.  A state updated in place needs none there.  Other shapes: the state
  *       before every 64-token chunk and the chunks' decays, (P * n + 1) * H floats per chunk, of as many
  *       chunks as fit 256 MB (one at least), and two states more when that is not all of them.  Here it
  *       may be smaller or NULL: the call then walks the sequence token by token, which takes 65 times as

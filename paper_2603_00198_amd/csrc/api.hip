@@ -294,11 +294,13 @@ int strd_ssd_prefill(const void *x, const float *dt, const float *A, const void 
     if (T > 0 && (!x || !dt || !B || !C || !y)) return STRD_EINVAL;
     const bool mfma = ssd_mfma_supported(T, T, H, P, G, n, io) || ssd_seg_supported(T, T, H, P, G, n, io);
     if (mfma && !aligned16(x, B, C, S_in, y, S_out, ws)) return STRD_EINVAL;
-    const size_t need = strd_ssd_prefill_workspace(T, H, P, G, n, chunk, io);
+    const bool in_place = overlap(S_in, S_out, (size_t)H * P * n * sizeof(float));
+    const bool quad = use_quad(T, T, H, P, G, n, io, in_place);
+    // what the kernel of this call needs: none in place, where there are no segments (as in strd_ssd_prefill_gather)
+    const size_t need = mfma && in_place ? 0 : strd_ssd_prefill_workspace(T, H, P, G, n, chunk, io);
     const bool missing = need && (!ws || ws_bytes < need);
     if (missing && mfma) return STRD_EWORKSPACE;
-    const bool in_place = overlap(S_in, S_out, (size_t)H * P * n * sizeof(float));
-    if (use_quad(T, T, H, P, G, n, io, in_place))
+    if (quad)
         return ssd_quad(x, dt, A, B, C, D, S_in, y, S_out, nullptr, 0, 0, T, H, G, n, ws, as_stream(stream));
     if (use_seg(T, T, H, P, G, n, io, in_place))
         return ssd_seg(x, dt, A, B, C, D, S_in, y, S_out, nullptr, 0, 0, T, H, P, G, n, ws, as_stream(stream));

@@ -157,3 +157,29 @@ def test_what_a_seam_reads_was_written(bad, where):
     assert not torch.isfinite(y[where:, h]).any() and not torch.isfinite(S[h]).any()
     other = torch.arange(H, device="cuda") != h
     assert torch.equal(y[:, other], y0[:, other])
+
+
+@pytest.mark.parametrize("heads,T", [(256, 4100), (512, 1000), (64, 16640)])
+def test_a_state_updated_in_place_needs_no_workspace(heads, T):
+    """It is walked, whatever the same call with two buffers does; gathered, too."""
+    G, n, M = 8, 128, 40
+    g = torch.Generator(device="cuda").manual_seed(heads)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    x, B, C, S_in = rn(T, heads, P).bfloat16(), rn(T, G, n).bfloat16(), rn(T, G, n).bfloat16(), rn(heads, P, n)
+    dt, A = torch.nn.functional.softplus(rn(T, heads)), -torch.exp(2 * torch.rand(heads, generator=g, device="cuda"))
+    L, st, ptr = strd.lib(), torch.cuda.current_stream().cuda_stream, lambda t: t.data_ptr()
+    size = L.strd_ssd_prefill_workspace(T, heads, P, G, n, 64, 1)
+    got = []
+    for ws in (torch.empty(max(size, 16), dtype=torch.uint8, device="cuda"), None):
+        y, S = torch.empty_like(x), S_in.clone()
+        rc = L.strd_ssd_prefill(ptr(x), ptr(dt), ptr(A), ptr(B), ptr(C), None, ptr(S), ptr(y), ptr(S), T, heads, P, G, n, 64, 1,
+                                None if ws is None else ptr(ws), 0 if ws is None else size, st)
+        assert rc == 0
+        got.append((y, S))
+    y, S = torch.empty_like(x), S_in.clone()
+    idx = torch.arange(T - M, dtype=torch.int32, device="cuda")
+    assert L.strd_ssd_prefill_gather(ptr(x), ptr(dt), ptr(A), ptr(B), ptr(C), None, ptr(S), ptr(idx), ptr(y), ptr(S), T - M, M, T - M, heads, P, G,
+                                     n, 64, 1, None, 0, st) == 0
+    got.append((y, S))
+    for y, S in got[1:]:
+        assert torch.equal(y, got[0][0]) and torch.equal(S, got[0][1])
