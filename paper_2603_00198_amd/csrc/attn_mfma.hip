@@ -39,7 +39,8 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLazySum = 256.f;  // what the probabilities of a lane's 8 keys may add up to before the reference moves
+constexpr float kLazy = 8.f;       // log2 of how far a probability may exceed 1 before the reference moves
+constexpr float kLazySum = 256.f;  // the same, of what the probabilities of a lane's 8 keys add up to
 
 // K rows are read 16 bytes per lane, lane = (row lane % 16, piece lane / 16), V with the transposing load,
 // 8 consecutive rows per half wave: both run fastest at a row pitch of 8 words modulo 32 (two pad
@@ -69,6 +70,7 @@ __global__ __launch_bounds__((G * NW + NC) * kWave) __attribute__((amdgpu_waves_
     const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v, bf16_t *__restrict__ o, int T,
     int Hq, int Hkv, float scale2, int nqb, int xcd_map) {
     constexpr int KS = D / 32, DT = D / 16, kBM = 32 * NW;
+    constexpr bool kBySum = NW == 8;  // whether the probabilities' sum or the scores' maximum says when the reference moves (below)
     using TileT = Tile<D, NC ? NC : NW, KC>;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lb = lane >> 4;
@@ -166,7 +168,8 @@ __global__ __launch_bounds__((G * NW + NC) * kWave) __attribute__((amdgpu_waves_
     for (int dt = 0; dt < DT; ++dt) oacc[dt][0] = oacc[dt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     // per query tile; l_run: this lane group's share of the row sum
     float m_run[2] = {-INFINITY, -INFINITY}, m_neg[2] = {0.f, 0.f}, l_run[2] = {0.f, 0.f};
-    bool fresh = true;  // some query of the wave has no reference yet (uniform)
+    bool fresh = true;  // some query of the wave has no reference yet (uniform; kBySum)
+    const float lazy_raw = kLazy / scale2;  // in raw score units
 
     constexpr int kRowB = TileT::kPitch * 2;  // row pitch of the tiles in bytes
     if (NC == 0) {
@@ -234,29 +237,48 @@ __global__ __launch_bounds__((G * NW + NC) * kWave) __attribute__((amdgpu_waves_
 #pragma unroll
                             for (int r = 0; r < 4; ++r)
                                 pf[qt][4 * j + r] = (bf16_t)ex2(fmaf(sacc[qt][j][r], scale2, m_neg[qt]));  // 2^((s - m) * scale * log2 e)
-                        ps[qt] = 0.f;
+                        ps[qt] = kBySum ? 0.f : l_run[qt];
 #pragma unroll
                         for (int e = 0; e < 8; e += 2)
                             ps[qt] = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[qt][e], pf[qt][e + 1]}, bf16x2{(bf16_t)1.f, (bf16_t)1.f}, ps[qt], false);
                     }
                 };
-                if (!fresh) probabilities();
-                // m_run (raw units) is the reference the exponentials are taken against, common to the four
-                // lane groups of a query.  Softmax does not care which reference is used, so it follows
-                // the running max lazily: it moves (and the accumulators are rescaled, and the groups
-                // talk) only when the 8 probabilities of some lane add up to more than 2^kLazy; until then they
-                // are merely allowed to exceed 1.  The sum says so without a look at the scores' maximum, which is only
-                // taken when the reference moves: vector instructions and products hardly overlap on a SIMD, and the maxima were a
-                // sixth of a block's vector instructions (layers of 33280 and 8448 tokens 8168 -> 7990 and 707 -> 699 us).
-                if (fresh || __any(fmaxf(ps[0], ps[1]) > kLazySum)) {
-                    bool unseen = false;
+                float tm[2];  // max of this lane's 8 raw scores per query tile
+                auto maxima = [&]() __attribute__((always_inline)) {
 #pragma unroll
                     for (int qt = 0; qt < 2; ++qt) {
-                        float t = sacc[qt][0][0];
+                        tm[qt] = sacc[qt][0][0];
 #pragma unroll
                         for (int j = 0; j < 2; ++j)
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) t = fmaxf(t, sacc[qt][j][r]);
+                            for (int r = 0; r < 4; ++r) tm[qt] = fmaxf(tm[qt], sacc[qt][j][r]);
+                    }
+                };
+                // m_run (raw units) is the reference the exponentials are taken against, common to the four
+                // lane groups of a query.  Softmax does not care which reference is used, so it follows
+                // the running max lazily: it moves (and the accumulators are rescaled, and the groups
+                // talk) only when some lane sees a score more than 2^kLazy above it; until then the
+                // probabilities are merely allowed to reach 2^kLazy instead of 1.
+                // Long sequences (kBySum) ask the sum of a lane's 8 probabilities instead, without a look at the scores' maximum, which is only
+                // taken when the reference moves: vector instructions and products hardly overlap on a SIMD, and the maxima were a
+                // sixth of a block's vector instructions.  A block in which it moves makes its probabilities twice for that, and of
+                // few blocks many are such.  us with maxima -> sums, scores of a standard deviation of 1 / 3 / 6: 32 / 8 heads of 128,
+                // 33280 tokens 6937 / 7070 / 7260 -> 6790 / 7070 / 7400, 8448 484 / 493 / 509 -> 474 / 491 / 525, 843 18.4 / 19.0 / 19.9 -> 18.3 / 20.1 /
+                // 22.4; 28 / 4 heads of 64, 8448 283 / 288 / 300 -> 266 / 285 / 320, 843 12.4 / 13.0 / 14.3 -> 12.0 / 13.7 / 16.5.
+                bool moves;
+                if constexpr (kBySum) {
+                    if (!fresh) probabilities();
+                    moves = fresh || __any(fmaxf(ps[0], ps[1]) > kLazySum);
+                    if (moves) maxima();
+                } else {
+                    maxima();
+                    moves = __any(tm[0] > m_run[0] + lazy_raw || tm[1] > m_run[1] + lazy_raw);
+                }
+                if (moves) {
+                    bool unseen = false;
+#pragma unroll
+                    for (int qt = 0; qt < 2; ++qt) {
+                        float t = tm[qt];
                         t = fmaxf(t, __shfl_xor(t, 16, kWave));
                         t = fmaxf(t, __shfl_xor(t, 32, kWave));
                         // (a query may not see any key of the groups behind the first, whose chunks start later)
@@ -270,11 +292,14 @@ __global__ __launch_bounds__((G * NW + NC) * kWave) __attribute__((amdgpu_waves_
                         m_neg[qt] = none ? 0.f : -nm * scale2;
                         unseen |= none;
                     }
-                    fresh = __any(unseen);
-                    probabilities();
+                    if constexpr (kBySum) {
+                        fresh = __any(unseen);
+                        probabilities();
+                    }
                 }
-                l_run[0] += ps[0];
-                l_run[1] += ps[1];
+                if constexpr (!kBySum) probabilities();
+                l_run[0] = kBySum ? l_run[0] + ps[0] : ps[0];
+                l_run[1] = kBySum ? l_run[1] + ps[1] : ps[1];
 #pragma unroll
                 for (int dp = 1; dp < DT / 4; ++dp)
                     lds_issue_tr8<0, 16 * kRowB, 32, 16 * kRowB + 32, 64, 16 * kRowB + 64, 96, 16 * kRowB + 96>(vp + 64 * dp, vr8[dp]);
