@@ -21,8 +21,6 @@
 namespace strd {
 namespace {
 
-constexpr float kMostSum = 1.152921505e18f;  // 2^60: what a sum of exponentials may reach before its reference moves
-
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -119,11 +117,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     float run_m[kTW], run_s[kTW];
 #pragma unroll
     for (int qt = 0; qt < kTW; ++qt) { run_m[qt] = -INFINITY; run_s[qt] = 0.f; }
-    // Once every lane has a maximum, from the first chunk, it is only a reference: exponentials against it are as exact above 1 as below,
-    // so the later chunks take no maxima (8 of a unit's 54 vector instructions, and the rescaling), unless a sum passes kMostSum: then
-    // the chunk is taken again, with maxima.  (32768 keys, 256 rows, this kernel 77.0 -> 71.9 us; 131072, 300 rows the call 724 -> 709, 28 heads of
-    // 64 450 -> 423.  A wave with one tile keeps its maxima: 131072 keys, 16 rows took 101 us instead of 99 without.)
-    bool have_ref = false;  // uniform
     // Tiles of this wave that hold a row at all: the others are no work (uniform).  (With that, no copy of a next chunk where there is
     // none, and the log-sum-exps at once in pass 2: 131072 keys, 16 text rows 141 -> 105 us; 32768, 20 55 -> 44; 2304, 37 19.0 -> 16.2;
     // 12 clips of 1500, 48 45 -> 40; 40 of 600, 30 60 -> 51.)
@@ -164,15 +157,46 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             run_s[qt] = run_s[qt] * ex2(run_m[qt] - ref) + ts;
             run_m[qt] = nm;
         };
-        auto add = [&](int qt, const f32x16 &acc) {  // the same against the reference there is
-            float ts = 0.f;
+        auto interleave = [] {  // per product: its share of the 16 fma / exp / add and of the 8 max3
 #pragma unroll
-            for (int i = 0; i < 16; ++i) ts += ex2(fmaf(acc[i], scale2, -run_m[qt]));
-            run_s[qt] += ts;
+            for (int i = 0; i < KS; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 24 / KS, 0);
+                __builtin_amdgcn_sched_group_barrier(0x400, 16 / KS, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 16 / KS, 0);
+            }
         };
-        auto tile_by_tile = [&]() {  // keys past the slice masked
-            bf16x8 kf[KS];
-            for (int kt = 0; kt < kRows / 32 && kbase + 32 * kt < key1; ++kt) {
+        static_assert(kTW == 2, "two query tiles per wave");
+        bf16x8 kf[KS];
+        if (ntile == 0) {  // (all branches on it are uniform)
+        } else if (ntile == 1 && kbase + kRows <= key1) {  // the products of the next key tile under the exponentials of this one
+            load_k(0, kf);
+            f32x16 acc0 = products(0, kf), acc1;
+#pragma unroll
+            for (int kt = 0; kt < kRows / 32; ++kt) {
+                if (kt + 1 < kRows / 32) {
+                    load_k(kt + 1, kf);
+                    acc1 = products(0, kf);
+                }
+                fold(0, acc0);
+                if (kt + 1 < kRows / 32) interleave();
+                acc0 = acc1;
+            }
+        } else if (kbase + kRows <= key1) {  // uniform: every key of the chunk belongs to the slice -- one straight block
+            load_k(0, kf);
+            f32x16 acc0 = products(0, kf), acc1;
+#pragma unroll
+            for (int kt = 0; kt < kRows / 32; ++kt) {
+                acc1 = products(1, kf);  // last use of this tile's fragments
+                if (kt + 1 < kRows / 32) load_k(kt + 1, kf);
+                fold(0, acc0);
+                interleave();
+                if (kt + 1 < kRows / 32) acc0 = products(0, kf);
+                fold(1, acc1);
+                if (kt + 1 < kRows / 32) interleave();
+            }
+        } else {
+            for (int kt = 0; kbase + 32 * kt < key1; ++kt) {  // ragged last chunk: tile by tile, keys past the slice masked
                 load_k(kt, kf);
                 f32x16 acc[kTW] = {products(0, kf), ntile > 1 ? products(1, kf) : zero16()};
                 if (kbase + 32 * kt + 32 > key1) {
@@ -184,65 +208,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                 }
                 fold(0, acc[0]);
                 if (ntile > 1) fold(1, acc[1]);
-            }
-        };
-        auto interleave = [](auto maxima) {  // per product: its share of the 16 fma / exp / add and of the 8 max3
-#pragma unroll
-            for (int i = 0; i < KS; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, (decltype(maxima)::value ? 24 : 16) / KS, 0);
-                __builtin_amdgcn_sched_group_barrier(0x400, 16 / KS, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 16 / KS, 0);
-            }
-        };
-        // a full chunk, one straight block
-        auto one_tile = [&]() {  // the products of the next key tile under the exponentials of this one
-            bf16x8 kf[KS];
-            load_k(0, kf);
-            f32x16 acc0 = products(0, kf), acc1;
-#pragma unroll
-            for (int kt = 0; kt < kRows / 32; ++kt) {
-                if (kt + 1 < kRows / 32) {
-                    load_k(kt + 1, kf);
-                    acc1 = products(0, kf);
-                }
-                fold(0, acc0);
-                if (kt + 1 < kRows / 32) interleave(std::true_type());
-                acc0 = acc1;
-            }
-        };
-        // ... with the running maximum or against the reference
-        auto two_tiles = [&](auto maxima) {
-            bf16x8 kf[KS];
-            load_k(0, kf);
-            f32x16 acc0 = products(0, kf), acc1;
-#pragma unroll
-            for (int kt = 0; kt < kRows / 32; ++kt) {
-                acc1 = products(1, kf);  // last use of this tile's fragments
-                if (kt + 1 < kRows / 32) load_k(kt + 1, kf);
-                decltype(maxima)::value ? fold(0, acc0) : add(0, acc0);
-                interleave(maxima);
-                if (kt + 1 < kRows / 32) acc0 = products(0, kf);
-                decltype(maxima)::value ? fold(1, acc1) : add(1, acc1);
-                if (kt + 1 < kRows / 32) interleave(maxima);
-            }
-        };
-        static_assert(kTW == 2, "two query tiles per wave");
-        if (ntile == 0) {  // (all branches are uniform)
-        } else if (kbase + kRows > key1) {
-            tile_by_tile();  // the ragged last chunk
-        } else if (ntile == 1) {
-            one_tile();
-        } else if (!have_ref) {
-            two_tiles(std::true_type());
-            have_ref = !__any(run_m[0] == -INFINITY || run_m[1] == -INFINITY);
-        } else {
-            const float s0 = run_s[0], s1 = run_s[1];
-            two_tiles(std::false_type());
-            if (__any(!(run_s[0] < kMostSum) || !(run_s[1] < kMostSum))) {
-                run_s[0] = s0;
-                run_s[1] = s1;
-                tile_by_tile();
             }
         }
         async_tile_wait();

@@ -34,7 +34,7 @@ def test_attention_scores_that_climb(T, Hq, d, rise, alone):
 
 
 @pytest.mark.parametrize("N,M,Hq,Hkv,d", [(1500, 20, 4, 2, 128), (1500, 70, 8, 2, 64), (40000, 33, 8, 8, 128)])
-@pytest.mark.parametrize("jump", [30.0, 58.0, 75.0, 200.0, -75.0])   # log2 of what later keys have over the first: the sums' limit is 2^60
+@pytest.mark.parametrize("jump", [30.0, 58.0, 75.0, 200.0, -75.0])   # log2 of what later keys have over the first
 def test_importance_scores_of_keys_far_above_the_first(N, M, Hq, Hkv, d, jump):
     print("[case] score climb N=%d M=%d d=%d jump=%s" % (N, M, d, jump), flush=True)
     g = torch.Generator().manual_seed(N + d)
@@ -47,3 +47,31 @@ def test_importance_scores_of_keys_far_above_the_first(N, M, Hq, Hkv, d, jump):
     q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
     s = strd.score_attn(q.cuda(), k.cuda())
     assert_close(s.cpu().numpy(), oracle.score_attn(f(q), f(k)), 1e-4, "scores", units=(0,))
+
+
+@pytest.mark.parametrize("N,M,Hq,Hkv,d,packed,cut", [(40000, 70, 32, 8, 128, 0, 1280), (65536, 40, 28, 4, 64, 0, 1024),
+                                                    (4000, 128, 32, 8, 128, 8, 768)])     # cut: keys per slice of pass 1
+@pytest.mark.parametrize("low", [-20.0, -21.5, -23.0, -24.25, -26.0])
+def test_importance_scores_lose_no_bits_where_a_few_late_keys_matter(N, M, Hq, Hkv, d, packed, cut, low):
+    """The first keys of every slice score 2^-40 to 2^-54 of a few late ones; two tiles of rows per wave.  All rows are
+    alike, so that the log-sum-exp's error does not average out, and all products are exact.  In units of log2 a late key's
+    weight is off by the rounding of s * scale - lse (< 8: 2^-22) and of lse (< 4: 2^-23, its logarithm an ulp, 2^-22, the scale 2^-23): 2.6e-7
+    with ln 2, in quadrature; the sums of up to 16 equal terms per lane add 2e-7.  Half as much again as the two give."""
+    print("[case] late keys N=%d M=%d d=%d packed=%d low=%s" % (N, M, d, packed, low), flush=True)
+    late = torch.tensor([cut + 300, cut + 450, 3 * cut + 200, 3 * cut + 500, 4 * cut + 700])      # none in the first 128 of a slice
+    q, k = torch.zeros(M, Hq, d), torch.zeros(N, Hkv, d)
+    q[:, :, 0] = 16.0
+    k[:, :, 0] = low * (d / 128) ** 0.5
+    k[late, :, 0] = torch.tensor([0.25, -0.5, 0.75, 0.125, -0.3125])[:, None] * (d / 128) ** 0.5
+    q, k = q.bfloat16(), k.bfloat16()
+    z = f(k[:, 0, 0]) * 16.0 / d ** 0.5
+    want = np.exp(z - z.max()) / np.exp(z - z.max()).sum()
+    if packed:
+        rows = lambda t, n: torch.cat([t.cuda(), torch.zeros(n, *t.shape[1:], dtype=t.dtype, device="cuda")])
+        k_all = torch.cat([rows(k, M)] * packed)
+        q_all = torch.cat([torch.cat([torch.zeros(N, Hq, d, dtype=q.dtype, device="cuda"), q.cuda()])] * packed)
+        s = strd.score_attn_varlen(q_all, k_all, [(N, M, 1)] * packed)
+    else:
+        s = strd.score_attn(q.cuda(), k.cuda())[None]
+    got = f(s[:, :N])[:, late.numpy()]
+    assert np.abs(got / want[late.numpy()] - 1).max() <= 5e-7, np.abs(got / want[late.numpy()] - 1).max()
