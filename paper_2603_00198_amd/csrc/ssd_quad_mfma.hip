@@ -568,7 +568,7 @@ __device__ __forceinline__ void helper_wave(LdsQ<NS> &lds, const QuadArgs &a, in
             async_tile_wait();
         lds_barrier();
     }
-    if (j == 0 && a.ltot) {
+    if (j == 0) {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             a.ltot[(size_t)seg * a.H + h0 + 2 * k + half] = ltot[k];
@@ -686,13 +686,16 @@ __global__ __launch_bounds__(kThreads) void ssd_quad_kernel(QuadArgs a, int nuni
 }
 
 // ---- the contribution of the incoming state to the tokens of segments 1.. and S_out -----
-// One workgroup per (four heads of a group, boundary b = 1..nseg), or a few that take its 64-token tiles in turn (share z); b < nseg: y of
-// segment b; b == nseg: S_out.  A wave per head and slab of 32 channels, with the scan's order of channels, so that a lane reads and writes 16 bytes
-// of a token's outputs.  Where the heads forget within a tile the kernel is a launch and one round of loads: the state E, the outputs
-// that wait in fp32 and the decays, which the segment's own scan has left, are requested before anything is waited for, and the c rows, which
-// the waves share, go through LDS (each wave with its own copy of them took 10 us longer for 7 boundaries of 128 heads, 23.5 us at 2176 tokens, this 14).  Where they
-// remember for longer it is bound by the way of the outputs from memory and back: c rows, outputs and decays come two tiles ahead
-// (8448 tokens of 128 heads with decays of 0.003 per token, the whole call: 253 us with the seams of ssd_seg, 180 one tile ahead with 8-byte accesses, 156).
+// One workgroup per (four heads of a group, boundary b = 1..nseg); b < nseg: y of segment b; b == nseg: S_out.  A wave per head and slab of 32
+// channels, with the scan's order of channels, so that a lane reads and writes 16 bytes of a token's outputs.  Where the heads forget within a
+// tile the kernel is a launch and a chain of loads: the last segment's state, the outputs that wait in fp32 and the decays, which the
+// segment's own scan has left, are requested first, then four times in turn what says whether a head's states hold a value that is not
+// finite, then the states before (one value at a time, each waited for); the c rows, which the waves share, go through LDS (each wave with its own copy
+// of them took 10 us longer for 7 boundaries of 128 heads, 23.5 us at 2176 tokens, this 14).  Where they remember for longer it is bound by the way of the
+// outputs from memory and back: c rows, outputs and decays are requested two tiles ahead, the outputs 16 bytes at a time (8448 tokens of 128 heads with decays
+// of 0.003 per token, the whole call: 263 us with ssd_seg, 162 here, 15 % more one tile ahead with 8-byte accesses).  In the compiled code a tile
+// waits for all of that, its successor's loads and the stores before it included, not for its own alone: the compiler, not the count below, waits for y
+// and the decays, and the gather form's index entries on their way to an address drain the same queue.
 // The boundaries of a head lie on one XCD: their states E are sums over the same final states.
 constexpr int kFixThreads = 512;
 constexpr int kFixTile = 64;  // tokens per tile: a lane per token
@@ -706,7 +709,7 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, i
     __shared__ TB ct[3][kFixTile / kQ];  // c rows of this tile and the next two
     const int unit = xcd_swizzle(blockIdx.x, nunits);
     if (unit >= nunits) return;
-    const int b = 1 + unit % a.nseg, h0 = unit / a.nseg * kHeads, z = blockIdx.y, nz = gridDim.y;
+    const int b = 1 + unit % a.nseg, h0 = unit / a.nseg * kHeads;
     const int lane = threadIdx.x & 63, lr = lane & 15, lb = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), cw = wave & 1;  // slab of this wave
     const int h = h0 + (wave >> 1);
@@ -732,7 +735,7 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, i
         f32x4 *dst = reinterpret_cast<f32x4 *>(a.S_out + (size_t)h * kP * NS);
         for (int s = b - 2; s >= 0 && f != 0.f; --s) {
             const f32x4 *src = reinterpret_cast<const f32x4 *>(a.lend + (size_t)s * seg_elems + (size_t)h * kP * NS);
-            for (int e = z * kStep + threadIdx.x % kStep; e < per; e += nz * kStep) dst[e] += f * src[e];
+            for (int e = threadIdx.x % kStep; e < per; e += kStep) dst[e] += f * src[e];
             f = weight(lost, f * fast_exp2(a.ltot[(size_t)s * a.H + h]));
         }
         return;
@@ -741,7 +744,6 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, i
     const int g = h / (a.H / a.G);
     const int seg_tok = a.seg_steps * kQ, tok0 = b * seg_tok, tend = min(a.T, tok0 + seg_tok);
     const int ntiles = (tend - tok0 + kFixTile - 1) / kFixTile;
-    if (z >= ntiles) return;
     auto row_of = [&](int t) -> size_t {
         t = min(t, a.T - 1);
         return GATHER ? (size_t)gather_row(a, t, a.idx[min(t, a.K - 1)]) : (size_t)t;
@@ -763,7 +765,7 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, i
     auto in_tile = [&](int k, int tt) { return (uint32_t)min(16 * tt + lr, a.T - 1 - (tok0 + k * kFixTile)); };  // tokens past T: the last
     auto y_of = [&](int k) { return a.y + (size_t)(tok0 + k * kFixTile) * HP + col; };
     const float *seam = a.seam + ((size_t)(b - 1) * a.H + h) * seg_tok;
-    copy_c(z, ct[0]);
+    copy_c(0, ct[0]);
     // E = state at the start of segment b, as A-operand fragments: rows p = chan_of(0, pt, lr) of the slab, k slots n = 32 ks + 4 lb + s
     // (s < 4), 32 ks + 16 + 4 lb + s - 4 (s >= 4)
     f32x4 e[2][KS][2];
@@ -788,16 +790,12 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, i
     constexpr int kLoads = kCopies + 5;  // a wave's loads per tile
     std::integral_constant<int, 0> P0;
     std::integral_constant<int, 1> P1;
-    if (z == 0) {
-        const float *yw = a.ybuf + (size_t)(b - 1) * kSeamTok * HP + col;
+    const float *yw = a.ybuf + (size_t)(b - 1) * kSeamTok * HP + col;
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt)
+    for (int tt = 0; tt < 4; ++tt)
 #pragma unroll
-            for (int pt = 0; pt < 2; ++pt) y0[tt][pt] = *reinterpret_cast<const f32x4 *>(yw + ((16 * tt + lr) * HP + 8 * lb + 4 * pt));
-        inc[0] = seam[min(lane, seg_tok - 1)];
-    } else {
-        load(z, P0);
-    }
+        for (int pt = 0; pt < 2; ++pt) y0[tt][pt] = *reinterpret_cast<const f32x4 *>(yw + ((16 * tt + lr) * HP + 8 * lb + 4 * pt));
+    inc[0] = seam[min(lane, seg_tok - 1)];
     const float lt = a.ltot[(size_t)(b - 1) * a.H + h];
     // tiles that anything of E reaches, for this head and for all four; the outputs of the first tile are written in any case
     int mine = 1, most = 1;
@@ -810,9 +808,9 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, i
         if (h0 + q == h) mine = max(n, 1), lost = l;
     }
     const int life_tok = a.life[(size_t)(b - 1) * a.H + h] * kQ;  // tokens whose decays are there; behind them they are zero
-    if (z + nz < most) {
-        copy_c(z + nz, ct[1]);
-        load(z + nz, P1);
+    if (most > 1) {
+        copy_c(1, ct[1]);
+        load(1, P1);
     }
     float f = weight(lost, fast_exp2(lt));
     for (int s = b - 2; s >= 0 && f != 0.f; --s) {
@@ -832,7 +830,7 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, i
         for (int tt = 0; tt < 4; ++tt)
             if (tok0 + k * kFixTile + 16 * tt + lr < tend) *reinterpret_cast<bf16x8 *>(y_of(k) + (in_tile(k, tt) * HP + 8 * lb)) = out[tt];
     };
-    int k = z, buf = 0, last = -1;  // last: the tile whose outputs wait to be stored
+    int k = 0, buf = 0, last = -1;  // last: the tile whose outputs wait to be stored
     bool ahead = false;             // the loads of the tile after this one are the newest of the wave
     // One tile, outputs in slot p; false after the last.
     auto tile = [&](auto p) __attribute__((always_inline)) {
@@ -865,12 +863,12 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, i
             }
             last = k;
         }
-        ahead = k + 2 * nz < most;
+        ahead = k + 2 < most;
         if (ahead) {
-            copy_c(k + 2 * nz, ct[buf == 0 ? 2 : buf - 1]);
-            load(k + 2 * nz, p);
+            copy_c(k + 2, ct[buf == 0 ? 2 : buf - 1]);
+            load(k + 2, p);
         }
-        k += nz;
+        ++k;
         buf = buf == 2 ? 0 : buf + 1;
         return k < most;
     };
@@ -879,38 +877,32 @@ __global__ __launch_bounds__(kFixThreads) void ssd_quad_fix_kernel(QuadArgs a, i
     if (last >= 0) store(last);
 }
 
-// Workgroups that share the tiles of a (boundary, four heads), a power of two: where decays are slow the state lives through all tiles of
-// a segment, so as many as still find a CU to themselves.
-int fix_shares(int nseg, int H) {
-    const long long wgs = (long long)nseg * (H / kHeads);
-    return wgs <= 64 ? 4 : wgs <= 128 ? 2 : 1;
-}
-
 template <int NS, bool GATHER>
 int launch(const QuadArgs &a, hipStream_t st) {
     const int nunits = a.nseg * a.wg_per_seg;
     const size_t smem = sizeof(LdsQ<NS>);
     if (!allow_dynamic_lds(reinterpret_cast<const void *>(&ssd_quad_kernel<NS, GATHER>), smem)) return STRD_EHIP;
     ssd_quad_kernel<NS, GATHER><<<xcd_grid(nunits), kThreads, smem, st>>>(a, nunits);
-    if (a.nseg > 1)  // (as many units again: a boundary per segment, the last one for S_out)
-        ssd_quad_fix_kernel<NS, GATHER><<<dim3(xcd_grid(nunits), fix_shares(a.nseg, a.H)), kFixThreads, 0, st>>>(a, nunits);
+    // (as many units again: a boundary per segment, the last one for S_out)
+    ssd_quad_fix_kernel<NS, GATHER><<<xcd_grid(nunits), kFixThreads, 0, st>>>(a, nunits);
     return launch_status();
 }
 
 struct Plan {
     int nseg, seg_steps;
     size_t lend, ltot, lost, seam, life, ybuf;  // bytes of the parts of the workspace
-    size_t bytes() const { return nseg > 1 ? lend + ltot + lost + seam + life + ybuf : 0; }
+    size_t bytes() const { return lend + ltot + lost + seam + life + ybuf; }
 };
 
-// How the sequence is cut: as many segments as it takes to give every CU a workgroup, each at least kMinSegSteps steps long.
+// How the sequence is cut: as many segments as it takes to give every CU a workgroup, each at least kMinSegSteps steps long; two at least
+// (ssd_quad_preferred).
 Plan plan_of(int T, int H, int n) {
     constexpr int kMinSegSteps = 8, kCUs = 256;
     const int nsteps = (T + kQ - 1) / kQ, wg = H / kHeads;
     const int s = max(1, min(kCUs / wg, nsteps / kMinSegSteps));  // (one round of the chip)
     Plan p;
-    p.seg_steps = max(1, (nsteps + s - 1) / s);
-    p.nseg = max(1, (nsteps + p.seg_steps - 1) / p.seg_steps);
+    p.seg_steps = (nsteps + s - 1) / s;
+    p.nseg = (nsteps + p.seg_steps - 1) / p.seg_steps;
     p.lend = align_up((size_t)(p.nseg - 1) * H * kP * n * sizeof(float), 256);
     p.ltot = align_up((size_t)p.nseg * H * sizeof(float), 256);
     p.lost = align_up((size_t)(p.nseg - 1) * H * 2 * sizeof(uint32_t), 256);
@@ -932,9 +924,10 @@ bool ssd_quad_supported(int T, int rows, int H, int P, int G, int n, strd_dtype 
 // Where this kernel is taken: in the place of ssd_seg's two-head form, where that one would be taken with segments of 32 steps of 64
 // tokens and more, and the segments here, twice as many, still leave the few CUs that they need (64 heads).  us of a call, before -> here, n = 128,
 // with decays of one per token and more (A = -1 to -7, dt = 0.8) / with
-// 0.003 of those: 128 heads, 8448 tokens 98.5 -> 89 / 253 -> 156, 33280 tokens 336 -> 280 / 1081 -> 505; 64 heads, 16640 tokens 106 -> 96 / 262 ->
-// 190; 256 heads, 8448 tokens 189 -> 155 / 535 -> 264; 96 heads, 12000 tokens 159 -> 105 / 386 -> 221; n = 64: 128 heads, 8448 tokens 80.7 -> 80.5 /
-// 185 -> 126, 33280 tokens 277 -> 253 / 846 -> 469.
+// 0.003 of those: 128 heads, 8448 tokens 119 -> 99 / 263 -> 162, 33280 tokens 356 -> 287 / 1087 -> 505; 64 heads, 16640 tokens 106 -> 97 / 268 ->
+// 197; 256 heads, 8448 tokens 196 -> 157 / 545 -> 268; 96 heads, 12000 tokens 164 -> 107 / 391 -> 189; 508 heads, 4500 tokens 213 -> 161 / 556 -> 259; n = 64:
+// 128 heads, 8448 tokens 87.5 -> 80.7 / 188 -> 126, 33280 tokens 282 -> 254 / 864 -> 471.  Error against 64 bits (2-norm), decays of one per token / 0.1 / 0.003 of
+// that: 128 heads, 8448 tokens 2.3440 -> 2.3435e-3 / 2.410 -> 2.404 / 3.28 -> 3.11; no larger at any of 1 to 0.0003 for 64 to 508 heads, n = 64 and 128.
 // Not taken: shorter sequences of fewer heads, where one workgroup per (head, 32 channels) is the slower one while heads forget (128 heads, 5630
 // tokens 89 -> 67) and the faster one while they do not (90 -> 114: seven eighths of the outputs are read and written again); up to 32 heads
 // neither gains (16 heads, 2176 tokens 31 -> 36).  512 heads and more, where ssd_seg is not taken either: here they are faster, 2176 tokens of
@@ -952,19 +945,14 @@ int ssd_quad(const void *x, const float *dt, const float *A, const void *B, cons
     a.nseg = p.nseg;
     a.seg_steps = p.seg_steps;
     a.wg_per_seg = H / kHeads;
-    a.lend = a.ltot = a.seam = a.ybuf = nullptr;
-    a.lost = nullptr;
-    a.life = nullptr;
-    if (a.nseg > 1) {
-        if (!ws) return STRD_EWORKSPACE;
-        char *w = (char *)ws;
-        a.lend = (float *)w;
-        a.ltot = (float *)(w + p.lend);
-        a.lost = (uint32_t *)(w + p.lend + p.ltot);
-        a.seam = (float *)(w + p.lend + p.ltot + p.lost);
-        a.life = (int32_t *)(w + p.lend + p.ltot + p.lost + p.seam);
-        a.ybuf = (float *)(w + p.lend + p.ltot + p.lost + p.seam + p.life);
-    }
+    if (!ws) return STRD_EWORKSPACE;
+    char *w = (char *)ws;
+    a.lend = (float *)w;
+    a.ltot = (float *)(w + p.lend);
+    a.lost = (uint32_t *)(w + p.lend + p.ltot);
+    a.seam = (float *)(w + p.lend + p.ltot + p.lost);
+    a.life = (int32_t *)(w + p.lend + p.ltot + p.lost + p.seam);
+    a.ybuf = (float *)(w + p.lend + p.ltot + p.lost + p.seam + p.life);
     if (n == 128) return idx ? launch<128, true>(a, st) : launch<128, false>(a, st);
     return idx ? launch<64, true>(a, st) : launch<64, false>(a, st);
 }
