@@ -1,5 +1,6 @@
 """Attention whose softmax reference follows the maximum lazily: scores that climb by less and by more than the slack per block of
-32 keys, all keys of a block alike or one of them alone, and scores that fall; the three forms of the kernel.  Needs a GPU."""
+32 keys, all keys of a block alike or one of them alone, and scores that fall; the three forms of the kernel.  Importance scores whose
+running maximum moves.  Needs a GPU."""
 import numpy as np
 import pytest
 import torch
@@ -47,6 +48,27 @@ def test_importance_scores_of_keys_far_above_the_first(N, M, Hq, Hkv, d, jump):
     q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
     s = strd.score_attn(q.cuda(), k.cuda())
     assert_close(s.cpu().numpy(), oracle.score_attn(f(q), f(k)), 1e-4, "scores", units=(0,))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("jump", [30.0, 58.0, 75.0, 200.0, -75.0])
+def test_packed_scores_of_keys_far_above_the_first(d, jump):
+    """Two tiles of rows per wave and six slices of two chunks of keys, the step in the second chunk of one."""
+    N, M, Hq, Hkv, nseq = 1500, 70, 8, 2, 48
+    print("[case] packed score climb d=%d jump=%s" % (d, jump), flush=True)
+    g = torch.Generator().manual_seed(d)
+    q, k = torch.randn(M, Hq, d, generator=g), torch.randn(N, Hkv, d, generator=g)
+    q[:, :, 0] = 16.0
+    up = torch.zeros(N)
+    up[N // 3 + 150:] = jump / 2
+    up[N // 2::97] = jump
+    k[:, :, 0] = (up / 1.4426950408889634 * d ** 0.5 / 16.0)[:, None]
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    k_all = torch.cat([k, torch.zeros(M, Hkv, d, dtype=k.dtype)]).cuda().repeat(nseq, 1, 1)
+    q_all = torch.cat([torch.zeros(N, Hq, d, dtype=q.dtype), q]).cuda().repeat(nseq, 1, 1)
+    s = strd.score_attn_varlen(q_all, k_all, [(N, M, 1)] * nseq)[:, :N]
+    assert (s == s[0]).all()
+    assert_close(s[0].cpu().numpy(), oracle.score_attn(f(q), f(k)), 1e-4, "scores", units=(0,))
 
 
 @pytest.mark.parametrize("N,M,Hq,Hkv,d,packed,cut", [(40000, 70, 32, 8, 128, 0, 1280), (65536, 40, 28, 4, 64, 0, 1024),

@@ -183,3 +183,31 @@ def test_a_state_updated_in_place_needs_no_workspace(heads, T):
     got.append((y, S))
     for y, S in got[1:]:
         assert torch.equal(y, got[0][0]) and torch.equal(S, got[0][1])
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("where", [5, 1500, 2111, 4097, -1])    # dt: in the first segment, two in the middle, the last; -1: S_in
+def test_scan_of_four_heads_never_forgets_a_step_or_a_state_that_is_not_finite(bad, where):
+    """dt of one head at one token: every later output of the head and its state; one entry of S_in: every output of its channel and that
+    entry at the end.  The steps before, the other heads, channels and entries keep their bits."""
+    T, G, n, h, p, e = 4100, 8, 128, 70, 37, 90
+    x, dt, A, B, C, D, S_in = _inputs(T, G, n, 1.0, 7)
+    y0, S0 = strd.ssd_prefill(x, dt, A, B, C, D, S_in)
+    other = torch.arange(H, device="cuda") != h
+    if where < 0:
+        S_in[h, p, e] = bad
+    else:
+        dt[where, h] = bad
+    y, S = strd.ssd_prefill(x, dt, A, B, C, D, S_in)
+    assert torch.equal(y[:, other], y0[:, other]) and torch.equal(S[other], S0[other])
+    if where < 0:
+        assert not torch.isfinite(y[:, h, p]).any() and not torch.isfinite(S[h, p, e])
+        rest = torch.ones(P, n, dtype=torch.bool, device="cuda")
+        rest[p, e] = False
+        # (a seam of that head adds terms of 2^-126 that it leaves out otherwise)
+        assert torch.allclose(S[h][rest], S0[h][rest], rtol=1e-6, atol=1e-30)
+        channels = torch.arange(P, device="cuda") != p
+        assert torch.allclose(y[:, h, channels].float(), y0[:, h, channels].float(), rtol=2 ** -7, atol=1e-30)
+    else:
+        assert torch.equal(y[:where // 32 * 32], y0[:where // 32 * 32])
+        assert not torch.isfinite(y[where:, h]).any() and not torch.isfinite(S[h]).any()
